@@ -76,6 +76,7 @@ struct DecodeParams {
   float* part_o;               // workspace [C, Hkv, n_splits, rows_pad, D]: unnormalised partial outputs
   float* part_ml;              // workspace [C, Hkv, n_splits, 3, rows_pad]: reference max (log2), row sum, flag
   int C, K, Hq, Hkv, n_pages, max_pages, n_splits, rows_pad;
+  int by_length;               // filled by the launcher: requests take the workgroups by falling context length (C <= 64)
   float c_log2;
 };
 hipError_t launch_draft_decode(const DecodeParams& p, int D, hipStream_t stream);

@@ -1529,36 +1529,55 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(const float* src, __bf16
 // 1..K-1 = multi-token positions, all of the anchor that follows the cached context) are the last
 // anchor's rows of the parallel-prediction mask: every cached key is visible, and the new key of
 // depth e is visible to the rows of depth >= e.  One workgroup per (context split, KV head,
-// request); its waves own 32 rows each of the K x (Hq/Hkv) query rows that share the KV head
-// (row = depth * group + head), loop over the split's 64-token pages with the forward's tile
-// routine, and leave an unnormalised partial (reference max, row sum, O) for the combine kernel.
+// request) loops over the split's 64-token pages with the forward's tile routine and leaves an
+// unnormalised partial (reference max, row sum, O) for the combine kernel.
 // The work is bound by reading the cache once; the matrix cores only keep the arithmetic off
 // the critical path.
+//
+// A wave owns 32 of the K x (Hq/Hkv) query rows that share the KV head (row = depth * group + head).  Where few
+// workgroups share a CU, the chain of one tile (LDS reads, matrix instructions, exponentials) and one tile's copy at a
+// time set the pace, not the memory system.  So kGroups groups of waves hold the same rows and take the split's tiles
+// in turn (tile i: group i % kGroups), kGroups tiles are copied at a time, and the groups are merged through LDS at
+// the end.  Where two groups are worth their LDS: see the launcher.
 // =====================================================================================
-template <int D, int kRing>
-__global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
+template <int D, int kGroups, int kThreads>
+__global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr int kBlocks = kTileBytes / 1024;
-  // kRing LDS buffers of one tile (K and V) each: two, or four at D = 64 when a workgroup has many tiles
-  constexpr int kCopiesPerTile = 2 * kBlocks;
-  static_assert((kRing - 2) * kCopiesPerTile <= 63, "the copies in flight behind a tile must fit the hardware's counter");
+  constexpr int kRing = 2 * kGroups;  // two rounds of kGroups consecutive tiles: one being read, one on its way
   __shared__ __attribute__((aligned(16))) char lds[kRing][2][kTileBytes];  // [buffer][K|V]
   __shared__ int tile_keys[kRing];  // keys present in the tile of each buffer (0 .. 64), set by the copying wave
   __shared__ int table_bad;         // the copying wave met a page id outside the pool
 
-  // The last wave of the workgroup only copies (global -> LDS), the others only compute.  The wait for
-  // a copy is counted per wave and in issue order, so the copying wave keeps kRing - 1 tiles in flight
-  // and waits for the oldest alone, and the computing waves never wait on a copy.  One workgroup barrier
-  // per tile hands the buffers over.
+  // The last wave of the workgroup only copies (global -> LDS), the others only compute: the wait for a copy is
+  // counted per wave, so the computing waves never wait on one.  One workgroup barrier per round hands the buffers
+  // over.  (Deeper rings, three rounds of one tile, took LDS from the workgroups that share a CU and were slower:
+  // 255 against 206 us on 64 equal contexts of 8,192 tokens.)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const int n_compute = (blockDim.x >> 6) - 1;
   const bool producer = wave == n_compute;
-  const int split = blockIdx.x, kvh = blockIdx.y, c = blockIdx.z;
+  const int split = blockIdx.x, kvh = blockIdx.y;
   const int group = p.Hq / p.Hkv;
   const int n_rows = p.K * group;
 
+  // Request of this workgroup: workgroups start in the order of blockIdx.z, and the requests take them by falling
+  // context length, so that the short ones fill the slots that the long ones leave (64 requests of 512 to 8,192
+  // tokens: see the launcher).  Every wave ranks the lengths for itself, one request per lane.
+  int c = blockIdx.z, n_ctx;
+  if (!p.by_length) {
+    n_ctx = p.ctx_len[c];
+  } else {
+    const int len = lane < p.C ? p.ctx_len[lane] : INT_MIN;
+    int rank = 0;
+    for (int j = 0; j < p.C; ++j) {
+      const int other = __builtin_amdgcn_readlane(len, j);
+      rank += (other > len || (other == len && j < lane)) ? 1 : 0;
+    }
+    c = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < p.C && rank == (int)blockIdx.z));
+    n_ctx = __builtin_amdgcn_readlane(len, c);
+  }
+
   // context of this request, clamped to what the block table can describe
-  int n_ctx = p.ctx_len[c];
   bool bad = n_ctx < 0 || n_ctx > p.max_pages * kKeysPerTile;
   n_ctx = n_ctx < 0 ? 0 : (n_ctx > p.max_pages * kKeysPerTile ? p.max_pages * kKeysPerTile : n_ctx);
   const int n_pg = (n_ctx + kKeysPerTile - 1) / kKeysPerTile;
@@ -1566,6 +1585,7 @@ __global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
   const int p0 = split * per < n_pg ? split * per : n_pg;
   const int p1 = p0 + per < n_pg ? p0 + per : n_pg;
   const int n_tiles = (p1 - p0) + (split == 0 ? 1 : 0);  // split 0 also takes the new keys
+  const int n_rounds = (n_tiles + kGroups - 1) / kGroups;
 
   // Tile i of this split is a cache page or, last in split 0, the K new keys.  Only the copying wave
   // reads the block table - through the scalar (constant) path, because a vector load would be ordered
@@ -1584,6 +1604,14 @@ __global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
     const __bf16* k_fill = p.k_new + ((size_t)c * p.K * p.Hkv + kvh) * D;
     const __bf16* v_fill = p.v_new + ((size_t)c * p.K * p.Hkv + kvh) * D;
     const int row_in_blk = lane / (D / 8), phys = lane % (D / 8);
+    // A whole page: 1 KiB pieces of consecutive memory, their addresses on the scalar unit (with per-lane 64-bit
+    // addresses this wave needed most of a microsecond to issue one tile's copies).  The chunk a lane fetches from a
+    // piece depends on the piece only through the swizzle, whose period is 16 rows.
+    constexpr int kPeriod = 16 / (512 / D);
+    uint32_t voff[kPeriod];
+#pragma unroll
+    for (int j = 0; j < kPeriod; ++j)
+      voff[j] = (uint32_t)(row_in_blk * D + ((phys ^ swz<D>(j * (512 / D) + row_in_blk)) << 3)) * 2u;
     int page_next = page_of(0);
     auto copy_tile = [&](int i) {
       const int page = page_next;
@@ -1601,7 +1629,17 @@ __global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
       if (lane == 0) tile_keys[i % kRing] = valid;
       // (untracked copies: a tracked one would make every workgroup barrier below wait for all of them)
       const uint32_t kdst = lds_scalar_addr(lds[i % kRing][0]), vdst = lds_scalar_addr(lds[i % kRing][1]);
-#pragma unroll 4
+      if (!is_new && valid == kKeysPerTile) {
+        const size_t first = ((size_t)page * p.Hkv + kvh) * (kKeysPerTile * D);
+        const __bf16* ks = uniform_ptr(p.k_pages + first);
+        const __bf16* vs = uniform_ptr(p.v_pages + first);
+#pragma unroll
+        for (int blk = 0; blk < kBlocks; ++blk) dma16_untracked(ks + blk * 512, voff[blk % kPeriod], kdst + blk * 1024);
+#pragma unroll
+        for (int blk = 0; blk < kBlocks; ++blk) dma16_untracked(vs + blk * 512, voff[blk % kPeriod], vdst + blk * 1024);
+        return;
+      }
+#pragma unroll 2
       for (int blk = 0; blk < kBlocks; ++blk) {
         const int row = blk * (512 / D) + row_in_blk;
         const int chunk = (phys ^ swz<D>(row)) << 3;
@@ -1621,28 +1659,31 @@ __global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
         dma16_untracked(vs, vdst + blk * 1024);
       }
     };
-    int issued = 0;
-    for (; issued < n_tiles && issued < kRing - 1; ++issued) copy_tile(issued);
-    for (int i = 0; i < n_tiles; ++i) {
-      // Tile i must have landed; the `later` tiles issued behind it may still be in flight.  Copies
-      // complete in issue order, so waiting until at most later * kCopiesPerTile accesses are outstanding
-      // is enough (anything else this wave may have in flight only makes the wait longer).
-      const int later = issued - 1 - i;  // 0 .. kRing - 2
-      if (later >= 2) wait_outstanding<kRing >= 4 ? 2 * kCopiesPerTile : 0>();
-      else if (later == 1) wait_outstanding<kCopiesPerTile>();
-      else wait_outstanding<0>();
-      if (i == n_tiles - 1 && lane == 0) table_bad = bad ? 1 : 0;  // every tile has been looked up by now
-      __syncthreads();  // tile i is published; the computing waves are done with tile i-1 ...
-      if (issued < n_tiles) copy_tile(issued++);  // ... whose buffer takes tile i + kRing - 1
+    int issued = 0;  // tiles
+    auto copy_round = [&] {
+      for (int t = 0; t < kGroups && issued < n_tiles; ++t) copy_tile(issued++);
+    };
+    copy_round();
+    for (int q = 0; q < n_rounds; ++q) {
+      wait_outstanding<0>();  // round q has landed
+      if (q == n_rounds - 1 && lane == 0) table_bad = bad ? 1 : 0;  // every tile has been looked up by now
+      __syncthreads();  // round q is published; the computing waves are done with round q-1 ...
+      copy_round();     // ... whose buffers take round q + 1
     }
-    if (n_tiles == 0) {
+    if (n_rounds == 0) {
       if (lane == 0) table_bad = 0;
       __syncthreads();
     }
-    return;  // barriers executed: max(n_tiles, 1), the same as the computing waves below
+    if (kGroups > 1) {  // the two barriers of the merge below
+      __syncthreads();
+      __syncthreads();
+    }
+    return;  // barriers executed: the same as the computing waves below
   }
 
-  const int r = wave * 32 + ln;  // query row of this lane (shared with lane ^ 32)
+  const int n_row_waves = p.rows_pad / 32;
+  const int grp = wave / n_row_waves;                    // which of the kGroups
+  const int r = (wave - grp * n_row_waves) * 32 + ln;    // query row of this lane (shared with lane ^ 32)
   const bool row_ok = r < n_rows;
   const int depth = row_ok ? r / group : 0, head = kvh * group + (row_ok ? r - depth * group : 0);
   bf16x8 qf[1][D / 16];
@@ -1658,9 +1699,11 @@ __global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
   const NatOff<D> no = nat_offsets<D>(lane);
   const TrOff<D> to = tr_offsets<D>(lane);
 
-  if (n_tiles == 0) __syncthreads();
-  for (int i = 0; i < n_tiles; ++i) {
-    __syncthreads();  // tile i has landed
+  if (n_rounds == 0) __syncthreads();
+  for (int q = 0; q < n_rounds; ++q) {
+    __syncthreads();  // round q has landed
+    const int i = q * kGroups + grp;
+    if (i >= n_tiles) continue;
     const int buf = i % kRing;
     const bool is_new = i >= p1 - p0;
     const int valid = __builtin_amdgcn_readfirstlane(tile_keys[buf]);
@@ -1673,6 +1716,39 @@ __global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
       const uint64_t bits = n >= 64 ? ~0ull : ((1ull << n) - 1);
       const uint32_t mw[2] = {(uint32_t)bits >> (4 * g), (uint32_t)(bits >> 32) >> (4 * g)};
       fwd_tile<D, 1, true, true>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
+    }
+  }
+
+  if (kGroups > 1) {
+    // Merge of the groups: each but the first leaves (max, sum, O) in the buffers, [value][lane] per wave, and the
+    // first adds them up in order.  A group that had no tile carries the start values, which add nothing.
+    constexpr int kVals = 2 + (D / 32) * 16;
+    static_assert((kGroups - 1) * (kThreads / 64 - 1) / kGroups * kVals * 256 <= (int)sizeof(lds), "merge records must fit");
+    float* x = reinterpret_cast<float*>(&lds[0][0][0]);
+    __syncthreads();  // every wave has left the tiles
+    if (grp > 0) {
+      float* mine = x + (size_t)(wave - n_row_waves) * (kVals * 64) + lane;
+      mine[0] = m[0];
+      mine[64] = lsum[0];
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mine[(2 + db * 16 + i) * 64] = o[0][db][i];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int og = 1; og < kGroups; ++og) {
+      const float* his = x + (size_t)((og - 1) * n_row_waves + wave) * (kVals * 64) + lane;
+      const float hm = his[0], hl = his[64];
+      const float mm = __builtin_fmaxf(m[0], hm);
+      const float a = exp2_fast(m[0] - mm), b = exp2_fast(hm - mm);
+      m[0] = mm;
+      lsum[0] = lsum[0] * a + hl * b;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[0][db][i] = o[0][db][i] * a + his[(2 + db * 16 + i) * 64] * b;
     }
   }
 
@@ -1700,18 +1776,27 @@ __global__ __launch_bounds__(320) void draft_decode_kernel(DecodeParams p) {
 }
 
 // Merges the splits of a request's rows: M = max m_s, L = sum l_s 2^(m_s - M), O = sum O_s 2^(m_s - M) / L.
-// One thread per (request, KV head, row, 4 features).  The loads of a batch of splits are issued
-// together (the loops are unrolled in batches with clamped indices): a thread's time is a few memory
-// round trips, not one per split.  Block 0 also sets the per-request status words, a wave per request.
-template <int D>
+// kLanes threads per (request, KV head, row, 4 features), kEach splits per thread, all of a thread's loads issued
+// before the first is used: the kernel's time is one memory round trip (two passes over the splits, and all status
+// words set by one workgroup, took 6.2 / 8.9 / 13.6 us for 4 x 16, 2 x 32 and 64 x 2 requests x splits; this 4.3 /
+// 4.0 / 6.3).  The threads of a row sit D/4 lanes apart and are merged by lane exchange.  The wave of a request's
+// first row of KV head 0 also sets its status word: every KV head's workgroups look at the same block-table entries,
+// so head 0's records tell.
+template <int D, int kLanes, int kEach>
 __global__ __launch_bounds__(256) void draft_decode_combine_kernel(DecodeParams p) {
-  constexpr int kBatch = 8;
+  constexpr int kPerRow = (D / 4) * kLanes, kRowsPerWave = 64 / kPerRow;
+  static_assert(kPerRow <= 64, "the threads of a row are one wave's");
   const int group = p.Hq / p.Hkv;
   const int n_rows = p.K * group;
-  const size_t n = (size_t)p.C * p.Hkv * n_rows * (D / 4);
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
-    const int c4 = (int)(idx % (D / 4));
-    size_t rem = idx / (D / 4);
+  const int lane = threadIdx.x & 63;
+  const int c4 = lane % (D / 4), sl = lane / (D / 4) % kLanes;
+  const size_t n = (size_t)p.C * p.Hkv * n_rows;
+  const size_t wave0 = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const size_t n_waves = (size_t)gridDim.x * (blockDim.x >> 6);
+  for (size_t first = wave0 * kRowsPerWave; first < n; first += n_waves * kRowsPerWave) {
+    const size_t row = first + lane / kPerRow;
+    const bool ok = row < n;
+    size_t rem = ok ? row : n - 1;
     const int r = (int)(rem % n_rows);
     rem /= n_rows;
     const int kvh = (int)(rem % p.Hkv);
@@ -1719,54 +1804,52 @@ __global__ __launch_bounds__(256) void draft_decode_combine_kernel(DecodeParams 
     const size_t rec0 = ((size_t)c * p.Hkv + kvh) * p.n_splits;
     const float* ml0 = p.part_ml + rec0 * 3 * p.rows_pad + r;
     const float* o0 = p.part_o + (rec0 * p.rows_pad + r) * D + c4 * 4;
-    float M = kNegInit;
-    for (int s0 = 0; s0 < p.n_splits; s0 += kBatch) {
-      float mv[kBatch];
+    float mv[kEach], lv[kEach];
+    f32x4 ov[kEach];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const int s = s0 + j < p.n_splits ? s0 + j : p.n_splits - 1;
-        mv[j] = ml0[(size_t)s * 3 * p.rows_pad];
-      }
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j) M = __builtin_fmaxf(M, mv[j]);
+    for (int j = 0; j < kEach; ++j) {  // (splits past the last are read as the last and weigh nothing)
+      const int s = sl * kEach + j < p.n_splits ? sl * kEach + j : p.n_splits - 1;
+      mv[j] = ml0[(size_t)s * 3 * p.rows_pad];
+      lv[j] = ml0[(size_t)s * 3 * p.rows_pad + p.rows_pad];
+      ov[j] = *reinterpret_cast<const f32x4*>(o0 + (size_t)s * p.rows_pad * D);
     }
+    bool any = false;
+    const bool flags = p.status && ok && r == 0 && kvh == 0;
+    if (flags) {
+      for (int s = lane % kPerRow; s < p.n_splits; s += kPerRow) any |= ml0[((size_t)s * 3 + 2) * p.rows_pad] != 0.f;
+    }
+    float M = mv[0];
+#pragma unroll
+    for (int j = 1; j < kEach; ++j) M = __builtin_fmaxf(M, mv[j]);
+#pragma unroll
+    for (int x = D / 4; x < kPerRow; x <<= 1) M = __builtin_fmaxf(M, __shfl_xor(M, x));
     float L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < p.n_splits; s0 += kBatch) {
-      float mv[kBatch], lv[kBatch];
-      f32x4 ov[kBatch];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const int s = s0 + j < p.n_splits ? s0 + j : p.n_splits - 1;
-        mv[j] = ml0[(size_t)s * 3 * p.rows_pad];
-        lv[j] = ml0[(size_t)s * 3 * p.rows_pad + p.rows_pad];
-        ov[j] = *reinterpret_cast<const f32x4*>(o0 + (size_t)s * p.rows_pad * D);
-      }
+    for (int j = 0; j < kEach; ++j) {
+      const float w = sl * kEach + j < p.n_splits ? exp2_fast(mv[j] - M) : 0.f;
+      L = __builtin_fmaf(lv[j], w, L);
+      acc += ov[j] * w;
+    }
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const float w = s0 + j < p.n_splits ? exp2_fast(mv[j] - M) : 0.f;
-        L = __builtin_fmaf(lv[j], w, L);
-        acc += ov[j] * w;
-      }
+    for (int x = D / 4; x < kPerRow; x <<= 1) {
+      L += __shfl_xor(L, x);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] += __shfl_xor(acc[j], x);
     }
     const float inv = 1.0f / L;
     const int depth = r / group, head = kvh * group + (r - depth * group);
-    u32x2 w2;
-    w2[0] = pack_bf16(acc[0] * inv, acc[1] * inv);
-    w2[1] = pack_bf16(acc[2] * inv, acc[3] * inv);
-    *reinterpret_cast<u32x2*>(p.o + (((size_t)c * p.K + depth) * p.Hq + head) * D + c4 * 4) = w2;
-    if (c4 == 0) p.lse[((size_t)c * p.Hq + head) * p.K + depth] = (M + __builtin_log2f(L)) * kLn2;
-  }
-  if (p.status && blockIdx.x == 0) {
-    // a request is flagged if any of its workgroups met a bad block-table entry or length
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
-    const int per_req = p.Hkv * p.n_splits;
-    for (int c = wave; c < p.C; c += nwv) {
-      bool any = false;
-      for (int w = lane; w < per_req; w += 64)
-        any |= p.part_ml[((size_t)c * per_req + w) * 3 * p.rows_pad + 2 * p.rows_pad] != 0.f;
-      const bool flagged = __builtin_amdgcn_ballot_w64(any) != 0;
-      if (lane == 0) p.status[c] = flagged ? 1 : 0;
+    if (ok && sl == 0) {
+      u32x2 w2;
+      w2[0] = pack_bf16(acc[0] * inv, acc[1] * inv);
+      w2[1] = pack_bf16(acc[2] * inv, acc[3] * inv);
+      *reinterpret_cast<u32x2*>(p.o + (((size_t)c * p.K + depth) * p.Hq + head) * D + c4 * 4) = w2;
+      if (c4 == 0) p.lse[((size_t)c * p.Hq + head) * p.K + depth] = (M + __builtin_log2f(L)) * kLn2;
+    }
+    const uint64_t votes = __builtin_amdgcn_ballot_w64(any);
+    if (flags && lane % kPerRow == 0) {
+      const uint64_t row_lanes = kPerRow == 64 ? ~0ull : ((1ull << (kPerRow & 63)) - 1) << lane;
+      p.status[c] = (votes & row_lanes) != 0 ? 1 : 0;
     }
   }
 }
@@ -1978,26 +2061,49 @@ hipError_t launch_bwd(const BwdParams& pin, int D, int key_lo, int a_hi, int acc
   return hipSuccess;
 }
 
-hipError_t launch_draft_decode(const DecodeParams& p, int D, hipStream_t stream) {
-  // one computing wave per 32 query rows, plus the wave that copies
-  const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C), block((unsigned)((p.rows_pad / 32 + 1) * 64));
-  // Long splits keep three tiles in flight per workgroup (4.4 against 4.1 TB/s on a batch that fills the
-  // memory system); short ones - the serving shapes - are a microsecond faster with two buffers, which
-  // let more workgroups share a CU.  D = 128 tiles are twice the size: two buffers.
-  const bool deep = D == 64 && (p.max_pages + p.n_splits - 1) / p.n_splits > 16;
+hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t stream) {
+  DecodeParams p = pin;
+  const int row_waves = p.rows_pad / 32;  // 1 .. 4
+  const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
+  // Requests of different lengths: with more workgroups than the two per CU that two groups leave room for, those of
+  // the longest requests start first (64 requests of 512 to 8,192 tokens, 1,024 workgroups: 161 us in order of the
+  // request, 125 us by length).  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
+  const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;
+  p.by_length = p.C > 1 && p.C <= 64 && n_wg > 512;
+  // Two groups of waves per workgroup cost twice the LDS.  At D = 64 two such workgroups still share a CU; at D = 128
+  // only one does, which pays while there is at most one per CU anyway.  us per call, one / two groups: D = 64, 64
+  // requests of 512 - 8,192 tokens 134 / 120, 16 of 2,000 - 20,000 89 / 81, 64 equal ones of 8,192 206 / 226 (226
+  // with one group and the earlier ring of four tiles); D = 128, 2 of 10,800 - 20,000 (256 workgroups) 23.1 / 21.2,
+  // 16 of 800 - 8,192 (1,024 workgroups) 54 / 66.  More than 64 query rows make nine waves, too many for two per CU.
+  const bool two = row_waves <= 2 && (D == 64 || n_wg <= 256);
+  const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + 1) * 64));
+  // (The bound of 576 threads, of which 320 are launched, has the compiler schedule for four waves per SIMD: 120
+  // against 136 us on the first of those batches.  The other forms run the same with either bound.)
   if (D == 64) {
-    if (deep) hipLaunchKernelGGL((draft_decode_kernel<64, 4>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((draft_decode_kernel<64, 2>), grid, block, 0, stream, p);
+    if (two) hipLaunchKernelGGL((draft_decode_kernel<64, 2, 576>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((draft_decode_kernel<64, 1, 320>), grid, block, 0, stream, p);
   } else {
-    hipLaunchKernelGGL((draft_decode_kernel<128, 2>), grid, block, 0, stream, p);
+    if (two) hipLaunchKernelGGL((draft_decode_kernel<128, 2, 320>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((draft_decode_kernel<128, 1, 320>), grid, block, 0, stream, p);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t n = (size_t)p.C * p.Hkv * p.K * (p.Hq / p.Hkv) * (D / 4);
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 256 * 16) blocks = 256 * 16;
-  if (D == 64) hipLaunchKernelGGL((draft_decode_combine_kernel<64>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL((draft_decode_combine_kernel<128>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  // threads per row and splits per thread: n_splits is at most 32
+  auto merge = [&](auto kernel, int rows_per_wave) {
+    const size_t waves = ((size_t)p.C * p.Hkv * p.K * (p.Hq / p.Hkv) + rows_per_wave - 1) / rows_per_wave;
+    size_t blocks = (waves + 3) / 4;
+    if (blocks > 256 * 16) blocks = 256 * 16;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  };
+  if (D == 64) {
+    if (p.n_splits <= 2) merge(draft_decode_combine_kernel<64, 1, 2>, 4);
+    else if (p.n_splits <= 8) merge(draft_decode_combine_kernel<64, 2, 4>, 2);
+    else merge(draft_decode_combine_kernel<64, 4, 8>, 1);
+  } else {
+    if (p.n_splits <= 2) merge(draft_decode_combine_kernel<128, 1, 2>, 2);
+    else if (p.n_splits <= 8) merge(draft_decode_combine_kernel<128, 2, 4>, 1);
+    else merge(draft_decode_combine_kernel<128, 2, 16>, 1);
+  }
   return hipGetLastError();
 }
 

@@ -139,3 +139,38 @@ def test_draft_decode_replays_from_a_hip_graph():
         o_eager, lse_eager, _ = r.run()
         assert np.array_equal(bf16_to_f64(o_graph), o_eager), rep
         assert np.array_equal(lse_graph.double().cpu().numpy(), lse_eager), rep
+
+
+RANKED = [
+    # name, number of requests, largest context, K, Hq, Hkv, D: batches of more workgroups than two per CU, whose requests are
+    # taken by falling length (up to 64 of them), over the merge kernel's forms (2, 3 to 8, more splits per request)
+    ("c64_d64", 64, 300, 4, 16, 8, 64),
+    ("c65_d64", 65, 300, 4, 16, 8, 64),
+    ("c64_d128", 64, 300, 5, 16, 8, 128),
+    ("c24_d128_one_group", 24, 1030, 8, 32, 8, 128),
+    ("c9_four_row_blocks", 9, 2000, 8, 128, 8, 64),
+    ("c8_d128_many_splits", 8, 4096, 3, 32, 8, 128),
+]
+
+
+@pytest.mark.parametrize("name,C,longest,K,Hq,Hkv,D", RANKED, ids=[c[0] for c in RANKED])
+def test_draft_decode_batches_taken_by_length(name, C, longest, K, Hq, Hkv, D):
+    """Lengths with ties, empty requests and the longest anywhere; then one request's table is spoiled: it alone is
+    flagged and no other request's output changes."""
+    rng = np.random.default_rng(C + D)
+    lens = rng.integers(0, longest, C)
+    lens[rng.integers(0, C, 4)] = 64
+    lens[rng.integers(0, C, 3)] = 0
+    lens[C // 2] = longest
+    print(f"case decode {name}: ctx={lens.tolist()} K={K} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
+    inp = make_decode_inputs(tuple(int(x) for x in lens), K, Hq, Hkv, D, 1100 + C)
+    r = DecodeRun(inp, K, Hq, Hkv, D)
+    assert C * Hkv * pe.peagle_draft_decode_splits(r.shape) > 512
+    o, lse, status = r.run()
+    assert (status == 0).all()
+    _check(inp, o, lse, r.shape.scale, name)
+    r.bt[C // 2, 0] = r.shape.n_pages                        # outside the pool: skipped and flagged
+    o2, lse2, status2 = r.run()
+    others = np.arange(C) != C // 2
+    assert status2[C // 2] == 1 and (status2[others] == 0).all()
+    assert np.array_equal(o2[others], o[others]) and np.array_equal(lse2[others], lse[others])
