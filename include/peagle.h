@@ -97,10 +97,11 @@ typedef struct peagle_tilemap_info {
  *   device      HIP device ordinal for the device copy, or -1 for a host-only map (introspection only)
  *   out         receives the handle; release with peagle_tilemap_destroy
  *
- * Geometry: a row tile is A consecutive anchors at all K depths (row r of the tile is depth r/A,
- * anchor r%A).  Its keys come from two streams: depth-0 key tiles of 64 consecutive anchors, and
+ * Geometry: a row tile is A consecutive anchors at all K depths (row r of the tile is anchor r/K,
+ * depth r%K).  Its keys come from two streams: depth-0 key tiles of 64 consecutive anchors, and
  * the chain key tiles holding the depth >= 1 positions of the tile's own anchors (key k of the
- * chain stream is depth 1 + k/A, anchor k%A).  Each (row tile, key tile) pair is classified
+ * chain stream is row k of the tile, the places of depth 0 staying empty; for K = 2, and wherever else
+ * they would cost a key tile, it is anchor k/(K-1), depth 1 + k%(K-1)).  Each (row tile, key tile) pair is classified
  * empty / full / partial from interval tests; partial pairs point into a pool of de-duplicated
  * bitmasks (the pool has O(1) entries because the mask is position-invariant).
  */

@@ -18,7 +18,7 @@ def build(verbose: bool = False, sanitize_host_to: str = "") -> str:
     code (tile-map builder, argument validation, launch drivers) carries AddressSanitizer and
     UndefinedBehaviorSanitizer; the device code is the same (no sanitizer runs on the GPU)."""
     out_path = sanitize_host_to or LIB
-    opt = ["-O1", "-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
+    opt = ["-O3", "-Xarch_host", "-O1", "-Xarch_host", "-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
            "-Xarch_host", "-fno-sanitize-recover=undefined", "-Xarch_host", "-fno-omit-frame-pointer",
            "-shared-libsan"] if sanitize_host_to else ["-O3"]
     cmd = [

@@ -41,10 +41,11 @@ __device__ __forceinline__ bool key_token(const DeviceTileMap& tm, int kt, int r
   }
   const int R = cid / tm.n_csub;
   const int ck = (cid - R * tm.n_csub) * kKeysPerTile + row;
-  const int e = ck / tm.A;
-  const int j = R * tm.A + (ck - e * tm.A);
-  tok = (1 + e) * L + j;
-  return ck < tm.A * (tm.K - 1) && j < L;
+  const int a = ck / tm.chain_slots;
+  const int e = tm.chain_first + ck - a * tm.chain_slots;
+  const int j = R * tm.A + a;
+  tok = e * L + j;
+  return e >= 1 && a < tm.A && j < L;
 }
 
 // Token of row `r` of row tile `rt`; false if the row is padding or beyond the sequence.
@@ -53,10 +54,9 @@ __device__ __forceinline__ bool row_token(const DeviceTileMap& tm, int rt, int r
     tok = tm.row_tok[(size_t)rt * kRowsPerTile + r];
     return tok >= 0;
   }
-  const int d = r / tm.A;
-  const int i = rt * tm.A + (r - d * tm.A);
-  tok = d * L + i;
-  return d < tm.K && i < L;
+  const int a = r / tm.K, i = rt * tm.A + a;
+  tok = (r - a * tm.K) * L + i;
+  return a < tm.A && i < L;
 }
 
 __device__ __forceinline__ uint4 ld16(const __bf16* p) { return *reinterpret_cast<const uint4*>(p); }
@@ -158,33 +158,48 @@ struct RowDmaLane {
   int row[kPer];     // row of the tile (index into a sampled map's row list)
   int chunk[kPer];   // element offset of the logical 16-byte chunk this lane fetches
   int stat_tok0, stat_a, stat_row;  // same for the row whose per-row statistic this lane copies (waves 0..3)
-  // Dense maps, row tiles whose 128 rows all exist: byte offset of each copy's source from the head's row of the
-  // tile's first anchor, ((d*L + a) * Hq) * D * 2 + 2 * chunk (and 4 * (d*L + a) for the statistic) - the same
-  // for every row tile and head, so a copy needs only a new scalar base.
-  uint32_t fast_off[kPer], fast_stat_off;
 };
 template <int D, int NW>
-__device__ __forceinline__ RowDmaLane<D, NW> row_dma_lane(const DeviceTileMap& tm, int L, int wave, int lane, int Hq = 0) {
+__device__ __forceinline__ RowDmaLane<D, NW> row_dma_lane(const DeviceTileMap& tm, int L, int wave, int lane) {
   RowDmaLane<D, NW> r;
   const int row_in_blk = lane / (D / 8), phys = lane % (D / 8);
 #pragma unroll
   for (int i = 0; i < RowDmaLane<D, NW>::kPer; ++i) {
     const int row = (i * NW + wave) * (512 / D) + row_in_blk;
-    const int A = tm.row_tok ? 1 : tm.A;  // a sampled map has no fixed geometry; rows come from its list
-    const int d = row / A, a = row - d * A;
-    r.tok0[i] = d * L + a;
-    r.a[i] = d < tm.K ? a : (1 << 30);
+    const int a = row / tm.K;  // (a sampled map has no fixed geometry; rows come from its list)
+    r.tok0[i] = (row - a * tm.K) * L + a;
+    r.a[i] = a < tm.A ? a : (1 << 30);
     r.row[i] = row;
     r.chunk[i] = (phys ^ swz<D>(row)) << 3;
-    r.fast_off[i] = (uint32_t)r.tok0[i] * (uint32_t)(Hq * D * 2) + (uint32_t)(r.chunk[i] * 2);
   }
   const int srow = (wave & 1) * 64 + lane;
-  const int A = tm.row_tok ? 1 : tm.A;
-  const int sd = srow / A, sa = srow - sd * A;
-  r.stat_tok0 = sd * L + sa;
-  r.stat_a = sd < tm.K ? sa : (1 << 30);
+  const int sa = srow / tm.K;
+  r.stat_tok0 = (srow - sa * tm.K) * L + sa;
+  r.stat_a = sa < tm.A ? sa : (1 << 30);
   r.stat_row = srow;
-  r.fast_stat_off = (uint32_t)r.stat_tok0 * 4u;
+  return r;
+}
+// Dense maps whose tensors span less than 4 GiB: byte offset of each copy's source from the head's row of the tile's
+// first anchor, ((d*L + a) * Hq) * D * 2 + 2 * chunk (and 4 * (d*L + a) for the statistic) - the same for every row
+// tile and head, so a copy needs only a new scalar base.
+template <int D, int NW>
+struct RowDmaOffsets {
+  uint32_t off[RowDmaLane<D, NW>::kPer], stat_off;
+};
+template <int D, int NW>
+__device__ __forceinline__ RowDmaOffsets<D, NW> row_dma_offsets(const DeviceTileMap& tm, int L, int wave, int lane, int Hq) {
+  RowDmaOffsets<D, NW> r;
+  const int row_in_blk = lane / (D / 8), phys = lane % (D / 8);
+  auto token = [&](int row) {
+    const int a = row / tm.K;
+    return (uint32_t)((row - a * tm.K) * L + a);
+  };
+#pragma unroll
+  for (int i = 0; i < RowDmaLane<D, NW>::kPer; ++i) {
+    const int row = (i * NW + wave) * (512 / D) + row_in_blk;
+    r.off[i] = token(row) * (uint32_t)(Hq * D * 2) + (uint32_t)((phys ^ swz<D>(row)) << 4);
+  }
+  r.stat_off = token((wave & 1) * 64 + lane) * 4u;
   return r;
 }
 // Tokens of the rows this lane copies for one row tile (-1: the row does not exist).  For a dense map
@@ -336,6 +351,41 @@ __device__ __forceinline__ void fwd_tile(const char* kt_lds, const char* vt_lds,
   }
 }
 
+// Tile that carries a bitmask: 32-key blocks that none of the wave's 32 rows can see are left out (of a row tile's
+// chain blocks a wave sees one or two of four; the second half of a diagonal depth-0 tile is often in the future of the
+// whole row tile), and the heads are taken one after the other, which needs fewer registers than fwd_tile.  Three of a
+// row tile's tiles are of this kind: at L = 1,391, K = 8 (14 tiles per row tile on average) the forward takes 183
+// instead of 199 us, at L = 4,096 in four segments 1,236 instead of 1,269.
+template <int D, int NH, bool SAFE>
+__device__ __forceinline__ void fwd_tile_masked(const char* kt_lds, const char* vt_lds, const NatOff<D>& no, const TrOff<D>& to,
+                                                const bf16x8 (&qf)[NH][D / 16], f32x16 (&o)[NH][D / 32], float (&m)[NH],
+                                                float (&lsum)[NH], const uint32_t (&mw)[2], float c) {
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    if (!wave_sees_block(mw[kb])) continue;
+#pragma unroll
+    for (int hh = 0; hh < NH; ++hh) {
+      f32x16 s = zero16();
+#pragma unroll
+      for (int st = 0; st < D / 16; ++st) s = mfma32(frag_nat<D>(kt_lds, no, kb, st), qf[hh][st], s);
+      bf16x8 pb[2];
+      if (SAFE) {
+        softmax_block<D / 32, true>(s, mw[kb], c, m[hh], lsum[hh], o[hh], pb);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = exp2_fast(mask_sel(s[i], mw[kb], 8 * (i / 4) + (i % 4)) * c);
+        pb[0] = pack8_sum(s, 0, lsum[hh]);
+        pb[1] = pack8_sum(s, 1, lsum[hh]);
+      }
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) o[hh][db] = mfma32(frag_tr<D>(vt_lds, to, kb * 32 + t * 16, db), pb[t], o[hh][db]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
 template <int D, int NH, bool SV>
 __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
@@ -389,8 +439,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
     TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
     dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
     dma_publish();
-    // The leading full tiles run in a counted loop of their own (no mask branch, accumulators
-    // stay in place); the partial tiles that end a row tile's list take the general loop.
+    // A row tile's list holds its full tiles first, then the partial ones: two loops (accumulators stay in place).
     int e = e0;
     auto full_tile = [&](int buf) {
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
@@ -415,14 +464,9 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
       if (e + 1 < e1)
         dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
-      if (cur.mask_id < 0) {
-        const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
-        fwd_tile<D, NH, false, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
-      } else {
-        const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + r) * 2);
-        const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
-        fwd_tile<D, NH, true, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
-      }
+      const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + r) * 2);
+      const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
+      fwd_tile_masked<D, NH, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       dma_publish();
       cur = nxt;
       nxt = take_entry(ahead);
@@ -460,13 +504,16 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
 // Backward, part 1: Delta = rowsum(dO * O) and dQ = scale * dS K, row-tile owned (same
 // decomposition as the forward).  Writes Delta [Hq, T] for part 2.
 // =====================================================================================
-template <int D, int NH, bool MASKED, int KB0 = 0, int KB1 = 2>
+template <int D, int NH, bool MASKED>
 __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, const NatOff<D>& no, const TrOff<D>& to,
                                         const bf16x8 (&qf)[NH][D / 16], const bf16x8 (&dof)[NH][D / 16],
                                         f32x16 (&dq)[NH][D / 32], const float (&lse2)[NH], const float (&delta)[NH],
                                         const uint32_t (&mw)[2], float c) {
 #pragma unroll
-  for (int kb = KB0; kb < KB1; ++kb) {
+  for (int kb = 0; kb < 2; ++kb) {
+    // A 32-key block of a masked tile that none of the wave's 32 rows can see contributes exact zeros and is left out
+    // (see fwd_tile_masked).
+    if (MASKED && !wave_sees_block(mw[kb])) continue;
     f32x16 s[NH], dp[NH];
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) {
@@ -593,22 +640,9 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
     const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
     if (e + 1 < e1)
       dma_key_tile<D, 4>(lds_scalar_addr(lds[buf ^ 1][0] + wave * 1024), lds_scalar_addr(lds[buf ^ 1][1] + wave * 1024), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane);
-    if (cur.mask_id < 0) {
-      const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
-      dq_tile<D, NH, false>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
-    } else {
-      const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + r) * 2);
-      const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
-      // A 32-key block that none of the wave's 32 rows can see contributes exact zeros and is left out:
-      // half of a row tile's chain keys are deeper than a given wave's rows, and the second half of a
-      // diagonal depth-0 tile is often in the future of the whole row tile.
-      // (The forward does not do this: at two heads per workgroup it has no registers to spare, and a
-      // second code path there spills.)
-      const bool see0 = wave_sees_block(mw[0]), see1 = wave_sees_block(mw[1]);
-      if (see0 && see1) dq_tile<D, NH, true>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
-      else if (see0) dq_tile<D, NH, true, 0, 1>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
-      else if (see1) dq_tile<D, NH, true, 1, 2>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
-    }
+    const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + r) * 2);
+    const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
+    dq_tile<D, NH, true>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
     dma_publish();
     cur = nxt;
     nxt = take_entry(ahead);
@@ -897,30 +931,30 @@ __global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
   // The remaining tiles, one barrier each: tile e sits in buffer (e - e0) % 3, tile e+1 is published, the
   // copy of tile e+2 goes to the buffer tile e-1 has left.
   int buf = 0;  // (e - e0) % 3: the pipelined part ends on a multiple of three
-  for (; e < e1; ++e) {
-    const u32x2 ahead = fetch_entry(tm.row_entries, entry_at(e + 3));
-    const int buf2 = buf == 0 ? 2 : buf - 1;
-    if (e + 2 < e1) dma_key_tile<D, 4, SV>(kl.k(buf2), kl.v(buf2), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
-    const char* kt_lds = lds[0][0] + buf * (2 * kTileBytes);
-    const char* vt_lds = kt_lds + kTileBytes;
-    if (t_cur.mask_id < 0) {
-      const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
-      dq_tile<D, 1, false>(kt_lds, vt_lds, no, to, qf, dof, dq, lse_used, delta_used, mw, p.c_log2);
-    } else {
-      const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)t_cur.mask_id * kRowsPerTile + r) * 2);
-      const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
-      // a 32-key block that none of the wave's 32 rows can see contributes exact zeros and is left out
-      const bool see0 = wave_sees_block(mw[0]), see1 = wave_sees_block(mw[1]);
-      if (see0 && see1) dq_tile<D, 1, true>(kt_lds, vt_lds, no, to, qf, dof, dq, lse_used, delta_used, mw, p.c_log2);
-      else if (see0) dq_tile<D, 1, true, 0, 1>(kt_lds, vt_lds, no, to, qf, dof, dq, lse_used, delta_used, mw, p.c_log2);
-      else if (see1) dq_tile<D, 1, true, 1, 2>(kt_lds, vt_lds, no, to, qf, dof, dq, lse_used, delta_used, mw, p.c_log2);
+  auto plain = [&](int e_end, auto masked_tag) {
+    constexpr bool MASKED = decltype(masked_tag)::value;
+    for (; e < e_end; ++e) {
+      const u32x2 ahead = fetch_entry(tm.row_entries, entry_at(e + 3));
+      const int buf2 = buf == 0 ? 2 : buf - 1;
+      if (e + 2 < e1) dma_key_tile<D, 4, SV>(kl.k(buf2), kl.v(buf2), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
+      const char* kt_lds = lds[0][0] + buf * (2 * kTileBytes);
+      const char* vt_lds = kt_lds + kTileBytes;
+      uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
+      if (MASKED) {
+        const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)t_cur.mask_id * kRowsPerTile + r) * 2);
+        mw[0] = w[0] >> (4 * g);
+        mw[1] = w[1] >> (4 * g);
+      }
+      dq_tile<D, 1, MASKED>(kt_lds, vt_lds, no, to, qf, dof, dq, lse_used, delta_used, mw, p.c_log2);
+      dma_publish();
+      t_cur = t_n1;
+      t_n1 = t_n2;
+      t_n2 = take_entry(ahead);
+      buf = buf == 2 ? 0 : buf + 1;
     }
-    dma_publish();
-    t_cur = t_n1;
-    t_n1 = t_n2;
-    t_n2 = take_entry(ahead);
-    buf = buf == 2 ? 0 : buf + 1;
-  }
+  };
+  plain(e0 + n_lead, std::false_type{});  // full tiles left over
+  plain(e1, std::true_type{});            // the tiles that carry a bitmask end the list
 
   if (row_ok) {
     if (p.rope_table) {
@@ -1099,11 +1133,57 @@ __device__ __forceinline__ void dkdv_rowtile_pipelined(const char* q_lds, const 
 #undef PEAGLE_PIPE_GROUP
 }
 
-// LISTED: the map names rows by explicit token lists (sampled / packed maps); their tokens are then
-// fetched an iteration before the copy that uses them.  A dense map computes them when it issues
-// the copy and carries no token registers.
-template <int D, bool LISTED, bool SV>
+// The same row tile against chain keys: rows and chain keys of a tile are ordered alike, so a wave's 32 keys are seen
+// by one or two of the four 32-row units (cm: the lane's key-major mask words).  Those are taken one by one, without the
+// pipeline above, which would run the matrix instructions of all four: an iteration is then bound by its copies
+// (dK/dV of eight packed sequences of 64 to 1,728 anchors: the step 3,600 -> 3,460 us).
+template <int D>
+__device__ __forceinline__ void dkdv_rowtile_chain(const char* q_lds, const char* do_lds, const float* nlse_lds,
+                                                   const float* ndelta_lds, const NatOff<D>& no, const TrOff<D>& to,
+                                                   const bf16x8 (&kf)[D / 16], const bf16x8 (&vf)[D / 16],
+                                                   f32x16 (&dk)[D / 32], f32x16 (&dv)[D / 32], int g, float c, u32x4 cm) {
+#pragma unroll 1
+  for (int u = 0; u < 4; ++u) {
+    const uint32_t mw = cm[0] >> (4 * g);
+    cm = u32x4{cm[1], cm[2], cm[3], 0u};
+    if (!wave_sees_block(mw)) continue;
+    const char* q = q_lds + u * (32 * 2 * D);
+    const char* d_o = do_lds + u * (32 * 2 * D);
+    f32x16 s, dp;
+    pipe_row_terms<0>(s, dp, nlse_lds + u * 32, ndelta_lds + u * 32, 0, g, false);
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) {
+      s = mfma32(frag_nat<D>(q, no, 0, st), kf[st], s);
+      dp = mfma32(frag_nat<D>(d_o, no, 0, st), vf[st], dp);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)mw, 8 * (i / 4) + (i % 4), 1);
+      const float pr = exp2_fast(s[i] * c);
+      s[i] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, pr) & keep);
+      dp[i] *= s[i];
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const bf16x8 pb = pack8(s, t), dsb = pack8(dp, t);
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db) {
+        dv[db] = mfma32(frag_tr<D>(d_o, to, t * 16, db), pb, dv[db]);
+        dk[db] = mfma32(frag_tr<D>(q, to, t * 16, db), dsb, dk[db]);
+      }
+    }
+  }
+}
+
+// How the rows of a row tile are found.  kRowsNear: dense map, tensors within reach of a 32-bit offset (RowDmaOffsets).
+// kRowsFar: dense map, larger tensors; tokens are computed when a copy is issued.  kRowsListed: the map names rows by
+// explicit token lists (sampled / packed maps); their tokens are fetched an iteration before the copy that uses them.
+// (A near loop that carried every row's token and anchor as the far one does reloaded spilled registers behind its own
+// copies, and waited for them: dK/dV at L = 4,096 2,226 us, now 2,152.)
+enum { kRowsNear = 0, kRowsFar = 1, kRowsListed = 2 };
+template <int D, int ROWS, bool SV>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p) {
+  constexpr bool LISTED = ROWS == kRowsListed;
   constexpr int kTileBytes = kRowsPerTile * D * 2;
   constexpr int kBufBytes = 2 * kTileBytes + 2 * kRowsPerTile * 4;  // Q | dO | lse2 | delta
   constexpr int kLdsBytes = 2 * kBufBytes;
@@ -1210,44 +1290,65 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
 
   // Q / dO row tiles and their per-row terms (-lse/scale, -Delta, prepared by the dQ kernel) go
   // straight from global memory into the LDS buffer that the next iteration reads.
-  const RowDmaLane<D, 4> rl = row_dma_lane<D, 4>(tm, p.L, wave, lane, p.Hq);
   using Toks = RowTokens<D, 4>;
-  // dense map whose row tiles hold 128 real rows, tensors within reach of a 32-bit offset: copies of whole row
-  // tiles take the short form
-  const bool fast_rows = !LISTED && tm.A * tm.K == kRowsPerTile && p.fast_rows;
-  // The rows a lane copies are kRowsApart apart; when that is a whole number of depths (A divides it), copy i
-  // reads fast_step elements behind copy i-1 for every lane: the step goes into the scalar base and one per-lane
-  // offset serves all copies.  Otherwise (fast_step = 0) each copy has its own per-lane offset.
+  RowDmaLane<D, 4> rl;
+  RowDmaOffsets<D, 4> ro;
+  if (ROWS == kRowsNear) ro = row_dma_offsets<D, 4>(tm, p.L, wave, lane, p.Hq);
+  else rl = row_dma_lane<D, 4>(tm, p.L, wave, lane);
+  // The rows a lane copies are kRowsApart apart; when that is a whole number of anchors (K divides it), copy i
+  // reads near_step elements behind copy i-1 for every lane: the step goes into the scalar base and one per-lane
+  // offset serves all copies.  Otherwise (near_step = 0) each copy has its own per-lane offset.
   constexpr int kRowsApart = 4 * (512 / D);
-  const size_t fast_step = kRowsApart % tm.A == 0 ? (size_t)(kRowsApart / tm.A) * p.L * p.Hq * D : 0;
-  // Everything but the one per-lane offset is computed on the scalar unit from values forced wave-uniform (the
+  const size_t near_step = kRowsApart % tm.K == 0 ? (size_t)(kRowsApart / tm.K) * p.Hq * D : 0;
+  // Everything but the per-lane offset is computed on the scalar unit from values forced wave-uniform (the
   // compiler otherwise carries the row tile and head in vector registers and builds each copy's 64-bit
   // address there): LDS addresses are plain integers from the buffer's base, the source pointers scalar
-  // multiplies and adds, and the choice between the two forms is made once, not per copy.
+  // multiplies and adds, and the choice between the forms is made once, not per copy.
   const uint32_t lds_addr0 = lds_scalar_addr(lds);
   const uint32_t wave_s = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
   constexpr int kPer = RowDmaLane<D, 4>::kPer;
-  auto issue_fast = [&](int hh, int rt, int buf) {
+  auto issue_near = [&](int hh, int rt, int buf) {
     const int hh_s = __builtin_amdgcn_readfirstlane(hh), rt_s = __builtin_amdgcn_readfirstlane(rt);
     const uint32_t dst = lds_addr0 + (uint32_t)buf * kBufBytes + wave_s * 1024;
     const size_t row0 = ((size_t)rt_s * tm.A * p.Hq + hh_s) * D;
     const __bf16* qs = p.q + row0;
     const __bf16* ds = p.d_o + row0;
-    if (fast_step) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) dma16_untracked(qs + i * fast_step, rl.fast_off[0], dst + i * 4 * 1024);
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) dma16_untracked(ds + i * fast_step, rl.fast_off[0], dst + kTileBytes + i * 4 * 1024);
-    } else {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) dma16_untracked(qs, rl.fast_off[i], dst + i * 4 * 1024);
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) dma16_untracked(ds, rl.fast_off[i], dst + kTileBytes + i * 4 * 1024);
-    }
     const float* stat0 = (wave_s < 2 ? p.nlse : p.delta) + (size_t)hh_s * p.T + (size_t)rt_s * tm.A;
-    dma4_untracked(stat0, rl.fast_stat_off,
-                   lds_addr0 + (uint32_t)buf * kBufBytes + 2 * kTileBytes + (wave_s < 2 ? 0 : kRowsPerTile * 4) +
-                       (wave_s & 1) * 64 * 4);
+    const uint32_t stat_dst = lds_addr0 + (uint32_t)buf * kBufBytes + 2 * kTileBytes + (wave_s < 2 ? 0 : kRowsPerTile * 4) +
+                              (wave_s & 1) * 64 * 4;
+    // rows are ordered anchor by anchor: those that exist are the first n_valid
+    const int left = p.L - rt_s * tm.A, n_valid = (left < tm.A ? left : tm.A) * tm.K;
+    if (n_valid == kRowsPerTile) {
+      if (near_step) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) dma16_untracked(qs + i * near_step, ro.off[0], dst + i * 4 * 1024);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) dma16_untracked(ds + i * near_step, ro.off[0], dst + kTileBytes + i * 4 * 1024);
+      } else {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) dma16_untracked(qs, ro.off[i], dst + i * 4 * 1024);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) dma16_untracked(ds, ro.off[i], dst + kTileBytes + i * 4 * 1024);
+      }
+      dma4_untracked(stat0, ro.stat_off, stat_dst);
+      return;
+    }
+    // (the last row tile of the sequence, and every tile of a map with A * K < 128: only the copies that hold rows
+    // past n_valid need per-lane addresses, which take those rows from the zero page)
+    const int row = (int)wave_s * (512 / D) + lane / (D / 8);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if ((int)(i * 4 + wave_s + 1) * (512 / D) <= n_valid) {
+        dma16_untracked(qs, ro.off[i], dst + i * 4 * 1024);
+        dma16_untracked(ds, ro.off[i], dst + kTileBytes + i * 4 * 1024);
+      } else {
+        const bool ok = row + i * kRowsApart < n_valid;
+        dma16_untracked(ok ? (const void*)((const char*)qs + ro.off[i]) : tm.zeros, dst + i * 4 * 1024);
+        dma16_untracked(ok ? (const void*)((const char*)ds + ro.off[i]) : tm.zeros, dst + kTileBytes + i * 4 * 1024);
+      }
+    }
+    const bool ok = (int)(wave_s & 1) * 64 + lane < n_valid;
+    dma4_untracked(ok ? (const void*)((const char*)stat0 + ro.stat_off) : tm.zeros, stat_dst);
   };
   auto issue = [&](int hh, const Toks& t, int buf) {
     char* base = lds + buf * kBufBytes;
@@ -1291,9 +1392,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   int rt_n = 0, rt_a = 0, mask_c = kSkip, mask_n = kSkip;
   Toks tok_n{};
   if (n_iter > 0) {
-    const Toks t0 = row_tokens<D, 4, LISTED>(tm, rl, take_entry(fetch_row_tile(0)).tile, p.L);
-    issue(h_lo, t0, 0);
-    tok_n = t0;
+    const int rt0 = take_entry(fetch_row_tile(0)).tile;
+    if (ROWS == kRowsNear) {
+      issue_near(h_lo, rt0, 0);
+    } else {
+      tok_n = row_tokens<D, 4, LISTED>(tm, rl, rt0, p.L);
+      issue(h_lo, tok_n, 0);
+    }
     mask_c = mask_of(0, take_entry(fetch_mask(0)));
     step(ei_n, hh_n);
     step(ei_a, hh_a);
@@ -1310,171 +1415,189 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   }
   dma_publish();
 
-  for (int it = 0; it < n_iter; ++it) {
-    const int buf = it & 1;
-    const bool have2 = it + 2 < n_iter, have3 = it + 3 < n_iter;
-    Toks tok_a = tok_n;
-    if (LISTED) {
-      if (have2) tok_a = row_tokens<D, 4, LISTED>(tm, rl, rt_a, p.L);
-      if (it + 1 < n_iter) issue(hh_n, tok_n, buf ^ 1);
-    } else {
-      if (it + 1 < n_iter) {
-        if (fast_rows && (rt_n + 1) * tm.A <= p.L) issue_fast(hh_n, rt_n, buf ^ 1);
-        else issue(hh_n, row_tokens<D, 4, LISTED>(tm, rl, rt_n, p.L), buf ^ 1);
+  auto run = [&](auto chain_tag) {
+    constexpr bool CHAIN = decltype(chain_tag)::value;
+    for (int it = 0; it < n_iter; ++it) {
+      const int buf = it & 1;
+      const bool have2 = it + 2 < n_iter, have3 = it + 3 < n_iter;
+      Toks tok_a = tok_n;
+      if (LISTED) {
+        if (have2) tok_a = row_tokens<D, 4, LISTED>(tm, rl, rt_a, p.L);
+        if (it + 1 < n_iter) issue(hh_n, tok_n, buf ^ 1);
+      } else {
+        if (it + 1 < n_iter) {
+          if (ROWS == kRowsNear) issue_near(hh_n, rt_n, buf ^ 1);
+          else issue(hh_n, row_tokens<D, 4, LISTED>(tm, rl, rt_n, p.L), buf ^ 1);
+        }
       }
-    }
-    // (fetched after the copies were issued: anything the copy code has to wait for - a reloaded register -
-    // then finds no list load in flight)
-    const u32x2 rt_raw = fetch_row_tile(have3 ? ei_b : 0);
-    const u32x2 mask_raw = fetch_mask(have2 ? ei_a : 0);
-    if (mask_c != kSkip) {
-      const char* q_lds = lds + buf * kBufBytes;
-      const char* do_lds = q_lds + kTileBytes;
-      const float* lse_lds = reinterpret_cast<const float*>(q_lds + 2 * kTileBytes);
-      const float* delta_lds = lse_lds + kRowsPerTile;
-      if (mask_c == -1) {
-        dkdv_rowtile_pipelined<D, 0>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
-      } else if (mask_c >= 0) {
-        // which of the tile's 128 rows see this lane's key: four words, one per 32-row unit
-        // (scalar base + small per-lane offset: no 64-bit per-lane address is kept across the loop)
-        const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
-        const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
-        dkdv_rowtile_pipelined<D, 1>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, false, cm);
-      } else if (LISTED) {  // only packed maps carry such ids
-        const bool lane_off = key_anchor < -mask_c - 2;
-        dkdv_rowtile_pipelined<D, 2>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, lane_off);
+      // (fetched after the copies were issued: anything the copy code has to wait for - a reloaded register -
+      // then finds no list load in flight)
+      const u32x2 rt_raw = fetch_row_tile(have3 ? ei_b : 0);
+      const u32x2 mask_raw = fetch_mask(have2 ? ei_a : 0);
+      if (mask_c != kSkip) {
+        const char* q_lds = lds + buf * kBufBytes;
+        const char* do_lds = q_lds + kTileBytes;
+        const float* lse_lds = reinterpret_cast<const float*>(q_lds + 2 * kTileBytes);
+        const float* delta_lds = lse_lds + kRowsPerTile;
+        if (CHAIN) {  // (chain tiles always carry a bitmask)
+          const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
+          const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
+          dkdv_rowtile_chain<D>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, cm);
+        } else if (mask_c == -1) {
+          dkdv_rowtile_pipelined<D, 0>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
+        } else if (mask_c >= 0) {
+          // which of the tile's 128 rows see this lane's key: four words, one per 32-row unit
+          // (scalar base + small per-lane offset: no 64-bit per-lane address is kept across the loop)
+          const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
+          const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
+          if (__builtin_amdgcn_ballot_w64((cm[0] | cm[1] | cm[2] | cm[3]) != 0) != 0)  // (else: every key is in the rows' future)
+            dkdv_rowtile_pipelined<D, 1>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, false, cm);
+        } else if (LISTED) {  // only packed maps carry such ids
+          const bool lane_off = key_anchor < -mask_c - 2;
+          dkdv_rowtile_pipelined<D, 2>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, lane_off);
+        }
       }
+      dma_publish();
+      if (LISTED) tok_n = tok_a;
+      rt_n = rt_a;
+      rt_a = take_entry(rt_raw).tile;
+      mask_c = mask_n;
+      mask_n = have2 ? mask_of(ei_a, take_entry(mask_raw)) : kSkip;
+      step(ei_n, hh_n);
+      step(ei_a, hh_a);
+      step(ei_b, hh_b);
     }
-    dma_publish();
-    if (LISTED) tok_n = tok_a;
-    rt_n = rt_a;
-    rt_a = take_entry(rt_raw).tile;
-    mask_c = mask_n;
-    mask_n = have2 ? mask_of(ei_a, take_entry(mask_raw)) : kSkip;
-    step(ei_n, hh_n);
-    step(ei_a, hh_a);
-    step(ei_b, hh_b);
-  }
+  };
+  // store from registers: lane <-> key, registers <-> d = db*32 + 8*q4 + 4g + j
+  auto store = [&](auto chain_tag) {
+    constexpr bool CHAIN = decltype(chain_tag)::value;
+    if (SV && CHAIN) {
+      // First-layer form: the chain keys' gradients are only ever needed summed over the keys (they all come from
+      // one shared vector), so each wave adds up its 32 keys here - dK after it has been turned back to the
+      // unrotated frame, key by key - and stores one row of D sums per tensor.  The sum over keys runs across
+      // lanes: the wave lays its values out in LDS as [d][key] (33 floats per d: conflict-free both ways) and lane
+      // l adds up row d = l (and l + 64).  The row tiles' buffers are free: every wave is past the loop's last
+      // barrier.  Keys that do not exist contribute zero.
+      float* red = reinterpret_cast<float*>(lds) + (size_t)wave * (D * 33);
+      static_assert(4 * D * 33 * 4 <= kLdsBytes, "the four waves' transposition buffers must fit");
+      const bool have = tile_present && key_ok;
+      const float* rope = p.rope_table && have ? p.rope_table + (size_t)token_position(tm, key_tok, p.L) * D : nullptr;
+      const int b_chain = (int)blockIdx.x - p.n_d0_items;
+      const int n_cpair = (tm.n_csub + 1) / 2;
+      const size_t prow = ((size_t)(p.rt_lo + b_chain / p.Hkv / n_cpair) * n_cpair + (b_chain / p.Hkv) % n_cpair) * 4 + wave;
+  #pragma unroll
+      for (int which = 0; which < 2; ++which) {  // 0: dK, 1: dV
+        if (which == 0 && rope) {
+  #pragma unroll
+          for (int db = 0; db < D / 64; ++db)
+  #pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+              const int d0 = db * 32 + 8 * q4 + 4 * g;
+              f32x4 lo, hi;
+  #pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                lo[j] = dk[db][4 * q4 + j];
+                hi[j] = dk[db + D / 64][4 * q4 + j];
+              }
+              rope_turn4<true>(lo, hi, *reinterpret_cast<const f32x4*>(rope + d0),
+                               *reinterpret_cast<const f32x4*>(rope + D / 2 + d0));
+  #pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                dk[db][4 * q4 + j] = lo[j];
+                dk[db + D / 64][4 * q4 + j] = hi[j];
+              }
+            }
+        }
+  #pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+  #pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int d = db * 32 + 8 * (i / 4) + 4 * g + (i % 4);
+            const float x = which ? dv[db][i] : dk[db][i] * p.scale;
+            red[d * 33 + ln] = have ? x : 0.f;
+          }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the wave's own LDS writes have landed
+        float* out = (which ? p.shared_dv_part : p.shared_dk_part) + (prow * p.Hkv + kvh) * D;
+  #pragma unroll
+        for (int d = lane; d < D; d += 64) {
+          float sum = 0.f;
+  #pragma unroll
+          for (int j = 0; j < 32; ++j) sum += red[d * 33 + j];
+          out[d] = sum;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // ... and its reads, before the buffer is written again
+      }
+      return;
+    }
 
-  if (SV && chain) {
-    // First-layer form: the chain keys' gradients are only ever needed summed over the keys (they all come from
-    // one shared vector), so each wave adds up its 32 keys here - dK after it has been turned back to the
-    // unrotated frame, key by key - and stores one row of D sums per tensor.  The sum over keys runs across
-    // lanes: the wave lays its values out in LDS as [d][key] (33 floats per d: conflict-free both ways) and lane
-    // l adds up row d = l (and l + 64).  The row tiles' buffers are free: every wave is past the loop's last
-    // barrier.  Keys that do not exist contribute zero.
-    float* red = reinterpret_cast<float*>(lds) + (size_t)wave * (D * 33);
-    static_assert(4 * D * 33 * 4 <= kLdsBytes, "the four waves' transposition buffers must fit");
-    const bool have = tile_present && key_ok;
-    const float* rope = p.rope_table && have ? p.rope_table + (size_t)token_position(tm, key_tok, p.L) * D : nullptr;
-    const int b_chain = (int)blockIdx.x - p.n_d0_items;
-    const int n_cpair = (tm.n_csub + 1) / 2;
-    const size_t prow = ((size_t)(p.rt_lo + b_chain / p.Hkv / n_cpair) * n_cpair + (b_chain / p.Hkv) % n_cpair) * 4 + wave;
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {  // 0: dK, 1: dV
-      if (which == 0 && rope) {
-#pragma unroll
+    if (tile_present) {
+      float* dkd;
+      float* dvd;
+      bool write = true, accumulate = false;
+      if (!CHAIN) {
+        const size_t row = (size_t)h_lo * p.L64 + (size_t)kt * kKeysPerTile + (kblk & 1) * 32 + ln;
+        dkd = p.dk_part + row * D;
+        dvd = p.dv_part + row * D;
+      } else {
+        write = key_ok;
+        accumulate = p.chain_accumulate != 0;
+        const size_t row = (size_t)(key_ok ? key_tok : 0) * p.Hkv + kvh;
+        dkd = p.dk_acc + row * D;
+        dvd = p.dv_acc + row * D;
+      }
+      if (CHAIN && write && p.rope_table) {
+        // k was the rotated copy: turn the chain keys' dK back (lane <-> key, both members of a feature
+        // pair in its registers).  Depth-0 keys are turned back where their per-head partials are summed.
+        const float* rope = p.rope_table + (size_t)token_position(tm, key_tok, p.L) * D;
+  #pragma unroll
         for (int db = 0; db < D / 64; ++db)
-#pragma unroll
+  #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) {
             const int d0 = db * 32 + 8 * q4 + 4 * g;
             f32x4 lo, hi;
-#pragma unroll
+  #pragma unroll
             for (int j = 0; j < 4; ++j) {
               lo[j] = dk[db][4 * q4 + j];
               hi[j] = dk[db + D / 64][4 * q4 + j];
             }
             rope_turn4<true>(lo, hi, *reinterpret_cast<const f32x4*>(rope + d0),
                              *reinterpret_cast<const f32x4*>(rope + D / 2 + d0));
-#pragma unroll
+  #pragma unroll
             for (int j = 0; j < 4; ++j) {
               dk[db][4 * q4 + j] = lo[j];
               dk[db + D / 64][4 * q4 + j] = hi[j];
             }
           }
       }
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int d = db * 32 + 8 * (i / 4) + 4 * g + (i % 4);
-          const float x = which ? dv[db][i] : dk[db][i] * p.scale;
-          red[d * 33 + ln] = have ? x : 0.f;
-        }
-      asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the wave's own LDS writes have landed
-      float* out = (which ? p.shared_dv_part : p.shared_dk_part) + (prow * p.Hkv + kvh) * D;
-#pragma unroll
-      for (int d = lane; d < D; d += 64) {
-        float sum = 0.f;
-#pragma unroll
-        for (int j = 0; j < 32; ++j) sum += red[d * 33 + j];
-        out[d] = sum;
+      if (write) {
+  #pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+  #pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            f32x4 a, c;
+  #pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              a[j] = dk[db][4 * q4 + j] * p.scale;
+              c[j] = dv[db][4 * q4 + j];
+            }
+            const int d0 = db * 32 + 8 * q4 + 4 * g;
+            if (accumulate) {
+              a += *reinterpret_cast<const f32x4*>(dkd + d0);
+              c += *reinterpret_cast<const f32x4*>(dvd + d0);
+            }
+            *reinterpret_cast<f32x4*>(dkd + d0) = a;
+            *reinterpret_cast<f32x4*>(dvd + d0) = c;
+          }
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // ... and its reads, before the buffer is written again
     }
-    return;
-  }
-
-  // store from registers: lane <-> key, registers <-> d = db*32 + 8*q4 + 4g + j
-  if (tile_present) {
-    float* dkd;
-    float* dvd;
-    bool write = true, accumulate = false;
-    if (!chain) {
-      const size_t row = (size_t)h_lo * p.L64 + (size_t)kt * kKeysPerTile + (kblk & 1) * 32 + ln;
-      dkd = p.dk_part + row * D;
-      dvd = p.dv_part + row * D;
-    } else {
-      write = key_ok;
-      accumulate = p.chain_accumulate != 0;
-      const size_t row = (size_t)(key_ok ? key_tok : 0) * p.Hkv + kvh;
-      dkd = p.dk_acc + row * D;
-      dvd = p.dv_acc + row * D;
-    }
-    if (write && chain && p.rope_table) {
-      // k was the rotated copy: turn the chain keys' dK back (lane <-> key, both members of a feature
-      // pair in its registers).  Depth-0 keys are turned back where their per-head partials are summed.
-      const float* rope = p.rope_table + (size_t)token_position(tm, key_tok, p.L) * D;
-#pragma unroll
-      for (int db = 0; db < D / 64; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int d0 = db * 32 + 8 * q4 + 4 * g;
-          f32x4 lo, hi;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            lo[j] = dk[db][4 * q4 + j];
-            hi[j] = dk[db + D / 64][4 * q4 + j];
-          }
-          rope_turn4<true>(lo, hi, *reinterpret_cast<const f32x4*>(rope + d0),
-                           *reinterpret_cast<const f32x4*>(rope + D / 2 + d0));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            dk[db][4 * q4 + j] = lo[j];
-            dk[db + D / 64][4 * q4 + j] = hi[j];
-          }
-        }
-    }
-    if (write) {
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          f32x4 a, c;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            a[j] = dk[db][4 * q4 + j] * p.scale;
-            c[j] = dv[db][4 * q4 + j];
-          }
-          const int d0 = db * 32 + 8 * q4 + 4 * g;
-          if (accumulate) {
-            a += *reinterpret_cast<const f32x4*>(dkd + d0);
-            c += *reinterpret_cast<const f32x4*>(dvd + d0);
-          }
-          *reinterpret_cast<f32x4*>(dkd + d0) = a;
-          *reinterpret_cast<f32x4*>(dvd + d0) = c;
-        }
-    }
+  };
+  // (two loops and two epilogues: accumulators that meet again behind them cost spills)
+  if (chain) {
+    run(std::true_type{});
+    store(std::true_type{});
+  } else {
+    run(std::false_type{});
+    store(std::false_type{});
   }
 }
 
@@ -2033,15 +2156,15 @@ hipError_t launch_bwd(const BwdParams& pin, int D, int key_lo, int a_hi, int acc
     {
       const dim3 grid((unsigned)(p.n_d0_items + n_chain_items));
       TimedSpan span(timer, kKindDkDv, stream);
-      const bool listed = p.tm.row_tok != nullptr;
       auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p); };
-      if (D == 64) {
-        if (listed) sv_dkdv ? go(dkdv_kernel<64, true, true>) : go(dkdv_kernel<64, true, false>);
-        else sv_dkdv ? go(dkdv_kernel<64, false, true>) : go(dkdv_kernel<64, false, false>);
-      } else {
-        if (listed) sv_dkdv ? go(dkdv_kernel<128, true, true>) : go(dkdv_kernel<128, true, false>);
-        else sv_dkdv ? go(dkdv_kernel<128, false, true>) : go(dkdv_kernel<128, false, false>);
-      }
+      auto pick = [&](auto rows) {
+        constexpr int ROWS = decltype(rows)::value;
+        if (D == 64) sv_dkdv ? go(dkdv_kernel<64, ROWS, true>) : go(dkdv_kernel<64, ROWS, false>);
+        else sv_dkdv ? go(dkdv_kernel<128, ROWS, true>) : go(dkdv_kernel<128, ROWS, false>);
+      };
+      if (listed_map) pick(std::integral_constant<int, kRowsListed>{});
+      else if (p.near_rows) pick(std::integral_constant<int, kRowsNear>{});
+      else pick(std::integral_constant<int, kRowsFar>{});
       hipError_t e = span.finish();
       if (e != hipSuccess) return e;
     }

@@ -67,13 +67,18 @@ void build_key_lists(peagle_tilemap* tm) {
   // sequence may start inside or after tile 2m: its row tiles see 2m+1 only, and they come after
   // every row tile that sees 2m - they are appended to the list of 2m with the id INT32_MIN, which
   // tells the waves that own the keys of 2m to sit the iteration out.
-  for (int32_t t0 = 0; t0 + 1 < tm->n_d0; t0 += 2) {
+  // The two chain tiles of a sampled row tile are such a pair too: the first is not listed when its slots hold depth-0
+  // rows only.
+  auto append_missing = [&](int32_t t0) {
     std::vector<TileEntry>& first = lists[t0];
     const std::vector<TileEntry>& second = lists[t0 + 1];
     const int32_t last_first = first.empty() ? -1 : first.back().tile;
     for (const TileEntry& en : second)
       if (en.tile > last_first) first.push_back(TileEntry{en.tile, INT32_MIN});
-  }
+  };
+  for (int32_t t0 = 0; t0 + 1 < tm->n_d0; t0 += 2) append_missing(t0);
+  if (tm->n_csub == 2)
+    for (int32_t t0 = tm->n_d0; t0 + 1 < tm->n_key_tiles; t0 += 2) append_missing(t0);
   tm->key_ptr.assign(tm->n_key_tiles + 1, 0);
   for (int32_t t = 0; t < tm->n_key_tiles; ++t) tm->key_ptr[t + 1] = tm->key_ptr[t] + (int32_t)lists[t].size();
   tm->key_entries.clear();
@@ -177,6 +182,8 @@ int upload_map(peagle_tilemap* tm, hipStream_t stream, bool wait) {
   tm->dview.masks_by_key = (const uint32_t*)(base + off[11]);
   tm->dview.A = tm->A;
   tm->dview.K = tm->K;
+  tm->dview.chain_slots = tm->chain_slots;
+  tm->dview.chain_first = tm->chain_first;
   tm->dview.S = tm->S;
   tm->dview.n_row_tiles = tm->n_row_tiles;
   tm->dview.n_d0 = tm->n_d0;
@@ -250,8 +257,13 @@ extern "C" int peagle_build_tilemap(int32_t L_max, int32_t K, const int32_t* seg
 
   tm->n_row_tiles = (L_max + A - 1) / A;
   tm->n_d0 = (L_max + kKeysPerTile - 1) / kKeysPerTile;
-  const int32_t chain_keys = A * (K - 1);
-  tm->n_csub = (chain_keys + kKeysPerTile - 1) / kKeysPerTile;
+  tm->n_csub = (A * (K - 1) + kKeysPerTile - 1) / kKeysPerTile;
+  // Chain keys sit in the slots of their own rows (row r of the tile <-> slot r, the slots of depth 0 unused): the
+  // chain part of the mask is then block-diagonal, and a wave's 32 rows see one 32-key block of it (K a divisor of
+  // 32) or two.  Where the unused slots would cost a key tile (K = 2) the slots hold depths 1 .. K-1 only.
+  const bool own_slots = (A * K + kKeysPerTile - 1) / kKeysPerTile == tm->n_csub;
+  tm->chain_slots = own_slots ? K : K - 1;
+  tm->chain_first = own_slots ? 0 : 1;
   const int64_t n_kt = (int64_t)tm->n_d0 + (int64_t)tm->n_row_tiles * tm->n_csub;
   if (n_kt > (int64_t)1 << 30) {
     delete tm;
@@ -278,27 +290,27 @@ extern "C" int peagle_build_tilemap(int32_t L_max, int32_t K, const int32_t* seg
       } else {
         std::fill(bits.begin(), bits.end(), 0u);
         for (int r = 0; r < rows_used; ++r) {
-          const int d = r / A;
-          const int64_t i = i0 + r % A;
+          const int64_t i = i0 + r / K;
           for (int kk = 0; kk < kKeysPerTile; ++kk)
-            if (sees(i, d, j0 + kk, 0)) bits[r * kMaskWordsPerRow + kk / 32] |= 1u << (kk % 32);
+            if (sees(i, r % K, j0 + kk, 0)) bits[r * kMaskWordsPerRow + kk / 32] |= 1u << (kk % 32);
         }
         en.mask_id = pool.intern(bits);
         ++tm->n_partial;
       }
       tm->row_entries.push_back(en);
     }
-    // chain stream: key kk of the stream is depth 1 + kk/A, anchor i0 + kk%A
+    // chain stream: slot ck is anchor i0 + ck / chain_slots, depth chain_first + ck % chain_slots
     for (int32_t s = 0; s < tm->n_csub; ++s) {
       std::fill(bits.begin(), bits.end(), 0u);
       bool any = false;
       for (int r = 0; r < rows_used; ++r) {
-        const int d = r / A;
-        const int64_t i = i0 + r % A;
+        const int d = r % K;
+        const int64_t i = i0 + r / K;
         for (int kk = 0; kk < kKeysPerTile; ++kk) {
           const int ck = s * kKeysPerTile + kk;
-          if (ck >= chain_keys) break;
-          if (sees(i, d, i0 + ck % A, 1 + ck / A)) {
+          if (ck >= A * tm->chain_slots) break;
+          const int e = tm->chain_first + ck % tm->chain_slots;
+          if (e >= 1 && sees(i, d, i0 + ck / tm->chain_slots, e)) {
             bits[r * kMaskWordsPerRow + kk / 32] |= 1u << (kk % 32);
             any = true;
           }
@@ -456,7 +468,8 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
     tm->seg_key_lo[sg] = seq_lo[first];
   }
   tm->n_d0 = (L + kKeysPerTile - 1) / kKeysPerTile;
-  tm->n_csub = K > 1 ? kRowsPerTile / kKeysPerTile : 0;  // a tile's chain keys are rows minus anchors: < 128
+  tm->n_csub = K > 1 ? kRowsPerTile / kKeysPerTile : 0;  // a chain key sits in the slot of its own row
+  tm->chain_slots = tm->chain_first = 0;                 // (they are listed, not computed)
   tm->n_key_tiles = tm->n_d0 + tm->n_row_tiles * tm->n_csub;
 
   // the masks depend on the sample and on where sequences start; equal ones are stored once
@@ -472,31 +485,24 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
     ids.push_back(tm->n_masks);
     return tm->n_masks++;
   };
-  std::vector<int32_t> chain_index((size_t)K * kRowsPerTile);  // [depth][anchor - a0] -> index in the tile's chain list
   tm->row_ptr.assign(tm->n_row_tiles + 1, 0);
   tm->row_tok.assign((size_t)tm->n_row_tiles * kRowsPerTile, -1);
   tm->chain_tok.assign((size_t)tm->n_row_tiles * tm->n_csub * kKeysPerTile, -1);
-  std::vector<int32_t> row_a(kRowsPerTile), row_d(kRowsPerTile), key_a, key_e;
+  std::vector<int32_t> row_a(kRowsPerTile), row_d(kRowsPerTile);
   for (int32_t R = 0; R < tm->n_row_tiles; ++R) {
     const int32_t a0 = tile_a0[R], a1 = tile_a1[R];
-    // rows of the tile, depth-major like the dense tile; chain keys = its rows of depth >= 1
+    // rows of the tile, anchor by anchor like the dense tile; its chain keys are its rows of depth >= 1, each in the
+    // slot of its own row (the slots of depth-0 rows stay empty)
     int rows_used = 0;
-    key_a.clear();
-    key_e.clear();
     const int32_t sg = tile_seg[R];
-    for (int32_t g = 0; g < K; ++g)
-      for (int32_t i = a0; i < a1; ++i)
-        if (depth_count[i] > g && (g == 0 ? seg_of_pos[i] : chain_seg(i)) == sg) {
+    for (int32_t i = a0; i < a1; ++i)
+      for (int32_t g = 0; g < depth_count[i]; ++g)
+        if ((g == 0 ? seg_of_pos[i] : chain_seg(i)) == sg) {
           row_a[rows_used] = i;
           row_d[rows_used] = g;
           tm->row_tok[(size_t)R * kRowsPerTile + rows_used] = tok_of[(size_t)g * L + i];
           tm->tok_pos[tok_of[(size_t)g * L + i]] = (int64_t)R * kRowsPerTile + rows_used;
           ++rows_used;
-          if (g >= 1) {
-            chain_index[(size_t)g * kRowsPerTile + (i - a0)] = (int32_t)key_a.size();
-            key_a.push_back(i);
-            key_e.push_back(g);
-          }
         }
     // depth-0 stream: keys of the tile's own sequence up to its last anchor.  Depth-0 keys are causal
     // in the anchor inside a sequence (sees(i, d, j, 0) == j <= i), so row r sees the keys
@@ -531,21 +537,26 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
     tm->key_side_id.insert(tm->key_side_id.end(), partial_key_ids.begin(), partial_key_ids.end());
     // chain stream
     for (int32_t sub = 0; sub < tm->n_csub; ++sub) {
-      const size_t k0 = (size_t)sub * kKeysPerTile;
-      if (k0 >= key_a.size()) break;
+      const int k0 = sub * kKeysPerTile;
       std::fill(bits.begin(), bits.end(), 0u);
       const int32_t kt = tm->n_d0 + R * tm->n_csub + sub;
-      for (int kk = 0; kk < kKeysPerTile && k0 + kk < key_a.size(); ++kk) {
-        const int32_t ja = key_a[k0 + kk], je = key_e[k0 + kk];
-        tm->chain_tok[((size_t)R * tm->n_csub + sub) * kKeysPerTile + kk] = tok_of[(size_t)je * L + ja];
-      }
-      // a chain key (j, e) is seen by the rows of its own anchor at depths >= e (sees(i, d, j, e) ==
-      // (j == i && e <= d)): walk each row's own chain instead of testing all pairs
-      for (int r = 0; r < rows_used; ++r)
-        for (int e = 1; e <= row_d[r]; ++e) {
-          const int64_t ck = (int64_t)chain_index[(size_t)e * kRowsPerTile + (row_a[r] - a0)] - (int64_t)k0;
-          if (ck >= 0 && ck < kKeysPerTile) bits[r * kMaskWordsPerRow + ck / 32] |= 1u << (ck % 32);
+      bool any = false;
+      for (int r = k0; r < rows_used && r < k0 + kKeysPerTile; ++r)
+        if (row_d[r] >= 1) {
+          tm->chain_tok[(size_t)R * kRowsPerTile + r] = tm->row_tok[(size_t)R * kRowsPerTile + r];
+          any = true;
         }
+      if (!any) continue;
+      // a chain key (j, e) is seen by the rows of its own anchor at depths >= e (sees(i, d, j, e) ==
+      // (j == i && e <= d)): the rows of an anchor follow one another, so row r of depth d sees the slots
+      // r - d + 1 .. r
+      for (int r = 0; r < rows_used; ++r) {
+        const int lo = std::max(0, r - row_d[r] + 1 - k0), hi = std::min(kKeysPerTile - 1, r - k0);  // inclusive
+        if (hi < lo) continue;
+        const uint64_t m = (hi >= 63 ? ~0ull : ((1ull << (hi + 1)) - 1)) & ~((1ull << lo) - 1);
+        bits[r * kMaskWordsPerRow] = (uint32_t)m;
+        bits[r * kMaskWordsPerRow + 1] = (uint32_t)(m >> 32);
+      }
       tm->row_entries.push_back(TileEntry{kt, append_mask(bits)});
       tm->key_side_id.push_back(tm->row_entries.back().mask_id);
       ++tm->n_partial;
@@ -656,7 +667,6 @@ extern "C" int peagle_tilemap_expand_rows(const peagle_tilemap_t* tm, int32_t L,
   if (row_begin < 0 || row_end < row_begin || row_end > T) return PEAGLE_EINVAL;
   const int64_t row_bytes = (T + 7) / 8;
   const int A = tm->A;
-  const int chain_keys = A * (tm->K - 1);
   std::memset(bits_out, 0, (size_t)((row_end - row_begin) * row_bytes));
   for (int64_t t = row_begin; t < row_end; ++t) {
     int32_t R;
@@ -670,7 +680,7 @@ extern "C" int peagle_tilemap_expand_rows(const peagle_tilemap_t* tm, int32_t L,
       const int d = (int)(t / L);
       if (i < sr.a_lo || i >= sr.a_hi) continue;
       R = (int32_t)(i / A);
-      r = d * A + (int)(i % A);  // row inside the tile
+      r = (int)(i % A) * tm->K + d;  // row inside the tile
     }
     uint8_t* dst = bits_out + (t - row_begin) * row_bytes;
     for (int32_t e = tm->row_ptr[R]; e < tm->row_ptr[R + 1]; ++e) {
@@ -689,10 +699,11 @@ extern "C" int peagle_tilemap_expand_rows(const peagle_tilemap_t* tm, int32_t L,
         } else {
           const int32_t cid = en.tile - tm->n_d0;
           const int ck = (cid % tm->n_csub) * kKeysPerTile + kk;
-          if (ck >= chain_keys) continue;
-          const int64_t j = (int64_t)(cid / tm->n_csub) * A + ck % A;
-          if (j >= L) continue;
-          tok = (int64_t)(1 + ck / A) * L + j;
+          if (ck >= A * tm->chain_slots) continue;
+          const int e = tm->chain_first + ck % tm->chain_slots;
+          const int64_t j = (int64_t)(cid / tm->n_csub) * A + ck / tm->chain_slots;
+          if (e < 1 || j >= L) continue;
+          tok = (int64_t)e * L + j;
         }
         dst[tok >> 3] |= (uint8_t)(1u << (tok & 7));
       }

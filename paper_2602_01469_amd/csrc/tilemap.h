@@ -1,9 +1,9 @@
 // Internal representation of the tile map (host side) and the device view handed to kernels.
 //
 // Geometry (see include/peagle.h): a row tile is A = 128/K anchors at all K depths (dense map) or a
-// run of anchors whose kept positions fill 128 rows (sampled / packed maps); key tiles are 64 wide
-// and come from two streams (depth-0 anchors, and the chain positions of a row tile's own
-// anchors).  The classification follows the parallel-prediction mask of Sec. 3 of the paper.
+// run of anchors whose kept positions fill 128 rows (sampled / packed maps), its rows ordered anchor by
+// anchor; key tiles are 64 wide and come from two streams (depth-0 anchors, and the chain positions of a
+// row tile's own anchors, each in the slot of its row).  The classification follows the parallel-prediction mask of Sec. 3 of the paper.
 #pragma once
 
 #include <cstdint>
@@ -40,6 +40,8 @@ struct DeviceTileMap {
   const int32_t* chain_tok;   // sampled maps only: [n_row_tiles * n_csub][64] token of each chain key, -1 = none
   const int32_t* tok_posid;   // sampled maps only: [T] sequence position (anchor - sequence start + depth) of each token
   int32_t A, K, S, n_row_tiles, n_d0, n_csub, n_key_tiles;
+  int32_t chain_slots, chain_first;  // dense maps: chain slot ck of a row tile is anchor ck / chain_slots of the tile,
+                                     // depth chain_first + ck % chain_slots (depth 0: the slot is unused)
 };
 
 }  // namespace peagle
@@ -57,6 +59,7 @@ struct peagle_tilemap {
   std::vector<int32_t> tok_posid;                // sampled map: token -> sequence position (rotary embedding)
   int32_t max_posid = 0;                         // largest entry of tok_posid
   int32_t n_row_tiles = 0, n_d0 = 0, n_csub = 0, n_key_tiles = 0;
+  int32_t chain_slots = 0, chain_first = 0;      // dense map, see DeviceTileMap
   std::vector<int32_t> seg_bounds;               // [S+1] anchors
   std::vector<int32_t> row_ptr;
   std::vector<int32_t> row_lead;                 // leading full entries per row tile

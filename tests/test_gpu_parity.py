@@ -776,3 +776,35 @@ def test_partitioned_step_replays_from_a_hip_graph():
             assert np.array_equal(got[n], want[n]), (replay, n)
         eager.step(0, 2)                                # the program's own eager work between replays
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("D,Hq,Hkv", [(64, 128, 2), (128, 64, 2)])
+def test_tensors_beyond_4_gib_equal_their_halves(D, Hq, Hkv):
+    """Q-shaped tensors just over 4 GiB (row copies then form 64-bit addresses) against the same problem with the query
+    heads in two calls of half the size: heads do not interact, so every result has the same bits."""
+    L, K = 2049, 128
+    T = L * K
+    assert T * Hq * D * 2 >= 1 << 32 > T * Hq * D
+    print(f"case beyond 4 GiB D={D} Hq={Hq}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(77)
+    rnd = lambda *sh: torch.randn(*sh, generator=g, device="cuda", dtype=torch.bfloat16)
+    q, d_o, k, v = rnd(T, Hq, D), rnd(T, Hq, D), rnd(T, Hkv, D), rnd(T, Hkv, D)
+    tm = pe.peagle_build_tilemap(L, K, None, device=0)
+
+    def run(q, d_o, k, v):
+        shape = pe.Shape(L, K, q.shape[1], k.shape[1], D)
+        o, dq = torch.empty_like(q), torch.empty_like(q)
+        lse = torch.empty((q.shape[1], T), device="cuda")
+        dk, dv = (torch.empty(k.shape, device="cuda") for _ in range(2))
+        ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
+        pe.peagle_attn_step_partitioned(tm, shape, 0, 1, q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
+        torch.cuda.synchronize()
+        return {"o": o, "dq": dq, "dk": dk, "dv": dv, "lse": lse.t()}
+
+    whole = run(q, d_o, k, v)
+    for h in range(2):
+        a, b = slice(h * Hq // 2, (h + 1) * Hq // 2), slice(h, h + 1)
+        half = run(q[:, a].contiguous(), d_o[:, a].contiguous(), k[:, b].contiguous(), v[:, b].contiguous())
+        for n, t in half.items():
+            assert torch.isfinite(t).all(), n
+            assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n

@@ -51,6 +51,15 @@ def test_tilemap_expands_to_oracle_mask_bit_exact(L, K):
     assert inf["n_masks"] <= 2 * 64 + inf["n_chain_sub_tiles"]   # O(1): one per residue of the tile offset
 
 
+@pytest.mark.parametrize("L,K", [(3, 2), (65, 2), (130, 2), (43, 3), (26, 5), (19, 7), (3, 65), (3, 66), (2, 128)])
+def test_chain_key_slots(L, K):
+    """Chain keys sit in the slots of their rows, or packed where the empty depth-0 slots would cost a key tile (K = 2,
+    K = 65): there are as many chain tiles as the keys need, and the mask comes out bit for bit."""
+    tm = pe.peagle_build_tilemap(L, K, None, device=-1)
+    assert tm.info()["n_chain_sub_tiles"] == -(-(128 // K) * (K - 1) // 64)
+    assert np.array_equal(_expand_all(tm, L), orc.element_mask(L, K))
+
+
 @pytest.mark.parametrize("L_max,L,K", [(256, 219, 8), (256, 1, 8), (256, 64, 4), (500, 333, 3), (512, 500, 1)])
 def test_crop_is_prefix_view(L_max, L, K):
     """Per-example mask = crop of the maximum-length mask (Sec. 3.1): same tile map, shorter L."""
