@@ -2123,12 +2123,15 @@ hipError_t launch_bwd(const BwdParams& pin, int D, int key_lo, int a_hi, int acc
     hipError_t e = span.finish();
     if (e != hipSuccess) return e;
   }
-  // dK/dV runs over chunks of at most 64 row tiles (dense maps): within a chunk the key tiles below
-  // its first anchor have equally long lists, which balances the workgroups the way the paper's
-  // segments do; each chunk is followed by its own reduction, later chunks adding to what the
-  // earlier ones wrote.
+  // dK/dV of a dense map runs over equal chunks of at most 128 row tiles, each followed by its own reduction, later
+  // chunks adding to what the earlier ones wrote.  The key tiles below a chunk's first anchor have equally long
+  // lists, which balances the workgroups the way the paper's segments do; but a small last chunk leaves most of the
+  // chip idle, and every chunk writes and sums all partials again.  dK/dV + reduction, us, chunks of 64 / up to 128:
+  // L = 1,391 361 / 311 (D = 128 482 / 389), L = 2,600 1,006 / 976, ten segments of 2,048 anchors 49,000 / 48,100;
+  // chunks of 128 and a remainder lose at L = 2,600 (998), whole segments of any length at 3,000 anchors of D = 128
+  // (1,493 against 1,431).
   const bool listed_map = p.tm.row_tok != nullptr;
-  const int chunk = listed_map ? n_rt : 64;
+  const int n_chunks = listed_map ? 1 : (n_rt + 127) / 128, chunk = (n_rt + n_chunks - 1) / n_chunks;
   const int seg_rt_lo = p.rt_lo, seg_rt_hi = p.rt_hi;
   for (int c0 = seg_rt_lo; c0 < seg_rt_hi; c0 += chunk) {
     p.rt_lo = c0;
@@ -2146,9 +2149,9 @@ hipError_t launch_bwd(const BwdParams& pin, int D, int key_lo, int a_hi, int acc
       const int n_pairs = (p.n_d0_tiles - p.d0_tile_lo + 1) / 2;
       const int equal = c_acc == INT_MAX ? 0 : (c_acc / kKeysPerTile - p.d0_tile_lo) / 2;
       const int shrinking = n_pairs - (equal > 0 ? equal : 0);
-      constexpr int kPasses = 4;
+      constexpr int kPasses = 8;  // (four: dK/dV at 4,096 anchors in two chunks 2,231 instead of 2,178 us)
       p.d0_step = (shrinking + kPasses - 1) / kPasses;
-      if (p.d0_step < 2) p.d0_step = 2;
+      if (p.d0_step < 1) p.d0_step = 1;
       p.d0_split = n_pairs - shrinking + p.d0_step;
       if (p.d0_split > n_pairs) p.d0_split = n_pairs;
     }

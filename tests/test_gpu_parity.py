@@ -808,3 +808,21 @@ def test_tensors_beyond_4_gib_equal_their_halves(D, Hq, Hkv):
         for n, t in half.items():
             assert torch.isfinite(t).all(), n
             assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
+
+
+@pytest.mark.parametrize("L_max,L,bounds", [(530, 530, None), (700, 517, None), (600, 600, [0, 520, 600])],
+                         ids=["two_chunks", "cropped", "chunks_then_a_segment"])
+def test_dense_segments_of_more_than_128_row_tiles(L_max, L, bounds):
+    """133, 130 and 130 + 20 row tiles (K = 32, four anchors each): a segment past 128 row tiles runs its dK/dV in two
+    equal chunks, the second adding to what the first wrote."""
+    K, Hq, Hkv, D, seed = 32, 2, 1, 64, 310
+    print(f"case dense chunks: L={L} of {L_max} K={K} bounds={bounds}", flush=True)
+    qb, kb, vb, dob = (rand_bits((L * K, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
+    tm = pe.peagle_build_tilemap(L_max, K, bounds, device=0)
+    r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
+    r.step(0, 1 if bounds is None else len(bounds) - 1)
+    got = r.results()
+    ref = _oracle(qb, kb, vb, dob, L, K, r.shape.scale)
+    _check_against_oracle(got, ref, f"dense chunks {L} {bounds}")
+    for n in ("dK", "dV"):                      # no key left out or counted twice at a chunk boundary
+        assert max_abs(got[n], ref[n]) <= 2e-2 * np.abs(ref[n]).max(), n
