@@ -94,10 +94,12 @@ struct KernelTimer {
 };
 
 hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer* timer = nullptr);
-// a_hi: end anchor of the segment (depth-0 keys [0, a_hi) are visible); depth-0 keys with anchor
-// below acc_below are added to dk_acc/dv_acc, the others overwritten.
-hipError_t launch_bwd(const BwdParams& p, int D, int key_lo, int a_hi, int acc_below, hipStream_t stream,
-                      KernelTimer* timer = nullptr);
+// dQ of the row range, and the per-row terms that dK/dV consumes.
+hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer* timer = nullptr);
+// dK/dV of one segment.  a_hi: end anchor of the segment (depth-0 keys [0, a_hi) are visible); depth-0 keys with
+// anchor below acc_below are added to dk_acc/dv_acc, the others overwritten.
+hipError_t launch_dkdv(const BwdParams& p, int D, int key_lo, int a_hi, int acc_below, hipStream_t stream,
+                       KernelTimer* timer = nullptr);
 // Dense bf16 MFMA issue loop on every CU: the measured matrix-core ceiling of the device, in TFLOP/s, on
 // constant small-integer operands or on changing pseudo-random ones (the chip clocks lower under the latter).
 hipError_t measure_mfma_ceiling(hipStream_t stream, bool random_operands, float* tflops);

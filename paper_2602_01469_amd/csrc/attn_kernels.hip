@@ -2102,27 +2102,30 @@ hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer
   return span.finish();
 }
 
-hipError_t launch_bwd(const BwdParams& pin, int D, int key_lo, int a_hi, int acc_below, hipStream_t stream,
-                      KernelTimer* timer) {
-  BwdParams p = pin;
+hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer* timer) {
   const int n_rt = p.rt_hi - p.rt_lo;
   if (n_rt <= 0) return hipSuccess;
   // First-layer form.  The dQ kernel reads chain V rows from the shared vector at D = 64 only: at D = 128 it has
   // no registers to spare (that instantiation spilled three times as much and ran 25 % slower), so there the
   // caller passes an expanded V in `v` for it; the dK/dV kernel takes the shared vector at either size.
-  const bool sv = p.v_shared != nullptr && D == 64, sv_dkdv = p.shared_dk_part != nullptr;
-  {
-    const dim3 grid((unsigned)(n_rt * p.Hq)), block(256);  // one query head per workgroup
-    TimedSpan span(timer, kKindDq, stream);
-    if (D == 64) {
-      if (sv) hipLaunchKernelGGL((dq_pipe_kernel<64, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((dq_pipe_kernel<64, false>), grid, block, 0, stream, p);
-    } else {
-      hipLaunchKernelGGL((dq_kernel<128>), grid, block, 0, stream, p);
-    }
-    hipError_t e = span.finish();
-    if (e != hipSuccess) return e;
+  const bool sv = p.v_shared != nullptr && D == 64;
+  const dim3 grid((unsigned)(n_rt * p.Hq)), block(256);  // one query head per workgroup
+  TimedSpan span(timer, kKindDq, stream);
+  if (D == 64) {
+    if (sv) hipLaunchKernelGGL((dq_pipe_kernel<64, true>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((dq_pipe_kernel<64, false>), grid, block, 0, stream, p);
+  } else {
+    hipLaunchKernelGGL((dq_kernel<128>), grid, block, 0, stream, p);
   }
+  return span.finish();
+}
+
+hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int acc_below, hipStream_t stream,
+                       KernelTimer* timer) {
+  BwdParams p = pin;
+  const int n_rt = p.rt_hi - p.rt_lo;
+  if (n_rt <= 0) return hipSuccess;
+  const bool sv_dkdv = p.shared_dk_part != nullptr;  // (first-layer form)
   // dK/dV of a dense map runs over equal chunks of at most 128 row tiles, each followed by its own reduction, later
   // chunks adding to what the earlier ones wrote.  The key tiles below a chunk's first anchor have equally long
   // lists, which balances the workgroups the way the paper's segments do; but a small last chunk leaves most of the
