@@ -558,15 +558,17 @@ __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, 
   }
 }
 
-// (This plain form serves D = 128, one query head per workgroup; D = 64 runs dq_pipe_kernel below.  NH stays a
-// named constant because dq_tile is written for NH heads sharing the K / V fragments.)
-template <int D>
+// (One query head per workgroup.  This plain form serves D = 128, and at D = 64 the row tiles with short lists, where
+// its three workgroups per CU cover one another's first loads and last stores; long lists run dq_pipe_kernel below.  NH
+// stays a named constant because dq_tile is written for NH heads sharing the K / V fragments.)
+template <int D, bool SV>
 __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   constexpr int NH = 1;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   __shared__ __attribute__((aligned(16))) char lds[2][2][kTileBytes];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
+  const KeyTileLds<D> kl(&lds[0][0][0], wave);
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
   const int hpg = group / NH;
@@ -617,10 +619,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   const int e_lead = e0 + tm.row_lead[rt];  // end of the leading run of full tiles
   TileEntry cur = load_entry(tm.row_entries, e0);
   TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
-  // (LDS addresses taken per copy from the buffers' pointers here, not through KeyTileLds: this kernel is at
-  // the register limit, and with the integer form the allocator spilled 96 registers instead
-  // of 37 and the kernel ran 7 % slower)
-  dma_key_tile<D, 4>(lds_scalar_addr(lds[0][0] + wave * 1024), lds_scalar_addr(lds[0][1] + wave * 1024), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane);
+  dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
   dma_publish();
 
   int e = e0;
@@ -628,7 +627,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
     const int buf = (e - e0) & 1;
     const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
     if (e + 1 < e1)
-      dma_key_tile<D, 4>(lds_scalar_addr(lds[buf ^ 1][0] + wave * 1024), lds_scalar_addr(lds[buf ^ 1][1] + wave * 1024), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane);
+      dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
     const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
     dq_tile<D, NH, false>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
     dma_publish();
@@ -639,7 +638,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
     const int buf = (e - e0) & 1;
     const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
     if (e + 1 < e1)
-      dma_key_tile<D, 4>(lds_scalar_addr(lds[buf ^ 1][0] + wave * 1024), lds_scalar_addr(lds[buf ^ 1][1] + wave * 1024), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane);
+      dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
     const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + r) * 2);
     const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
     dq_tile<D, NH, true>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
@@ -2022,8 +2021,15 @@ __global__ __launch_bounds__(256) void mfma_ceiling_kernel(float* out, int iters
 namespace {
 
 // Query heads of one KV group that share a workgroup's K/V tiles in the forward: two at D = 64 (the register
-// budget of two waves per SIMD allows it), one at D = 128.  The backward kernels take one head per workgroup.
-inline int pick_nh(int group, int D) { return (D == 64 && group % 2 == 0) ? 2 : 1; }
+// budget of two waves per SIMD allows it) unless the row tiles' lists are short - then four one-head workgroups per
+// CU cover one another's first loads and last stores -, one at D = 128.  The line lies where both take the same time;
+// forward us, one / two heads, by mean list length: L = 128, K = 4 (4) 10 / 13, L = 700, K = 8 (8) 60 / 64, eight
+// packed sequences (12) 743 / 737, L = 1,391 (13) 171 / 165, L = 4,096 (35) 1,149 / 1,113.  A head's results do not
+// depend on the choice.  The backward kernels take one head per workgroup.
+constexpr int kOneHeadMeanTiles = 10;
+inline int pick_nh(int group, int D, int mean_tiles) {
+  return (D == 64 && group % 2 == 0 && mean_tiles > kOneHeadMeanTiles) ? 2 : 1;
+}
 
 struct TimedSpan {
   KernelTimer* t;
@@ -2083,7 +2089,7 @@ hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer
   const int n_rt = p.rt_hi - p.rt_lo;
   if (n_rt <= 0) return hipSuccess;
   const int group = p.Hq / p.Hkv;
-  const int nh = pick_nh(group, D);
+  const int nh = pick_nh(group, D, p.mean_tiles);
   const dim3 grid((unsigned)(n_rt * (p.Hq / nh))), block(256);
   TimedSpan span(timer, kKindFwd, stream);
   const bool sv = p.v_shared != nullptr;  // first-layer form: kernels that read chain V rows from the shared vector
@@ -2109,13 +2115,21 @@ hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer*
   // no registers to spare (that instantiation spilled three times as much and ran 25 % slower), so there the
   // caller passes an expanded V in `v` for it; the dK/dV kernel takes the shared vector at either size.
   const bool sv = p.v_shared != nullptr && D == 64;
-  const dim3 grid((unsigned)(n_rt * p.Hq)), block(256);  // one query head per workgroup
+  // D = 64: the row tiles [rt_lo, plain_hi) have short lists (see dq_plain_hi) and run the plain kernel.
   TimedSpan span(timer, kKindDq, stream);
+  auto go = [&](auto kernel, int rt_lo, int rt_hi) {
+    if (rt_lo >= rt_hi) return;
+    BwdParams q = p;
+    q.rt_lo = rt_lo;
+    q.rt_hi = rt_hi;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((rt_hi - rt_lo) * p.Hq)), dim3(256), 0, stream, q);  // one head per workgroup
+  };
   if (D == 64) {
-    if (sv) hipLaunchKernelGGL((dq_pipe_kernel<64, true>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((dq_pipe_kernel<64, false>), grid, block, 0, stream, p);
+    const int plain_hi = p.plain_hi < p.rt_lo ? p.rt_lo : (p.plain_hi > p.rt_hi ? p.rt_hi : p.plain_hi);
+    go(sv ? dq_pipe_kernel<64, true> : dq_pipe_kernel<64, false>, plain_hi, p.rt_hi);
+    go(sv ? dq_kernel<64, true> : dq_kernel<64, false>, p.rt_lo, plain_hi);
   } else {
-    hipLaunchKernelGGL((dq_kernel<128>), grid, block, 0, stream, p);
+    go(dq_kernel<128, false>, p.rt_lo, p.rt_hi);
   }
   return span.finish();
 }

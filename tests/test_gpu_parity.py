@@ -826,3 +826,41 @@ def test_dense_segments_of_more_than_128_row_tiles(L_max, L, bounds):
     _check_against_oracle(got, ref, f"dense chunks {L} {bounds}")
     for n in ("dK", "dV"):                      # no key left out or counted twice at a chunk boundary
         assert max_abs(got[n], ref[n]) <= 2e-2 * np.abs(ref[n]).max(), n
+
+
+@pytest.mark.parametrize("qscale", [1.0, 12.0])
+def test_row_tiles_on_both_sides_of_the_dq_kernel_choice(qscale):
+    """Lists of 3 to 34 key tiles at D = 64: short ones run the plain dQ kernel, long ones the pipelined one, with every
+    remainder of its groups of three tiles and (large logits) with normalised and unnormalised probabilities.  The whole
+    sequence, its segments one by one and a crop agree bit for bit."""
+    L, K, Hq, Hkv, D, bounds = 2000, 4, 2, 1, 64, [0, 1472, 1568, 2000]
+    print(f"case dq choice qscale={qscale}", flush=True)
+    T = L * K
+    qb, kb, vb, dob = (rand_bits((T, Hq, D), 320, qscale), rand_bits((T, Hkv, D), 321), rand_bits((T, Hkv, D), 322),
+                       rand_bits((T, Hq, D), 323))
+    tm = pe.peagle_build_tilemap(L, K, bounds, device=0)
+    r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
+    r.step(0, 3)
+    got = r.results()
+    ref = _oracle(qb, kb, vb, dob, L, K, r.shape.scale)
+    assert rel_l2(got["O"], ref["O"]) <= FWD_REL
+    for n in ("dQ", "dK", "dV"):
+        assert rel_l2(got[n], ref[n]) <= GRAD_REL, n
+    r2 = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
+    for s in range(3):
+        r2.step(s, s + 1)
+    g2 = r2.results()
+    for n in got:
+        assert np.array_equal(g2[n], got[n]), n
+    Lc = 1600                                            # rows of a prefix view: the same tiles, the same bits
+    keep = np.concatenate([d * L + np.arange(Lc) for d in range(K)])
+    rc = Run(tm, Lc, K, Hq, Hkv, D, qb[keep], kb[keep], vb[keep], dob[keep])
+    rc.step(0, 3)
+    gc = rc.results()
+    whole = np.concatenate([d * Lc + np.arange(1600 // 32 * 32) for d in range(K)])
+    back = np.concatenate([d * L + np.arange(1600 // 32 * 32) for d in range(K)])
+    assert np.array_equal(gc["dQ"][whole], got["dQ"][back]) and np.array_equal(gc["O"][whole], got["O"][back])
+
+
+def test_sampled_map_of_long_lists_runs_the_pipelined_dq():
+    test_sampled_sequences_match_oracle("long_lists", 3000, 4, 2, 1, 64, 0.8, 395, None)

@@ -365,3 +365,8 @@ def test_rope_step_with_shared_chain_vectors_matches_oracle(name, seq_lens, K, H
             assert rel_l2(got[n], ref[n]) <= GRAD_REL, n
     else:
         assert not got["dK_shared"].any() and not got["dV_shared"].any()
+
+
+def test_shared_chain_vectors_with_lists_on_both_sides_of_the_dq_kernel_choice():
+    test_rope_step_with_shared_chain_vectors_matches_oracle("dense_long_lists", (1800,), 4, 2, 1, 64, None, 3080,
+                                                            [0, 640, 1800], True)
