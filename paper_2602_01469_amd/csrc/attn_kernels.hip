@@ -2207,17 +2207,20 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   DecodeParams p = pin;
   const int row_waves = p.rows_pad / 32;  // 1 .. 4
   const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
-  // Requests of different lengths: with more workgroups than the two per CU that two groups leave room for, those of
-  // the longest requests start first (64 requests of 512 to 8,192 tokens, 1,024 workgroups: 161 us in order of the
-  // request, 125 us by length).  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
   const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;
-  p.by_length = p.C > 1 && p.C <= 64 && n_wg > 512;
-  // Two groups of waves per workgroup cost twice the LDS.  At D = 64 two such workgroups still share a CU; at D = 128
-  // only one does, which pays while there is at most one per CU anyway.  us per call, one / two groups: D = 64, 64
-  // requests of 512 - 8,192 tokens 134 / 120, 16 of 2,000 - 20,000 89 / 81, 64 equal ones of 8,192 206 / 226 (226
-  // with one group and the earlier ring of four tiles); D = 128, 2 of 10,800 - 20,000 (256 workgroups) 23.1 / 21.2,
-  // 16 of 800 - 8,192 (1,024 workgroups) 54 / 66.  More than 64 query rows make nine waves, too many for two per CU.
-  const bool two = row_waves <= 2 && (D == 64 || n_wg <= 256);
+  const bool long_pieces = (p.max_pages + p.n_splits - 1) / p.n_splits > 16;  // pages of the longest request's pieces
+  // Two groups of waves per workgroup cost twice the LDS.  At D = 64 two such workgroups still share a CU (of one group,
+  // five do), which is enough while there are no more, or where pieces are long and few; at D = 128 one does, which pays
+  // while there is at most one per CU anyway.  us per call, one / two groups: D = 64, 4 requests of 2,048 - 4,096 tokens
+  // (512 workgroups) 20.3 / 19.1, 64 of 512 - 8,192 (pieces of up to 64 pages) 134 / 120, 16 of 2,000 - 20,000 (39) 89 /
+  // 80, 55 of 1,691 - 2,469 (13) 67 / 77, 64 of 100 - 1,000 (8) 30 / 41; D = 128, 2 of 10,800 - 20,000 (256 workgroups)
+  // 23.1 / 21.2, 16 of 800 - 8,192 (1,024) 54 / 66.  More than 64 query rows make nine waves, too many for two per CU.
+  const bool two = row_waves <= 2 && (D == 64 ? n_wg <= 512 || long_pieces : n_wg <= 256);
+  // Long pieces of requests of different lengths: with more workgroups than two per CU, those of the longest requests
+  // start first.  us per call in order of the request / by length: the 64 requests of 512 to 8,192 tokens above 161 /
+  // 120, at D = 128 149 / 133; but 35 of 2,137 - 3,838 at D = 128 (pieces of 8 pages) 70.8 / 74.7: ranking costs most of
+  // a page's time.  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
+  p.by_length = p.C > 1 && p.C <= 64 && n_wg > 512 && long_pieces;
   const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + 1) * 64));
   // (The bound of 576 threads, of which 320 are launched, has the compiler schedule for four waves per SIMD: 120
   // against 136 us on the first of those batches.  The other forms run the same with either bound.)

@@ -142,19 +142,21 @@ def test_draft_decode_replays_from_a_hip_graph():
 
 
 RANKED = [
-    # name, number of requests, largest context, K, Hq, Hkv, D: batches of more workgroups than two per CU, whose requests are
-    # taken by falling length (up to 64 of them), over the merge kernel's forms (2, 3 to 8, more splits per request)
-    ("c64_d64", 64, 300, 4, 16, 8, 64),
-    ("c65_d64", 65, 300, 4, 16, 8, 64),
-    ("c64_d128", 64, 300, 5, 16, 8, 128),
-    ("c24_d128_one_group", 24, 1030, 8, 32, 8, 128),
-    ("c9_four_row_blocks", 9, 2000, 8, 128, 8, 64),
-    ("c8_d128_many_splits", 8, 4096, 3, 32, 8, 128),
+    # name, number of requests, largest context, K, Hq, Hkv, D, taken by falling length?: batches of more workgroups than
+    # two per CU, with pieces of more than 16 pages and shorter ones, over the merge kernel's forms (2, 3 to 8, more
+    # splits per request)
+    ("c64_d64", 64, 2200, 4, 16, 8, 64, True),
+    ("c65_d64", 65, 2200, 4, 16, 8, 64, False),
+    ("c64_d64_short_pieces", 64, 300, 4, 16, 8, 64, False),
+    ("c64_d128", 64, 2200, 5, 16, 8, 128, True),
+    ("c24_d128", 24, 6500, 8, 32, 8, 128, True),
+    ("c9_four_row_blocks", 9, 2000, 8, 128, 8, 64, False),
+    ("c8_d128_many_splits", 8, 4096, 3, 32, 8, 128, False),
 ]
 
 
-@pytest.mark.parametrize("name,C,longest,K,Hq,Hkv,D", RANKED, ids=[c[0] for c in RANKED])
-def test_draft_decode_batches_taken_by_length(name, C, longest, K, Hq, Hkv, D):
+@pytest.mark.parametrize("name,C,longest,K,Hq,Hkv,D,ranked", RANKED, ids=[c[0] for c in RANKED])
+def test_draft_decode_batches_of_many_workgroups(name, C, longest, K, Hq, Hkv, D, ranked):
     """Lengths with ties, empty requests and the longest anywhere; then one request's table is spoiled: it alone is
     flagged and no other request's output changes."""
     rng = np.random.default_rng(C + D)
@@ -165,7 +167,8 @@ def test_draft_decode_batches_taken_by_length(name, C, longest, K, Hq, Hkv, D):
     print(f"case decode {name}: ctx={lens.tolist()} K={K} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
     inp = make_decode_inputs(tuple(int(x) for x in lens), K, Hq, Hkv, D, 1100 + C)
     r = DecodeRun(inp, K, Hq, Hkv, D)
-    assert C * Hkv * pe.peagle_draft_decode_splits(r.shape) > 512
+    splits = pe.peagle_draft_decode_splits(r.shape)
+    assert C * Hkv * splits > 512 and ranked == (C <= 64 and -(-r.shape.max_pages // splits) > 16)
     o, lse, status = r.run()
     assert (status == 0).all()
     _check(inp, o, lse, r.shape.scale, name)
