@@ -3,7 +3,7 @@
 //
 // The builder never touches the O((nK)^2) element mask: every (row tile, key tile) pair is
 // classified with interval tests, and only the O(1) distinct partial patterns are expanded
-// element by element (from the visibility rule) into the de-duplicated mask pool.
+// row by row (from the visibility rule) into the de-duplicated mask pool.
 #include "tilemap.h"
 
 #include <hip/hip_runtime.h>
@@ -24,9 +24,19 @@ namespace {
 
 // Visibility rule of the parallel-prediction mask in anchor coordinates (Sec. 3; Sec. 3.2,
 // dependency of (p, d) on (p-1, d-1)): depth-0 keys are causal in the anchor, keys of depth
-// e >= 1 are visible only on the row's own anchor and only up to the row's depth.
-inline bool sees(int64_t i, int d, int64_t j, int e) {
-  return e == 0 ? (j <= i) : (j == i && e <= d);
+// e >= 1 are visible only on the row's own anchor and only up to the row's depth:
+//   sees(i, d, j, e) = e == 0 ? j <= i : j == i && e <= d.
+// Along the keys of a tile that is one run for every row and tile, so masks are built a row at a time.
+
+// Row r of a mask sees the keys [lo, hi] of the tile (clipped to it); false if there are none.
+bool set_key_range(std::vector<uint32_t>& bits, int r, int64_t lo, int64_t hi) {
+  lo = std::max<int64_t>(lo, 0);
+  hi = std::min<int64_t>(hi, kKeysPerTile - 1);
+  if (hi < lo) return false;
+  const uint64_t m = (hi >= 63 ? ~0ull : ((1ull << (hi + 1)) - 1)) & ~((1ull << lo) - 1);
+  bits[r * kMaskWordsPerRow] = (uint32_t)m;
+  bits[r * kMaskWordsPerRow + 1] = (uint32_t)(m >> 32);
+  return true;
 }
 
 struct MaskPool {
@@ -274,7 +284,6 @@ extern "C" int peagle_build_tilemap(int32_t L_max, int32_t K, const int32_t* seg
   MaskPool pool;
   pool.storage = &tm->masks;
   std::vector<uint32_t> bits(kMaskWords);
-  const int rows_used = A * K;
 
   tm->row_ptr.assign(tm->n_row_tiles + 1, 0);
   for (int32_t R = 0; R < tm->n_row_tiles; ++R) {
@@ -288,12 +297,9 @@ extern "C" int peagle_build_tilemap(int32_t L_max, int32_t K, const int32_t* seg
       if (j1 <= i0) {                         // every key is visible to every row: full
         ++tm->n_full;
       } else {
-        std::fill(bits.begin(), bits.end(), 0u);
-        for (int r = 0; r < rows_used; ++r) {
-          const int64_t i = i0 + r / K;
-          for (int kk = 0; kk < kKeysPerTile; ++kk)
-            if (sees(i, r % K, j0 + kk, 0)) bits[r * kMaskWordsPerRow + kk / 32] |= 1u << (kk % 32);
-        }
+        std::fill(bits.begin(), bits.end(), 0u);  // sees(i, d, j, 0): j <= i
+        for (int a = 0; a < A; ++a)
+          for (int d = 0; d < K; ++d) set_key_range(bits, a * K + d, 0, i0 + a - j0);
         en.mask_id = pool.intern(bits);
         ++tm->n_partial;
       }
@@ -301,21 +307,13 @@ extern "C" int peagle_build_tilemap(int32_t L_max, int32_t K, const int32_t* seg
     }
     // chain stream: slot ck is anchor i0 + ck / chain_slots, depth chain_first + ck % chain_slots
     for (int32_t s = 0; s < tm->n_csub; ++s) {
-      std::fill(bits.begin(), bits.end(), 0u);
+      std::fill(bits.begin(), bits.end(), 0u);  // sees(i, d, i, e): e <= d, the slots of depths 1 .. d of anchor i
       bool any = false;
-      for (int r = 0; r < rows_used; ++r) {
-        const int d = r % K;
-        const int64_t i = i0 + r / K;
-        for (int kk = 0; kk < kKeysPerTile; ++kk) {
-          const int ck = s * kKeysPerTile + kk;
-          if (ck >= A * tm->chain_slots) break;
-          const int e = tm->chain_first + ck % tm->chain_slots;
-          if (e >= 1 && sees(i, d, i0 + ck / tm->chain_slots, e)) {
-            bits[r * kMaskWordsPerRow + kk / 32] |= 1u << (kk % 32);
-            any = true;
-          }
+      for (int a = 0; a < A; ++a)
+        for (int d = 1; d < K; ++d) {
+          const int64_t depth0 = (int64_t)a * tm->chain_slots - tm->chain_first - (int64_t)s * kKeysPerTile;
+          any |= set_key_range(bits, a * K + d, depth0 + 1, depth0 + d);
         }
-      }
       if (!any) continue;
       const int32_t kt = tm->n_d0 + R * tm->n_csub + s;
       tm->row_entries.push_back(TileEntry{kt, pool.intern(bits)});
@@ -520,15 +518,7 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
         continue;
       }
       std::fill(bits.begin(), bits.end(), 0u);
-      for (int r = 0; r < rows_used; ++r) {
-        const int64_t lo = std::max<int64_t>(0, (int64_t)sb - j0);
-        const int64_t hi = std::min<int64_t>(kKeysPerTile - 1, (int64_t)row_a[r] - j0);  // inclusive
-        if (hi < lo) continue;
-        const uint64_t upto_hi = hi >= 63 ? ~0ull : ((1ull << (hi + 1)) - 1);
-        const uint64_t m = upto_hi & ~((1ull << lo) - 1);
-        bits[r * kMaskWordsPerRow] = (uint32_t)m;
-        bits[r * kMaskWordsPerRow + 1] = (uint32_t)(m >> 32);
-      }
+      for (int r = 0; r < rows_used; ++r) set_key_range(bits, r, (int64_t)sb - j0, (int64_t)row_a[r] - j0);
       partial_entries.push_back(TileEntry{c, append_mask(bits)});
       partial_key_ids.push_back(j1 <= a0 ? -2 - sb : partial_entries.back().mask_id);
       ++tm->n_partial;
@@ -550,13 +540,7 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
       // a chain key (j, e) is seen by the rows of its own anchor at depths >= e (sees(i, d, j, e) ==
       // (j == i && e <= d)): the rows of an anchor follow one another, so row r of depth d sees the slots
       // r - d + 1 .. r
-      for (int r = 0; r < rows_used; ++r) {
-        const int lo = std::max(0, r - row_d[r] + 1 - k0), hi = std::min(kKeysPerTile - 1, r - k0);  // inclusive
-        if (hi < lo) continue;
-        const uint64_t m = (hi >= 63 ? ~0ull : ((1ull << (hi + 1)) - 1)) & ~((1ull << lo) - 1);
-        bits[r * kMaskWordsPerRow] = (uint32_t)m;
-        bits[r * kMaskWordsPerRow + 1] = (uint32_t)(m >> 32);
-      }
+      for (int r = 0; r < rows_used; ++r) set_key_range(bits, r, r - row_d[r] + 1 - k0, r - k0);
       tm->row_entries.push_back(TileEntry{kt, append_mask(bits)});
       tm->key_side_id.push_back(tm->row_entries.back().mask_id);
       ++tm->n_partial;
