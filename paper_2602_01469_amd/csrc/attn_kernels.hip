@@ -1182,6 +1182,10 @@ enum { kRowsNear = 0, kRowsFar = 1, kRowsListed = 2 };
 template <int D, int ROWS, bool SV>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p) {
   constexpr bool LISTED = ROWS == kRowsListed;
+  // Blocks that no row sees are left out at D = 64.  At D = 128, with one wave per SIMD, nothing covers the unpipelined
+  // chain routine, and the second loop costs the first: dK/dV at 1,391 anchors 378 us with both, 338 with one pipelined
+  // loop for all tiles, at 3,000 anchors 1,410 and 1,320.
+  constexpr bool kSkips = D == 64;
   constexpr int kTileBytes = kRowsPerTile * D * 2;
   constexpr int kBufBytes = 2 * kTileBytes + 2 * kRowsPerTile * 4;  // Q | dO | lse2 | delta
   constexpr int kLdsBytes = 2 * kBufBytes;
@@ -1437,7 +1441,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
         const char* do_lds = q_lds + kTileBytes;
         const float* lse_lds = reinterpret_cast<const float*>(q_lds + 2 * kTileBytes);
         const float* delta_lds = lse_lds + kRowsPerTile;
-        if (CHAIN) {  // (chain tiles always carry a bitmask)
+        if (kSkips && CHAIN) {  // (chain tiles always carry a bitmask)
           const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
           const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
           dkdv_rowtile_chain<D>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, cm);
@@ -1448,7 +1452,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
           // (scalar base + small per-lane offset: no 64-bit per-lane address is kept across the loop)
           const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
           const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
-          if (__builtin_amdgcn_ballot_w64((cm[0] | cm[1] | cm[2] | cm[3]) != 0) != 0)  // (else: every key is in the rows' future)
+          if (!kSkips || __builtin_amdgcn_ballot_w64((cm[0] | cm[1] | cm[2] | cm[3]) != 0) != 0)  // (else: every key is in the rows' future)
             dkdv_rowtile_pipelined<D, 1>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, false, cm);
         } else if (LISTED) {  // only packed maps carry such ids
           const bool lane_off = key_anchor < -mask_c - 2;
@@ -1589,8 +1593,12 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
       }
     }
   };
-  // (two loops and two epilogues: accumulators that meet again behind them cost spills)
-  if (chain) {
+  // (D = 64: two loops and two epilogues: accumulators that meet again behind them cost spills)
+  if (!kSkips) {
+    run(std::false_type{});
+    if (chain) store(std::true_type{});
+    else store(std::false_type{});
+  } else if (chain) {
     run(std::true_type{});
     store(std::true_type{});
   } else {
