@@ -71,23 +71,6 @@ int32_t mean_tiles(const peagle_tilemap_t* tm, int32_t L) {
   return (tm->row_ptr[n] + n / 2) / n;
 }
 
-// Row tiles [0, dq_plain_hi) run the plain dQ kernel at D = 64.  The two kernels round differently, so the choice is
-// made where neither a cut into segments nor (dense maps) a crop changes it: by a row tile's own list length in a
-// dense map, whose lists grow with the row tile, by the mean list length in a sampled or packed one.
-// dQ us, plain / pipelined kernel for all row tiles, by mean list length: L = 700 (8) 86 / 101, eight packed sequences
-// (12.5) 1,094 / 1,240, L = 1,391 (14) 250 / 275, L = 4,096 (35) 1,656 / 1,639, sampled 8,192 (67) 3,277 / 3,195.
-constexpr int32_t kPlainTiles = 24;
-int32_t dq_plain_hi(const peagle_tilemap_t* tm, int32_t L) {
-  if (tm->sampled) return mean_tiles(tm, L) <= kPlainTiles ? tm->n_row_tiles : 0;
-  int32_t lo = 0, hi = row_tiles(tm, L);
-  while (lo < hi) {
-    const int32_t mid = lo + (hi - lo) / 2;
-    if (tm->row_ptr[mid + 1] - tm->row_ptr[mid] <= kPlainTiles) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
-}
-
 FwdParams make_fwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const SegRange& sr, const void* q,
                    const void* k, const void* v, void* o, float* lse, const SharedForm& sf = SharedForm()) {
   FwdParams p{};
@@ -143,7 +126,7 @@ BwdParams make_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const Se
   p.s_hi = sr.s_hi;
   p.cropped = sr.cropped;
   p.near_rows = (size_t)p.T * s->Hq * s->D * 2 < ((size_t)1 << 32) ? 1 : 0;
-  p.plain_hi = dq_plain_hi(tm, s->L);
+  p.mean_tiles = mean_tiles(tm, s->L);
   p.chain_accumulate = chain_accumulate;
   p.c_log2 = s->scale * 1.4426950408889634f;
   p.scale = s->scale;

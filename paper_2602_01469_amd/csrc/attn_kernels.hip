@@ -517,7 +517,11 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
 // Backward, part 1: Delta = rowsum(dO * O) and dQ = scale * dS K, row-tile owned (same
 // decomposition as the forward).  Writes Delta [Hq, T] for part 2.
 // =====================================================================================
-template <int D, int NH, bool MASKED>
+// |lse| up to which (log2 units) the D = 64 kernels leave a row's probabilities unnormalised, see dq_pipe_kernel.
+constexpr float kDqLseRange = 64.f;
+
+// FROM_DELTA: -Delta is the start value of the dP sum, as in dq_pipe_body, instead of being subtracted at its end.
+template <int D, int NH, bool MASKED, bool FROM_DELTA = false>
 __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, const NatOff<D>& no, const TrOff<D>& to,
                                         const bf16x8 (&qf)[NH][D / 16], const bf16x8 (&dof)[NH][D / 16],
                                         f32x16 (&dq)[NH][D / 32], const float (&lse2)[NH], const float (&delta)[NH],
@@ -531,7 +535,8 @@ __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, 
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) {
       s[hh] = zero16();
-      dp[hh] = zero16();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dp[hh][i] = FROM_DELTA ? -delta[hh] : 0.f;
     }
 #pragma unroll
     for (int st = 0; st < D / 16; ++st) {
@@ -554,7 +559,7 @@ __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, 
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const float pr = exp2_fast(__builtin_fmaf(s[hh][i], c, nl));
-        s[hh][i] = pr * (dp[hh][i] - dl);
+        s[hh][i] = pr * (FROM_DELTA ? dp[hh][i] : dp[hh][i] - dl);
       }
       dsb[hh][0] = pack8(s[hh], 0);
       dsb[hh][1] = pack8(s[hh], 1);
@@ -571,13 +576,17 @@ __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, 
   }
 }
 
-// (One query head per workgroup.  This plain form serves D = 128, and at D = 64 the row tiles with short lists, where
-// its three workgroups per CU cover one another's first loads and last stores; long lists run dq_pipe_kernel below.  NH
-// stays a named constant because dq_tile is written for NH heads sharing the K / V fragments.)
+// (One query head per workgroup.  This plain form serves D = 128, and at D = 64 launches of many workgroups with short
+// lists, where three per CU cover one another's first loads and last stores; the others run dq_pipe_kernel below.  At
+// D = 64 it does the arithmetic of dq_pipe_kernel step for step - unnormalised probabilities where that kernel leaves
+// them so, -Delta as the start value of dP in the tiles which that kernel pipelines - so that a row's dQ has the same
+// bits from either and the launcher may choose freely.  NH stays a named constant because dq_tile is written for NH
+// heads sharing the K / V fragments.)
 template <int D, bool SV>
 __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   constexpr int NH = 1;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
+  constexpr bool kAsPipe = D == 64;
   __shared__ __attribute__((aligned(16))) char lds[2][2][kTileBytes];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
@@ -633,20 +642,36 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   TileEntry cur = load_entry(tm.row_entries, e0);
   TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
   dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
+
+  float row_factor = p.scale;
+  int e_pipe = e0;  // end of the tiles that dq_pipe_kernel would run in its pipeline
+  if (kAsPipe) {    // (see there; lse2 is not needed unchanged from here on)
+    const bool unnormalised = __syncthreads_or(row_ok && !(__builtin_fabsf(lse2[0]) <= kDqLseRange)) == 0;
+    if (unnormalised) {
+      row_factor = exp2_fast(-lse2[0]) * p.scale;
+      lse2[0] = 0.f;
+      e_pipe = e0 + tm.row_lead[rt] / 3 * 3;
+    }
+  }
   dma_publish();
 
   int e = e0;
-  for (; e < e_lead; ++e) {  // leading full tiles: counted loop, no mask branch
-    const int buf = (e - e0) & 1;
-    const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
-    if (e + 1 < e1)
-      dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
-    const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
-    dq_tile<D, NH, false>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
-    dma_publish();
-    cur = nxt;
-    nxt = take_entry(ahead);
-  }
+  auto full_tiles = [&](int e_end, auto from_delta_tag) {  // leading full tiles: counted loop, no mask branch
+    constexpr bool FROM_DELTA = decltype(from_delta_tag)::value;
+    for (; e < e_end; ++e) {
+      const int buf = (e - e0) & 1;
+      const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
+      if (e + 1 < e1)
+        dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+      const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
+      dq_tile<D, NH, false, FROM_DELTA>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
+      dma_publish();
+      cur = nxt;
+      nxt = take_entry(ahead);
+    }
+  };
+  if (kAsPipe) full_tiles(e_pipe, std::true_type{});
+  full_tiles(e_lead, std::false_type{});
   for (; e < e1; ++e) {
     const int buf = (e - e0) & 1;
     const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
@@ -693,7 +718,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
     for (int hh = 0; hh < NH; ++hh) {
       __bf16* drow = p.dq + ((size_t)tq * p.Hq + h0 + hh) * D;
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db) store_row_bf16(drow + db * 32, dq[hh][db], p.scale, g);
+      for (int db = 0; db < D / 32; ++db) store_row_bf16(drow + db * 32, dq[hh][db], row_factor, g);
     }
   }
 }
@@ -800,7 +825,6 @@ template <int D, bool SV>
 __global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr int N2 = D / 16;
-  constexpr float kLseRange = 64.f;  // log2 units
   __shared__ __attribute__((aligned(16))) char lds[3][2][kTileBytes];  // [buffer][K|V]
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
@@ -865,7 +889,7 @@ __global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
   if (e0 + 1 < e1) dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
 
   // unnormalised probabilities for the whole workgroup, or normalised ones for the whole workgroup
-  const bool in_range = __builtin_fabsf(lse2) <= kLseRange;  // (false for NaN)
+  const bool in_range = __builtin_fabsf(lse2) <= kDqLseRange;  // (false for NaN)
   const bool unnormalised = __syncthreads_or(row_ok && !in_range) == 0;
   const float lse_used[1] = {unnormalised ? 0.f : lse2};
   const float delta_used[1] = {delta};
@@ -2122,22 +2146,23 @@ hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer*
   // no registers to spare (that instantiation spilled three times as much and ran 25 % slower), so there the
   // caller passes an expanded V in `v` for it; the dK/dV kernel takes the shared vector at either size.
   const bool sv = p.v_shared != nullptr && D == 64;
-  // D = 64: the row tiles [rt_lo, plain_hi) have short lists (see dq_plain_hi) and run the plain kernel.
+  // D = 64: the plain kernel where the lists are short and the workgroups many - two full rounds of the three per CU
+  // that it runs -, the pipelined one elsewhere; a row's dQ has the same bits from both.  One launch in either case: the
+  // row tiles of one launch split between the two kernels by list length ran one launch after the other, each leaving
+  // the chip to drain (2,048 anchors, K = 4, 4 heads: 66 us).  us, pipelined / plain, by mean list length (workgroups):
+  // many workgroups, L = 411, 64 heads (6; 1,664) 57 / 52, L = 1,391, 64 heads (14; 5,568) 289 / 262, L = 1,000, 32
+  // heads (11; 2,016) 91 / 85, L = 2,048, 16 heads (19; 2,048) 132 / 128, packed to L = 6,420, 4 heads (12; 1,612) 90 /
+  // 83; few, L = 1,000, 4 heads (11; 252) 24 / 29, 16 heads (11; 1,008) 49 / 54, L = 2,048, K = 4, 16 heads (18; 1,024)
+  // 73 / 75, L = 3,000, 8 heads (26; 1,504) 131 / 132; long lists, L = 4,096, 16 heads (35; 4,096) 422 / 427, 64 heads
+  // (35; 16,384) 1,666 / 1,646, L = 8,000, 4 heads (65; 2,000) 376 / 392, sampled 8,192 (67) 3,195 / 3,277.
+  constexpr int kPlainMeanTiles = 24, kPlainWorkgroups = 2 * 3 * 256;
+  const int n_wg = n_rt * p.Hq;  // one query head per workgroup
+  const bool plain = p.mean_tiles <= kPlainMeanTiles && n_wg >= kPlainWorkgroups;
   TimedSpan span(timer, kKindDq, stream);
-  auto go = [&](auto kernel, int rt_lo, int rt_hi) {
-    if (rt_lo >= rt_hi) return;
-    BwdParams q = p;
-    q.rt_lo = rt_lo;
-    q.rt_hi = rt_hi;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((rt_hi - rt_lo) * p.Hq)), dim3(256), 0, stream, q);  // one head per workgroup
-  };
-  if (D == 64) {
-    const int plain_hi = p.plain_hi < p.rt_lo ? p.rt_lo : (p.plain_hi > p.rt_hi ? p.rt_hi : p.plain_hi);
-    go(sv ? dq_pipe_kernel<64, true> : dq_pipe_kernel<64, false>, plain_hi, p.rt_hi);
-    go(sv ? dq_kernel<64, true> : dq_kernel<64, false>, p.rt_lo, plain_hi);
-  } else {
-    go(dq_kernel<128, false>, p.rt_lo, p.rt_hi);
-  }
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(256), 0, stream, p); };
+  if (D == 128) go(dq_kernel<128, false>);
+  else if (plain) go(sv ? dq_kernel<64, true> : dq_kernel<64, false>);
+  else go(sv ? dq_pipe_kernel<64, true> : dq_pipe_kernel<64, false>);
   return span.finish();
 }
 

@@ -71,6 +71,17 @@ class SampledRun(Run):
         self.ws = torch.empty(pe.peagle_workspace_bytes(tm, self.shape), dtype=torch.uint8, device="cuda")
 
 
+def mean_list(tm):
+    """Mean length of a map's row-tile lists (uncropped), which the launchers choose kernels by."""
+    i = tm.info()
+    return (i["n_full"] + i["n_partial"]) / i["n_row_tiles"]
+
+
+def runs_plain_dq(tm, Hq):
+    """Which dQ kernel one launch over the whole map runs at D = 64 (short lists, many workgroups: the plain one)."""
+    return mean_list(tm) < 24 and tm.info()["n_row_tiles"] * Hq >= 2 * 3 * 256
+
+
 def rel_l2(a, b):
     return float(np.linalg.norm((a - b).ravel()) / max(np.linalg.norm(b.ravel()), 1e-300))
 

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2602_01469_amd as pe
-from gpu_harness import Run, bf16_to_f64, max_abs, rand_bits, rel_l2, to_dev_bf16
+from gpu_harness import Run, bf16_to_f64, max_abs, mean_list, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
 from oracle import peagle_oracle as orc
 from peagle_inputs import CONFIGS, bf16_bits_to_f64, make_inputs
 
@@ -829,16 +829,17 @@ def test_dense_segments_of_more_than_128_row_tiles(L_max, L, bounds):
 
 
 @pytest.mark.parametrize("qscale", [1.0, 12.0])
-def test_row_tiles_on_both_sides_of_the_dq_kernel_choice(qscale):
-    """Lists of 3 to 34 key tiles at D = 64: short ones run the plain dQ kernel, long ones the pipelined one, with every
-    remainder of its groups of three tiles and (large logits) with normalised and unnormalised probabilities.  The whole
-    sequence, its segments one by one and a crop agree bit for bit."""
+def test_pipelined_dq_over_lists_of_every_length(qscale):
+    """Lists of 3 to 34 key tiles at D = 64, few workgroups: the pipelined dQ kernel with every remainder of its groups of
+    three tiles and (large logits) with normalised and unnormalised probabilities.  The whole sequence, its segments one
+    by one and a crop agree bit for bit."""
     L, K, Hq, Hkv, D, bounds = 2000, 4, 2, 1, 64, [0, 1472, 1568, 2000]
     print(f"case dq choice qscale={qscale}", flush=True)
     T = L * K
     qb, kb, vb, dob = (rand_bits((T, Hq, D), 320, qscale), rand_bits((T, Hkv, D), 321), rand_bits((T, Hkv, D), 322),
                        rand_bits((T, Hq, D), 323))
     tm = pe.peagle_build_tilemap(L, K, bounds, device=0)
+    assert not runs_plain_dq(tm, Hq)
     r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
     r.step(0, 3)
     got = r.results()
@@ -862,5 +863,81 @@ def test_row_tiles_on_both_sides_of_the_dq_kernel_choice(qscale):
     assert np.array_equal(gc["dQ"][whole], got["dQ"][back]) and np.array_equal(gc["O"][whole], got["O"][back])
 
 
+def _map_of(form):
+    """A map with lists of 3 to 34 (dense), 2 to 14 (packed) or 2 to 30 (sampled) tiles, and its L and K."""
+    if form == "dense":
+        return pe.peagle_build_tilemap(2011, 4, [0, 1472, 2011], device=0), 2011, 4
+    if form == "k7":                                # row tiles of 126 rows
+        return pe.peagle_build_tilemap(1200, 7, None, device=0), 1200, 7
+    if form == "packed":
+        lens = [700, 3, 411, 64, 1, 129, 620]
+        return pe.peagle_build_tilemap_packed(lens, 8, device=0), sum(lens), 8
+    from peagle_inputs import cod_depth_counts
+    count = cod_depth_counts(1700, 5, 0.8, 331)
+    return pe.peagle_build_tilemap_sampled(count, 5, [0, 650, 1700], device=0), 1700, 5
+
+
+@pytest.mark.parametrize("qscale", [1.0, 12.0, 40.0])
+@pytest.mark.parametrize("form", ["dense", "k7", "packed", "sampled"])
+def test_both_dq_kernels_give_the_same_bits(form, qscale):
+    """Forty query heads in one call (many workgroups: the plain dQ kernel at D = 64) against the same heads in calls of one
+    key / value head's group each (few workgroups: the pipelined kernel).  At the larger scales some or all workgroups
+    have row sums outside the range of unnormalised probabilities."""
+    print(f"case dq kernels {form} qscale={qscale}", flush=True)
+    tm, L, K = _map_of(form)
+    T, Hq, Hkv, D = tm.tokens(L), 40, 20, 64
+    assert runs_plain_dq(tm, Hq) and not runs_plain_dq(tm, Hq // Hkv)
+    g = torch.Generator(device="cuda").manual_seed(335)
+    rnd = lambda H, f=1.0: (torch.randn(T, H, D, generator=g, device="cuda") * f).to(torch.bfloat16)
+    q, k, v, d_o = rnd(Hq, qscale), rnd(Hkv), rnd(Hkv), rnd(Hq)
+
+    def run(q, k, v, d_o):
+        shape = pe.Shape(L, K, q.shape[1], k.shape[1], D)
+        o, dq = (torch.full_like(q, float("nan")) for _ in range(2))
+        lse = torch.full((q.shape[1], T), float("nan"), device="cuda")
+        dk, dv = (torch.full(k.shape, float("nan"), device="cuda") for _ in range(2))
+        ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
+        pe.peagle_attn_step_partitioned(tm, shape, 0, tm.info()["S"], q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
+        torch.cuda.synchronize()
+        return {"o": o, "dq": dq, "lse": lse.t(), "dk": dk, "dv": dv}
+
+    whole = run(q, k, v, d_o)
+    for h in range(0, Hkv, 3):
+        a, b = slice(h * (Hq // Hkv), (h + 1) * (Hq // Hkv)), slice(h, h + 1)
+        part = run(q[:, a].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(), d_o[:, a].contiguous())
+        for n, t in part.items():
+            assert torch.isfinite(t).all(), n
+            assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(2, 1), (64, 32)])
+def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
+    """Six hundred anchors alone (short lists, at many heads the plain dQ kernel) and packed in front of a sequence of five
+    thousand (long lists, the pipelined one)."""
+    K, D, own, other = 8, 64, 600, 5000
+    print(f"case packed neighbours Hq={Hq}", flush=True)
+    maps = [pe.peagle_build_tilemap_packed(lens, K, device=0) for lens in ([own], [own, other])]
+    assert runs_plain_dq(maps[0], Hq) == (Hq == 64) and not runs_plain_dq(maps[1], Hq)
+    g = torch.Generator(device="cuda").manual_seed(337)
+    L = own + other
+    full = [torch.randn(K, L, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq)]
+    results = []
+    for tm, n in zip(maps, (own, L)):
+        q, k, v, d_o = (t[:, :n].reshape(K * n, t.shape[2], D).contiguous() for t in full)
+        shape = pe.Shape(n, K, Hq, Hkv, D)
+        o, dq = torch.empty_like(q), torch.empty_like(q)
+        lse = torch.empty((Hq, K * n), device="cuda")
+        dk, dv = (torch.empty(k.shape, device="cuda") for _ in range(2))
+        ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
+        pe.peagle_attn_step_partitioned(tm, shape, 0, 1, q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
+        torch.cuda.synchronize()
+        results.append({m: t.view(K, n, -1, D)[:, :own] for m, t in (("o", o), ("dq", dq), ("dk", dk), ("dv", dv))})
+    for m in results[0]:
+        assert torch.equal(results[0][m], results[1][m]), m
+
+
 def test_sampled_map_of_long_lists_runs_the_pipelined_dq():
+    from peagle_inputs import cod_depth_counts
+    tm = pe.peagle_build_tilemap_sampled(cod_depth_counts(3000, 4, 0.8, 395), 4, None, device=0)
+    assert mean_list(tm) > 24 and not runs_plain_dq(tm, 2)
     test_sampled_sequences_match_oracle("long_lists", 3000, 4, 2, 1, 64, 0.8, 395, None)

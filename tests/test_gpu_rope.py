@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2602_01469_amd as pe
-from gpu_harness import Run, SampledRun, attach_rope, bf16_to_f64, max_abs, rand_bits, rel_l2, to_dev_bf16
+from gpu_harness import Run, SampledRun, attach_rope, bf16_to_f64, max_abs, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
 from oracle import peagle_oracle as orc
 from peagle_inputs import CONFIGS, bf16_bits_to_f64, cod_depth_counts, f32_to_bf16_bits, make_inputs
 from test_gpu_parity import (FWD_REL, GRAD_REL, LSE_ABS, PART_REL, _check_against_oracle, _check_o_abs)
@@ -367,6 +367,39 @@ def test_rope_step_with_shared_chain_vectors_matches_oracle(name, seq_lens, K, H
         assert not got["dK_shared"].any() and not got["dV_shared"].any()
 
 
-def test_shared_chain_vectors_with_lists_on_both_sides_of_the_dq_kernel_choice():
+def test_shared_chain_vectors_with_lists_of_every_length():
     test_rope_step_with_shared_chain_vectors_matches_oracle("dense_long_lists", (1800,), 4, 2, 1, 64, None, 3080,
                                                             [0, 640, 1800], True)
+
+
+def test_shared_chain_vectors_give_the_same_bits_from_both_dq_kernels():
+    """Forty query heads at once (the plain dQ kernel) against one group at a time (the pipelined one), first-layer form."""
+    L, K, Hq, Hkv, D = 1500, 4, 40, 20, 64
+    print("case rope shared dq kernels", flush=True)
+    tm = pe.peagle_build_tilemap(L, K, [0, 640, 1500], device=0)
+    assert runs_plain_dq(tm, Hq) and not runs_plain_dq(tm, Hq // Hkv)
+    T = tm.tokens(L)
+    g = torch.Generator(device="cuda").manual_seed(3090)
+    rnd = lambda *sh: torch.randn(*sh, generator=g, device="cuda").to(torch.bfloat16)
+    q, d_o, k, v, ks, vs = rnd(T, Hq, D), rnd(T, Hq, D), rnd(L, Hkv, D), rnd(L, Hkv, D), rnd(Hkv, D), rnd(Hkv, D)
+    table = torch.empty((pe.peagle_rope_positions(tm, L), 2, D // 2), dtype=torch.float32, device="cuda")
+    pe.peagle_rope_table(BASE, D, table.shape[0], table)
+
+    def run(q, d_o, k, v, ks, vs):
+        shape = pe.Shape(L, K, q.shape[1], k.shape[1], D)
+        o, dq = (torch.full_like(q, float("nan")) for _ in range(2))
+        lse = torch.full((q.shape[1], T), float("nan"), device="cuda")
+        dk, dv = (torch.full(k.shape, float("nan"), device="cuda") for _ in range(2))
+        dks, dvs = (torch.full(ks.shape, float("nan"), device="cuda") for _ in range(2))
+        ws = torch.empty(pe.peagle_rope_shared_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
+        pe.peagle_attn_step_rope_shared(tm, shape, q, k, ks, v, vs, d_o, table, o, lse, dq, dk, dv, dks, dvs, ws)
+        torch.cuda.synchronize()
+        return {"o": o, "dq": dq, "dk": dk, "dv": dv}
+
+    whole = run(q, d_o, k, v, ks, vs)
+    for h in range(0, Hkv, 6):
+        a, b = slice(h * (Hq // Hkv), (h + 1) * (Hq // Hkv)), slice(h, h + 1)
+        part = run(*(t[:, a].contiguous() for t in (q, d_o)), *(t[:, b].contiguous() for t in (k, v)), ks[b], vs[b])
+        for n, t in part.items():
+            assert torch.isfinite(t).all(), n
+            assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
