@@ -444,8 +444,10 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
 
   // One pass over the row tile's key tiles.  The first pass keeps the softmax reference at 0
   // (no running max: fewer vector instructions per score); it is exact as long as every row
-  // sum stays inside the fp32 / bf16 exponent range.  If any row of the workgroup leaves
-  // [2^-100, 2^100] (or is not finite) the tile is recomputed with the running-max form.
+  // sum stays inside the fp32 / bf16 exponent range.  If any row of a head leaves [2^-100, 2^100]
+  // (or is not finite) the tile is recomputed with the running-max form, for that head alone: the
+  // workgroup's other head keeps its first pass, so that a head's results do not depend on which
+  // heads share its workgroup.
   auto pass = [&](auto safe_tag) {
     constexpr bool SAFE = decltype(safe_tag)::value;
 #pragma unroll
@@ -491,18 +493,10 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
       cur = nxt;
       nxt = take_entry(ahead);
     }
-    bool bad = false;
 #pragma unroll
-    for (int hh = 0; hh < NH; ++hh) {
-      l_tot[hh] = sum_halves(lsum[hh]);
-      bad |= !(l_tot[hh] > 0x1p-100f && l_tot[hh] < 0x1p100f);
-    }
-    return bad && row_ok;
+    for (int hh = 0; hh < NH; ++hh) l_tot[hh] = sum_halves(lsum[hh]);
   };
-  if (__syncthreads_or(pass(std::false_type{}))) (void)pass(std::true_type{});
-
-#pragma unroll
-  for (int hh = 0; hh < NH; ++hh) {
+  auto store = [&](int hh) {
     const float inv = 1.0f / l_tot[hh];
     if (row_ok) {
       __bf16* orow = p.o + ((size_t)tq * p.Hq + h0 + hh) * D;
@@ -510,6 +504,25 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
       for (int db = 0; db < D / 32; ++db) store_row_bf16(orow + db * 32, o[hh][db], inv, g);
       if (g == 0) p.lse[(size_t)(h0 + hh) * p.T + tq] = (m[hh] + __builtin_log2f(l_tot[hh])) * kLn2;
     }
+  };
+  pass(std::false_type{});
+  int bad = 0;  // a bit per head
+#pragma unroll
+  for (int hh = 0; hh < NH; ++hh)
+    if (row_ok && !(l_tot[hh] > 0x1p-100f && l_tot[hh] < 0x1p100f)) bad |= 1 << hh;
+  int redo = 0;
+  if (__syncthreads_or(bad)) {
+#pragma unroll
+    for (int hh = 0; hh < NH; ++hh) redo |= (NH == 1 || __syncthreads_or(bad & (1 << hh))) ? 1 << hh : 0;
+  }
+#pragma unroll
+  for (int hh = 0; hh < NH; ++hh)
+    if (!(redo & (1 << hh))) store(hh);
+  if (redo) {
+    pass(std::true_type{});
+#pragma unroll
+    for (int hh = 0; hh < NH; ++hh)
+      if (redo & (1 << hh)) store(hh);
   }
 }
 

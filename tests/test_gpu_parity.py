@@ -208,6 +208,43 @@ def test_large_logits_take_the_running_max_path(qscale):
         assert rel_l2(got[n], ref[n]) <= GRAD_REL, n
 
 
+def _heads_run(tm, L, K, q, k, v, d_o):
+    """A step over the heads given, [T, H, D] tensors on the device."""
+    shape = pe.Shape(L, K, q.shape[1], k.shape[1], q.shape[2])
+    o, dq = (torch.full_like(q, float("nan")) for _ in range(2))
+    lse = torch.full((q.shape[1], q.shape[0]), float("nan"), device="cuda")
+    dk, dv = (torch.full(k.shape, float("nan"), device="cuda") for _ in range(2))
+    ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
+    pe.peagle_attn_step_partitioned(tm, shape, 0, tm.info()["S"], q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
+    torch.cuda.synchronize()
+    return {"o": o, "dq": dq, "lse": lse.t(), "dk": dk, "dv": dv}
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_a_head_does_not_depend_on_the_heads_beside_it(D):
+    """Heads of ordinary and of very large logits in turn.  At D = 64 two heads of a group share a forward workgroup where
+    lists are long, none where they are short: each head alone, and the crop to short lists, give the same bits."""
+    L, K, Hq, Hkv, Lc = 2000, 4, 4, 2, 896
+    print(f"case neighbouring heads D={D}", flush=True)
+    tm = pe.peagle_build_tilemap(L, K, None, device=0)
+    assert mean_list(tm) > 11 and mean_list(pe.peagle_build_tilemap(Lc, K, None, device=-1)) < 10
+    g = torch.Generator(device="cuda").manual_seed(340)
+    q, k, v, d_o = (torch.randn(L * K, H, D, generator=g, device="cuda") for H in (Hq, Hkv, Hkv, Hq))
+    q[:, 1::2] *= 40.0
+    q, k, v, d_o = (t.to(torch.bfloat16) for t in (q, k, v, d_o))
+    whole = _heads_run(tm, L, K, q, k, v, d_o)
+    for h in range(Hq):
+        b = slice(h // 2, h // 2 + 1)
+        alone = _heads_run(tm, L, K, q[:, h:h + 1].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(),
+                           d_o[:, h:h + 1].contiguous())
+        for n in ("o", "lse", "dq"):
+            assert torch.equal(whole[n][:, h:h + 1], alone[n]), (n, h)
+    cut = lambda t: t.reshape(K, L, t.shape[1], -1)[:, :Lc].reshape(K * Lc, t.shape[1], -1).contiguous()
+    crop = _heads_run(tm, Lc, K, *(cut(t) for t in (q, k, v, d_o)))
+    for n in ("o", "lse", "dq"):                    # (896 anchors are whole row tiles)
+        assert torch.equal(cut(whole[n]).view_as(crop[n]), crop[n]), n
+
+
 def test_run_to_run_determinism():
     L, K, Hq, Hkv, D = 300, 8, 4, 2, 64
     print("case determinism", flush=True)
@@ -891,20 +928,10 @@ def test_both_dq_kernels_give_the_same_bits(form, qscale):
     rnd = lambda H, f=1.0: (torch.randn(T, H, D, generator=g, device="cuda") * f).to(torch.bfloat16)
     q, k, v, d_o = rnd(Hq, qscale), rnd(Hkv), rnd(Hkv), rnd(Hq)
 
-    def run(q, k, v, d_o):
-        shape = pe.Shape(L, K, q.shape[1], k.shape[1], D)
-        o, dq = (torch.full_like(q, float("nan")) for _ in range(2))
-        lse = torch.full((q.shape[1], T), float("nan"), device="cuda")
-        dk, dv = (torch.full(k.shape, float("nan"), device="cuda") for _ in range(2))
-        ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
-        pe.peagle_attn_step_partitioned(tm, shape, 0, tm.info()["S"], q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
-        torch.cuda.synchronize()
-        return {"o": o, "dq": dq, "lse": lse.t(), "dk": dk, "dv": dv}
-
-    whole = run(q, k, v, d_o)
+    whole = _heads_run(tm, L, K, q, k, v, d_o)
     for h in range(0, Hkv, 3):
         a, b = slice(h * (Hq // Hkv), (h + 1) * (Hq // Hkv)), slice(h, h + 1)
-        part = run(q[:, a].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(), d_o[:, a].contiguous())
+        part = _heads_run(tm, L, K, q[:, a].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(), d_o[:, a].contiguous())
         for n, t in part.items():
             assert torch.isfinite(t).all(), n
             assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
@@ -923,15 +950,8 @@ def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
     full = [torch.randn(K, L, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq)]
     results = []
     for tm, n in zip(maps, (own, L)):
-        q, k, v, d_o = (t[:, :n].reshape(K * n, t.shape[2], D).contiguous() for t in full)
-        shape = pe.Shape(n, K, Hq, Hkv, D)
-        o, dq = torch.empty_like(q), torch.empty_like(q)
-        lse = torch.empty((Hq, K * n), device="cuda")
-        dk, dv = (torch.empty(k.shape, device="cuda") for _ in range(2))
-        ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
-        pe.peagle_attn_step_partitioned(tm, shape, 0, 1, q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
-        torch.cuda.synchronize()
-        results.append({m: t.view(K, n, -1, D)[:, :own] for m, t in (("o", o), ("dq", dq), ("dk", dk), ("dv", dv))})
+        r = _heads_run(tm, n, K, *(t[:, :n].reshape(K * n, t.shape[2], D).contiguous() for t in full))
+        results.append({m: r[m].view(K, n, -1, D)[:, :own] for m in ("o", "dq", "dk", "dv")})
     for m in results[0]:
         assert torch.equal(results[0][m], results[1][m]), m
 
