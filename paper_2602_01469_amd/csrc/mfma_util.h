@@ -162,7 +162,14 @@ __device__ __forceinline__ const T* uniform_ptr(const T* p) {
 // read before it may be overwritten.  The wait is explicit because a workgroup barrier by itself
 // only orders ordinary LDS traffic; it is an assembly statement with a memory clobber so that it
 // stays behind every earlier LDS read.
+//
+// The wait is written twice.  The assembly statement is the one that the copies' order rests on; the builtin before it
+// (vmcnt 0, other counters unconstrained) tells the compiler that its own loads have arrived too.  Without it the
+// compiler, for which a load issued before a loop may still be in flight on some path, places the wait for that load
+// inside the loop - behind the next tile's untracked copies, which the hardware counter then waits for as well (dK/dV
+// at D = 64, full tiles: 2.36 instead of 2.17 us per row tile with one workgroup per CU).
 __device__ __forceinline__ void dma_publish() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);
   asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
   __syncthreads();
 }

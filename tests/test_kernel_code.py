@@ -1,0 +1,69 @@
+"""What the compiler made of the kernels, read from the library's own code object: properties that the kernels' speed
+rests on, that no result shows, and that a change of source or compiler can silently lose."""
+import re
+import struct
+import subprocess
+
+import pytest
+
+import paper_2602_01469_amd as pe
+from paper_2602_01469_amd.binding import lib_path
+
+LLVM = "/opt/rocm/llvm/bin/"
+BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """The gfx950 code objects inside the built library, one file each."""
+    pe.load_library()
+    data = open(lib_path(), "rb").read()
+    out, at = [], data.find(BUNDLE)
+    while at >= 0:
+        pos = at + len(BUNDLE)
+        (n,) = struct.unpack_from("<Q", data, pos)
+        pos += 8
+        for _ in range(n):
+            off, size, name_len = struct.unpack_from("<QQQ", data, pos)
+            name = data[pos + 24:pos + 24 + name_len]
+            pos += 24 + name_len
+            if b"gfx950" in name and size:
+                path = tmp_path_factory.mktemp("co") / f"{len(out)}.co"
+                path.write_bytes(data[at + off:at + off + size])
+                out.append(str(path))
+        at = data.find(BUNDLE, at + 1)
+    assert out
+    return out
+
+
+def _tool(name, *args):
+    return subprocess.run([LLVM + name, *args], check=True, stdout=subprocess.PIPE, text=True).stdout
+
+
+def _matrix_stretches(disassembly):
+    """(kernel, instructions up to the last matrix instruction) of every stretch without a branch or barrier that holds at
+    least 32 matrix instructions."""
+    kernel, stretch = "", []
+    for line in disassembly.splitlines() + ["<end>:"]:
+        label = re.match(r"^[0-9a-f]* ?<(\S+)>:", line)
+        if label or re.match(r"\s+s_(c?branch|barrier)", line):
+            mfma = [i for i, s in enumerate(stretch) if s.startswith("v_mfma")]
+            if len(mfma) >= 32:
+                yield kernel, stretch[:mfma[-1]]
+            stretch = []
+            kernel = label.group(1) if label else kernel
+        elif line.startswith("\t"):
+            stretch.append(line.strip())
+
+
+def test_full_row_tiles_of_dkdv_wait_for_no_load(code_objects):
+    """The D = 64 dK/dV kernel computes a row tile while the next one is copied: a stretch of matrix instructions that
+    loads nothing itself (the full row tiles) must not wait for vector memory, which would be the next tile's copies."""
+    seen = 0
+    for co in code_objects:
+        for kernel, s in _matrix_stretches(_tool("llvm-objdump", "-d", "--no-show-raw-insn", co)):
+            if "dkdv_kernelILi64E" not in kernel or any(re.match(r"(global|flat|scratch|buffer)_load", x) for x in s):
+                continue
+            seen += 1
+            assert not any("vmcnt" in x for x in s), kernel
+    assert seen >= 6  # dense near and far, listed; with and without the shared vector
