@@ -1129,8 +1129,8 @@ __device__ __forceinline__ void dkdv_pipe_group(DkdvPipe<D>& P, const char* q_ld
 #pragma unroll
       for (int i = gd.e0 + n * j / NG; i < gd.e0 + n * (j + 1) / NG; ++i) {
         float pr = exp2_fast(P.sc[vu][i] * c);
-        if (MODE == 1) {  // the lane's key-major mask word of this unit: bit of row 8*(i/4) + 4g + i%4
-          const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)(cm[gd.vunit & 3] >> (4 * g)), 8 * (i / 4) + (i % 4), 1);
+        if (MODE == 1) {  // the lane's key-major mask word of this unit, shifted down by 4g: bit of row 8*(i/4) + 4g + i%4
+          const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)cm[gd.vunit & 3], 8 * (i / 4) + (i % 4), 1);
           pr = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, pr) & keep);
         }
         P.sc[vu][i] = pr;
@@ -1304,7 +1304,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   bf16x8 kf[D / 16], vf[D / 16];
   int key_tok = 0;
   const bool key_ok = tile_present && key_token(tm, kt, (kblk & 1) * 32 + ln, p.L, key_tok);
-  const int key_anchor = kt * kKeysPerTile + (kblk & 1) * 32 + ln;  // meaningful for depth-0 tiles only
+  // first key of the wave (anchor; meaningful for depth-0 tiles only)
+  const int key0 = __builtin_amdgcn_readfirstlane(kt * kKeysPerTile + (kblk & 1) * 32);
   {
     const size_t off = ((size_t)(key_ok ? key_tok : 0) * p.Hkv + kvh) * D + g * 8;
 #pragma unroll
@@ -1488,11 +1489,25 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
           // which of the tile's 128 rows see this lane's key: four words, one per 32-row unit
           // (scalar base + small per-lane offset: no 64-bit per-lane address is kept across the loop)
           const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
-          const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
+          u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
+          // (Shifted to the lane's half here, behind a statement the compiler cannot look through.  Left to itself it
+          // tests the unshifted words against sixteen bits that it shifts up before the loop, keeps those in registers
+          // across it, spills them, and reloads them behind the copies just issued.)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            uint32_t x = cm[w] >> (4 * g);
+            asm volatile("" : "+v"(x));
+            cm[w] = x;
+          }
           if (!kSkips || __builtin_amdgcn_ballot_w64((cm[0] | cm[1] | cm[2] | cm[3]) != 0) != 0)  // (else: every key is in the rows' future)
             dkdv_rowtile_pipelined<D, 1>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, false, cm);
         } else if (LISTED) {  // only packed maps carry such ids
-          const bool lane_off = key_anchor < -mask_c - 2;
+          // keys in front of the row's sequence are off; as a lane mask in scalar registers (a vector register that held
+          // each lane's key across the loop was spilled, and reloading it waited for the copies just issued)
+          int n_off = -__builtin_amdgcn_readfirstlane(mask_c) - 2 - key0;
+          n_off = n_off < 0 ? 0 : (n_off > 32 ? 32 : n_off);
+          const uint64_t off32 = (1ull << n_off) - 1;
+          const bool lane_off = __builtin_amdgcn_inverse_ballot_w64(off32 | off32 << 32);
           dkdv_rowtile_pipelined<D, 2>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, lane_off);
         }
       }

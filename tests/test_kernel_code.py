@@ -67,3 +67,15 @@ def test_full_row_tiles_of_dkdv_wait_for_no_load(code_objects):
             seen += 1
             assert not any("vmcnt" in x for x in s), kernel
     assert seen >= 6  # dense near and far, listed; with and without the shared vector
+
+
+def test_no_kernel_spills(code_objects):
+    """No kernel keeps registers in scratch memory: a reload inside a loop waits for the copies issued before it."""
+    spilling, seen = {}, 0
+    for co in code_objects:
+        notes = _tool("llvm-readobj", "--notes", co)
+        for name, size in re.findall(r"\.name:\s+(\S+).*?\.private_segment_fixed_size:\s+(\d+)", notes, re.S):
+            seen += 1
+            if int(size):
+                spilling[name] = int(size)
+    assert seen >= 30 and not spilling
