@@ -1721,6 +1721,8 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(const float* src, __bf16
 // in turn (tile i: group i % kGroups), kGroups tiles are copied at a time, and the groups are merged through LDS at
 // the end.  Where two groups are worth their LDS: see the launcher.
 // =====================================================================================
+constexpr int kLongPiece = 16;  // pages; see the launcher
+
 template <int D, int kGroups, int kThreads>
 __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
@@ -1743,18 +1745,23 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
 
   // Request of this workgroup: workgroups start in the order of blockIdx.z, and the requests take them by falling
   // context length, so that the short ones fill the slots that the long ones leave (64 requests of 512 to 8,192
-  // tokens: see the launcher).  Every wave ranks the lengths for itself, one request per lane.
+  // tokens: see the launcher).  Every wave ranks the lengths for itself, one request per lane - unless no request is as
+  // long as the table allows for, where the order earns nothing and ranking is most of a workgroup's time (16 requests of
+  // 500 to 1,000 tokens in a table for 20,000, D = 128, ranked / not: 28.2 / 26.9 us; 64 in a table for 8,192, D = 64:
+  // 42.3 / 33.3).
   int c = blockIdx.z, n_ctx;
   if (!p.by_length) {
     n_ctx = p.ctx_len[c];
   } else {
     const int len = lane < p.C ? p.ctx_len[lane] : INT_MIN;
-    int rank = 0;
-    for (int j = 0; j < p.C; ++j) {
-      const int other = __builtin_amdgcn_readlane(len, j);
-      rank += (other > len || (other == len && j < lane)) ? 1 : 0;
+    if (__builtin_amdgcn_ballot_w64(len > kLongPiece * kKeysPerTile * p.n_splits) != 0) {
+      int rank = 0;
+      for (int j = 0; j < p.C; ++j) {
+        const int other = __builtin_amdgcn_readlane(len, j);
+        rank += (other > len || (other == len && j < lane)) ? 1 : 0;
+      }
+      c = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < p.C && rank == (int)blockIdx.z));
     }
-    c = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < p.C && rank == (int)blockIdx.z));
     n_ctx = __builtin_amdgcn_readlane(len, c);
   }
 
@@ -2269,7 +2276,7 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   const int row_waves = p.rows_pad / 32;  // 1 .. 4
   const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
   const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;
-  const bool long_pieces = (p.max_pages + p.n_splits - 1) / p.n_splits > 16;  // pages of the longest request's pieces
+  const bool long_pieces = (p.max_pages + p.n_splits - 1) / p.n_splits > kLongPiece;  // pages of the longest request's pieces
   // Two groups of waves per workgroup cost twice the LDS.  At D = 64 two such workgroups still share a CU (of one group,
   // five do), which is enough while there are no more, or where pieces are long and few; at D = 128 one does, which pays
   // while there is at most one per CU anyway.  us per call, one / two groups: D = 64, 4 requests of 2,048 - 4,096 tokens

@@ -177,3 +177,22 @@ def test_draft_decode_batches_of_many_workgroups(name, C, longest, K, Hq, Hkv, D
     others = np.arange(C) != C // 2
     assert status2[C // 2] == 1 and (status2[others] == 0).all()
     assert np.array_equal(o2[others], o[others]) and np.array_equal(lse2[others], lse[others])
+
+
+@pytest.mark.parametrize("longest", [1000, 2 * 16 * 64, 2 * 16 * 64 + 1, 8192])
+def test_draft_decode_in_a_table_wider_than_its_requests(longest):
+    """Sixty-four requests in a table of 128 pages, two pieces each: taken by falling length only if one of them is longer
+    than two pieces of sixteen pages."""
+    C, K, Hq, Hkv, D = 64, 4, 16, 8, 64
+    rng = np.random.default_rng(longest)
+    lens = rng.integers(0, 1000, C)
+    lens[C // 3] = longest
+    print(f"case decode wide table: longest {longest}", flush=True)
+    inp = make_decode_inputs(tuple(int(x) for x in lens), K, Hq, Hkv, D, 1200)
+    table = np.full((C, 128), -1, dtype=np.int32)
+    table[:, :inp["max_pages"]] = inp["block_table"]
+    r = DecodeRun(inp | {"block_table": table, "max_pages": 128}, K, Hq, Hkv, D)
+    assert pe.peagle_draft_decode_splits(r.shape) == 2
+    o, lse, status = r.run()
+    assert (status == 0).all()
+    _check(inp, o, lse, r.shape.scale, f"wide table {longest}")
