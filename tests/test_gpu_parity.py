@@ -81,8 +81,8 @@ def _oracle(qb, kb, vb, dob, L, K, scale):
 
 SMALL = [
     # name, L, K, Hq, Hkv, D, seed, bounds, L_max
-    ("two_heads_per_wg", 128, 4, 4, 1, 64, 100, None, None),
-    ("one_head_per_wg", 128, 4, 3, 3, 64, 110, None, None),
+    ("even_group", 128, 4, 4, 1, 64, 100, None, None),
+    ("odd_group", 128, 4, 3, 3, 64, 110, None, None),
     ("ragged_tail", 100, 8, 4, 2, 64, 120, None, None),
     ("k_not_dividing_128", 50, 3, 2, 1, 64, 130, None, None),
     ("k1_plain_causal", 300, 1, 2, 2, 64, 140, None, None),
@@ -156,10 +156,10 @@ def test_small_cases_match_oracle(name, L, K, Hq, Hkv, D, seed, bounds, L_max):
 
 
 @pytest.mark.parametrize("bounds", [None, [0, 1040, 1500]], ids=["one_pass", "two_segments"])
-def test_dense_segments_longer_than_one_dkdv_launch(bounds):
-    """94 row tiles in one segment (or 65 + 29): the dK/dV launcher cuts a dense segment into launches of at
-    most 64 row tiles, later launches adding to what earlier ones wrote, each followed by its own reduction;
-    every element of every output against the oracle."""
+def test_dense_segments_of_many_row_tiles(bounds):
+    """94 row tiles in one segment (or 65 + 29): more row tiles than key-tile pairs in one dK/dV launch, and a second
+    segment adding to what the first wrote, each followed by its own reduction; every element of every output
+    against the oracle.  (Segments cut into several launches: test_dense_segments_of_more_than_128_row_tiles.)"""
     L, K, Hq, Hkv, D, seed = 1500, 8, 2, 1, 64, 290
     print(f"case dense long segments: L={L} K={K} Hq={Hq} Hkv={Hkv} D={D} seed={seed} bounds={bounds}", flush=True)
     qb, kb, vb, dob = (rand_bits((L * K, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
@@ -180,15 +180,30 @@ def test_dense_segments_longer_than_one_dkdv_launch(bounds):
         assert rel_l2(got[n], whole[n]) <= PART_REL, n
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (4, 2)])
+def test_two_heads_per_forward_workgroup_match_oracle(Hq, Hkv):
+    """Lists long enough (mean above 10) for the forward to take the heads of a group two at a time at D = 64."""
+    L, K, D, seed = 1290, 4, 64, 296
+    print(f"case two heads per workgroup Hq={Hq} Hkv={Hkv}", flush=True)
+    qb, kb, vb, dob = (rand_bits((L * K, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
+    tm = pe.peagle_build_tilemap(L, K, [0, 640, L], device=0)
+    assert mean_list(tm) > 11
+    r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
+    r.step(0, 2)
+    _check_against_oracle(r.results(), _oracle(qb, kb, vb, dob, L, K, r.shape.scale), "two heads per workgroup")
+
+
+@pytest.mark.parametrize("L", [600, 2000])
 @pytest.mark.parametrize("qscale", [10.0, 12.0, 40.0])
-def test_large_logits_take_the_running_max_path(qscale):
+def test_large_logits_take_the_running_max_path(qscale, L):
     """Scores far outside the exponent range that the forward's first pass (reference max fixed at
-    0) can hold: the kernel must detect it and redo the row tile with the running-max form.  The dQ
-    kernel leaves its probabilities unnormalised only while |lse| <= 64 in log2 units: at the smaller
-    scales some workgroups are inside that range and some outside, at the largest none is inside, and
-    the sequence is long enough for the pipelined groups of three full tiles to occur."""
-    L, K, Hq, Hkv, D = 600, 4, 4, 2, 64
-    print(f"case large_logits qscale={qscale}", flush=True)
+    0) can hold: the kernel must detect it and redo the row tile with the running-max form, with one head
+    per workgroup (short lists) and with two.  The dQ kernel leaves its probabilities unnormalised only
+    while |lse| <= 64 in log2 units: at the smaller scales some workgroups are inside that range and some
+    outside, at the largest none is inside, and both sequences are long enough for the pipelined kernel's
+    groups of three full tiles to occur (the plain one: test_both_dq_kernels_give_the_same_bits)."""
+    K, Hq, Hkv, D = 4, 4, 2, 64
+    print(f"case large_logits qscale={qscale} L={L}", flush=True)
     T = L * K
     qb, kb, vb, dob = (rand_bits((T, Hq, D), 300, qscale), rand_bits((T, Hkv, D), 301), rand_bits((T, Hkv, D), 302),
                        rand_bits((T, Hq, D), 303))
@@ -198,6 +213,11 @@ def test_large_logits_take_the_running_max_path(qscale):
     r.bwd()
     got = r.results()
     ref = _oracle(qb, kb, vb, dob, L, K, r.shape.scale)
+    assert (mean_list(tm) < 10) == (L == 600) and (mean_list(tm) > 11) == (L == 2000) and not runs_plain_dq(tm, Hq)
+    outside = np.abs(ref["LSE"]) * np.log2(np.e) > 64                                  # [Hq, K * L]
+    row_tile = np.arange(T) % L // 32
+    share = np.mean([outside[h, row_tile == t].any() for h in range(Hq) for t in range(row_tile.max() + 1)])
+    assert share == 1 if qscale == 40.0 else 0 < share < 1, share                      # workgroups outside dQ's range
     lse_span = ref["LSE"].max() - ref["LSE"].min()
     assert lse_span > 60 * (qscale / 12.0)       # the case really leaves the comfortable range
     assert not any(np.isnan(got[n]).any() for n in got)
@@ -613,7 +633,7 @@ PACKED = [
     ("segments_across_sequences_sampled", (100, 37, 64, 1, 90), 8, 2, 1, 64, 0.8, 420, [0, 50, 120, 292], 1),
     ("d128_two", (90, 60), 8, 2, 1, 128, None, 430, [0, 64, 150], 0),
     ("k1_three", (130, 130, 130), 1, 2, 2, 64, None, 440, [0, 200, 390], 0),
-    # more than 64 row tiles in a segment: the dK/dV launches are split into chunks
+    # more than 64 row tiles in a segment (one dK/dV launch: only dense segments are cut into chunks)
     ("long_packed_chunks", (700, 900, 500), 8, 2, 1, 64, None, 450, None, 0),
     ("long_sampled_chunks_alg1", (1500, 800), 8, 2, 1, 64, 0.8, 460, [0, 2050, 2300], 1),
 ]

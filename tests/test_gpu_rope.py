@@ -368,6 +368,8 @@ def test_rope_step_with_shared_chain_vectors_matches_oracle(name, seq_lens, K, H
 
 
 def test_shared_chain_vectors_with_lists_of_every_length():
+    """The pipelined dQ kernel (few workgroups) over lists that do and do not fill its groups of three."""
+    assert not runs_plain_dq(pe.peagle_build_tilemap(1800, 4, [0, 640, 1800], device=-1), 2)
     test_rope_step_with_shared_chain_vectors_matches_oracle("dense_long_lists", (1800,), 4, 2, 1, 64, None, 3080,
                                                             [0, 640, 1800], True)
 
