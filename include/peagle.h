@@ -163,8 +163,8 @@ int peagle_attn_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* shape, int
 
 /*
  * Within-sequence gradient accumulation (Sec. 3.2, Algorithm 1 for dense position sets): runs
- * forward + backward for segments seg_begin .. seg_end-1 one after another and accumulates dK/dV
- * across them in fp32.  Each query row is computed in exactly one segment.
+ * forward and dQ over the rows of segments seg_begin .. seg_end-1, then dK/dV segment by segment,
+ * accumulated across them in fp32.  Each query row is computed in exactly one segment.
  *
  * dK/dV need no zeroing when segments run in increasing order starting at 0: a depth-0 key first
  * touched by segment s is overwritten there and added to by later segments; chain keys are written
@@ -286,7 +286,7 @@ size_t peagle_rope_workspace_bytes(const peagle_tilemap_t* tm, const peagle_shap
 
 /*
  * peagle_attn_step_partitioned on unrotated Q and K: both are rotated by their tokens' positions
- * (one streaming pass each, into the workspace), every segment's forward and backward run on the
+ * (one streaming pass each, into the workspace), forward and backward of all segments run on the
  * rotated copies, and dQ, dK are returned with respect to the unrotated inputs: the gradient
  * vectors are turned back (R^T) in fp32 inside the kernels that store them (dQ kernel, chain-key
  * epilogue of the dK/dV kernel, summation of the depth-0 partials), so dk_acc stays in the

@@ -1,5 +1,5 @@
 // C-ABI entry points: host-side validation and the sequence-partition driver (Sec. 3.2 of the
-// paper: one forward+backward pass per segment, dK/dV accumulated across segments in fp32).
+// paper: forward and dQ over all segments of a call, then dK/dV segment by segment, accumulated in fp32).
 #include <climits>
 #include <cmath>
 #include <mutex>

@@ -2086,6 +2086,8 @@ __global__ __launch_bounds__(256) void mfma_ceiling_kernel(float* out, int iters
 
 namespace {
 
+constexpr int kCus = 256;  // compute units of the device
+
 // Query heads of one KV group that share a workgroup's K/V tiles in the forward: two at D = 64 (the register
 // budget of two waves per SIMD allows it) unless the row tiles' lists are short - then four one-head workgroups per
 // CU cover one another's first loads and last stores -, one at D = 128.  The line lies where both take the same time;
@@ -2190,7 +2192,7 @@ hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer*
   // 83; few, L = 1,000, 4 heads (11; 252) 24 / 29, 16 heads (11; 1,008) 49 / 54, L = 2,048, K = 4, 16 heads (18; 1,024)
   // 73 / 75, L = 3,000, 8 heads (26; 1,504) 131 / 132; long lists, L = 4,096, 16 heads (35; 4,096) 422 / 427, 64 heads
   // (35; 16,384) 1,666 / 1,646, L = 8,000, 4 heads (65; 2,000) 376 / 392, sampled 8,192 (67) 3,195 / 3,277.
-  constexpr int kPlainMeanTiles = 24, kPlainWorkgroups = 2 * 3 * 256;
+  constexpr int kPlainMeanTiles = 24, kPlainWorkgroups = 2 * 3 * kCus;
   const int n_wg = n_rt * p.Hq;  // one query head per workgroup
   const bool plain = p.mean_tiles <= kPlainMeanTiles && n_wg >= kPlainWorkgroups;
   TimedSpan span(timer, kKindDq, stream);
@@ -2259,7 +2261,7 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
       const int key_first = p.d0_tile_lo * kKeysPerTile;
       const size_t n = 2 * (size_t)(c_a_hi - key_first) * p.Hkv * (D / 4);
       size_t blocks = (n + 255) / 256;
-      if (blocks > 256 * 16) blocks = 256 * 16;
+      if (blocks > kCus * 16) blocks = kCus * 16;
       const dim3 grid((unsigned)blocks), block(256);
       TimedSpan span(timer, kKindReduce, stream);
       if (D == 64) hipLaunchKernelGGL((reduce_partials_kernel<64>), grid, block, 0, stream, p, key_first, c_a_hi, c_acc);
@@ -2283,12 +2285,12 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   // (512 workgroups) 20.3 / 19.1, 64 of 512 - 8,192 (pieces of up to 64 pages) 134 / 120, 16 of 2,000 - 20,000 (39) 89 /
   // 80, 55 of 1,691 - 2,469 (13) 67 / 77, 64 of 100 - 1,000 (8) 30 / 41; D = 128, 2 of 10,800 - 20,000 (256 workgroups)
   // 23.1 / 21.2, 16 of 800 - 8,192 (1,024) 54 / 66.  More than 64 query rows make nine waves, too many for two per CU.
-  const bool two = row_waves <= 2 && (D == 64 ? n_wg <= 512 || long_pieces : n_wg <= 256);
+  const bool two = row_waves <= 2 && (D == 64 ? n_wg <= 2 * kCus || long_pieces : n_wg <= kCus);
   // Long pieces of requests of different lengths: with more workgroups than two per CU, those of the longest requests
   // start first.  us per call in order of the request / by length: the 64 requests of 512 to 8,192 tokens above 161 /
   // 120, at D = 128 149 / 133; but 35 of 2,137 - 3,838 at D = 128 (pieces of 8 pages) 70.8 / 74.7: ranking costs most of
   // a page's time.  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
-  p.by_length = p.C > 1 && p.C <= 64 && n_wg > 512 && long_pieces;
+  p.by_length = p.C > 1 && p.C <= 64 && n_wg > 2 * kCus && long_pieces;
   const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + 1) * 64));
   // (The bound of 576 threads, of which 320 are launched, has the compiler schedule for four waves per SIMD: 120
   // against 136 us on the first of those batches.  The other forms run the same with either bound.)
@@ -2305,7 +2307,7 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   auto merge = [&](auto kernel, int rows_per_wave) {
     const size_t waves = ((size_t)p.C * p.Hkv * p.K * (p.Hq / p.Hkv) + rows_per_wave - 1) / rows_per_wave;
     size_t blocks = (waves + 3) / 4;
-    if (blocks > 256 * 16) blocks = 256 * 16;
+    if (blocks > kCus * 16) blocks = kCus * 16;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p);
   };
   if (D == 64) {
@@ -2324,7 +2326,7 @@ hipError_t launch_cast_bf16(const float* src, void* dst, size_t n, hipStream_t s
   const size_t n4 = n / 4;
   if (n4 == 0) return hipSuccess;
   size_t blocks = (n4 + 255) / 256;
-  if (blocks > 256 * 16) blocks = 256 * 16;
+  if (blocks > kCus * 16) blocks = kCus * 16;
   hipLaunchKernelGGL(cast_bf16_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, src, (__bf16*)dst, n4);
   return hipGetLastError();
 }
