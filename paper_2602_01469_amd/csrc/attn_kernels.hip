@@ -181,7 +181,8 @@ __device__ __forceinline__ RowDmaLane<D, NW> row_dma_lane(const DeviceTileMap& t
 }
 // Dense maps whose tensors span less than 4 GiB: byte offset of each copy's source from the head's row of the tile's
 // first anchor, ((d*L + a) * Hq) * D * 2 + 2 * chunk (and 4 * (d*L + a) for the statistic) - the same for every row
-// tile and head, so a copy needs only a new scalar base.
+// tile and head, so a copy needs only a new scalar base.  (Where the rows a lane copies are a whole number of anchors
+// apart, the copies' offsets differ by a scalar step and off[0] is all that is kept.)
 template <int D, int NW>
 struct RowDmaOffsets {
   uint32_t off[RowDmaLane<D, NW>::kPer], stat_off;
@@ -1061,13 +1062,98 @@ struct PipeGroup {
 };
 constexpr PipeGroup kPipeGroups[8] = {{0, 0, -1, 0, 0}, {0, 1, 0, 0, 16}, {1, 0, 1, 0, 8},  {0, 2, 1, 8, 16},
                                       {1, 1, 2, 0, 8},  {0, 3, 2, 8, 16}, {1, 2, 3, 0, 16}, {1, 3, -1, 0, 0}};
-constexpr int kPipeAhead = 2;
+// (Fragments ahead, dK/dV of a step at D = 64, us: one 2,285, two 2,258, three 2,435 - spills.  At D = 128, with one wave per
+// SIMD and room for more, L = 10,816: two 13,436, four 13,229; six against four 14,226 and 13,879 on another box.)
+template <int D>
+constexpr int kPipeAhead = D == 128 ? 4 : 2;
+// The copies of the next row tile are issued one after every kCopyEvery-th matrix instruction.  Issued all together, each
+// holds its wave for about 100 cycles (the address unit takes 1 KiB of copies in 25, and the other waves issue theirs at
+// the same time): 17 copies at D = 128 were 2,085 of an iteration's 9,100 cycles, 9 at D = 64 1,275 of 6,400.  dK/dV, us,
+// together / spread: D = 128 L = 10,816 14,650 / 13,820, L = 1,391 354 / 333, K = 7 L = 4,000 2,025 / 1,890; D = 64, where
+// another wave of the SIMD covers most of it, L = 4,096 2,160 / 2,130, 4 heads (one workgroup per CU) L = 3,000 395 / 361.
+// (Every third or sixth: the same within 0.5 %.)
+constexpr int kCopyEvery = 4;
+
+// f(0), f(1), .. f(N-1), the argument a compile-time constant.
+template <int J, int N, class F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (J < N) {
+    f(std::integral_constant<int, J>{});
+    unrolled<J + 1, N>(f);
+  }
+}
+
+// The copies that a routine issues between its matrix instructions: none, or this wave's share of the next row tile.
+struct NoCopies {
+  template <int M>
+  __device__ __forceinline__ void after() const {}
+};
+template <int D, bool WHOLE>
+struct NextRowTile {
+  const __bf16 *q, *d_o;           // the head's row of the tile's first anchor
+  const float* stat;
+  const RowDmaOffsets<D, 4>& ro;   // WHOLE: of copy 0 only, copy i reads i * step behind it
+  uint32_t step;
+  uint32_t dst, stat_dst;          // LDS
+  bool last_ok, stat_ok;           // not WHOLE: the lane's row of the last copy, and of the statistic, exists
+  const void* zeros;
+  static constexpr int kPer = RowDmaLane<D, 4>::kPer;
+  static constexpr int kCopies = 2 * kPer + 1;
+  template <int C>
+  __device__ __forceinline__ void issue() const {
+    constexpr int i = C >> 1, kOff = (C & 1) * kRowsPerTile * D * 2 + i * 4096;
+    const __bf16* base = C & 1 ? d_o : q;
+    if constexpr (C == 2 * kPer) {
+      if (WHOLE) dma4_untracked_at<0>(stat, ro.stat_off, stat_dst);
+      else dma4_untracked(stat_ok ? (const void*)((const char*)stat + ro.stat_off) : zeros, stat_dst);
+    } else if constexpr (WHOLE) {
+      dma16_untracked_at<kOff>(base, ro.off[0] + i * step, dst);
+    } else if constexpr (i < kPer - 1) {
+      dma16_untracked_at<kOff>(base, ro.off[i], dst);
+    } else {
+      dma16_untracked(last_ok ? (const void*)((const char*)base + ro.off[i]) : zeros, dst + kOff);
+    }
+  }
+  template <int M>
+  __device__ __forceinline__ void after() const {  // behind matrix instruction M of the row tile
+    if constexpr (M % kCopyEvery == 0 && M / kCopyEvery < kCopies) issue<M / kCopyEvery>();
+  }
+};
+
+// The same for rows named by token lists: an address per lane and copy.
+template <int D>
+struct NextListedRowTile {
+  const __bf16 *q, *d_o;           // the head's row of token 0
+  const float* stat;
+  const RowTokens<D, 4>& t;
+  const RowDmaLane<D, 4>& rl;
+  int Hq;
+  uint32_t dst, stat_dst;
+  const void* zeros;
+  static constexpr int kPer = RowDmaLane<D, 4>::kPer;
+  static constexpr int kCopies = 2 * kPer + 1;
+  template <int C>
+  __device__ __forceinline__ void issue() const {
+    if constexpr (C == 2 * kPer) {
+      dma4_untracked(t.stat_tok >= 0 ? (const void*)(stat + t.stat_tok) : zeros, stat_dst);
+    } else {
+      constexpr int i = C >> 1;
+      const bool ok = t.tok[i] >= 0;
+      const size_t off = (size_t)(ok ? t.tok[i] : 0) * (Hq * D) + rl.chunk[i];
+      dma16_untracked(ok ? (const void*)((C & 1 ? d_o : q) + off) : zeros, dst + (C & 1) * kRowsPerTile * D * 2 + i * 4096);
+    }
+  }
+  template <int M>
+  __device__ __forceinline__ void after() const {
+    if constexpr (M % kCopyEvery == 0 && M / kCopyEvery < kCopies) issue<M / kCopyEvery>();
+  }
+};
 
 template <int D>
 struct DkdvPipe {
   f32x16 sc[2], dpc[2];        // S and dP accumulators of the units in flight (unit & 1)
   u32x4 pb[2][2], dsb[2][2];   // P and dS of a unit as bf16 B operands, per 16-row step
-  bf16x8 ring[kPipeAhead];     // A operands on their way from LDS
+  bf16x8 ring[kPipeAhead<D>];  // A operands on their way from LDS
 };
 
 // A operand of matrix instruction j of a group: S / dP read natural fragments (even j: Q, odd j: dO),
@@ -1096,8 +1182,8 @@ __device__ __forceinline__ void pipe_row_terms(f32x16& s, f32x16& dp, const floa
   }
 }
 
-template <int D, int MODE, int G>
-__device__ __forceinline__ void dkdv_pipe_group(DkdvPipe<D>& P, const char* q_lds, const char* do_lds,
+template <int D, int MODE, int G, class Copies>
+__device__ __forceinline__ void dkdv_pipe_group(const Copies& copies, DkdvPipe<D>& P, const char* q_lds, const char* do_lds,
                                                 const float* nlse_lds, const float* ndelta_lds, const NatOff<D>& no,
                                                 const TrOff<D>& to, const bf16x8 (&kf)[D / 16],
                                                 const bf16x8 (&vf)[D / 16], f32x16 (&dk)[D / 32], f32x16 (&dv)[D / 32],
@@ -1108,9 +1194,9 @@ __device__ __forceinline__ void dkdv_pipe_group(DkdvPipe<D>& P, const char* q_ld
   constexpr int u = gd.unit & 1, vu = gd.vunit & 1;
   if (G + 1 < 8 && gn.kind == 0)  // the next group starts S / dP of a unit: fetch its per-row terms now
     pipe_row_terms<MODE>(P.sc[gn.unit & 1], P.dpc[gn.unit & 1], nlse_lds, ndelta_lds, gn.unit * 32, g, lane_off);
-#pragma unroll
-  for (int j = 0; j < NG; ++j) {
-    const int slot = (G * NG + j) % kPipeAhead;  // the instruction kPipeAhead later takes the slot this one frees
+  unrolled<0, NG>([&](auto j_tag) {
+    constexpr int j = decltype(j_tag)::value;
+    const int slot = (G * NG + j) % kPipeAhead<D>;  // the instruction kPipeAhead<D> later takes the slot this one frees
     const bf16x8 a = P.ring[slot];
     if (gd.kind == 0) {
       if (j & 1) P.dpc[u] = mfma32(a, vf[j >> 1], P.dpc[u]);
@@ -1120,10 +1206,10 @@ __device__ __forceinline__ void dkdv_pipe_group(DkdvPipe<D>& P, const char* q_ld
       if (j & 1) dk[db] = mfma32(a, __builtin_bit_cast(bf16x8, P.dsb[u][tt]), dk[db]);
       else dv[db] = mfma32(a, __builtin_bit_cast(bf16x8, P.pb[u][tt]), dv[db]);
     }
-    if (j + kPipeAhead < NG)
-      P.ring[slot] = pipe_frag<D, gd.kind>(q_lds, do_lds, no, to, gd.unit * 32, j + kPipeAhead);
+    if (j + kPipeAhead<D> < NG)
+      P.ring[slot] = pipe_frag<D, gd.kind>(q_lds, do_lds, no, to, gd.unit * 32, j + kPipeAhead<D>);
     else if (G + 1 < 8)
-      P.ring[slot] = pipe_frag<D, gn.kind>(q_lds, do_lds, no, to, gn.unit * 32, j + kPipeAhead - NG);
+      P.ring[slot] = pipe_frag<D, gn.kind>(q_lds, do_lds, no, to, gn.unit * 32, j + kPipeAhead<D> - NG);
     if (gd.vunit >= 0) {
       const int n = gd.e1 - gd.e0;
 #pragma unroll
@@ -1141,12 +1227,13 @@ __device__ __forceinline__ void dkdv_pipe_group(DkdvPipe<D>& P, const char* q_ld
         }
       }
     }
+    copies.template after<G * NG + j>();
     __builtin_amdgcn_sched_barrier(0);
-  }
+  });
 }
 
-template <int D, int MODE>
-__device__ __forceinline__ void dkdv_rowtile_pipelined(const char* q_lds, const char* do_lds, const float* nlse_lds,
+template <int D, int MODE, class Copies>
+__device__ __forceinline__ void dkdv_rowtile_pipelined(const Copies& copies, const char* q_lds, const char* do_lds, const float* nlse_lds,
                                                        const float* ndelta_lds, const NatOff<D>& no, const TrOff<D>& to,
                                                        const bf16x8 (&kf)[D / 16], const bf16x8 (&vf)[D / 16],
                                                        f32x16 (&dk)[D / 32], f32x16 (&dv)[D / 32], int g, float c,
@@ -1154,9 +1241,9 @@ __device__ __forceinline__ void dkdv_rowtile_pipelined(const char* q_lds, const 
   DkdvPipe<D> P;
   pipe_row_terms<MODE>(P.sc[0], P.dpc[0], nlse_lds, ndelta_lds, 0, g, lane_off);
 #pragma unroll
-  for (int j = 0; j < kPipeAhead; ++j) P.ring[j] = pipe_frag<D, 0>(q_lds, do_lds, no, to, 0, j);
+  for (int j = 0; j < kPipeAhead<D>; ++j) P.ring[j] = pipe_frag<D, 0>(q_lds, do_lds, no, to, 0, j);
 #define PEAGLE_PIPE_GROUP(G) \
-  dkdv_pipe_group<D, MODE, G>(P, q_lds, do_lds, nlse_lds, ndelta_lds, no, to, kf, vf, dk, dv, g, c, lane_off, cm)
+  dkdv_pipe_group<D, MODE, G>(copies, P, q_lds, do_lds, nlse_lds, ndelta_lds, no, to, kf, vf, dk, dv, g, c, lane_off, cm)
   PEAGLE_PIPE_GROUP(0);
   PEAGLE_PIPE_GROUP(1);
   PEAGLE_PIPE_GROUP(2);
@@ -1210,12 +1297,20 @@ __device__ __forceinline__ void dkdv_rowtile_chain(const char* q_lds, const char
   }
 }
 
-// How the rows of a row tile are found.  kRowsNear: dense map, tensors within reach of a 32-bit offset (RowDmaOffsets).
-// kRowsFar: dense map, larger tensors; tokens are computed when a copy is issued.  kRowsListed: the map names rows by
-// explicit token lists (sampled / packed maps); their tokens are fetched an iteration before the copy that uses them.
+// How the rows of a row tile are found.
+//   kRowsWhole, kRowsMost: dense map, tensors within reach of a 32-bit offset (RowDmaOffsets), L >= A: every row tile but the
+//     sequence's last holds the same rows, and the copies of the next one ride between the matrix instructions
+//     (NextRowTile).  Whole: the rows a lane copies are a whole number of anchors apart (K divides kRowsApart, so that
+//     A * K = 128): one per-lane offset and a scalar step address every copy.  Most: an offset per copy, and the last copy
+//     of a tile holds the rows past A * K (A * K > 128 - kRowsApart).
+//   kRowsFar: any other dense map; tokens are computed when a copy is issued.
+//   kRowsListed: the map names rows by explicit token lists (sampled / packed maps); their tokens are fetched an
+//     iteration before the copy that uses them.
 // (A near loop that carried every row's token and anchor as the far one does reloaded spilled registers behind its own
 // copies, and waited for them: dK/dV at L = 4,096 2,226 us, now 2,152.)
-enum { kRowsNear = 0, kRowsFar = 1, kRowsListed = 2 };
+enum { kRowsWhole = 0, kRowsFar = 1, kRowsListed = 2, kRowsMost = 3 };
+template <int D>
+constexpr int kRowsApart = 4 * (512 / D);  // rows of the tile between two copies of a lane
 template <int D, int ROWS, bool SV>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p) {
   constexpr bool LISTED = ROWS == kRowsListed;
@@ -1333,13 +1428,9 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   using Toks = RowTokens<D, 4>;
   RowDmaLane<D, 4> rl;
   RowDmaOffsets<D, 4> ro;
-  if (ROWS == kRowsNear) ro = row_dma_offsets<D, 4>(tm, p.L, wave, lane, p.Hq);
+  constexpr bool kWhole = ROWS == kRowsWhole, kNear = kWhole || ROWS == kRowsMost;
+  if (kNear) ro = row_dma_offsets<D, 4>(tm, p.L, wave, lane, p.Hq);
   else rl = row_dma_lane<D, 4>(tm, p.L, wave, lane);
-  // The rows a lane copies are kRowsApart apart; when that is a whole number of anchors (K divides it), copy i
-  // reads near_step elements behind copy i-1 for every lane: the step goes into the scalar base and one per-lane
-  // offset serves all copies.  Otherwise (near_step = 0) each copy has its own per-lane offset.
-  constexpr int kRowsApart = 4 * (512 / D);
-  const size_t near_step = kRowsApart % tm.K == 0 ? (size_t)(kRowsApart / tm.K) * p.Hq * D : 0;
   // Everything but the per-lane offset is computed on the scalar unit from values forced wave-uniform (the
   // compiler otherwise carries the row tile and head in vector registers and builds each copy's 64-bit
   // address there): LDS addresses are plain integers from the buffer's base, the source pointers scalar
@@ -1347,48 +1438,54 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   const uint32_t lds_addr0 = lds_scalar_addr(lds);
   const uint32_t wave_s = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
   constexpr int kPer = RowDmaLane<D, 4>::kPer;
-  auto issue_near = [&](int hh, int rt, int buf) {
+  const int full_rows = tm.A * tm.K;  // rows of every tile but the sequence's last
+  auto next_rows = [&](int hh, int rt, int buf) {
     const int hh_s = __builtin_amdgcn_readfirstlane(hh), rt_s = __builtin_amdgcn_readfirstlane(rt);
-    const uint32_t dst = lds_addr0 + (uint32_t)buf * kBufBytes + wave_s * 1024;
     const size_t row0 = ((size_t)rt_s * tm.A * p.Hq + hh_s) * D;
-    const __bf16* qs = p.q + row0;
-    const __bf16* ds = p.d_o + row0;
-    const float* stat0 = (wave_s < 2 ? p.nlse : p.delta) + (size_t)hh_s * p.T + (size_t)rt_s * tm.A;
-    const uint32_t stat_dst = lds_addr0 + (uint32_t)buf * kBufBytes + 2 * kTileBytes + (wave_s < 2 ? 0 : kRowsPerTile * 4) +
-                              (wave_s & 1) * 64 * 4;
-    // rows are ordered anchor by anchor: those that exist are the first n_valid
-    const int left = p.L - rt_s * tm.A, n_valid = (left < tm.A ? left : tm.A) * tm.K;
-    if (n_valid == kRowsPerTile) {
-      if (near_step) {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) dma16_untracked(qs + i * near_step, ro.off[0], dst + i * 4 * 1024);
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) dma16_untracked(ds + i * near_step, ro.off[0], dst + kTileBytes + i * 4 * 1024);
-      } else {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) dma16_untracked(qs, ro.off[i], dst + i * 4 * 1024);
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) dma16_untracked(ds, ro.off[i], dst + kTileBytes + i * 4 * 1024);
-      }
-      dma4_untracked(stat0, ro.stat_off, stat_dst);
+    const uint32_t at = lds_addr0 + (uint32_t)buf * kBufBytes;
+    return NextRowTile<D, kWhole>{
+        p.q + row0, p.d_o + row0, (wave_s < 2 ? p.nlse : p.delta) + (size_t)hh_s * p.T + (size_t)rt_s * tm.A, ro,
+        (uint32_t)(kRowsApart<D> / tm.K * p.Hq * D * 2), at + wave_s * 1024,
+        at + 2 * kTileBytes + (wave_s < 2 ? 0 : kRowsPerTile * 4) + (wave_s & 1) * 64 * 4,
+        kRowsPerTile - kRowsApart<D> + (int)wave_s * (512 / D) + lane / (D / 8) < full_rows,
+        (int)(wave_s & 1) * 64 + lane < full_rows, tm.zeros};
+  };
+  // rows are ordered anchor by anchor: those that exist are the first rows_of()
+  auto rows_of = [&](int rt) {
+    const int left = p.L - __builtin_amdgcn_readfirstlane(rt) * tm.A;
+    return (left < tm.A ? left : tm.A) * tm.K;
+  };
+  auto issue_near = [&](int hh, int rt, int buf) {
+    const auto n = next_rows(hh, rt, buf);
+    const int n_valid = rows_of(rt);
+    if (n_valid == full_rows) {
+      unrolled<0, n.kCopies>([&](auto c) { n.template issue<decltype(c)::value>(); });
       return;
     }
-    // (the last row tile of the sequence, and every tile of a map with A * K < 128: only the copies that hold rows
-    // past n_valid need per-lane addresses, which take those rows from the zero page)
+    // (the last row tile of the sequence: only the copies that hold rows past n_valid need per-lane addresses, which take
+    // those rows from the zero page)
     const int row = (int)wave_s * (512 / D) + lane / (D / 8);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
+      const uint32_t off = kWhole ? ro.off[0] + i * n.step : ro.off[i];
       if ((int)(i * 4 + wave_s + 1) * (512 / D) <= n_valid) {
-        dma16_untracked(qs, ro.off[i], dst + i * 4 * 1024);
-        dma16_untracked(ds, ro.off[i], dst + kTileBytes + i * 4 * 1024);
+        dma16_untracked(n.q, off, n.dst + i * 4 * 1024);
+        dma16_untracked(n.d_o, off, n.dst + kTileBytes + i * 4 * 1024);
       } else {
-        const bool ok = row + i * kRowsApart < n_valid;
-        dma16_untracked(ok ? (const void*)((const char*)qs + ro.off[i]) : tm.zeros, dst + i * 4 * 1024);
-        dma16_untracked(ok ? (const void*)((const char*)ds + ro.off[i]) : tm.zeros, dst + kTileBytes + i * 4 * 1024);
+        const bool ok = row + i * kRowsApart<D> < n_valid;
+        dma16_untracked(ok ? (const void*)((const char*)n.q + off) : tm.zeros, n.dst + i * 4 * 1024);
+        dma16_untracked(ok ? (const void*)((const char*)n.d_o + off) : tm.zeros, n.dst + kTileBytes + i * 4 * 1024);
       }
     }
     const bool ok = (int)(wave_s & 1) * 64 + lane < n_valid;
-    dma4_untracked(ok ? (const void*)((const char*)stat0 + ro.stat_off) : tm.zeros, stat_dst);
+    dma4_untracked(ok ? (const void*)((const char*)n.stat + ro.stat_off) : tm.zeros, n.stat_dst);
+  };
+  auto next_listed = [&](int hh, const Toks& t, int buf) {
+    const int hh_s = __builtin_amdgcn_readfirstlane(hh);
+    const uint32_t at = lds_addr0 + (uint32_t)buf * kBufBytes;
+    return NextListedRowTile<D>{p.q + (size_t)hh_s * D, p.d_o + (size_t)hh_s * D, (wave_s < 2 ? p.nlse : p.delta) + (size_t)hh_s * p.T,
+                                t, rl, p.Hq, at + wave_s * 1024,
+                                at + 2 * kTileBytes + (wave_s < 2 ? 0 : kRowsPerTile * 4) + (wave_s & 1) * 64 * 4, tm.zeros};
   };
   auto issue = [&](int hh, const Toks& t, int buf) {
     char* base = lds + buf * kBufBytes;
@@ -1433,7 +1530,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   Toks tok_n{};
   if (n_iter > 0) {
     const int rt0 = take_entry(fetch_row_tile(0)).tile;
-    if (ROWS == kRowsNear) {
+    if (kNear) {
       issue_near(h_lo, rt0, 0);
     } else {
       tok_n = row_tokens<D, 4, LISTED>(tm, rl, rt0, p.L);
@@ -1458,17 +1555,33 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   auto run = [&](auto chain_tag) {
     constexpr bool CHAIN = decltype(chain_tag)::value;
     for (int it = 0; it < n_iter; ++it) {
+      if (D == 128) {
+        // K and V of the wave's keys stay in accumulation registers, where the matrix instructions read them directly.
+        // (Left to itself the compiler puts them there too, but copies four registers before each use.)
+#pragma unroll
+        for (int st = 0; st < D / 16; ++st) {
+          u32x4 a = __builtin_bit_cast(u32x4, kf[st]), b = __builtin_bit_cast(u32x4, vf[st]);
+          asm volatile("" : "+a"(a), "+a"(b));
+          kf[st] = __builtin_bit_cast(bf16x8, a);
+          vf[st] = __builtin_bit_cast(bf16x8, b);
+        }
+      }
       const int buf = it & 1;
+      const bool have1 = it + 1 < n_iter;
+      // Does the routine of this iteration issue the next one's copies itself?  At D = 64 (depth-0 keys of dense maps; a
+      // second body per mode, or a lane's address per copy, costs spilled registers) its unmasked form always does: the
+      // next row tile is never the sequence's last, which a list starts with, and behind the last one it copies row tile
+      // 0, which nobody reads.  At D = 128 both forms have a body without.
+      const bool rides = D == 64 ? kNear && !CHAIN && mask_c == -1
+                                 : (kNear || LISTED) && have1 && mask_c >= -1 && (LISTED || rows_of(rt_n) == full_rows);
       const bool have2 = it + 2 < n_iter, have3 = it + 3 < n_iter;
       Toks tok_a = tok_n;
       if (LISTED) {
         if (have2) tok_a = row_tokens<D, 4, LISTED>(tm, rl, rt_a, p.L);
-        if (it + 1 < n_iter) issue(hh_n, tok_n, buf ^ 1);
-      } else {
-        if (it + 1 < n_iter) {
-          if (ROWS == kRowsNear) issue_near(hh_n, rt_n, buf ^ 1);
-          else issue(hh_n, row_tokens<D, 4, LISTED>(tm, rl, rt_n, p.L), buf ^ 1);
-        }
+        if (have1 && !rides) issue(hh_n, tok_n, buf ^ 1);
+      } else if (have1 && !rides) {
+        if (kNear) issue_near(hh_n, rt_n, buf ^ 1);
+        else issue(hh_n, row_tokens<D, 4, LISTED>(tm, rl, rt_n, p.L), buf ^ 1);
       }
       // (fetched after the copies were issued: anything the copy code has to wait for - a reloaded register -
       // then finds no list load in flight)
@@ -1484,7 +1597,14 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
           const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
           dkdv_rowtile_chain<D>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, cm);
         } else if (mask_c == -1) {
-          dkdv_rowtile_pipelined<D, 0>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
+          if (kNear && rides)
+            dkdv_rowtile_pipelined<D, 0>(next_rows(D == 64 ? h_lo : hh_n, have1 ? rt_n : 0, buf ^ 1), q_lds, do_lds, lse_lds,
+                                         delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
+          else if (D == 128 && LISTED && rides)
+            dkdv_rowtile_pipelined<D, 0>(next_listed(hh_n, tok_n, buf ^ 1), q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv,
+                                         g, p.c_log2);
+          else if (!kNear || D == 128)
+            dkdv_rowtile_pipelined<D, 0>(NoCopies{}, q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
         } else if (mask_c >= 0) {
           // which of the tile's 128 rows see this lane's key: four words, one per 32-row unit
           // (scalar base + small per-lane offset: no 64-bit per-lane address is kept across the loop)
@@ -1500,7 +1620,17 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
             cm[w] = x;
           }
           if (!kSkips || __builtin_amdgcn_ballot_w64((cm[0] | cm[1] | cm[2] | cm[3]) != 0) != 0)  // (else: every key is in the rows' future)
-            dkdv_rowtile_pipelined<D, 1>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, false, cm);
+          {
+            if (D == 128 && LISTED && rides)
+              dkdv_rowtile_pipelined<D, 1>(next_listed(hh_n, tok_n, buf ^ 1), q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk,
+                                           dv, g, p.c_log2, false, cm);
+            else if (D == 128 && kNear && rides)
+              dkdv_rowtile_pipelined<D, 1>(next_rows(hh_n, rt_n, buf ^ 1), q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv,
+                                           g, p.c_log2, false, cm);
+            else
+              dkdv_rowtile_pipelined<D, 1>(NoCopies{}, q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, false,
+                                           cm);
+          }
         } else if (LISTED) {  // only packed maps carry such ids
           // keys in front of the row's sequence are off; as a lane mask in scalar registers (a vector register that held
           // each lane's key across the loop was spilled, and reloading it waited for the copies just issued)
@@ -1508,7 +1638,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
           n_off = n_off < 0 ? 0 : (n_off > 32 ? 32 : n_off);
           const uint64_t off32 = (1ull << n_off) - 1;
           const bool lane_off = __builtin_amdgcn_inverse_ballot_w64(off32 | off32 << 32);
-          dkdv_rowtile_pipelined<D, 2>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, lane_off);
+          dkdv_rowtile_pipelined<D, 2>(NoCopies{}, q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, lane_off);
         }
       }
       dma_publish();
@@ -2251,8 +2381,11 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
         if (D == 64) sv_dkdv ? go(dkdv_kernel<64, ROWS, true>) : go(dkdv_kernel<64, ROWS, false>);
         else sv_dkdv ? go(dkdv_kernel<128, ROWS, true>) : go(dkdv_kernel<128, ROWS, false>);
       };
+      const bool near = p.near_rows && p.L >= p.tm.A;
+      const int apart = D == 64 ? kRowsApart<64> : kRowsApart<128>;
       if (listed_map) pick(std::integral_constant<int, kRowsListed>{});
-      else if (p.near_rows) pick(std::integral_constant<int, kRowsNear>{});
+      else if (near && apart % p.tm.K == 0) pick(std::integral_constant<int, kRowsWhole>{});
+      else if (near && p.tm.A * p.tm.K > kRowsPerTile - apart) pick(std::integral_constant<int, kRowsMost>{});
       else pick(std::integral_constant<int, kRowsFar>{});
       hipError_t e = span.finish();
       if (e != hipSuccess) return e;

@@ -148,6 +148,15 @@ __device__ __forceinline__ void dma16_untracked(const void* sbase, uint32_t voff
 __device__ __forceinline__ void dma4_untracked(const void* sbase, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
 }
+// The same with the LDS address given as a scalar base and a constant, added on the way into M0.
+template <int OFF>
+__device__ __forceinline__ void dma16_untracked_at(const void* sbase, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(lds_base), "n"(OFF) : "memory", "m0", "scc");
+}
+template <int OFF>
+__device__ __forceinline__ void dma4_untracked_at(const void* sbase, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(sbase), "s"(lds_base), "n"(OFF) : "memory", "m0", "scc");
+}
 // A pointer the compiler can prove wave-uniform (so that it lives in scalar registers).
 template <class T>
 __device__ __forceinline__ const T* uniform_ptr(const T* p) {

@@ -885,6 +885,24 @@ def test_dense_segments_of_more_than_128_row_tiles(L_max, L, bounds):
         assert max_abs(got[n], ref[n]) <= 2e-2 * np.abs(ref[n]).max(), n
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("K,L", [(8, 15), (8, 16), (8, 17), (8, 130), (4, 31), (4, 100), (5, 24), (5, 25), (5, 201), (7, 19), (7, 73),
+                                 (33, 2), (33, 10), (43, 7), (32, 9)])
+def test_every_way_dkdv_finds_its_rows(K, L, D):
+    """Row tiles of 128 rows at a constant step, of fewer with the missing ones in a tile's last copy (K = 5, 7; K = 33 at
+    D = 64), and of neither kind (K = 43; K = 33 at D = 128; L short of one tile); one tile, one and a bit, several."""
+    Hq, Hkv, seed = 4, 2, 330 + K
+    print(f"case rows: L={L} K={K} D={D}", flush=True)
+    qb, kb, vb, dob = (rand_bits((L * K, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
+    r = Run(pe.peagle_build_tilemap(L, K, None, device=0), L, K, Hq, Hkv, D, qb, kb, vb, dob)
+    r.step(0, 1)
+    got = r.results()
+    ref = _oracle(qb, kb, vb, dob, L, K, r.shape.scale)
+    _check_against_oracle(got, ref, f"rows {K} {L} {D}")
+    for n in ("dK", "dV"):                      # no row left out, read twice or taken from beyond the sequence
+        assert max_abs(got[n], ref[n]) <= 2e-2 * np.abs(ref[n]).max(), n
+
+
 @pytest.mark.parametrize("qscale", [1.0, 12.0])
 def test_pipelined_dq_over_lists_of_every_length(qscale):
     """Lists of 3 to 34 key tiles at D = 64, few workgroups: the pipelined dQ kernel with every remainder of its groups of
