@@ -92,10 +92,18 @@ struct KeyTileLds {
   __device__ __forceinline__ uint32_t v(int slot) const { return k(slot) + kKeysPerTile * D * 2; }
 };
 
+// The lane's number, computed anew where it stands: what is derived from it takes no register before and after.
+__device__ __forceinline__ int lane_id() {
+  int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(l));
+  return l;
+}
+
 // Key tile straight into its swizzled LDS image (K and V): wave w of NW fills the 1 KiB blocks
 // w, w + NW, ...; lane l of block b owns LDS bytes [1024 b + 16 l, +16), i.e. tile row
 // b*(512/D) + l/(D/8) and physical chunk l%(D/8), and fetches the logical chunk that lives there.
-template <int D, int NW, bool SV = false>
+// LEAN: the lane's coordinates in tiles that need an address per lane are computed anew rather than held in registers.
+template <int D, int NW, bool SV = false, bool LEAN = false>
 __device__ __forceinline__ void dma_key_tile(uint32_t kd, uint32_t vd, const __bf16* kbase, const __bf16* vbase,
                                              int Hkv, int kvh, const DeviceTileMap& tm, int kt, int L, int wave,
                                              int lane, const __bf16* v_shared = nullptr) {
@@ -103,20 +111,23 @@ __device__ __forceinline__ void dma_key_tile(uint32_t kd, uint32_t vd, const __b
   // wave), as wave-uniform integers - see KeyTileLds
   constexpr int kBlocks = kKeysPerTile * D * 2 / 1024;
   static_assert(kBlocks % NW == 0, "tile must split evenly over the waves");
-  const int row_in_blk = lane / (D / 8), phys = lane % (D / 8);
   if (kt < tm.n_d0 && (kt + 1) * kKeysPerTile <= L) {
     // A whole tile of depth-0 keys: the rows a lane copies are NW * 512/D apart (a multiple of the swizzle
     // period), so its byte offset from each copy's first row is one value, the same for every tile, and the
     // rest of the address is wave-uniform.
-    const int row0 = wave * (512 / D) + row_in_blk;
-    const uint32_t voff = (uint32_t)((row0 * Hkv) * D + ((phys ^ swz<D>(row0)) << 3)) * 2u;
+    const int row0 = wave * (512 / D) + lane / (D / 8);
+    const uint32_t voff = (uint32_t)((row0 * Hkv) * D + ((lane % (D / 8) ^ swz<D>(row0)) << 3)) * 2u;
 #pragma unroll
     for (int i = 0; i < kBlocks / NW; ++i) {
       const size_t first = ((size_t)(kt * kKeysPerTile + i * NW * (512 / D)) * Hkv + kvh) * D;
       dma16_untracked(uniform_ptr(kbase + first), voff, kd + i * NW * 1024);
       dma16_untracked(uniform_ptr(vbase + first), voff, vd + i * NW * 1024);
     }
-  } else if (SV && kt >= tm.n_d0) {
+    return;
+  }
+  const int l = LEAN ? lane_id() : lane;
+  const int row_in_blk = l / (D / 8), phys = l % (D / 8);
+  if (SV && kt >= tm.n_d0) {
     // First-layer form, chain tile: every key's value row is the one shared vector of its KV head.  (SV is a
     // template flag: kernels of the ordinary step carry none of this.)
 #pragma unroll
@@ -407,12 +418,14 @@ __device__ __forceinline__ void fwd_tile_masked(const char* kt_lds, const char* 
   }
 }
 
-template <int D, int NH, bool SV>
-__global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
+template <int D, int NH, bool SV, int PER_SIMD>
+__global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
+  // Three workgroups per CU leave 168 registers: what only masked tiles and the last stores need is computed there.
+  constexpr bool LEAN = PER_SIMD == 3;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   __shared__ __attribute__((aligned(16))) char lds[2][2][kTileBytes];  // [buffer][K|V]
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
+  const int tid = threadIdx.x, wave = LEAN ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
@@ -425,15 +438,15 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   const int h0 = kvh * group + hc * NH;
 
   const int r = wave * 32 + ln;  // row of the tile owned by this lane (shared with lane^32)
-  int tq;
-  const bool row_ok = row_token(tm, rt, r, p.L, tq);
+  int tq_held;
+  const bool row_ok = row_token(tm, rt, r, p.L, tq_held);
 
   bf16x8 qf[NH][D / 16];
 #pragma unroll
   for (int hh = 0; hh < NH; ++hh)
 #pragma unroll
     for (int st = 0; st < D / 16; ++st)
-      qf[hh][st] = as_frag(row_ok ? ld16(p.q + ((size_t)tq * p.Hq + h0 + hh) * D + st * 16 + g * 8)
+      qf[hh][st] = as_frag(row_ok ? ld16(p.q + ((size_t)tq_held * p.Hq + h0 + hh) * D + st * 16 + g * 8)
                                   : make_uint4(0, 0, 0, 0));
 
   f32x16 o[NH][D / 32];
@@ -460,14 +473,14 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
     }
     TileEntry cur = load_entry(tm.row_entries, e0);
     TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
-    dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
+    dma_key_tile<D, 4, SV, LEAN>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
     dma_publish();
     // A row tile's list holds its full tiles first, then the partial ones: two loops (accumulators stay in place).
     int e = e0;
     auto full_tile = [&](int buf) {
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
       if (e + 1 < e1)
-        dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+        dma_key_tile<D, 4, SV, LEAN>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
       const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
       fwd_tile<D, NH, false, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       dma_publish();
@@ -486,9 +499,10 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
       const int buf = (e - e0) & 1;
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
       if (e + 1 < e1)
-        dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
-      const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + r) * 2);
-      const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
+        dma_key_tile<D, 4, SV, LEAN>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+      const int l = LEAN ? lane_id() : lane;
+      const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + wave * 32 + (l & 31)) * 2);
+      const uint32_t mw[2] = {w[0] >> (4 * (l >> 5)), w[1] >> (4 * (l >> 5))};
       fwd_tile_masked<D, NH, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       dma_publish();
       cur = nxt;
@@ -499,7 +513,9 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   };
   auto store = [&](int hh) {
     const float inv = 1.0f / l_tot[hh];
-    if (row_ok) {
+    const int l = LEAN ? lane_id() : lane, g = l >> 5;
+    int tq = tq_held;
+    if (LEAN ? row_token(tm, rt, wave * 32 + (l & 31), p.L, tq) : row_ok) {
       __bf16* orow = p.o + ((size_t)tq * p.Hq + h0 + hh) * D;
 #pragma unroll
       for (int db = 0; db < D / 32; ++db) store_row_bf16(orow + db * 32, o[hh][db], inv, g);
@@ -2218,15 +2234,23 @@ namespace {
 
 constexpr int kCus = 256;  // compute units of the device
 
-// Query heads of one KV group that share a workgroup's K/V tiles in the forward: two at D = 64 (the register
-// budget of two waves per SIMD allows it) unless the row tiles' lists are short - then four one-head workgroups per
-// CU cover one another's first loads and last stores -, one at D = 128.  The line lies where both take the same time;
-// forward us, one / two heads, by mean list length: L = 128, K = 4 (4) 10 / 13, L = 700, K = 8 (8) 60 / 64, eight
-// packed sequences (12) 743 / 737, L = 1,391 (13) 171 / 165, L = 4,096 (35) 1,149 / 1,113.  A head's results do not
-// depend on the choice.  The backward kernels take one head per workgroup.
-constexpr int kOneHeadMeanTiles = 10;
-inline int pick_nh(int group, int D, int mean_tiles) {
-  return (D == 64 && group % 2 == 0 && mean_tiles > kOneHeadMeanTiles) ? 2 : 1;
+// The forward's form at D = 64, by the mean length of the row tiles' lists and the number of workgroups of two query heads
+// (which share K/V tiles): one head per workgroup (four per CU) where lists are short - the workgroups cover one another's
+// first loads and last stores - or two-head workgroups too few to fill the chip; two heads at three per CU where there are
+// at least four for each; two heads at two per CU (registers to schedule with) in between.  A head's results do not
+// depend on the choice.  Forward us, one head / two heads at two per CU / at three, by (mean list; two-head workgroups):
+//   short lists: 64 heads, L = 700 (8; 1,408) 58 / 65 / 65, L = 1,000 (11; 2,016) 100 / 98 / 97;
+//   few: 4 heads, L = 1,391 (13; 174) 30 / 37 / 40, L = 2,048 (19; 256) 40 / 47 / 52, L = 4,096 (35; 512) 88 / 92 / 98, eight packed
+//     sequences (12; 806) 59 / 67 / 67;  in between: L = 8,000 (65; 1,000) 268 / 261 / 270;
+//   many: 16 heads, L = 2,048 (19; 1,024) 86 / 85 / 84, L = 4,096 (35; 2,048) 287 / 272 / 271; 64 heads, L = 1,391 (13; 2,784) 166 /
+//     159 / 151, eight packed sequences (12; 12,896) 715 / 751 / 674, L = 4,096 (35; 8,192) 1,124 / 1,057 / 1,031, L = 20,480 (165;
+//     40,960) 25,720 / 24,000 / 23,810.
+constexpr int kOneHeadMeanTiles = 10, kFewMeanTiles = 24;
+enum class FwdForm { kOneHead, kTwoHeads, kTwoHeadsThreePerCu };
+inline FwdForm pick_fwd_form(int group, int mean_tiles, int two_head_wgs) {
+  if (group % 2 != 0 || mean_tiles <= kOneHeadMeanTiles || two_head_wgs <= 2 * kCus) return FwdForm::kOneHead;
+  if (two_head_wgs >= 4 * kCus) return FwdForm::kTwoHeadsThreePerCu;
+  return mean_tiles <= kFewMeanTiles ? FwdForm::kOneHead : FwdForm::kTwoHeads;
 }
 
 struct TimedSpan {
@@ -2286,22 +2310,20 @@ KernelTimer::~KernelTimer() {
 hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer* timer) {
   const int n_rt = p.rt_hi - p.rt_lo;
   if (n_rt <= 0) return hipSuccess;
-  const int group = p.Hq / p.Hkv;
-  const int nh = pick_nh(group, D, p.mean_tiles);
-  const dim3 grid((unsigned)(n_rt * (p.Hq / nh))), block(256);
-  TimedSpan span(timer, kKindFwd, stream);
   const bool sv = p.v_shared != nullptr;  // first-layer form: kernels that read chain V rows from the shared vector
-  if (D == 64) {
-    if (nh == 2) {
-      if (sv) hipLaunchKernelGGL((fwd_kernel<64, 2, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((fwd_kernel<64, 2, false>), grid, block, 0, stream, p);
-    } else {
-      if (sv) hipLaunchKernelGGL((fwd_kernel<64, 1, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((fwd_kernel<64, 1, false>), grid, block, 0, stream, p);
-    }
+  if (D == 128 && sv) return hipErrorInvalidValue;  // (D = 128 has no such instantiation: its callers expand V instead)
+  TimedSpan span(timer, kKindFwd, stream);
+  auto go = [&](auto kernel, int heads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_rt * (p.Hq / heads))), dim3(256), 0, stream, p);
+  };
+  if (D == 128) {
+    go(fwd_kernel<128, 1, false, 2>, 1);
   } else {
-    if (sv) return hipErrorInvalidValue;  // (D = 128 has no such instantiation: its callers expand V instead)
-    hipLaunchKernelGGL((fwd_kernel<128, 1, false>), grid, block, 0, stream, p);
+    switch (pick_fwd_form(p.Hq / p.Hkv, p.mean_tiles, n_rt * (p.Hq / 2))) {
+      case FwdForm::kOneHead: go(sv ? fwd_kernel<64, 1, true, 2> : fwd_kernel<64, 1, false, 2>, 1); break;
+      case FwdForm::kTwoHeads: go(sv ? fwd_kernel<64, 2, true, 2> : fwd_kernel<64, 2, false, 2>, 2); break;
+      case FwdForm::kTwoHeadsThreePerCu: go(sv ? fwd_kernel<64, 2, true, 3> : fwd_kernel<64, 2, false, 3>, 2); break;
+    }
   }
   return span.finish();
 }

@@ -265,6 +265,30 @@ def test_a_head_does_not_depend_on_the_heads_beside_it(D):
         assert torch.equal(cut(whole[n]).view_as(crop[n]), crop[n]), n
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 4), (16, 4)], ids=["two_per_cu", "three_per_cu"])
+def test_two_head_forward_workgroups_give_the_bits_of_one_head_ones(Hq, Hkv):
+    """752 and 1,504 workgroups of two heads with long lists (the forward's two-head forms at D = 64) against each group of
+    heads alone (few workgroups: one head each); every other head's row tiles are done again with the running max."""
+    L, K, D = 3000, 8, 64
+    print(f"case forward forms Hq={Hq}", flush=True)
+    tm = pe.peagle_build_tilemap(L, K, None, device=0)
+    wgs = tm.info()["n_row_tiles"] * Hq // 2
+    assert mean_list(tm) > 25 and (512 < wgs < 1024) == (Hq == 8) and (wgs >= 1024) == (Hq == 16)
+    assert tm.info()["n_row_tiles"] * (Hq // Hkv) // 2 <= 512
+    g = torch.Generator(device="cuda").manual_seed(341)
+    q, k, v, d_o = (torch.randn(L * K, H, D, generator=g, device="cuda") for H in (Hq, Hkv, Hkv, Hq))
+    q[:, 1::2] *= 40.0
+    q, k, v, d_o = (t.to(torch.bfloat16) for t in (q, k, v, d_o))
+    whole = _heads_run(tm, L, K, q, k, v, d_o)
+    n = Hq // Hkv
+    for h in range(Hkv):
+        a, b = slice(h * n, (h + 1) * n), slice(h, h + 1)
+        alone = _heads_run(tm, L, K, *(t.contiguous() for t in (q[:, a], k[:, b], v[:, b], d_o[:, a])))
+        for name in ("o", "lse"):
+            assert torch.isfinite(alone[name]).all(), name
+            assert torch.equal(whole[name][:, a], alone[name]), (name, h)
+
+
 def test_run_to_run_determinism():
     L, K, Hq, Hkv, D = 300, 8, 4, 2, 64
     print("case determinism", flush=True)
