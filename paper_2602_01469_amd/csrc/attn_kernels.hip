@@ -1869,7 +1869,9 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(const float* src, __bf16
 // =====================================================================================
 constexpr int kLongPiece = 16;  // pages; see the launcher
 
-template <int D, int kGroups, int kThreads>
+// ONE: one piece per request, whose results are written here; otherwise a partial record per piece, which the combine
+// kernel merges.
+template <int D, int kGroups, int kThreads, bool ONE>
 __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr int kBlocks = kTileBytes / 1024;
@@ -2086,8 +2088,20 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
     }
   }
 
-  // partial record of this split: lane <-> row, registers <-> d = db*32 + 8*q4 + 4g + j
   const float l_tot = sum_halves(lsum[0]);
+  if (ONE) {
+    if (row_ok) {
+      const float inv = 1.0f / l_tot;
+      __bf16* orow = p.o + (((size_t)c * p.K + depth) * p.Hq + head) * D;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db) store_row_bf16(orow + db * 32, o[0][db], inv, g);
+      if (g == 0) p.lse[((size_t)c * p.Hq + head) * p.K + depth] = (m[0] + __builtin_log2f(l_tot)) * kLn2;
+    }
+    if (p.status && kvh == 0 && tid == 0) p.status[c] = bad || table_bad != 0;  // (table_bad: written before the last barrier)
+    return;
+  }
+
+  // partial record of this split: lane <-> row, registers <-> d = db*32 + 8*q4 + 4g + j
   const size_t rec = ((size_t)c * p.Hkv + kvh) * p.n_splits + split;
   if (r < p.rows_pad) {
     float* po = p.part_o + (rec * p.rows_pad + r) * D;
@@ -2428,8 +2442,32 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
   return hipSuccess;
 }
 
+// Pieces that each request's context is cut into, at most p.n_splits (which the workspace is laid out for: a thousand
+// workgroups, at least four pages each).  As few as leave no CU without a workgroup, since every piece pays the chain of
+// round trips at a workgroup's start and end again; for two workgroups per CU where pieces would be longer than kLongPiece
+// pages, and all where they would still be longer than two of those: requests differ in length, and the longest one's
+// pieces would be waited for.  us per call, pieces a request (workgroups) as laid out / as taken here: D = 64, 4 requests of 2,048 - 4,096 tokens
+// 14.5 (16; 512) / 12.7 (8; 256), 16 of 1,000 16.2 (4; 512) / 13.4 (2; 256), 8 of 300 - 3,000 17.5 (12; 768) / 15.2 (4; 256), 4 of
+// 8,000 - 20,000 29.1 (32; 1,024) / 26.8 (16; 512; 8 pieces 29.9), 16 of 2,000 - 20,000 stay at 8 (78; 4 pieces 88), 64 of 100 -
+// 1,000 27.9 (2; 1,024) / 19.7 (1; 512); D = 128, 16 of 800 - 8,192 41.9 (16; 1,024) / 36.5 (8; 512).
+// One piece leaves its rows' results itself, without the launch that merges pieces (4 of 64 - 256 tokens 9.4 / 6.6).  Up to
+// kOnePiece pages that is worth a longer chain in fewer workgroups, pieces 2 or 3 / 1: D = 64, one request of 512 tokens
+// 9.2 / 8.2, 4 of 768 10.4 / 9.9, 2 of 1,000 (16 pages) 9.7 / 11.9; D = 128, 4 of 512 11.7 / 10.8, 4 of 768 12.3 / 13.0.
+constexpr int kOnePiece64 = 12, kOnePiece128 = 8;  // pages
+inline int pieces(const DecodeParams& p, int D) {
+  auto at_least = [&](int wgs) {
+    const int n = (wgs + p.C * p.Hkv - 1) / (p.C * p.Hkv);
+    return n < p.n_splits ? n : p.n_splits;
+  };
+  auto pages = [&](int n) { return (p.max_pages + n - 1) / n; };
+  if (p.max_pages <= (D == 64 ? kOnePiece64 : kOnePiece128)) return 1;
+  if (pages(at_least(kCus)) <= kLongPiece) return at_least(kCus);
+  return pages(at_least(2 * kCus)) <= 2 * kLongPiece ? at_least(2 * kCus) : p.n_splits;
+}
+
 hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t stream) {
   DecodeParams p = pin;
+  p.n_splits = pieces(p, D);
   const int row_waves = p.rows_pad / 32;  // 1 .. 4
   const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
   const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;
@@ -2449,15 +2487,15 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + 1) * 64));
   // (The bound of 576 threads, of which 320 are launched, has the compiler schedule for four waves per SIMD: 120
   // against 136 us on the first of those batches.  The other forms run the same with either bound.)
-  if (D == 64) {
-    if (two) hipLaunchKernelGGL((draft_decode_kernel<64, 2, 576>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((draft_decode_kernel<64, 1, 320>), grid, block, 0, stream, p);
-  } else {
-    if (two) hipLaunchKernelGGL((draft_decode_kernel<128, 2, 320>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((draft_decode_kernel<128, 1, 320>), grid, block, 0, stream, p);
-  }
+  auto go = [&](auto one_tag) {
+    constexpr bool ONE = decltype(one_tag)::value;
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, p); };
+    if (D == 64) two ? run(draft_decode_kernel<64, 2, 576, ONE>) : run(draft_decode_kernel<64, 1, 320, ONE>);
+    else two ? run(draft_decode_kernel<128, 2, 320, ONE>) : run(draft_decode_kernel<128, 1, 320, ONE>);
+  };
+  p.n_splits == 1 ? go(std::true_type{}) : go(std::false_type{});
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || p.n_splits == 1) return e;
   // threads per row and splits per thread: n_splits is at most 32
   auto merge = [&](auto kernel, int rows_per_wave) {
     const size_t waves = ((size_t)p.C * p.Hkv * p.K * (p.Hq / p.Hkv) + rows_per_wave - 1) / rows_per_wave;

@@ -196,3 +196,23 @@ def test_draft_decode_in_a_table_wider_than_its_requests(longest):
     o, lse, status = r.run()
     assert (status == 0).all()
     _check(inp, o, lse, r.shape.scale, f"wide table {longest}")
+
+
+@pytest.mark.parametrize("D,pages", [(64, 1), (64, 12), (64, 13), (128, 8), (128, 9)])
+def test_draft_decode_with_one_piece_and_with_more(D, pages):
+    """Tables of up to 12 (D = 64) or 8 (D = 128) pages are not cut: the kernel leaves output, LSE and status itself.  Two
+    blocks of 32 query rows, the second ragged; empty, page-edge and full requests; one with a page outside the pool."""
+    K, Hq, Hkv, n = 5, 16, 2, 64 * pages
+    lens = (n, 0, 1, n - 1, min(n, 65), n, 64)
+    print(f"case decode one piece: {pages} pages D={D}", flush=True)
+    inp = make_decode_inputs(lens, K, Hq, Hkv, D, 1300 + pages)
+    r = DecodeRun(inp, K, Hq, Hkv, D)
+    assert r.shape.max_pages == pages
+    o, lse, status = r.run()
+    assert (status == 0).all()
+    _check(inp, o, lse, r.shape.scale, f"one piece {pages} {D}")
+    r.bt[5, pages - 1] = r.shape.n_pages
+    o2, lse2, status2 = r.run()
+    assert status2.tolist() == [0, 0, 0, 0, 0, 1, 0]
+    others = np.arange(len(lens)) != 5
+    assert np.array_equal(o2[others], o[others]) and np.array_equal(lse2[others], lse[others])
