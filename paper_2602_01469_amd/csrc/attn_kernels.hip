@@ -1198,6 +1198,42 @@ __device__ __forceinline__ void pipe_row_terms(f32x16& s, f32x16& dp, const floa
   }
 }
 
+// The vector work that the group table gives to matrix instruction M, in three stages a matrix instruction apart: scale,
+// exponentiate (and mask), multiply with dP and round.  (All three behind the same matrix instruction, each waited for the one
+// before it, and a no-op stood between exponential and product: dK/dV at D = 128, one wave per SIMD, L = 10,816 13,376 ->
+// 13,072 us, L = 1,391 325 -> 317; D = 64 L = 4,096 2,046 -> 2,018, L = 20,480 46,720 -> 46,090, 4 heads L = 3,000 362 -> 342.)  The last
+// two scores of a unit are finished behind the first two matrix instructions of the next group, which needs them only in
+// its second half; a unit's per-row terms take the registers of the unit two before it after that.
+template <int D, int MODE, int STAGE, int M>
+__device__ __forceinline__ void dkdv_vector_work(DkdvPipe<D>& P, float c, const u32x4& cm) {
+  constexpr int NG = D / 8;
+  if constexpr (M >= 0) {
+    constexpr PipeGroup gd = kPipeGroups[M / NG];
+    if constexpr (gd.vunit >= 0) {
+      constexpr int vu = gd.vunit & 1, j = M % NG, n = gd.e1 - gd.e0;
+#pragma unroll
+      for (int i = gd.e0 + n * j / NG; i < gd.e0 + n * (j + 1) / NG; ++i) {
+        if (STAGE == 1) {
+          P.sc[vu][i] *= c;
+        } else if (STAGE == 2) {
+          float pr = exp2_fast(P.sc[vu][i]);
+          if (MODE == 1) {  // the lane's key-major mask word of this unit, shifted down by 4g: bit of row 8*(i/4) + 4g + i%4
+            const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)cm[gd.vunit & 3], 8 * (i / 4) + (i % 4), 1);
+            pr = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, pr) & keep);
+          }
+          P.sc[vu][i] = pr;
+        } else {
+          P.dpc[vu][i] *= P.sc[vu][i];
+          if (i & 1) {
+            P.pb[vu][i >> 3][(i & 7) >> 1] = pack_bf16(P.sc[vu][i - 1], P.sc[vu][i]);
+            P.dsb[vu][i >> 3][(i & 7) >> 1] = pack_bf16(P.dpc[vu][i - 1], P.dpc[vu][i]);
+          }
+        }
+      }
+    }
+  }
+}
+
 template <int D, int MODE, int G, class Copies>
 __device__ __forceinline__ void dkdv_pipe_group(const Copies& copies, DkdvPipe<D>& P, const char* q_lds, const char* do_lds,
                                                 const float* nlse_lds, const float* ndelta_lds, const NatOff<D>& no,
@@ -1207,9 +1243,7 @@ __device__ __forceinline__ void dkdv_pipe_group(const Copies& copies, DkdvPipe<D
   constexpr int NG = D / 8;  // matrix instructions per group
   constexpr PipeGroup gd = kPipeGroups[G];
   constexpr PipeGroup gn = kPipeGroups[G + 1 < 8 ? G + 1 : 7];
-  constexpr int u = gd.unit & 1, vu = gd.vunit & 1;
-  if (G + 1 < 8 && gn.kind == 0)  // the next group starts S / dP of a unit: fetch its per-row terms now
-    pipe_row_terms<MODE>(P.sc[gn.unit & 1], P.dpc[gn.unit & 1], nlse_lds, ndelta_lds, gn.unit * 32, g, lane_off);
+  constexpr int u = gd.unit & 1;
   unrolled<0, NG>([&](auto j_tag) {
     constexpr int j = decltype(j_tag)::value;
     const int slot = (G * NG + j) % kPipeAhead<D>;  // the instruction kPipeAhead<D> later takes the slot this one frees
@@ -1226,23 +1260,13 @@ __device__ __forceinline__ void dkdv_pipe_group(const Copies& copies, DkdvPipe<D
       P.ring[slot] = pipe_frag<D, gd.kind>(q_lds, do_lds, no, to, gd.unit * 32, j + kPipeAhead<D>);
     else if (G + 1 < 8)
       P.ring[slot] = pipe_frag<D, gn.kind>(q_lds, do_lds, no, to, gn.unit * 32, j + kPipeAhead<D> - NG);
-    if (gd.vunit >= 0) {
-      const int n = gd.e1 - gd.e0;
-#pragma unroll
-      for (int i = gd.e0 + n * j / NG; i < gd.e0 + n * (j + 1) / NG; ++i) {
-        float pr = exp2_fast(P.sc[vu][i] * c);
-        if (MODE == 1) {  // the lane's key-major mask word of this unit, shifted down by 4g: bit of row 8*(i/4) + 4g + i%4
-          const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)cm[gd.vunit & 3], 8 * (i / 4) + (i % 4), 1);
-          pr = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, pr) & keep);
-        }
-        P.sc[vu][i] = pr;
-        P.dpc[vu][i] *= pr;
-        if (i & 1) {
-          P.pb[vu][i >> 3][(i & 7) >> 1] = pack_bf16(P.sc[vu][i - 1], P.sc[vu][i]);
-          P.dsb[vu][i >> 3][(i & 7) >> 1] = pack_bf16(P.dpc[vu][i - 1], P.dpc[vu][i]);
-        }
-      }
-    }
+    constexpr int M = G * NG + j;
+    // stage 3 before stage 2 before stage 1: neighbouring instructions do not depend on one another
+    dkdv_vector_work<D, MODE, 3, M - 2>(P, c, cm);
+    dkdv_vector_work<D, MODE, 2, M - 1>(P, c, cm);
+    dkdv_vector_work<D, MODE, 1, M>(P, c, cm);
+    if (j == 2 && G + 1 < 8 && gn.kind == 0)  // the next group starts S / dP of a unit: fetch its per-row terms now
+      pipe_row_terms<MODE>(P.sc[gn.unit & 1], P.dpc[gn.unit & 1], nlse_lds, ndelta_lds, gn.unit * 32, g, lane_off);
     copies.template after<G * NG + j>();
     __builtin_amdgcn_sched_barrier(0);
   });
