@@ -1136,27 +1136,32 @@ struct NextRowTile {
   }
 };
 
-// The same for rows named by token lists: an address per lane and copy.
-template <int D>
+// The same for rows named by token lists.  A row that does not exist is read from the tile's first row, which every key of
+// the tile sees or is masked for like the missing one, and its -lse/scale of -infinity makes its probabilities zero: no
+// copy of Q or dO has to choose between two addresses.  FAR: offsets past 4 GiB.  (dK/dV, us, with 64-bit addresses chosen
+// per lane and the copies issued together at D = 64 / so: sampled 8,192 4,581 / 4,357, eight packed sequences 1,388 / 1,318;
+// D = 128, riding before too, sampled 4,096 1,349 / 1,233, packed 1,556 / 1,417.)
+template <int D, bool FAR>
 struct NextListedRowTile {
   const __bf16 *q, *d_o;           // the head's row of token 0
   const float* stat;
   const RowTokens<D, 4>& t;
   const RowDmaLane<D, 4>& rl;
-  int Hq;
+  uint32_t stride;                 // bytes from token to token
   uint32_t dst, stat_dst;
-  const void* zeros;
+  const void* no_row;              // the statistic of a row that does not exist
   static constexpr int kPer = RowDmaLane<D, 4>::kPer;
   static constexpr int kCopies = 2 * kPer + 1;
   template <int C>
   __device__ __forceinline__ void issue() const {
     if constexpr (C == 2 * kPer) {
-      dma4_untracked(t.stat_tok >= 0 ? (const void*)(stat + t.stat_tok) : zeros, stat_dst);
+      dma4_untracked(t.stat_tok >= 0 ? (const void*)(stat + t.stat_tok) : no_row, stat_dst);
     } else {
-      constexpr int i = C >> 1;
-      const bool ok = t.tok[i] >= 0;
-      const size_t off = (size_t)(ok ? t.tok[i] : 0) * (Hq * D) + rl.chunk[i];
-      dma16_untracked(ok ? (const void*)((C & 1 ? d_o : q) + off) : zeros, dst + (C & 1) * kRowsPerTile * D * 2 + i * 4096);
+      constexpr int i = C >> 1, kOff = (C & 1) * kRowsPerTile * D * 2 + i * 4096;
+      const uint32_t tok = (uint32_t)(t.tok[i] ^ (t.tok[i] >> 31));
+      const __bf16* base = C & 1 ? d_o : q;
+      if constexpr (FAR) dma16_untracked((const char*)base + ((size_t)tok * stride + 2 * rl.chunk[i]), dst + kOff);
+      else dma16_untracked_at<kOff>(base, tok * stride + 2 * rl.chunk[i], dst);
     }
   }
   template <int M>
@@ -1344,16 +1349,16 @@ __device__ __forceinline__ void dkdv_rowtile_chain(const char* q_lds, const char
 //     A * K = 128): one per-lane offset and a scalar step address every copy.  Most: an offset per copy, and the last copy
 //     of a tile holds the rows past A * K (A * K > 128 - kRowsApart).
 //   kRowsFar: any other dense map; tokens are computed when a copy is issued.
-//   kRowsListed: the map names rows by explicit token lists (sampled / packed maps); their tokens are fetched an
-//     iteration before the copy that uses them.
+//   kRowsListed, kRowsListedFar: the map names rows by explicit token lists (sampled / packed maps); their tokens are
+//     fetched an iteration before the copy that uses them, and the copies ride too (NextListedRowTile).
 // (A near loop that carried every row's token and anchor as the far one does reloaded spilled registers behind its own
 // copies, and waited for them: dK/dV at L = 4,096 2,226 us, now 2,152.)
-enum { kRowsWhole = 0, kRowsFar = 1, kRowsListed = 2, kRowsMost = 3 };
+enum { kRowsWhole = 0, kRowsFar = 1, kRowsListed = 2, kRowsMost = 3, kRowsListedFar = 4 };
 template <int D>
 constexpr int kRowsApart = 4 * (512 / D);  // rows of the tile between two copies of a lane
 template <int D, int ROWS, bool SV>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p) {
-  constexpr bool LISTED = ROWS == kRowsListed;
+  constexpr bool LISTED = ROWS == kRowsListed || ROWS == kRowsListedFar;
   // Blocks that no row sees are left out at D = 64.  At D = 128, with one wave per SIMD, nothing covers the unpipelined
   // chain routine, and the second loop costs the first: dK/dV at 1,391 anchors 378 us with both, 338 with one pipelined
   // loop for all tiles, at 3,000 anchors 1,410 and 1,320.
@@ -1523,11 +1528,17 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   auto next_listed = [&](int hh, const Toks& t, int buf) {
     const int hh_s = __builtin_amdgcn_readfirstlane(hh);
     const uint32_t at = lds_addr0 + (uint32_t)buf * kBufBytes;
-    return NextListedRowTile<D>{p.q + (size_t)hh_s * D, p.d_o + (size_t)hh_s * D, (wave_s < 2 ? p.nlse : p.delta) + (size_t)hh_s * p.T,
-                                t, rl, p.Hq, at + wave_s * 1024,
-                                at + 2 * kTileBytes + (wave_s < 2 ? 0 : kRowsPerTile * 4) + (wave_s & 1) * 64 * 4, tm.zeros};
+    return NextListedRowTile<D, ROWS == kRowsListedFar>{
+        p.q + (size_t)hh_s * D, p.d_o + (size_t)hh_s * D, (wave_s < 2 ? p.nlse : p.delta) + (size_t)hh_s * p.T, t, rl,
+        (uint32_t)p.Hq * (D * 2), at + wave_s * 1024,
+        at + 2 * kTileBytes + (wave_s < 2 ? 0 : kRowsPerTile * 4) + (wave_s & 1) * 64 * 4, wave_s < 2 ? tm.no_row : tm.zeros};
   };
   auto issue = [&](int hh, const Toks& t, int buf) {
+    if (LISTED) {
+      const auto n = next_listed(hh, t, buf);
+      unrolled<0, n.kCopies>([&](auto c) { n.template issue<decltype(c)::value>(); });
+      return;
+    }
     char* base = lds + buf * kBufBytes;
     dma_row_tile<D, 4>(base, p.q, p.Hq, hh, tm, rl, t, wave);
     dma_row_tile<D, 4>(base + kTileBytes, p.d_o, p.Hq, hh, tm, rl, t, wave);
@@ -1608,11 +1619,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
       }
       const int buf = it & 1;
       const bool have1 = it + 1 < n_iter;
-      // Does the routine of this iteration issue the next one's copies itself?  At D = 64 (depth-0 keys of dense maps; a
-      // second body per mode, or a lane's address per copy, costs spilled registers) its unmasked form always does: the
-      // next row tile is never the sequence's last, which a list starts with, and behind the last one it copies row tile
-      // 0, which nobody reads.  At D = 128 both forms have a body without.
-      const bool rides = D == 64 ? kNear && !CHAIN && mask_c == -1
+      // Does the routine of this iteration issue the next one's copies itself?  At D = 64 (depth-0 keys; a second body
+      // per mode costs spilled registers) its unmasked form always does: the next row tile is never the sequence's
+      // last, which a list starts with, and behind the last one it copies a tile that nobody reads (row tile 0 of a dense
+      // map).  At D = 128 both forms have a body without.
+      const bool rides = D == 64 ? (kNear || LISTED) && !CHAIN && mask_c == -1
                                  : (kNear || LISTED) && have1 && mask_c >= -1 && (LISTED || rows_of(rt_n) == full_rows);
       const bool have2 = it + 2 < n_iter, have3 = it + 3 < n_iter;
       Toks tok_a = tok_n;
@@ -1640,10 +1651,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
           if (kNear && rides)
             dkdv_rowtile_pipelined<D, 0>(next_rows(D == 64 ? h_lo : hh_n, have1 ? rt_n : 0, buf ^ 1), q_lds, do_lds, lse_lds,
                                          delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
-          else if (D == 128 && LISTED && rides)
-            dkdv_rowtile_pipelined<D, 0>(next_listed(hh_n, tok_n, buf ^ 1), q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv,
+          else if (LISTED && rides)  // (behind the last row tile: tok_n still names its rows)
+            dkdv_rowtile_pipelined<D, 0>(next_listed(D == 64 ? h_lo : hh_n, tok_n, buf ^ 1), q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv,
                                          g, p.c_log2);
-          else if (!kNear || D == 128)
+          else if (ROWS == kRowsFar || D == 128)
             dkdv_rowtile_pipelined<D, 0>(NoCopies{}, q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
         } else if (mask_c >= 0) {
           // which of the tile's 128 rows see this lane's key: four words, one per 32-row unit
@@ -2443,7 +2454,8 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
       };
       const bool near = p.near_rows && p.L >= p.tm.A;
       const int apart = D == 64 ? kRowsApart<64> : kRowsApart<128>;
-      if (listed_map) pick(std::integral_constant<int, kRowsListed>{});
+      if (listed_map && p.near_rows) pick(std::integral_constant<int, kRowsListed>{});
+      else if (listed_map) pick(std::integral_constant<int, kRowsListedFar>{});
       else if (near && apart % p.tm.K == 0) pick(std::integral_constant<int, kRowsWhole>{});
       else if (near && p.tm.A * p.tm.K > kRowsPerTile - apart) pick(std::integral_constant<int, kRowsMost>{});
       else pick(std::integral_constant<int, kRowsFar>{});

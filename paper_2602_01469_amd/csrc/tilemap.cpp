@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
+#include <cstddef>
 #include <cstring>
 #include <map>
 #include <new>
@@ -117,15 +119,23 @@ int upload_map(peagle_tilemap* tm, hipStream_t stream, bool wait) {
   int prev = -1;
   if (hipGetDevice(&prev) != hipSuccess || hipSetDevice(tm->device) != hipSuccess) return PEAGLE_EHIP;
   constexpr int kArrays = 12;
-  static const char kZeros[256] = {0};
+  struct Constants {
+    char zeros[256];
+    float no_row[64];
+  };
+  static const Constants kConstants = [] {
+    Constants c{};
+    for (float& x : c.no_row) x = -HUGE_VALF;
+    return c;
+  }();
   const size_t sz[kArrays] = {tm->row_ptr.size() * sizeof(int32_t), tm->row_entries.size() * sizeof(TileEntry),
                               tm->key_ptr.size() * sizeof(int32_t), tm->key_entries.size() * sizeof(TileEntry),
                               tm->masks.size() * sizeof(uint32_t), tm->key_seg_ptr.size() * sizeof(int32_t),
-                              sizeof(kZeros), tm->row_lead.size() * sizeof(int32_t),
+                              sizeof(kConstants), tm->row_lead.size() * sizeof(int32_t),
                               tm->row_tok.size() * sizeof(int32_t), tm->chain_tok.size() * sizeof(int32_t),
                               tm->tok_posid.size() * sizeof(int32_t), tm->masks.size() * sizeof(uint32_t)};
   const void* src[kArrays] = {tm->row_ptr.data(), tm->row_entries.data(), tm->key_ptr.data(),
-                              tm->key_entries.data(), tm->masks.data(), tm->key_seg_ptr.data(), kZeros,
+                              tm->key_entries.data(), tm->masks.data(), tm->key_seg_ptr.data(), &kConstants,
                               tm->row_lead.data(), tm->row_tok.data(), tm->chain_tok.data(), tm->tok_posid.data(),
                               nullptr /* the key-major masks are written into the staging image below */};
   size_t off[kArrays], total = 0;
@@ -185,6 +195,7 @@ int upload_map(peagle_tilemap* tm, hipStream_t stream, bool wait) {
   tm->dview.masks = (const uint32_t*)(base + off[4]);
   tm->dview.key_seg_ptr = (const int32_t*)(base + off[5]);
   tm->dview.zeros = base + off[6];
+  tm->dview.no_row = base + off[6] + offsetof(Constants, no_row);
   tm->dview.row_lead = (const int32_t*)(base + off[7]);
   tm->dview.row_tok = tm->row_tok.empty() ? nullptr : (const int32_t*)(base + off[8]);
   tm->dview.chain_tok = tm->chain_tok.empty() ? nullptr : (const int32_t*)(base + off[9]);
@@ -502,6 +513,8 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
           tm->tok_pos[tok_of[(size_t)g * L + i]] = (int64_t)R * kRowsPerTile + rows_used;
           ++rows_used;
         }
+    const int32_t stand_in = rows_used > 0 ? ~tm->row_tok[(size_t)R * kRowsPerTile] : -1;
+    for (int r = rows_used; r < kRowsPerTile; ++r) tm->row_tok[(size_t)R * kRowsPerTile + r] = stand_in;
     // depth-0 stream: keys of the tile's own sequence up to its last anchor.  Depth-0 keys are causal
     // in the anchor inside a sequence (sees(i, d, j, 0) == j <= i), so row r sees the keys
     // [sb, row_a[r]] of a tile: a contiguous bit range.  Full tiles are listed first.

@@ -36,7 +36,9 @@ struct DeviceTileMap {
   const uint32_t* masks;      // [n_masks][128][2]: bit k%32 of word k/32 of row r: row r sees key k
   const uint32_t* masks_by_key;  // [n_masks][64][4]: the same bits key-major (bit r%32 of word r/32 of key k)
   const void* zeros;          // 256 zero bytes: source of rows that do not exist, for direct-to-LDS loads
-  const int32_t* row_tok;     // sampled maps only (else null): [n_row_tiles][128] token of each row, -1 = no row
+  const void* no_row;         // -infinity (fp32): -lse/scale of a row that does not exist
+  const int32_t* row_tok;     // sampled maps only (else null): [n_row_tiles][128] token of each row; of a row that does not
+                              // exist the complement of the tile's first token (negative)
   const int32_t* chain_tok;   // sampled maps only: [n_row_tiles * n_csub][64] token of each chain key, -1 = none
   const int32_t* tok_posid;   // sampled maps only: [T] sequence position (anchor - sequence start + depth) of each token
   int32_t A, K, S, n_row_tiles, n_d0, n_csub, n_key_tiles;

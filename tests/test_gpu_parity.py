@@ -891,6 +891,53 @@ def test_tensors_beyond_4_gib_equal_their_halves(D, Hq, Hkv):
             assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
 
 
+@pytest.mark.parametrize("D,Hq,Hkv", [(64, 176, 2), (128, 88, 2)])
+def test_listed_tensors_beyond_4_gib_equal_their_halves(D, Hq, Hkv):
+    """The same for a packed batch, whose rows are named by lists; each row tile lacks 32 of its 128 rows."""
+    lens, K = [1000, 1049], 96
+    tm = pe.peagle_build_tilemap_packed(lens, K, device=0)
+    L, T = sum(lens), tm.tokens(sum(lens))
+    assert T * Hq * D * 2 >= 1 << 32 > T * Hq * D
+    print(f"case listed beyond 4 GiB D={D} Hq={Hq}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(78)
+    rnd = lambda H: torch.randn(T, H, D, generator=g, device="cuda", dtype=torch.bfloat16)
+    q, d_o, k, v = rnd(Hq), rnd(Hq), rnd(Hkv), rnd(Hkv)
+    whole = _heads_run(tm, L, K, q, k, v, d_o)
+    for h in range(2):
+        a, b = slice(h * Hq // 2, (h + 1) * Hq // 2), slice(h, h + 1)
+        half = _heads_run(tm, L, K, *(t.contiguous() for t in (q[:, a], k[:, b], v[:, b], d_o[:, a])))
+        for n, t in half.items():
+            assert torch.isfinite(t).all(), n
+            assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_a_nan_stays_in_the_sequences_that_see_it(D):
+    """Rows that a listed row tile lacks are read from the tile's own first row: a sequence of NaN queries and gradients
+    packed first (its first row is token 0), between or last leaves every bit of the others as it was."""
+    lens, K, Hq, Hkv = [37, 150, 5, 90], 7, 4, 2
+    tm = pe.peagle_build_tilemap_packed(lens, K, device=0)
+    L, T, start = sum(lens), tm.tokens(sum(lens)), np.concatenate([[0], np.cumsum(lens)])
+    print(f"case NaN beside D={D}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(79)
+    q, k, v, d_o = (torch.randn(T, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq))
+    clean = _heads_run(tm, L, K, q, k, v, d_o)
+    anchor = torch.arange(T, device="cuda") % L               # (every depth kept: token d * L + i)
+    for s in (0, 2, 3):
+        own = (anchor >= int(start[s])) & (anchor < int(start[s + 1]))
+        spoilt_q, spoilt_do = q.clone(), d_o.clone()
+        spoilt_q[own], spoilt_do[own] = float("nan"), float("nan")
+        got = _heads_run(tm, L, K, spoilt_q, k, v, spoilt_do)
+        for n in ("o", "lse", "dq"):
+            assert torch.equal(got[n][~own], clean[n][~own]), (n, s)
+        # (key tiles are shared at a sequence's ends, and a zero probability times a NaN dP is NaN there, as ever)
+        tiles = {int(start[s]) // 64, (int(start[s + 1]) - 1) // 64}
+        apart = ~own & ~torch.isin(anchor // 64, torch.tensor(sorted(tiles), device="cuda"))
+        apart |= ~own & (torch.arange(T, device="cuda") >= L)  # chain keys are in tiles of their own rows
+        for n in ("dk", "dv"):
+            assert torch.equal(got[n][apart], clean[n][apart]), (n, s)
+
+
 @pytest.mark.parametrize("L_max,L,bounds", [(530, 530, None), (700, 517, None), (600, 600, [0, 520, 600])],
                          ids=["two_chunks", "cropped", "chunks_then_a_segment"])
 def test_dense_segments_of_more_than_128_row_tiles(L_max, L, bounds):
