@@ -1912,16 +1912,18 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
   constexpr int kBlocks = kTileBytes / 1024;
   constexpr int kRing = 2 * kGroups;  // two rounds of kGroups consecutive tiles: one being read, one on its way
   __shared__ __attribute__((aligned(16))) char lds[kRing][2][kTileBytes];  // [buffer][K|V]
-  __shared__ int tile_keys[kRing];  // keys present in the tile of each buffer (0 .. 64), set by the copying wave
-  __shared__ int table_bad;         // the copying wave met a page id outside the pool
+  __shared__ int tile_keys[kRing];  // keys present in the tile of each buffer (0 .. 64), set by the wave that copies K
+  __shared__ int table_bad;         // the wave that copies K met a page id outside the pool
 
-  // The last wave of the workgroup only copies (global -> LDS), the others only compute: the wait for a copy is
-  // counted per wave, so the computing waves never wait on one.  One workgroup barrier per round hands the buffers
-  // over.  (Deeper rings, three rounds of one tile, took LDS from the workgroups that share a CU and were slower:
+  // The last two waves of the workgroup only copy (global -> LDS; one K, one V), the others only compute: the wait for a
+  // copy is counted per wave, so the computing waves never wait on one.  One workgroup barrier per round hands the
+  // buffers over.  (One wave for both took most of a round to issue its copies, 16 or 32 a tile: 64 requests of 512 to 8,192
+  // tokens 121.3 us against 117.8 now, D = 128 32 of 512 12.6 / 11.9, 4 of 512 10.8 / 10.4, 35 of 2,137 to 3,838 58.8 / 57.2.  Deeper rings, three rounds of one tile, took LDS from the workgroups that share a CU and were slower:
   // 255 against 206 us on 64 equal contexts of 8,192 tokens.)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
-  const int n_compute = (blockDim.x >> 6) - 1;
-  const bool producer = wave == n_compute;
+  const int n_compute = (blockDim.x >> 6) - 2;
+  const bool producer = wave >= n_compute;
+  const bool copies_v = wave > n_compute;  // (a copying wave: V rather than K)
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int group = p.Hq / p.Hkv;
   const int n_rows = p.K * group;
@@ -1958,10 +1960,10 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
   const int n_tiles = (p1 - p0) + (split == 0 ? 1 : 0);  // split 0 also takes the new keys
   const int n_rounds = (n_tiles + kGroups - 1) / kGroups;
 
-  // Tile i of this split is a cache page or, last in split 0, the K new keys.  Only the copying wave
-  // reads the block table - through the scalar (constant) path, because a vector load would be ordered
-  // behind its copies and using the result would wait for all of them, and one tile ahead of its use,
-  // so that the load's latency is off the path; it tells the computing waves how many keys each tile
+  // Tile i of this split is a cache page or, last in split 0, the K new keys.  Only the copying waves
+  // read the block table - through the scalar (constant) path, because a vector load would be ordered
+  // behind their copies and using the result would wait for all of them, and one tile ahead of its use,
+  // so that the load's latency is off the path; the one that copies K tells the computing waves how many keys each tile
   // holds through tile_keys[] (a page id outside the pool makes the tile empty and flags the request).
   typedef const int32_t __attribute__((address_space(4))) * ConstTable;
   auto page_of = [&](int i) {
@@ -1972,8 +1974,8 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
     // Rows of a tile that hold no key (tail of the last page, rows past the K new keys, an empty tile)
     // are filled from the request's first new key, which is always present and finite user data: their
     // probabilities are masked to zero, and zero times a finite value adds nothing.
-    const __bf16* k_fill = p.k_new + ((size_t)c * p.K * p.Hkv + kvh) * D;
-    const __bf16* v_fill = p.v_new + ((size_t)c * p.K * p.Hkv + kvh) * D;
+    const __bf16* fill = uniform_ptr((copies_v ? p.v_new : p.k_new) + ((size_t)c * p.K * p.Hkv + kvh) * D);
+    const __bf16* pages = uniform_ptr(copies_v ? p.v_pages : p.k_pages);
     const int row_in_blk = lane / (D / 8), phys = lane % (D / 8);
     // A whole page: 1 KiB pieces of consecutive memory, their addresses on the scalar unit (with per-lane 64-bit
     // addresses this wave needed most of a microsecond to issue one tile's copies).  The chunk a lane fetches from a
@@ -1997,37 +1999,24 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
           valid = 0;
         }
       }
-      if (lane == 0) tile_keys[i % kRing] = valid;
+      if (lane == 0 && !copies_v) tile_keys[i % kRing] = valid;
       // (untracked copies: a tracked one would make every workgroup barrier below wait for all of them)
-      const uint32_t kdst = lds_scalar_addr(lds[i % kRing][0]), vdst = lds_scalar_addr(lds[i % kRing][1]);
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_scalar_addr(lds[i % kRing][0]) + (copies_v ? kTileBytes : 0));
       if (!is_new && valid == kKeysPerTile) {
-        const size_t first = ((size_t)page * p.Hkv + kvh) * (kKeysPerTile * D);
-        const __bf16* ks = uniform_ptr(p.k_pages + first);
-        const __bf16* vs = uniform_ptr(p.v_pages + first);
+        const __bf16* src = uniform_ptr(pages + ((size_t)page * p.Hkv + kvh) * (kKeysPerTile * D));
 #pragma unroll
-        for (int blk = 0; blk < kBlocks; ++blk) dma16_untracked(ks + blk * 512, voff[blk % kPeriod], kdst + blk * 1024);
-#pragma unroll
-        for (int blk = 0; blk < kBlocks; ++blk) dma16_untracked(vs + blk * 512, voff[blk % kPeriod], vdst + blk * 1024);
+        for (int blk = 0; blk < kBlocks; ++blk) dma16_untracked(src + blk * 512, voff[blk % kPeriod], dst + blk * 1024);
         return;
       }
 #pragma unroll 2
       for (int blk = 0; blk < kBlocks; ++blk) {
         const int row = blk * (512 / D) + row_in_blk;
         const int chunk = (phys ^ swz<D>(row)) << 3;
-        const __bf16 *ks, *vs;
-        if (row >= valid) {
-          ks = k_fill + chunk;
-          vs = v_fill + chunk;
-        } else if (is_new) {
-          ks = k_fill + (size_t)row * p.Hkv * D + chunk;
-          vs = v_fill + (size_t)row * p.Hkv * D + chunk;
-        } else {
-          const size_t off = (((size_t)page * p.Hkv + kvh) * kKeysPerTile + row) * D + chunk;
-          ks = p.k_pages + off;
-          vs = p.v_pages + off;
-        }
-        dma16_untracked(ks, kdst + blk * 1024);
-        dma16_untracked(vs, vdst + blk * 1024);
+        const __bf16* src;
+        if (row >= valid) src = fill + chunk;
+        else if (is_new) src = fill + (size_t)row * p.Hkv * D + chunk;
+        else src = pages + (((size_t)page * p.Hkv + kvh) * kKeysPerTile + row) * D + chunk;
+        dma16_untracked(src, dst + blk * 1024);
       }
     };
     int issued = 0;  // tiles
@@ -2037,12 +2026,12 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
     copy_round();
     for (int q = 0; q < n_rounds; ++q) {
       wait_outstanding<0>();  // round q has landed
-      if (q == n_rounds - 1 && lane == 0) table_bad = bad ? 1 : 0;  // every tile has been looked up by now
+      if (q == n_rounds - 1 && lane == 0 && !copies_v) table_bad = bad ? 1 : 0;  // every tile has been looked up by now
       __syncthreads();  // round q is published; the computing waves are done with round q-1 ...
       copy_round();     // ... whose buffers take round q + 1
     }
     if (n_rounds == 0) {
-      if (lane == 0) table_bad = 0;
+      if (lane == 0 && !copies_v) table_bad = 0;
       __syncthreads();
     }
     if (kGroups > 1) {  // the two barriers of the merge below
@@ -2094,7 +2083,7 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
     // Merge of the groups: each but the first leaves (max, sum, O) in the buffers, [value][lane] per wave, and the
     // first adds them up in order.  A group that had no tile carries the start values, which add nothing.
     constexpr int kVals = 2 + (D / 32) * 16;
-    static_assert((kGroups - 1) * (kThreads / 64 - 1) / kGroups * kVals * 256 <= (int)sizeof(lds), "merge records must fit");
+    static_assert((kGroups - 1) * (kThreads / 64 - 2) / kGroups * kVals * 256 <= (int)sizeof(lds), "merge records must fit");
     float* x = reinterpret_cast<float*>(&lds[0][0][0]);
     __syncthreads();  // every wave has left the tiles
     if (grp > 0) {
@@ -2513,21 +2502,21 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   // while there is at most one per CU anyway.  us per call, one / two groups: D = 64, 4 requests of 2,048 - 4,096 tokens
   // (512 workgroups) 20.3 / 19.1, 64 of 512 - 8,192 (pieces of up to 64 pages) 134 / 120, 16 of 2,000 - 20,000 (39) 89 /
   // 80, 55 of 1,691 - 2,469 (13) 67 / 77, 64 of 100 - 1,000 (8) 30 / 41; D = 128, 2 of 10,800 - 20,000 (256 workgroups)
-  // 23.1 / 21.2, 16 of 800 - 8,192 (1,024) 54 / 66.  More than 64 query rows make nine waves, too many for two per CU.
+  // 23.1 / 21.2, 16 of 800 - 8,192 (1,024) 54 / 66.  More than 64 query rows make ten waves, too many for two per CU.
   const bool two = row_waves <= 2 && (D == 64 ? n_wg <= 2 * kCus || long_pieces : n_wg <= kCus);
   // Long pieces of requests of different lengths: with more workgroups than two per CU, those of the longest requests
   // start first.  us per call in order of the request / by length: the 64 requests of 512 to 8,192 tokens above 161 /
   // 120, at D = 128 149 / 133; but 35 of 2,137 - 3,838 at D = 128 (pieces of 8 pages) 70.8 / 74.7: ranking costs most of
   // a page's time.  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
   p.by_length = p.C > 1 && p.C <= 64 && n_wg > 2 * kCus && long_pieces;
-  const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + 1) * 64));
-  // (The bound of 576 threads, of which 320 are launched, has the compiler schedule for four waves per SIMD: 120
+  const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + 2) * 64));
+  // (The bound of 576 threads, of which 384 are launched, has the compiler schedule for four waves per SIMD: 120
   // against 136 us on the first of those batches.  The other forms run the same with either bound.)
   auto go = [&](auto one_tag) {
     constexpr bool ONE = decltype(one_tag)::value;
     auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, p); };
-    if (D == 64) two ? run(draft_decode_kernel<64, 2, 576, ONE>) : run(draft_decode_kernel<64, 1, 320, ONE>);
-    else two ? run(draft_decode_kernel<128, 2, 320, ONE>) : run(draft_decode_kernel<128, 1, 320, ONE>);
+    if (D == 64) two ? run(draft_decode_kernel<64, 2, 576, ONE>) : run(draft_decode_kernel<64, 1, 384, ONE>);
+    else two ? run(draft_decode_kernel<128, 2, 384, ONE>) : run(draft_decode_kernel<128, 1, 384, ONE>);
   };
   p.n_splits == 1 ? go(std::true_type{}) : go(std::false_type{});
   hipError_t e = hipGetLastError();
