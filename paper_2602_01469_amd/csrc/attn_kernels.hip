@@ -1136,9 +1136,10 @@ struct NextRowTile {
   }
 };
 
-// The same for rows named by token lists.  A row that does not exist is read from the tile's first row, which every key of
-// the tile sees or is masked for like the missing one, and its -lse/scale of -infinity makes its probabilities zero: no
-// copy of Q or dO has to choose between two addresses.  FAR: offsets past 4 GiB.  (dK/dV, us, with 64-bit addresses chosen
+// The same for rows named by token lists.  A row that does not exist is read from the tile's last row and its -lse/scale of
+// -infinity makes its probabilities zero: no copy of Q or dO has to choose between two addresses.  (Zero times a NaN of that
+// row is a NaN: the last row, because a key that is taken with a unit of missing rows - chain keys at D = 64 are taken unit
+// by unit - is taken with the last row's unit anyway.)  FAR: offsets past 4 GiB.  (dK/dV, us, with 64-bit addresses chosen
 // per lane and the copies issued together at D = 64 / so: sampled 8,192 4,581 / 4,357, eight packed sequences 1,388 / 1,318;
 // D = 128, riding before too, sampled 4,096 1,349 / 1,233, packed 1,556 / 1,417.)
 template <int D, bool FAR>

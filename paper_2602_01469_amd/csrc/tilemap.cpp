@@ -513,7 +513,7 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
           tm->tok_pos[tok_of[(size_t)g * L + i]] = (int64_t)R * kRowsPerTile + rows_used;
           ++rows_used;
         }
-    const int32_t stand_in = rows_used > 0 ? ~tm->row_tok[(size_t)R * kRowsPerTile] : -1;
+    const int32_t stand_in = rows_used > 0 ? ~tm->row_tok[(size_t)R * kRowsPerTile + rows_used - 1] : -1;
     for (int r = rows_used; r < kRowsPerTile; ++r) tm->row_tok[(size_t)R * kRowsPerTile + r] = stand_in;
     // depth-0 stream: keys of the tile's own sequence up to its last anchor.  Depth-0 keys are causal
     // in the anchor inside a sequence (sees(i, d, j, 0) == j <= i), so row r sees the keys

@@ -38,7 +38,7 @@ struct DeviceTileMap {
   const void* zeros;          // 256 zero bytes: source of rows that do not exist, for direct-to-LDS loads
   const void* no_row;         // -infinity (fp32): -lse/scale of a row that does not exist
   const int32_t* row_tok;     // sampled maps only (else null): [n_row_tiles][128] token of each row; of a row that does not
-                              // exist the complement of the tile's first token (negative)
+                              // exist the complement of the tile's last token (negative)
   const int32_t* chain_tok;   // sampled maps only: [n_row_tiles * n_csub][64] token of each chain key, -1 = none
   const int32_t* tok_posid;   // sampled maps only: [T] sequence position (anchor - sequence start + depth) of each token
   int32_t A, K, S, n_row_tiles, n_d0, n_csub, n_key_tiles;

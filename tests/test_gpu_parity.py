@@ -913,8 +913,8 @@ def test_listed_tensors_beyond_4_gib_equal_their_halves(D, Hq, Hkv):
 
 @pytest.mark.parametrize("D", [64, 128])
 def test_a_nan_stays_in_the_sequences_that_see_it(D):
-    """Rows that a listed row tile lacks are read from the tile's own first row: a sequence of NaN queries and gradients
-    packed first (its first row is token 0), between or last leaves every bit of the others as it was."""
+    """Rows that a listed row tile lacks are read from the tile's own last row: a sequence of NaN queries and gradients
+    packed first, between or last leaves every bit of the others as it was."""
     lens, K, Hq, Hkv = [37, 150, 5, 90], 7, 4, 2
     tm = pe.peagle_build_tilemap_packed(lens, K, device=0)
     L, T, start = sum(lens), tm.tokens(sum(lens)), np.concatenate([[0], np.cumsum(lens)])
@@ -936,6 +936,34 @@ def test_a_nan_stays_in_the_sequences_that_see_it(D):
         apart |= ~own & (torch.arange(T, device="cuda") >= L)  # chain keys are in tiles of their own rows
         for n in ("dk", "dv"):
             assert torch.equal(got[n][apart], clean[n][apart]), (n, s)
+
+
+@pytest.mark.parametrize("D,spoilt,kept", [(64, 0, (32, 126)), (64, 125, (0, 64)), (128, 0, (0, 0)), (128, 125, (0, 0))])
+def test_a_nan_row_stays_with_the_chain_keys_that_share_its_unit(D, spoilt, kept):
+    """Row tiles of 18 anchors of K = 7: 126 rows and two missing ones.  At D = 64 chain keys are taken with the 32-row units
+    that hold rows of their anchors, so a NaN first row (unit 0) reaches those of the first 32 slots and a NaN last row (unit
+    3) those of the slots from 64 on, whose anchors reach unit 3; the missing rows (unit 3 as well) carry it no further.  At
+    D = 128 a chain key is taken with the whole tile.  No other tile's chain keys see the row at all."""
+    lens, K, Hq, Hkv, first = [37, 150, 90], 7, 4, 2, 37 + 18      # (the second tile of the second sequence)
+    tm = pe.peagle_build_tilemap_packed(lens, K, device=0)
+    L, T = sum(lens), tm.tokens(sum(lens))
+    assert T == L * K and 128 // K == 18                           # every depth kept: token d * L + i
+    print(f"case NaN in one row D={D} row={spoilt}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(80)
+    q, k, v, d_o = (torch.randn(T, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq))
+    clean = _heads_run(tm, L, K, q, k, v, d_o)
+    tok = torch.arange(T, device="cuda")
+    anchor, depth = tok % L, tok // L
+    mine = (anchor >= first) & (anchor < first + 18)
+    slot = (anchor - first) * K + depth                            # row of the tile, and slot of its chain key
+    for t in (q, d_o):
+        t[mine & (slot == spoilt)] = float("nan")
+    got = _heads_run(tm, L, K, q, k, v, d_o)
+    apart = (depth >= 1) & (~mine | (slot >= kept[0]) & (slot < kept[1]))
+    for n in ("dk", "dv"):
+        assert torch.isfinite(got[n][apart]).all(), n
+        # (the forward takes the tile's other rows again with the running max: the same to rounding, not to the bit)
+        assert _grad_rel(got[n][apart].double().cpu().numpy(), clean[n][apart].double().cpu().numpy()) <= GRAD_REL, n
 
 
 @pytest.mark.parametrize("L_max,L,bounds", [(530, 530, None), (700, 517, None), (600, 600, [0, 520, 600])],
