@@ -355,8 +355,8 @@ int peagle_attn_step_rope_shared(const peagle_tilemap_t* tm, const peagle_shape_
  *                clamped, nothing is read out of bounds), else 0
  *   workspace    device, >= peagle_draft_decode_workspace_bytes(); contents undefined before and after
  *
- * The context of every request is cut into up to peagle_draft_decode_splits() pieces that run in
- * parallel (one workgroup per piece, KV head and request); more than one are merged by a second launch.
+ * The context of every request is cut into peagle_draft_decode_splits() pieces that run in parallel
+ * (one workgroup per piece, KV head and request); more than one are merged by a second launch.
  * Nothing is allocated and nothing is copied to the host: the call can sit in a serving loop.
  */
 #define PEAGLE_PAGE_TOKENS 64

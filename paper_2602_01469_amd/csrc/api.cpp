@@ -455,9 +455,10 @@ int check_decode(const peagle_decode_shape_t* s) {
   return PEAGLE_OK;
 }
 
-// Pieces each request's context is cut into: enough workgroups to cover the chip a few times over,
-// but at least four pages per piece so that the partial records stay small next to the cache read.
-int decode_splits(const peagle_decode_shape_t* s) {
+// Pieces per request that the workspace is laid out for (the launch may take fewer, see draft_pieces()): enough workgroups to
+// cover the chip a few times over, but at least four pages per piece so that the partial records stay small next to the
+// cache read.
+int laid_out_pieces(const peagle_decode_shape_t* s) {
   const int64_t want = (1024 + (int64_t)s->C * s->Hkv - 1) / ((int64_t)s->C * s->Hkv);
   const int64_t most = (s->max_pages + 3) / 4;
   int64_t n = want < most ? want : most;
@@ -471,7 +472,7 @@ struct DecodeWs {
 };
 DecodeWs decode_ws(const peagle_decode_shape_t* s) {
   DecodeWs w;
-  w.n_splits = decode_splits(s);
+  w.n_splits = laid_out_pieces(s);
   w.rows_pad = (s->K * (s->Hq / s->Hkv) + 31) / 32 * 32;
   const size_t recs = (size_t)s->C * s->Hkv * w.n_splits;
   w.o_off = 0;
@@ -483,7 +484,8 @@ DecodeWs decode_ws(const peagle_decode_shape_t* s) {
 }  // namespace
 
 extern "C" int32_t peagle_draft_decode_splits(const peagle_decode_shape_t* shape) {
-  return check_decode(shape) == PEAGLE_OK ? decode_splits(shape) : -1;
+  if (check_decode(shape) != PEAGLE_OK) return -1;
+  return peagle::draft_pieces((int64_t)shape->C * shape->Hkv, shape->max_pages, laid_out_pieces(shape), shape->D);
 }
 
 extern "C" size_t peagle_draft_decode_workspace_bytes(const peagle_decode_shape_t* shape) {

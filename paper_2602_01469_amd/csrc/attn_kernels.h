@@ -77,11 +77,15 @@ struct DecodeParams {
   int32_t* status;             // [C] or null: 1 if the request's block table or length was out of range
   float* part_o;               // workspace [C, Hkv, n_splits, rows_pad, D]: unnormalised partial outputs
   float* part_ml;              // workspace [C, Hkv, n_splits, 3, rows_pad]: reference max (log2), row sum, flag
-  int C, K, Hq, Hkv, n_pages, max_pages, n_splits, rows_pad;
+  int C, K, Hq, Hkv, n_pages, max_pages, rows_pad;
+  int n_splits;                // pieces the workspace is laid out for; the launcher replaces it by draft_pieces()
   int by_length;               // filled by the launcher: requests take the workgroups by falling context length (C <= 64)
   float c_log2;
 };
 hipError_t launch_draft_decode(const DecodeParams& p, int D, hipStream_t stream);
+// Pieces per request that the launch takes (host only): workgroups per piece are requests x KV heads, `laid_out` is the
+// number of pieces that the workspace has records for.
+int draft_pieces(int64_t wgs_per_piece, int max_pages, int laid_out, int D);
 
 // Optional per-kernel timing: an event pair is recorded around every launch on the launch stream.
 enum KernelKind { kKindFwd = 0, kKindDq = 1, kKindDkDv = 2, kKindReduce = 3, kKindRope = 4, kNumKinds = 5 };

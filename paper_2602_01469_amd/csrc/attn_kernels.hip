@@ -2468,7 +2468,7 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
   return hipSuccess;
 }
 
-// Pieces that each request's context is cut into, at most p.n_splits (which the workspace is laid out for: a thousand
+// Pieces that each request's context is cut into, at most `laid_out` (which the workspace is laid out for: a thousand
 // workgroups, at least four pages each).  As few as leave no CU without a workgroup, since every piece pays the chain of
 // round trips at a workgroup's start and end again; for two workgroups per CU where pieces would be longer than kLongPiece
 // pages, and all where they would still be longer than two of those: requests differ in length, and the longest one's
@@ -2480,20 +2480,20 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
 // kOnePiece pages that is worth a longer chain in fewer workgroups, pieces 2 or 3 / 1: D = 64, one request of 512 tokens
 // 9.2 / 8.2, 4 of 768 10.4 / 9.9, 2 of 1,000 (16 pages) 9.7 / 11.9; D = 128, 4 of 512 11.7 / 10.8, 4 of 768 12.3 / 13.0.
 constexpr int kOnePiece64 = 12, kOnePiece128 = 8;  // pages
-inline int pieces(const DecodeParams& p, int D) {
+int draft_pieces(int64_t wgs_per_piece, int max_pages, int laid_out, int D) {
   auto at_least = [&](int wgs) {
-    const int n = (wgs + p.C * p.Hkv - 1) / (p.C * p.Hkv);
-    return n < p.n_splits ? n : p.n_splits;
+    const int n = (int)((wgs + wgs_per_piece - 1) / wgs_per_piece);
+    return n < laid_out ? n : laid_out;
   };
-  auto pages = [&](int n) { return (p.max_pages + n - 1) / n; };
-  if (p.max_pages <= (D == 64 ? kOnePiece64 : kOnePiece128)) return 1;
+  auto pages = [&](int n) { return (max_pages + n - 1) / n; };
+  if (max_pages <= (D == 64 ? kOnePiece64 : kOnePiece128)) return 1;
   if (pages(at_least(kCus)) <= kLongPiece) return at_least(kCus);
-  return pages(at_least(2 * kCus)) <= 2 * kLongPiece ? at_least(2 * kCus) : p.n_splits;
+  return pages(at_least(2 * kCus)) <= 2 * kLongPiece ? at_least(2 * kCus) : laid_out;
 }
 
 hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t stream) {
   DecodeParams p = pin;
-  p.n_splits = pieces(p, D);
+  p.n_splits = draft_pieces((int64_t)p.C * p.Hkv, p.max_pages, p.n_splits, D);
   const int row_waves = p.rows_pad / 32;  // 1 .. 4
   const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
   const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;

@@ -55,6 +55,15 @@ def _check(inp, o, lse, scale, what):
         assert max_abs(lse[c], rl) <= LSE_ABS, (what, c)
 
 
+def _form(shape):
+    """(pieces, two wave groups?, requests ranked by length?) of a shape: the launcher's choice of kernel, on the pieces that
+    it reports."""
+    pieces = pe.peagle_draft_decode_splits(shape)
+    wgs, long = shape.C * shape.Hkv * pieces, -(-shape.max_pages // pieces) > 16
+    two = shape.K * (shape.Hq // shape.Hkv) <= 64 and (wgs <= 512 or long if shape.D == 64 else wgs <= 256)
+    return pieces, two, 1 < shape.C <= 64 and wgs > 512 and long
+
+
 DECODE = [
     # name, ctx_lens, K, Hq, Hkv, D, seed
     ("paper_c4_k7", (900, 1500, 333, 2048), 7, 64, 8, 64, 1000),
@@ -85,8 +94,7 @@ def test_draft_decode_matches_oracle(name, ctx_lens, K, Hq, Hkv, D, seed):
     o2, lse2, _ = r.run()                                   # same buffers, same workspace: identical bits
     assert np.array_equal(o, o2) and np.array_equal(lse, lse2)
     if name == "long_pieces_mixed_batch":                   # the case exists to reach two wave groups and the ranking
-        splits = pe.peagle_draft_decode_splits(r.shape)
-        assert D == 64 and -(-r.shape.max_pages // splits) > 16 and len(ctx_lens) * Hkv * splits > 512, splits
+        assert _form(r.shape) == (8, True, True)
 
 
 def test_draft_decode_large_logits():
@@ -141,22 +149,26 @@ def test_draft_decode_replays_from_a_hip_graph():
         assert np.array_equal(lse_graph.double().cpu().numpy(), lse_eager), rep
 
 
-RANKED = [
-    # name, number of requests, largest context, K, Hq, Hkv, D, taken by falling length?: batches of more workgroups than
-    # two per CU, with pieces of more than 16 pages and shorter ones, over the merge kernel's forms (2, 3 to 8, more
-    # splits per request)
-    ("c64_d64", 64, 2200, 4, 16, 8, 64, True),
-    ("c65_d64", 65, 2200, 4, 16, 8, 64, False),
-    ("c64_d64_short_pieces", 64, 300, 4, 16, 8, 64, False),
-    ("c64_d128", 64, 2200, 5, 16, 8, 128, True),
-    ("c24_d128", 24, 6500, 8, 32, 8, 128, True),
-    ("c9_four_row_blocks", 9, 2000, 8, 128, 8, 64, False),
-    ("c8_d128_many_splits", 8, 4096, 3, 32, 8, 128, False),
+BATCHES = [
+    # name, number of requests, largest context, K, Hq, Hkv, D, form (see _form): every kernel, more and fewer workgroups than
+    # two per CU, more and fewer pieces than the merge kernels' limits (none, 2, 3 to 8, more)
+    ("c64_d64", 64, 2200, 4, 16, 8, 64, (2, True, True)),
+    ("c65_d64", 65, 2200, 4, 16, 8, 64, (2, True, False)),
+    ("c64_d64_one_piece", 64, 300, 4, 16, 8, 64, (1, True, False)),
+    ("c65_d64_one_piece", 65, 300, 4, 16, 8, 64, (1, False, False)),
+    ("c64_d128", 64, 2200, 5, 16, 8, 128, (2, False, True)),
+    ("c24_d128", 24, 6500, 8, 32, 8, 128, (6, False, True)),
+    ("c9_four_row_blocks", 9, 2000, 8, 128, 8, 64, (4, False, False)),
+    ("c64_four_row_blocks", 64, 8300, 8, 32, 2, 64, (8, False, True)),
+    ("c8_d128", 8, 4096, 3, 32, 8, 128, (4, True, False)),
+    ("c2_d128_many_pieces", 2, 20000, 5, 32, 4, 128, (32, True, False)),
+    ("c4_d128_one_piece", 4, 500, 5, 32, 4, 128, (1, True, False)),
+    ("c70_d128_one_piece_three_row_blocks", 70, 500, 6, 64, 4, 128, (1, False, False)),
 ]
 
 
-@pytest.mark.parametrize("name,C,longest,K,Hq,Hkv,D,ranked", RANKED, ids=[c[0] for c in RANKED])
-def test_draft_decode_batches_of_many_workgroups(name, C, longest, K, Hq, Hkv, D, ranked):
+@pytest.mark.parametrize("name,C,longest,K,Hq,Hkv,D,form", BATCHES, ids=[c[0] for c in BATCHES])
+def test_draft_decode_batches(name, C, longest, K, Hq, Hkv, D, form):
     """Lengths with ties, empty requests and the longest anywhere; then one request's table is spoiled: it alone is
     flagged and no other request's output changes."""
     rng = np.random.default_rng(C + D)
@@ -167,8 +179,7 @@ def test_draft_decode_batches_of_many_workgroups(name, C, longest, K, Hq, Hkv, D
     print(f"case decode {name}: ctx={lens.tolist()} K={K} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
     inp = make_decode_inputs(tuple(int(x) for x in lens), K, Hq, Hkv, D, 1100 + C)
     r = DecodeRun(inp, K, Hq, Hkv, D)
-    splits = pe.peagle_draft_decode_splits(r.shape)
-    assert C * Hkv * splits > 512 and ranked == (C <= 64 and -(-r.shape.max_pages // splits) > 16)
+    assert _form(r.shape) == form
     o, lse, status = r.run()
     assert (status == 0).all()
     _check(inp, o, lse, r.shape.scale, name)
@@ -196,6 +207,32 @@ def test_draft_decode_in_a_table_wider_than_its_requests(longest):
     o, lse, status = r.run()
     assert (status == 0).all()
     _check(inp, o, lse, r.shape.scale, f"wide table {longest}")
+
+
+@pytest.mark.parametrize("C,ctx,Hq,Hkv,D", [(4, 4096, 64, 8, 64), (1, 20000, 8, 8, 64), (55, 2469, 64, 8, 64), (3, 700, 16, 2, 64),
+                                             (16, 8192, 32, 4, 128), (35, 3838, 32, 4, 128), (5, 512, 32, 4, 128)])
+def test_draft_decode_leaves_a_partial_record_for_each_piece(C, ctx, Hq, Hkv, D):
+    """peagle_draft_decode_splits() pieces of every request and KV head each leave one record of unnormalised rows at the
+    start of the workspace; a single piece leaves none."""
+    print(f"case decode records: {C} of {ctx} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
+    K, pages = 3, -(-ctx // 64)
+    shape = pe.DecodeShape(C, K, Hq, Hkv, D, 8, pages)
+    rows_pad = -(-K * (Hq // Hkv) // 32) * 32
+    rec = rows_pad * D
+    g = torch.Generator(device="cuda").manual_seed(1400 + C)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v, kp, vp = rnd(C, K, Hq, D), rnd(C, K, Hkv, D), rnd(C, K, Hkv, D), rnd(8, Hkv, 64, D), rnd(8, Hkv, 64, D)
+    table = torch.randint(0, 8, (C, pages), generator=g, device="cuda", dtype=torch.int32)
+    lens, status = (torch.full((C,), n, dtype=torch.int32, device="cuda") for n in (ctx, -7))
+    o, lse = torch.empty_like(q), torch.empty((C, Hq, K), device="cuda")
+    ws = torch.full((pe.peagle_draft_decode_workspace_bytes(shape),), 0x5A, dtype=torch.uint8, device="cuda")
+    pe.peagle_draft_decode(shape, q, k, v, kp, vp, table, lens, o, lse, status, ws)
+    torch.cuda.synchronize()
+    assert (status == 0).all()
+    laid_out = ws.numel() // (4 * rows_pad * (D + 3))        # (beside a record's rows: maximum, sum and flag of each)
+    written = (ws[:4 * laid_out * rec].view(torch.int32).view(laid_out, rec) != 0x5A5A5A5A).any(1).cpu().numpy()
+    pieces = pe.peagle_draft_decode_splits(shape)
+    assert written.tolist() == [pieces > 1 and r < C * Hkv * pieces for r in range(laid_out)]
 
 
 @pytest.mark.parametrize("D,pages", [(64, 1), (64, 12), (64, 13), (128, 8), (128, 9)])
