@@ -2469,26 +2469,33 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
 }
 
 // Pieces that each request's context is cut into, at most `laid_out` (which the workspace is laid out for: a thousand
-// workgroups, at least four pages each).  As few as leave no CU without a workgroup, since every piece pays the chain of
-// round trips at a workgroup's start and end again; for two workgroups per CU where pieces would be longer than kLongPiece
-// pages, and all where they would still be longer than two of those: requests differ in length, and the longest one's
-// pieces would be waited for.  us per call, pieces a request (workgroups) as laid out / as taken here: D = 64, 4 requests of 2,048 - 4,096 tokens
-// 14.5 (16; 512) / 12.7 (8; 256), 16 of 1,000 16.2 (4; 512) / 13.4 (2; 256), 8 of 300 - 3,000 17.5 (12; 768) / 15.2 (4; 256), 4 of
-// 8,000 - 20,000 29.1 (32; 1,024) / 26.8 (16; 512; 8 pieces 29.9), 16 of 2,000 - 20,000 stay at 8 (78; 4 pieces 88), 64 of 100 -
-// 1,000 27.9 (2; 1,024) / 19.7 (1; 512); D = 128, 16 of 800 - 8,192 41.9 (16; 1,024) / 36.5 (8; 512).
+// workgroups, at least four pages each).  Every piece pays the chain of round trips at a workgroup's start and end again, so
+// fewer are taken, in two steps.  One workgroup per CU while pieces stay within kLongPiece pages: at D = 64 at least one, at
+// D = 128 at most one, because there two wave groups fill a CU's LDS and a second workgroup costs them (see the launch).
+// Otherwise at most two workgroups per CU, all running at once, while pieces stay within 32 pages (D = 64) or 20 (D = 128,
+// one wave group).  All others as laid out: requests differ in length, and the longest one's pieces would be waited for.
+// us per call, pieces a request (workgroups) as laid out / as taken: D = 64, 4 requests of 2,048 - 4,096 tokens 14.7 (16; 512) /
+// 12.8 (8; 256), 16 of 1,000 16.2 (4; 512) / 13.4 (2; 256), 8 of 300 - 3,000 17.5 (12; 768) / 15.2 (4; 256), 4 of 8,000 - 20,000
+// 29.1 (32; 1,024) / 26.8 (16; 512; 8 pieces 29.9), 64 of 100 - 1,000 27.5 (2; 1,024) / 19.1 (1; 512), 12 of 3,000 - 6,000 30.8
+// (11; 1,056) / 27.0 (5; 480; 6 pieces, 576 workgroups, 28.2); D = 128, 16 of 800 - 8,192 42.8 (16; 1,024) / 37.8 (8; 512), 3 of
+// 13,701 - 18,407 26.6 (32; 384) / 25.4 (21; 252; 22 pieces, 264 workgroups, 28.4), 35 of 2,137 - 3,838 57.6 (8; 1,120) / 46.8 (3;
+// 420; 4 pieces, 560 workgroups, 57.5).  As laid out: D = 64, 16 of 2,000 - 20,000 78 (8; 1,024; 4 pieces 88), 55 of 1,691 - 2,469
+// 56.3 (3; 1,320; 2 pieces, 880 workgroups, 59.0); D = 128, 27 of 3,914 - 6,578 83 (10; 1,080; 4 pieces of 26 pages 62), but 46
+// of 511 and one of 3,558 33 (6; 1,104; 2 pieces of 28 pages 46).  260 batches drawn over numbers and lengths, against all
+// pieces as laid out (and one copying wave): evenly spread lengths, D = 64 / 128, -10 / -9 % in the mean, +7 / +3 % at worst;
+// one to three long requests among short ones -12 / -7 %, +3 / +10 %.
 // One piece leaves its rows' results itself, without the launch that merges pieces (4 of 64 - 256 tokens 9.4 / 6.6).  Up to
 // kOnePiece pages that is worth a longer chain in fewer workgroups, pieces 2 or 3 / 1: D = 64, one request of 512 tokens
 // 9.2 / 8.2, 4 of 768 10.4 / 9.9, 2 of 1,000 (16 pages) 9.7 / 11.9; D = 128, 4 of 512 11.7 / 10.8, 4 of 768 12.3 / 13.0.
-constexpr int kOnePiece64 = 12, kOnePiece128 = 8;  // pages
+constexpr int kOnePiece64 = 12, kOnePiece128 = 8, kLongestPiece64 = 32, kLongestPiece128 = 20;  // pages
 int draft_pieces(int64_t wgs_per_piece, int max_pages, int laid_out, int D) {
-  auto at_least = [&](int wgs) {
-    const int n = (int)((wgs + wgs_per_piece - 1) / wgs_per_piece);
-    return n < laid_out ? n : laid_out;
-  };
+  auto within = [&](int64_t n) { return (int)(n < 1 ? 1 : n < laid_out ? n : laid_out); };
   auto pages = [&](int n) { return (max_pages + n - 1) / n; };
   if (max_pages <= (D == 64 ? kOnePiece64 : kOnePiece128)) return 1;
-  if (pages(at_least(kCus)) <= kLongPiece) return at_least(kCus);
-  return pages(at_least(2 * kCus)) <= 2 * kLongPiece ? at_least(2 * kCus) : laid_out;
+  const int one_per_cu = within((D == 64 ? kCus + wgs_per_piece - 1 : kCus) / wgs_per_piece);
+  if (pages(one_per_cu) <= kLongPiece) return one_per_cu;
+  const int two_per_cu = within(2 * kCus / wgs_per_piece);
+  return pages(two_per_cu) <= (D == 64 ? kLongestPiece64 : kLongestPiece128) ? two_per_cu : laid_out;
 }
 
 hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t stream) {

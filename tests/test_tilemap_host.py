@@ -589,6 +589,24 @@ def test_draft_decode_validates_before_launch():
     assert pe.peagle_draft_decode_splits(pe.DecodeShape(512, 3, 8, 8, 64, 5000, 4000)) == 1
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_draft_decode_takes_fewer_pieces_only_where_they_fit(D):
+    """The workspace is laid out for about 1,024 workgroups.  Several pieces a request, but fewer than that, make no more
+    workgroups than run at once: two per CU (512), at D = 128 one (256) where a workgroup's two wave groups fill its LDS."""
+    fewer = 0
+    for base in (1, 12, 24, 48, 72, 96, 108, 140, 160, 171, 184, 212, 250, 256, 257, 320, 440, 512, 513, 800):
+        for pages in (1, 8, 9, 12, 13, 16, 17, 24, 32, 33, 39, 48, 60, 64, 80, 94, 128, 200, 313):
+            pieces = pe.peagle_draft_decode_splits(pe.DecodeShape(base, 7, 8, 1, D, 1000, pages))
+            laid_out = max(1, min(-(-1024 // base), -(-pages // 4), 32))
+            per_piece = -(-pages // pieces)
+            assert 1 <= pieces <= laid_out
+            if 1 < pieces < laid_out:
+                fewer += 1
+                assert base * pieces <= 512 and per_piece <= 32, (base, pages, pieces)
+                assert D == 64 or base * pieces <= 256 or per_piece <= 20, (base, pages, pieces)
+    assert fewer > 30
+
+
 def test_draft_decode_static_validates_before_launch():
     """The entry point with the library's own scratch array: same checks, and shapes whose partial records
     exceed the array are refused with the workspace error."""
