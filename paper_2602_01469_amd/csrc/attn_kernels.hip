@@ -1916,15 +1916,17 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
   __shared__ int tile_keys[kRing];  // keys present in the tile of each buffer (0 .. 64), set by the wave that copies K
   __shared__ int table_bad;         // the wave that copies K met a page id outside the pool
 
-  // The last two waves of the workgroup only copy (global -> LDS; one K, one V), the others only compute: the wait for a
-  // copy is counted per wave, so the computing waves never wait on one.  One workgroup barrier per round hands the
-  // buffers over.  (One wave for both took most of a round to issue its copies, 16 or 32 a tile: 64 requests of 512 to 8,192
-  // tokens 121.3 us against 117.8 now, D = 128 32 of 512 12.6 / 11.9, 4 of 512 10.8 / 10.4, 35 of 2,137 to 3,838 58.8 / 57.2.  Deeper rings, three rounds of one tile, took LDS from the workgroups that share a CU and were slower:
-  // 255 against 206 us on 64 equal contexts of 8,192 tokens.)
+  // The last two waves of the workgroup only copy (global -> LDS; one K, one V; with three row blocks at D = 128 the last one
+  // both), the others only compute: the wait for a copy is counted per wave, so the computing waves never wait on one.  One
+  // workgroup barrier per round hands the buffers over.  (One wave for both takes most of a round to issue its copies, 16 or
+  // 32 a tile.  us, one / two: 4 requests of 2,048 - 4,096 tokens 14.1 / 13.1, 32 of 1,000 - 4,096 37.0 / 35.6, 64 of 512 - 8,192
+  // 120.8 / 119.6; D = 128 16.3 / 15.2, 41.5 / 40.6, 133.2 / 130.7.  Deeper rings, three rounds of one tile, took LDS from the
+  // workgroups that share a CU and were slower: 255 against 206 us on 64 equal contexts of 8,192 tokens.)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
-  const int n_compute = (blockDim.x >> 6) - 2;
+  const int n_compute = kGroups * (p.rows_pad / 32);
   const bool producer = wave >= n_compute;
   const bool copies_v = wave > n_compute;  // (a copying wave: V rather than K)
+  const bool copies_both = D == 128 && kGroups == 1 && (int)(blockDim.x >> 6) == n_compute + 1;  // (three row blocks: see the launcher)
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int group = p.Hq / p.Hkv;
   const int n_rows = p.K * group;
@@ -1986,23 +1988,9 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
 #pragma unroll
     for (int j = 0; j < kPeriod; ++j)
       voff[j] = (uint32_t)(row_in_blk * D + ((phys ^ swz<D>(j * (512 / D) + row_in_blk)) << 3)) * 2u;
-    int page_next = page_of(0);
-    auto copy_tile = [&](int i) {
-      const int page = page_next;
-      page_next = page_of(i + 1);
-      const bool is_new = i >= p1 - p0;
-      int valid = p.K;
-      if (!is_new) {
-        valid = n_ctx - (p0 + i) * kKeysPerTile;
-        valid = valid > kKeysPerTile ? kKeysPerTile : valid;
-        if (page < 0 || page >= p.n_pages) {
-          bad = true;
-          valid = 0;
-        }
-      }
-      if (lane == 0 && !copies_v) tile_keys[i % kRing] = valid;
+    auto copy_half = [&](int i, int page, bool is_new, int valid, const __bf16* pages, const __bf16* fill, bool v_half) {
       // (untracked copies: a tracked one would make every workgroup barrier below wait for all of them)
-      const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_scalar_addr(lds[i % kRing][0]) + (copies_v ? kTileBytes : 0));
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_scalar_addr(lds[i % kRing][0]) + (v_half ? kTileBytes : 0));
       if (!is_new && valid == kKeysPerTile) {
         const __bf16* src = uniform_ptr(pages + ((size_t)page * p.Hkv + kvh) * (kKeysPerTile * D));
 #pragma unroll
@@ -2019,6 +2007,25 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
         else src = pages + (((size_t)page * p.Hkv + kvh) * kKeysPerTile + row) * D + chunk;
         dma16_untracked(src, dst + blk * 1024);
       }
+    };
+    int page_next = page_of(0);
+    auto copy_tile = [&](int i) {
+      const int page = page_next;
+      page_next = page_of(i + 1);
+      const bool is_new = i >= p1 - p0;
+      int valid = p.K;
+      if (!is_new) {
+        valid = n_ctx - (p0 + i) * kKeysPerTile;
+        valid = valid > kKeysPerTile ? kKeysPerTile : valid;
+        if (page < 0 || page >= p.n_pages) {
+          bad = true;
+          valid = 0;
+        }
+      }
+      if (lane == 0 && !copies_v) tile_keys[i % kRing] = valid;
+      copy_half(i, page, is_new, valid, pages, fill, copies_v);
+      if (copies_both)
+        copy_half(i, page, is_new, valid, uniform_ptr(p.v_pages), uniform_ptr(p.v_new + ((size_t)c * p.K * p.Hkv + kvh) * D), true);
     };
     int issued = 0;  // tiles
     auto copy_round = [&] {
@@ -2505,21 +2512,28 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
   const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;
   const bool long_pieces = (p.max_pages + p.n_splits - 1) / p.n_splits > kLongPiece;  // pages of the longest request's pieces
-  // Two groups of waves per workgroup cost twice the LDS.  At D = 64 two such workgroups still share a CU (of one group,
-  // five do), which is enough while there are no more, or where pieces are long and few; at D = 128 one does, which pays
-  // while there is at most one per CU anyway.  us per call, one / two groups: D = 64, 4 requests of 2,048 - 4,096 tokens
-  // (512 workgroups) 20.3 / 19.1, 64 of 512 - 8,192 (pieces of up to 64 pages) 134 / 120, 16 of 2,000 - 20,000 (39) 89 /
-  // 80, 55 of 1,691 - 2,469 (13) 67 / 77, 64 of 100 - 1,000 (8) 30 / 41; D = 128, 2 of 10,800 - 20,000 (256 workgroups)
-  // 23.1 / 21.2, 16 of 800 - 8,192 (1,024) 54 / 66.  More than 64 query rows make ten waves, too many for two per CU.
+  // Two groups of waves per workgroup cost twice the LDS.  At D = 64 two such workgroups still share a CU (of one group, four
+  // do), which is enough while there are no more, or where pieces are long and few; at D = 128 one does (of one group, two),
+  // which pays while there is at most one per CU anyway.  us per call, one / two groups (pages of the longest pieces;
+  // workgroups): D = 64, 4 requests of 2,048 - 4,096 tokens (8; 256) 14.7 / 12.9, 64 of 100 - 1,000 (16; 512) 24.3 / 19.4, 64 of 512 -
+  // 8,192 (64; 1,024) 133 / 120, 16 of 2,000 - 20,000 (40; 1,024) 86 / 80, 55 of 1,691 - 2,469 (13; 1,320) 56.8 / 57.2, 65 of 300 (5;
+  // 520) 13.6 / 16.7, 128 of 300 (5; 1,024) 20.8 / 24.7; D = 128, 2 of 10,800 - 20,000 (10; 256) 23.8 / 21.6, 16 of 800 - 4,096 (16;
+  // 256) 31.0 / 25.3, 70 of 500 (8; 280) 22.0 / 26.7, 64 of 3,000 - 4,000 (16; 1,024) 110 / 117, 64 of 512 - 8,192 (32; 1,024) 130 / 142,
+  // but 35 of 2,137 - 3,838 (20; 420) 49.0 / 47.4.  More than 64 query rows make eight waves or ten, too many for two per CU.
   const bool two = row_waves <= 2 && (D == 64 ? n_wg <= 2 * kCus || long_pieces : n_wg <= kCus);
   // Long pieces of requests of different lengths: with more workgroups than two per CU, those of the longest requests
-  // start first.  us per call in order of the request / by length: the 64 requests of 512 to 8,192 tokens above 161 /
-  // 120, at D = 128 149 / 133; but 35 of 2,137 - 3,838 at D = 128 (pieces of 8 pages) 70.8 / 74.7: ranking costs most of
-  // a page's time.  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
+  // start first.  us per call in order of the request / by length: the 64 requests of 512 to 8,192 tokens above 144 /
+  // 120, at D = 128 148 / 130, 16 of 2,000 - 20,000 86 / 80.  Ranking costs most of a page's time: with pieces of 8 pages, 35 of
+  // 2,137 - 3,838 at D = 128 took 70.8 / 74.7.  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
   p.by_length = p.C > 1 && p.C <= 64 && n_wg > 2 * kCus && long_pieces;
-  const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + 2) * 64));
+  // Copying waves: two, but with three row blocks at D = 128 one, because two workgroups of five waves share a CU's four SIMDs
+  // badly (us, one / two copying waves, 96 query rows: 64 requests of 512 - 8,192 tokens 144 / 151, 32 of 1,000 - 4,096 46 / 59, 128
+  // of 300 23.0 / 25.4; but D = 64 64 of 512 - 8,192 143 / 131, and D = 128 with one, two and four row blocks 133 / 131, 41.5 /
+  // 40.6 and 64.6 / 62.5 on such batches).
+  const int copying = D == 128 && row_waves == 3 ? 1 : 2;
+  const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + copying) * 64));
   // (The bound of 576 threads, of which 384 are launched, has the compiler schedule for four waves per SIMD: 120
-  // against 136 us on the first of those batches.  The other forms run the same with either bound.)
+  // against 136 us on the 64 requests of 512 to 8,192 tokens.  The other forms run the same with either bound.)
   auto go = [&](auto one_tag) {
     constexpr bool ONE = decltype(one_tag)::value;
     auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, p); };

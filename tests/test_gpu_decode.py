@@ -164,6 +164,7 @@ BATCHES = [
     ("c2_d128_many_pieces", 2, 20000, 5, 32, 4, 128, (32, True, False)),
     ("c4_d128_one_piece", 4, 500, 5, 32, 4, 128, (1, True, False)),
     ("c70_d128_one_piece_three_row_blocks", 70, 500, 6, 64, 4, 128, (1, False, False)),
+    ("c9_d128_three_row_blocks", 9, 4096, 5, 64, 4, 128, (7, False, False)),
 ]
 
 
