@@ -1344,7 +1344,7 @@ __device__ __forceinline__ void dkdv_rowtile_chain(const char* q_lds, const char
 }
 
 // How the rows of a row tile are found.
-//   kRowsWhole, kRowsMost: dense map, tensors within reach of a 32-bit offset (RowDmaOffsets), L >= A: every row tile but the
+//   kRowsWhole, kRowsMost: dense map, tensors within reach of a 32-bit offset (RowDmaOffsets): every row tile but the
 //     sequence's last holds the same rows, and the copies of the next one ride between the matrix instructions
 //     (NextRowTile).  Whole: the rows a lane copies are a whole number of anchors apart (K divides kRowsApart, so that
 //     A * K = 128): one per-lane offset and a scalar step address every copy.  Most: an offset per copy, and the last copy
@@ -1623,7 +1623,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
       // Does the routine of this iteration issue the next one's copies itself?  At D = 64 (depth-0 keys; a second body
       // per mode costs spilled registers) its unmasked form always does: the next row tile is never the sequence's
       // last, which a list starts with, and behind the last one it copies a tile that nobody reads (row tile 0 of a dense
-      // map).  At D = 128 both forms have a body without.
+      // map, which is whole wherever a row tile is unmasked: row 0 sees one key only).  At D = 128 both forms have a body without.
       const bool rides = D == 64 ? (kNear || LISTED) && !CHAIN && mask_c == -1
                                  : (kNear || LISTED) && have1 && mask_c >= -1 && (LISTED || rows_of(rt_n) == full_rows);
       const bool have2 = it + 2 < n_iter, have3 = it + 3 < n_iter;
@@ -2449,12 +2449,11 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
         if (D == 64) sv_dkdv ? go(dkdv_kernel<64, ROWS, true>) : go(dkdv_kernel<64, ROWS, false>);
         else sv_dkdv ? go(dkdv_kernel<128, ROWS, true>) : go(dkdv_kernel<128, ROWS, false>);
       };
-      const bool near = p.near_rows && p.L >= p.tm.A;
       const int apart = D == 64 ? kRowsApart<64> : kRowsApart<128>;
       if (listed_map && p.near_rows) pick(std::integral_constant<int, kRowsListed>{});
       else if (listed_map) pick(std::integral_constant<int, kRowsListedFar>{});
-      else if (near && apart % p.tm.K == 0) pick(std::integral_constant<int, kRowsWhole>{});
-      else if (near && p.tm.A * p.tm.K > kRowsPerTile - apart) pick(std::integral_constant<int, kRowsMost>{});
+      else if (p.near_rows && apart % p.tm.K == 0) pick(std::integral_constant<int, kRowsWhole>{});
+      else if (p.near_rows && p.tm.A * p.tm.K > kRowsPerTile - apart) pick(std::integral_constant<int, kRowsMost>{});
       else pick(std::integral_constant<int, kRowsFar>{});
       hipError_t e = span.finish();
       if (e != hipSuccess) return e;

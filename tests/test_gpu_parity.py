@@ -985,11 +985,11 @@ def test_dense_segments_of_more_than_128_row_tiles(L_max, L, bounds):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("K,L", [(8, 15), (8, 16), (8, 17), (8, 130), (4, 31), (4, 100), (5, 24), (5, 25), (5, 201), (7, 19), (7, 73),
-                                 (33, 2), (33, 10), (43, 7), (32, 9)])
+@pytest.mark.parametrize("K,L", [(8, 3), (8, 15), (8, 16), (8, 17), (8, 130), (4, 31), (4, 100), (5, 24), (5, 25), (5, 201), (7, 19), (7, 73),
+                                 (7, 5), (33, 2), (33, 10), (43, 2), (43, 7), (32, 9)])
 def test_every_way_dkdv_finds_its_rows(K, L, D):
     """Row tiles of 128 rows at a constant step, of fewer with the missing ones in a tile's last copy (K = 5, 7; K = 33 at
-    D = 64), and of neither kind (K = 43; K = 33 at D = 128; L short of one tile); one tile, one and a bit, several."""
+    D = 64), and of neither kind (K = 43; K = 33 at D = 128); less than one tile, one, one and a bit, several."""
     Hq, Hkv, seed = 4, 2, 330 + K
     print(f"case rows: L={L} K={K} D={D}", flush=True)
     qb, kb, vb, dob = (rand_bits((L * K, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
