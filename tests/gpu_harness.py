@@ -82,6 +82,14 @@ def runs_plain_dq(tm, Hq):
     return mean_list(tm) < 24 and tm.info()["n_row_tiles"] * Hq >= 2 * 3 * 256
 
 
+def fwd_form(tm, Hq, Hkv):
+    """Which forward one launch over the whole map runs at D = 64: query heads per workgroup, workgroups per CU."""
+    mean, two_head_wgs = int(mean_list(tm) + 0.5), tm.info()["n_row_tiles"] * (Hq // 2)
+    if Hq // Hkv % 2 or mean <= 10 or two_head_wgs <= 512 or (two_head_wgs < 1024 and mean <= 24):
+        return "one head"
+    return "two heads, three per CU" if two_head_wgs >= 1024 else "two heads, two per CU"
+
+
 def rel_l2(a, b):
     return float(np.linalg.norm((a - b).ravel()) / max(np.linalg.norm(b.ravel()), 1e-300))
 

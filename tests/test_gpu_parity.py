@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2602_01469_amd as pe
-from gpu_harness import Run, bf16_to_f64, max_abs, mean_list, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
+from gpu_harness import Run, bf16_to_f64, fwd_form, max_abs, mean_list, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
 from oracle import peagle_oracle as orc
 from peagle_inputs import CONFIGS, bf16_bits_to_f64, make_inputs
 
@@ -180,47 +180,54 @@ def test_dense_segments_of_many_row_tiles(bounds):
         assert rel_l2(got[n], whole[n]) <= PART_REL, n
 
 
-@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (4, 2)])
+@pytest.mark.parametrize("Hq,Hkv", [(56, 14), (56, 28)])
 def test_two_heads_per_forward_workgroup_match_oracle(Hq, Hkv):
-    """Lists long enough (mean above 10) for the forward to take the heads of a group two at a time at D = 64."""
+    """Lists long enough (mean above 10) and heads enough for the forward to take the heads of a group two at a time at D =
+    64, three workgroups per CU; the first and the last KV head's groups against the oracle."""
     L, K, D, seed = 1290, 4, 64, 296
     print(f"case two heads per workgroup Hq={Hq} Hkv={Hkv}", flush=True)
     qb, kb, vb, dob = (rand_bits((L * K, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
     tm = pe.peagle_build_tilemap(L, K, [0, 640, L], device=0)
-    assert mean_list(tm) > 11
+    assert fwd_form(tm, Hq, Hkv) == "two heads, three per CU"
     r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
     r.step(0, 2)
-    _check_against_oracle(r.results(), _oracle(qb, kb, vb, dob, L, K, r.shape.scale), "two heads per workgroup")
+    got = r.results()
+    for h in (0, Hkv - 1):
+        a, b = slice(h * (Hq // Hkv), (h + 1) * (Hq // Hkv)), slice(h, h + 1)
+        part = {"O": got["O"][:, a], "LSE": got["LSE"][a], "dQ": got["dQ"][:, a], "dK": got["dK"][:, b], "dV": got["dV"][:, b]}
+        _check_against_oracle(part, _oracle(qb[:, a], kb[:, b], vb[:, b], dob[:, a], L, K, r.shape.scale), f"two heads, group {h}")
 
 
-@pytest.mark.parametrize("L", [600, 2000])
+@pytest.mark.parametrize("L,Hq", [(600, 4), (2000, 4), (2000, 36)])
 @pytest.mark.parametrize("qscale", [10.0, 12.0, 40.0])
-def test_large_logits_take_the_running_max_path(qscale, L):
+def test_large_logits_take_the_running_max_path(qscale, L, Hq):
     """Scores far outside the exponent range that the forward's first pass (reference max fixed at
     0) can hold: the kernel must detect it and redo the row tile with the running-max form, with one head
-    per workgroup (short lists) and with two.  The dQ kernel leaves its probabilities unnormalised only
+    per workgroup and (36 heads) with two.  The dQ kernel leaves its probabilities unnormalised only
     while |lse| <= 64 in log2 units: at the smaller scales some workgroups are inside that range and some
-    outside, at the largest none is inside, and both sequences are long enough for the pipelined kernel's
-    groups of three full tiles to occur (the plain one: test_both_dq_kernels_give_the_same_bits)."""
-    K, Hq, Hkv, D = 4, 4, 2, 64
-    print(f"case large_logits qscale={qscale} L={L}", flush=True)
+    outside, at the largest none is inside.  Both sequences are long enough for the pipelined kernel's
+    groups of three full tiles to occur; 36 heads take the plain one.  The first two KV heads against the oracle."""
+    K, Hkv, D = 4, Hq // 2, 64
+    print(f"case large_logits qscale={qscale} L={L} Hq={Hq}", flush=True)
     T = L * K
     qb, kb, vb, dob = (rand_bits((T, Hq, D), 300, qscale), rand_bits((T, Hkv, D), 301), rand_bits((T, Hkv, D), 302),
                        rand_bits((T, Hq, D), 303))
     tm = pe.peagle_build_tilemap(L, K, None, device=0)
+    assert fwd_form(tm, Hq, Hkv) == ("one head" if Hq == 4 else "two heads, three per CU")
+    assert (mean_list(tm) < 10) == (L == 600) and (mean_list(tm) > 11) == (L == 2000) and runs_plain_dq(tm, Hq) == (Hq == 36)
     r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
     r.fwd()
     r.bwd()
     got = r.results()
-    ref = _oracle(qb, kb, vb, dob, L, K, r.shape.scale)
-    assert (mean_list(tm) < 10) == (L == 600) and (mean_list(tm) > 11) == (L == 2000) and not runs_plain_dq(tm, Hq)
+    assert not any(np.isnan(got[n]).any() for n in got)
+    got = {"O": got["O"][:, :4], "LSE": got["LSE"][:4], "dQ": got["dQ"][:, :4], "dK": got["dK"][:, :2], "dV": got["dV"][:, :2]}
+    ref = _oracle(qb[:, :4], kb[:, :2], vb[:, :2], dob[:, :4], L, K, r.shape.scale)
     outside = np.abs(ref["LSE"]) * np.log2(np.e) > 64                                  # [Hq, K * L]
     row_tile = np.arange(T) % L // 32
-    share = np.mean([outside[h, row_tile == t].any() for h in range(Hq) for t in range(row_tile.max() + 1)])
+    share = np.mean([outside[h, row_tile == t].any() for h in range(4) for t in range(row_tile.max() + 1)])
     assert share == 1 if qscale == 40.0 else 0 < share < 1, share                      # workgroups outside dQ's range
     lse_span = ref["LSE"].max() - ref["LSE"].min()
     assert lse_span > 60 * (qscale / 12.0)       # the case really leaves the comfortable range
-    assert not any(np.isnan(got[n]).any() for n in got)
     assert rel_l2(got["O"], ref["O"]) <= FWD_REL
     # |LSE| is in the hundreds here: fp32 resolution of the stored value dominates the bf16-sum term
     assert max_abs(got["LSE"], ref["LSE"]) <= LSE_ABS + 2e-6 * np.abs(ref["LSE"]).max()
@@ -243,17 +250,18 @@ def _heads_run(tm, L, K, q, k, v, d_o):
 @pytest.mark.parametrize("D", [64, 128])
 def test_a_head_does_not_depend_on_the_heads_beside_it(D):
     """Heads of ordinary and of very large logits in turn.  At D = 64 two heads of a group share a forward workgroup where
-    lists are long, none where they are short: each head alone, and the crop to short lists, give the same bits."""
-    L, K, Hq, Hkv, Lc = 2000, 4, 4, 2, 896
+    heads are many and lists long, none where they are not: heads alone, and the crop to short lists, give the same bits."""
+    L, K, Hq, Hkv, Lc = 2000, 4, 36, 18, 896
     print(f"case neighbouring heads D={D}", flush=True)
     tm = pe.peagle_build_tilemap(L, K, None, device=0)
-    assert mean_list(tm) > 11 and mean_list(pe.peagle_build_tilemap(Lc, K, None, device=-1)) < 10
+    assert fwd_form(tm, Hq, Hkv) == "two heads, three per CU" and fwd_form(tm, 1, 1) == "one head"
+    assert fwd_form(pe.peagle_build_tilemap(Lc, K, None, device=-1), Hq, Hkv) == "one head"
     g = torch.Generator(device="cuda").manual_seed(340)
     q, k, v, d_o = (torch.randn(L * K, H, D, generator=g, device="cuda") for H in (Hq, Hkv, Hkv, Hq))
     q[:, 1::2] *= 40.0
     q, k, v, d_o = (t.to(torch.bfloat16) for t in (q, k, v, d_o))
     whole = _heads_run(tm, L, K, q, k, v, d_o)
-    for h in range(Hq):
+    for h in (0, 1, 2, 17, Hq - 2, Hq - 1):
         b = slice(h // 2, h // 2 + 1)
         alone = _heads_run(tm, L, K, q[:, h:h + 1].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(),
                            d_o[:, h:h + 1].contiguous())
@@ -272,9 +280,8 @@ def test_two_head_forward_workgroups_give_the_bits_of_one_head_ones(Hq, Hkv):
     L, K, D = 3000, 8, 64
     print(f"case forward forms Hq={Hq}", flush=True)
     tm = pe.peagle_build_tilemap(L, K, None, device=0)
-    wgs = tm.info()["n_row_tiles"] * Hq // 2
-    assert mean_list(tm) > 25 and (512 < wgs < 1024) == (Hq == 8) and (wgs >= 1024) == (Hq == 16)
-    assert tm.info()["n_row_tiles"] * (Hq // Hkv) // 2 <= 512
+    assert fwd_form(tm, Hq, Hkv) == ("two heads, two per CU" if Hq == 8 else "two heads, three per CU")
+    assert fwd_form(tm, Hq // Hkv, 1) == "one head"
     g = torch.Generator(device="cuda").manual_seed(341)
     q, k, v, d_o = (torch.randn(L * K, H, D, generator=g, device="cuda") for H in (Hq, Hkv, Hkv, Hq))
     q[:, 1::2] *= 40.0

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2602_01469_amd as pe
-from gpu_harness import Run, SampledRun, attach_rope, bf16_to_f64, max_abs, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
+from gpu_harness import Run, SampledRun, attach_rope, bf16_to_f64, fwd_form, max_abs, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
 from oracle import peagle_oracle as orc
 from peagle_inputs import CONFIGS, bf16_bits_to_f64, cod_depth_counts, f32_to_bf16_bits, make_inputs
 from test_gpu_parity import (FWD_REL, GRAD_REL, LSE_ABS, PART_REL, _check_against_oracle, _check_o_abs)
@@ -374,34 +374,51 @@ def test_shared_chain_vectors_with_lists_of_every_length():
                                                             [0, 640, 1800], True)
 
 
+def _shared_run(tm, L, K, q, d_o, k, v, ks, vs):
+    """A first-layer step over the heads given, tensors on the device."""
+    D = q.shape[2]
+    table = torch.empty((pe.peagle_rope_positions(tm, L), 2, D // 2), dtype=torch.float32, device="cuda")
+    pe.peagle_rope_table(BASE, D, table.shape[0], table)
+    shape = pe.Shape(L, K, q.shape[1], k.shape[1], D)
+    o, dq = (torch.full_like(q, float("nan")) for _ in range(2))
+    lse = torch.full((q.shape[1], q.shape[0]), float("nan"), device="cuda")
+    dk, dv = (torch.full(k.shape, float("nan"), device="cuda") for _ in range(2))
+    dks, dvs = (torch.full(ks.shape, float("nan"), device="cuda") for _ in range(2))
+    ws = torch.empty(pe.peagle_rope_shared_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
+    pe.peagle_attn_step_rope_shared(tm, shape, q, k, ks, v, vs, d_o, table, o, lse, dq, dk, dv, dks, dvs, ws)
+    torch.cuda.synchronize()
+    return {"o": o, "lse": lse.t(), "dq": dq, "dk": dk, "dv": dv, "dks": dks[None], "dvs": dvs[None]}
+
+
+def _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, seed, groups):
+    """All heads at once against the given KV heads' groups one at a time: the same bits."""
+    T = tm.tokens(L)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rnd = lambda *sh: torch.randn(*sh, generator=g, device="cuda").to(torch.bfloat16)
+    q, d_o, k, v, ks, vs = rnd(T, Hq, D), rnd(T, Hq, D), rnd(L, Hkv, D), rnd(L, Hkv, D), rnd(Hkv, D), rnd(Hkv, D)
+    whole = _shared_run(tm, L, K, q, d_o, k, v, ks, vs)
+    for h in groups:
+        a, b = slice(h * (Hq // Hkv), (h + 1) * (Hq // Hkv)), slice(h, h + 1)
+        part = _shared_run(tm, L, K, *(t[:, a].contiguous() for t in (q, d_o)), *(t[:, b].contiguous() for t in (k, v)), ks[b], vs[b])
+        for n, t in part.items():
+            assert torch.isfinite(t).all(), n
+            assert torch.equal(whole[n][:, a if n in ("o", "lse", "dq") else b], t), n
+
+
 def test_shared_chain_vectors_give_the_same_bits_from_both_dq_kernels():
     """Forty query heads at once (the plain dQ kernel) against one group at a time (the pipelined one), first-layer form."""
     L, K, Hq, Hkv, D = 1500, 4, 40, 20, 64
     print("case rope shared dq kernels", flush=True)
     tm = pe.peagle_build_tilemap(L, K, [0, 640, 1500], device=0)
     assert runs_plain_dq(tm, Hq) and not runs_plain_dq(tm, Hq // Hkv)
-    T = tm.tokens(L)
-    g = torch.Generator(device="cuda").manual_seed(3090)
-    rnd = lambda *sh: torch.randn(*sh, generator=g, device="cuda").to(torch.bfloat16)
-    q, d_o, k, v, ks, vs = rnd(T, Hq, D), rnd(T, Hq, D), rnd(L, Hkv, D), rnd(L, Hkv, D), rnd(Hkv, D), rnd(Hkv, D)
-    table = torch.empty((pe.peagle_rope_positions(tm, L), 2, D // 2), dtype=torch.float32, device="cuda")
-    pe.peagle_rope_table(BASE, D, table.shape[0], table)
+    _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, 3090, range(0, Hkv, 6))
 
-    def run(q, d_o, k, v, ks, vs):
-        shape = pe.Shape(L, K, q.shape[1], k.shape[1], D)
-        o, dq = (torch.full_like(q, float("nan")) for _ in range(2))
-        lse = torch.full((q.shape[1], T), float("nan"), device="cuda")
-        dk, dv = (torch.full(k.shape, float("nan"), device="cuda") for _ in range(2))
-        dks, dvs = (torch.full(ks.shape, float("nan"), device="cuda") for _ in range(2))
-        ws = torch.empty(pe.peagle_rope_shared_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
-        pe.peagle_attn_step_rope_shared(tm, shape, q, k, ks, v, vs, d_o, table, o, lse, dq, dk, dv, dks, dvs, ws)
-        torch.cuda.synchronize()
-        return {"o": o, "dq": dq, "dk": dk, "dv": dv}
 
-    whole = run(q, d_o, k, v, ks, vs)
-    for h in range(0, Hkv, 6):
-        a, b = slice(h * (Hq // Hkv), (h + 1) * (Hq // Hkv)), slice(h, h + 1)
-        part = run(*(t[:, a].contiguous() for t in (q, d_o)), *(t[:, b].contiguous() for t in (k, v)), ks[b], vs[b])
-        for n, t in part.items():
-            assert torch.isfinite(t).all(), n
-            assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
+@pytest.mark.parametrize("Hq,form", [(8, "two heads, two per CU"), (16, "two heads, three per CU")])
+def test_shared_chain_vectors_give_the_same_bits_from_every_forward(Hq, form):
+    """Two-head workgroups of the forward that reads the shared value vector against one-head ones (each group alone)."""
+    L, K, Hkv, D = 3000, 8, 4, 64
+    print(f"case rope shared forward forms Hq={Hq}", flush=True)
+    tm = pe.peagle_build_tilemap(L, K, None, device=0)
+    assert fwd_form(tm, Hq, Hkv) == form and fwd_form(tm, Hq // Hkv, 1) == "one head"
+    _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, 3100, range(Hkv))
