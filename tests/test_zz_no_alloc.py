@@ -42,7 +42,7 @@ CALLS = [
     # ctx_lens, K, Hq, Hkv, D, seed: a batch with many splits first, then a smaller one that leaves most of the
     # first call's records in the array untouched
     ((4096, 1500, 333, 2048), 7, 64, 8, 64, 2000),
-    ((300, 70), 3, 16, 2, 64, 2010),
+    ((1000, 70), 3, 16, 2, 64, 2010),
 ]
 
 
@@ -51,6 +51,7 @@ def test_static_scratch_entry_point_matches_the_workspace_one_on_two_calls_in_a_
         print(f"case decode static: ctx={ctx_lens} K={K} Hq={Hq} Hkv={Hkv} D={D} seed={seed}", flush=True)
         inp = make_decode_inputs(ctx_lens, K, Hq, Hkv, D, seed)
         r = DecodeRun(inp, K, Hq, Hkv, D)
+        assert pe.peagle_draft_decode_splits(r.shape) > 1      # (a single piece leaves no records)
         o_ws, lse_ws, st_ws = r.run()
         o_st, lse_st, st_st = _static_call(r)
         assert (st_st == 0).all() and np.array_equal(st_st, st_ws)
