@@ -8,7 +8,7 @@ import torch
 import paper_2602_01469_amd as pe
 from gpu_harness import bf16_to_f64, max_abs, rel_l2, to_dev_bf16
 from oracle import peagle_oracle as orc
-from peagle_inputs import bf16_bits_to_f64, make_decode_inputs
+from peagle_inputs import bf16_bits_to_f64, f32_to_bf16_bits, make_decode_inputs
 from test_gpu_parity import FWD_REL, LSE_ABS, _check_o_abs
 
 pytestmark = pytest.mark.gpu
@@ -97,9 +97,51 @@ def test_draft_decode_matches_oracle(name, ctx_lens, K, Hq, Hkv, D, seed):
         assert _form(r.shape) == (8, True, True)
 
 
+def _with_probabilities_in_bf16(q, k, v, scale, pieces):
+    """Attention of one query row in 64 bits but for what the kernel rounds: each piece's probabilities, relative to the
+    largest score of its first 32 keys, and the output."""
+    s = (k @ q) * (scale * np.log2(np.e))
+    to_bf16 = lambda x: bf16_bits_to_f64(f32_to_bf16_bits(x.astype(np.float32)))
+    m = [s[p[:32]].max() for p in pieces]
+    ps = [to_bf16(np.exp2(s[p] - r)) for p, r in zip(pieces, m)]
+    w = [2.0 ** (r - max(m)) for r in m]
+    o = sum(x * (p @ v[i]) for x, p, i in zip(w, ps, pieces)) / sum(x * p.sum() for x, p in zip(w, ps))
+    return to_bf16(o)
+
+
+@pytest.mark.parametrize("D,ctx", [(64, 709), (128, 500)])
+def test_draft_decode_in_one_piece_is_no_less_exact_than_in_pieces_of_four_pages(D, ctx):
+    """A key whose score is the reference maximum has the probability 1, without rounding, and in rows of few heavy keys that
+    counts: every four pages used to start two references (two wave groups that take the pages in turn).  One piece for all
+    pages must not be further from 64 bits than that."""
+    C, K, Hkv = 4, 5, 4
+    Hq = 8 * Hkv
+    print(f"case decode exactness D={D} ctx={ctx}", flush=True)
+    inp = make_decode_inputs((ctx,) * C, K, Hq, Hkv, D, 1500 + D)
+    r = DecodeRun(inp, K, Hq, Hkv, D)
+    assert pe.peagle_draft_decode_splits(r.shape) == 1
+    o, _, _ = r.run()
+    f = bf16_bits_to_f64
+    pages = [np.arange(a, min(a + 64, ctx)) for a in range(0, ctx, 64)]
+    err = {"one piece": 0.0, "four pages": 0.0}
+    for c in range(C):
+        ref, _ = _oracle(inp, c, r.shape.scale)
+        k, v = (np.concatenate([f(inp[n + "_ctx"][c]), f(inp[n + "_new"][c])]) for n in ("k", "v"))
+        for d in range(K):
+            new = np.arange(ctx, ctx + d + 1)
+            pieces = [np.concatenate(pages[a + g:a + 4:2] + ([new] if a + g == 0 else []))
+                      for a in range(0, len(pages), 4) for g in (0, 1) if a + g < len(pages)]
+            for h in range(Hq):
+                kv = h // (Hq // Hkv)
+                old = _with_probabilities_in_bf16(f(inp["q_new"][c])[d, h], k[:, kv], v[:, kv], r.shape.scale, pieces)
+                err["four pages"] += ((old - ref[d, h]) ** 2).sum()
+        err["one piece"] += ((o[c] - ref) ** 2).sum()
+    print(err, flush=True)
+    assert err["one piece"] <= err["four pages"]
+
+
 def test_draft_decode_large_logits():
     """Queries twelve times larger: near one-hot rows, reference max far from zero."""
-    from peagle_inputs import f32_to_bf16_bits
     print("case decode large logits", flush=True)
     inp = make_decode_inputs((700, 90), 5, 16, 2, 64, 1100)
     inp["q_new"] = f32_to_bf16_bits((bf16_bits_to_f64(inp["q_new"]) * 12.0).astype(np.float32))
