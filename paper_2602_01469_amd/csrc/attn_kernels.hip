@@ -24,10 +24,10 @@ constexpr float kLn2 = 0.6931471805599453f;
 // How far the running reference max may lag, log2 units (moving it costs a pass over the accumulators).  A drafting step keeps
 // it closer: the key that is the reference has a probability of exactly 1, unrounded, and the fewer pieces a context is cut
 // into, the fewer references it starts.  Error against 64 bits, rel-L2, mean of 31 batches (and the worst of them against the
-// cut for a thousand workgroups with a lag of 8, 2.255e-3): lag 8 2.265e-3 (+2.9 %), 2 2.223e-3 (+1.4 %), 1 2.178e-3 (-0.7 %),
-// 0 2.114e-3 (-2.9 %).  us at a lag of 8 / 1 / 0: 4 requests of 2,048 - 4,096 tokens 12.5 / 12.8 / 12.9, 64 of 100 - 1,000 19.3 /
-// 20.1 / 20.3, 64 of 512 - 8,192 119.8 / 120.5 / 120.5, D = 128 35 of 2,137 - 3,838 46.9 / 48.2 / 49.9.
-constexpr int kLag = 8, kDraftLag = 1;
+// cut for a thousand workgroups with a lag of 8, 2.255e-3): lag 8 2.265e-3 (+2.9 %), 2 2.223e-3 (+1.4 %, batches of one piece
+// only), 1 2.178e-3 (-0.7 %).  us at a lag of 8 / 2 / 1: 4 requests of 2,048 - 4,096 tokens 12.4 / 12.7 / 13.0, 64 of 512 -
+// 8,192 119.7 / 119.8 / 120.2, D = 128 35 of 2,137 - 3,838 46.0 / 47.3 / 48.0; one piece, 64 of 100 - 1,000 18.8 / 19.7 / 19.9.
+constexpr int kLag = 8, kDraftLag = 2, kDraftLagOnePiece = 1;
 constexpr float kNegInit = -1.0e30f;
 // Bits of a 32-key mask word (already shifted right by 4g) that belong to the keys a lane holds in the
 // C layout of a transposed score block: keys 8*(i/4) + 4g + i%4, i = 0..15.
@@ -1355,7 +1355,10 @@ __device__ __forceinline__ void dkdv_rowtile_chain(const char* q_lds, const char
 //     (NextRowTile).  Whole: the rows a lane copies are a whole number of anchors apart (K divides kRowsApart, so that
 //     A * K = 128): one per-lane offset and a scalar step address every copy.  Most: an offset per copy, and the last copy
 //     of a tile holds the rows past A * K (A * K > 128 - kRowsApart).
-//   kRowsFar: any other dense map; tokens are computed when a copy is issued.
+//   kRowsFar: any other dense map - larger tensors, and the K whose tiles lack more rows than their last copies hold (D = 128:
+//     22, 26 to 28, 33 to 37, 43 to 56, 65 to 112; D = 64: 43 to 48, 65 to 96); tokens are computed when a copy is issued, and
+//     none rides.
+//     (Step of 4 heads, D = 128, in the loops of before copies rode / now: K = 33 957 / 920 us, K = 20, Most, 832 / 710.)
 //   kRowsListed, kRowsListedFar: the map names rows by explicit token lists (sampled / packed maps); their tokens are
 //     fetched an iteration before the copy that uses them, and the copies ride too (NextListedRowTile).
 // (A near loop that carried every row's token and anchor as the far one does reloaded spilled registers behind its own
@@ -1917,6 +1920,7 @@ template <int D, int kGroups, int kThreads, bool ONE>
 __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr int kBlocks = kTileBytes / 1024;
+  constexpr int LAG = ONE ? kDraftLagOnePiece : kDraftLag;
   constexpr int kRing = 2 * kGroups;  // two rounds of kGroups consecutive tiles: one being read, one on its way
   __shared__ __attribute__((aligned(16))) char lds[kRing][2][kTileBytes];  // [buffer][K|V]
   __shared__ int tile_keys[kRing];  // keys present in the tile of each buffer (0 .. 64), set by the wave that copies K
@@ -1925,8 +1929,8 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
   // The last two waves of the workgroup only copy (global -> LDS; one K, one V; with three row blocks at D = 128 the last one
   // both), the others only compute: the wait for a copy is counted per wave, so the computing waves never wait on one.  One
   // workgroup barrier per round hands the buffers over.  (One wave for both takes most of a round to issue its copies, 16 or
-  // 32 a tile.  us, one / two: 4 requests of 2,048 - 4,096 tokens 14.1 / 13.1, 32 of 1,000 - 4,096 37.0 / 35.6, 64 of 512 - 8,192
-  // 120.8 / 119.6; D = 128 16.3 / 15.2, 41.5 / 40.6, 133.2 / 130.7.  Deeper rings, three rounds of one tile, took LDS from the
+  // 32 a tile.  us, one / two: 4 requests of 2,048 - 4,096 tokens 14.0 / 13.1, 32 of 1,000 - 4,096 36.9 / 35.9, 64 of 512 - 8,192
+  // 121.4 / 119.4; D = 128 16.3 / 15.4, 42.5 / 41.9, 133.8 / 130.9.  Deeper rings, three rounds of one tile, took LDS from the
   // workgroups that share a CU and were slower: 255 against 206 us on 64 equal contexts of 8,192 tokens.)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const int n_compute = kGroups * (p.rows_pad / 32);
@@ -2083,13 +2087,13 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
     const int valid = __builtin_amdgcn_readfirstlane(tile_keys[buf]);
     if (!is_new && valid == kKeysPerTile) {
       const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
-      fwd_tile<D, 1, false, true, kDraftLag>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
+      fwd_tile<D, 1, false, true, LAG>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
     } else {
       // keys [0, n) of the tile are visible: n = the page's valid tokens, or depth + 1 of the new keys
       const int n = is_new ? depth + 1 : valid;
       const uint64_t bits = n >= 64 ? ~0ull : ((1ull << n) - 1);
       const uint32_t mw[2] = {(uint32_t)bits >> (4 * g), (uint32_t)(bits >> 32) >> (4 * g)};
-      fwd_tile<D, 1, true, true, kDraftLag>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
+      fwd_tile<D, 1, true, true, LAG>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
     }
   }
 
@@ -2486,19 +2490,20 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
 // D = 128 at most one, because there two wave groups fill a CU's LDS and a second workgroup costs them (see the launch).
 // Otherwise at most two workgroups per CU, all running at once, while pieces stay within 32 pages (D = 64) or 20 (D = 128,
 // one wave group).  All others as laid out: requests differ in length, and the longest one's pieces would be waited for.
-// us per call, pieces a request (workgroups) as laid out / as taken: D = 64, 4 requests of 2,048 - 4,096 tokens 14.7 (16; 512) /
-// 12.8 (8; 256), 16 of 1,000 16.2 (4; 512) / 13.4 (2; 256), 8 of 300 - 3,000 17.5 (12; 768) / 15.2 (4; 256), 4 of 8,000 - 20,000
-// 29.1 (32; 1,024) / 26.8 (16; 512; 8 pieces 29.9), 64 of 100 - 1,000 27.5 (2; 1,024) / 19.1 (1; 512), 12 of 3,000 - 6,000 30.8
-// (11; 1,056) / 27.0 (5; 480; 6 pieces, 576 workgroups, 28.2); D = 128, 16 of 800 - 8,192 42.8 (16; 1,024) / 37.8 (8; 512), 3 of
-// 13,701 - 18,407 26.6 (32; 384) / 25.4 (21; 252; 22 pieces, 264 workgroups, 28.4), 35 of 2,137 - 3,838 57.6 (8; 1,120) / 46.8 (3;
-// 420; 4 pieces, 560 workgroups, 57.5).  As laid out: D = 64, 16 of 2,000 - 20,000 78 (8; 1,024; 4 pieces 88), 55 of 1,691 - 2,469
-// 56.3 (3; 1,320; 2 pieces, 880 workgroups, 59.0); D = 128, 27 of 3,914 - 6,578 83 (10; 1,080; 4 pieces of 26 pages 62), but 46
-// of 511 and one of 3,558 33 (6; 1,104; 2 pieces of 28 pages 46).  260 batches drawn over numbers and lengths, against all
-// pieces as laid out (and one copying wave): evenly spread lengths, D = 64 / 128, -10 / -9 % in the mean, +7 / +3 % at worst;
-// one to three long requests among short ones -12 / -7 %, +3 / +10 %.
-// One piece leaves its rows' results itself, without the launch that merges pieces (4 of 64 - 256 tokens 9.4 / 6.6).  Up to
-// kOnePiece pages that is worth a longer chain in fewer workgroups, pieces 2 or 3 / 1: D = 64, one request of 512 tokens
-// 9.2 / 8.2, 4 of 768 10.4 / 9.9, 2 of 1,000 (16 pages) 9.7 / 11.9; D = 128, 4 of 512 11.7 / 10.8, 4 of 768 12.3 / 13.0.
+// us per call (thirty in one graph), pieces a request (workgroups) as laid out / as taken: D = 64, 4 requests of 2,048 -
+// 4,096 tokens 14.3 (16; 512) / 12.7 (8; 256), 16 of 1,000 15.9 (4; 512) / 13.6 (2; 256), 8 of 300 - 3,000 16.7 (12; 768) /
+// 14.8 (4; 256), 4 of 8,000 - 20,000 28.6 (32; 1,024) / 26.3 (16; 512; 8 pieces 30.5), 64 of 100 - 1,000 27.2 (2; 1,024) /
+// 19.8 (1; 512), 12 of 3,000 - 6,000 30.5 (11; 1,056) / 26.7 (5; 480; 6 pieces, 576 workgroups, 28.4); D = 128, 16 of 800 -
+// 8,192 43.5 (16; 1,024) / 38.3 (8; 512), 3 of 13,701 - 18,407 26.7 (32; 384) / 25.4 (21; 252; 22 pieces, 264 workgroups,
+// 28.5), 35 of 2,137 - 3,838 58.2 (8; 1,120) / 48.0 (3; 420; 4 pieces, 560 workgroups, 57.5). As laid out: D = 64, 16 of
+// 2,000 - 20,000 78 (8; 1,024; 4 pieces 88), 55 of 1,691 - 2,469 56 (3; 1,320; 2 pieces, 880 workgroups, 59); D = 128, 27 of
+// 3,914 - 6,578 81 (10; 1,080; 4 pieces of 26 pages 62), but 46 of 511 and one of 3,558 34 (6; 1,104; 2 pieces of 28 pages
+// 49). 260 batches drawn over numbers and lengths, against all pieces as laid out (and one copying wave): evenly spread
+// lengths, D = 64 / 128, -9 / -8 % in the mean, +5 / +2 % at worst; one to three long requests among short ones -11 / -4 %,
+// +3 / +16 %.
+// One piece leaves its rows' results itself, without the launch that merges pieces (4 of 64 - 256 tokens 9.4 / 6.6). Up to
+// kOnePiece pages that is worth a longer chain in fewer workgroups, pieces 2 or 3 / 1: D = 64, one request of 512 tokens 9.1
+// / 8.3, 4 of 768 10.4 / 10.3, 2 of 1,000 (16 pages) 9.8 / 12.4; D = 128, 4 of 512 11.8 / 11.2, 4 of 768 12.5 / 13.7.
 constexpr int kOnePiece64 = 12, kOnePiece128 = 8, kLongestPiece64 = 32, kLongestPiece128 = 20;  // pages
 int draft_pieces(int64_t wgs_per_piece, int max_pages, int laid_out, int D) {
   auto within = [&](int64_t n) { return (int)(n < 1 ? 1 : n < laid_out ? n : laid_out); };
@@ -2517,24 +2522,25 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
   const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;
   const bool long_pieces = (p.max_pages + p.n_splits - 1) / p.n_splits > kLongPiece;  // pages of the longest request's pieces
-  // Two groups of waves per workgroup cost twice the LDS.  At D = 64 two such workgroups still share a CU (of one group, four
+  // Two groups of waves per workgroup cost twice the LDS. At D = 64 two such workgroups still share a CU (of one group, four
   // do), which is enough while there are no more, or where pieces are long and few; at D = 128 one does (of one group, two),
-  // which pays while there is at most one per CU anyway.  us per call, one / two groups (pages of the longest pieces;
-  // workgroups): D = 64, 4 requests of 2,048 - 4,096 tokens (8; 256) 14.7 / 12.9, 64 of 100 - 1,000 (16; 512) 24.3 / 19.4, 64 of 512 -
-  // 8,192 (64; 1,024) 133 / 120, 16 of 2,000 - 20,000 (40; 1,024) 86 / 80, 55 of 1,691 - 2,469 (13; 1,320) 56.8 / 57.2, 65 of 300 (5;
-  // 520) 13.6 / 16.7, 128 of 300 (5; 1,024) 20.8 / 24.7; D = 128, 2 of 10,800 - 20,000 (10; 256) 23.8 / 21.6, 16 of 800 - 4,096 (16;
-  // 256) 31.0 / 25.3, 70 of 500 (8; 280) 22.0 / 26.7, 64 of 3,000 - 4,000 (16; 1,024) 110 / 117, 64 of 512 - 8,192 (32; 1,024) 130 / 142,
-  // but 35 of 2,137 - 3,838 (20; 420) 49.0 / 47.4.  More than 64 query rows make eight waves or ten, too many for two per CU.
+  // which pays while there is at most one per CU anyway. us per call, one / two groups (pages of the longest pieces;
+  // workgroups): D = 64, 4 requests of 2,048 - 4,096 tokens (8; 256) 15.1 / 13.1, 64 of 100 - 1,000 (16; 512) 25.5 / 19.8, 64
+  // of 512 - 8,192 (64; 1,024) 133 / 119, 16 of 2,000 - 20,000 (40; 1,024) 85 / 77, 55 of 1,691 - 2,469 (13; 1,320) 56.6 /
+  // 56.6, 65 of 300 (5; 520) 14.3 / 16.8, 128 of 300 (5; 1,024) 20.9 / 25.1; D = 128, 2 of 10,800 - 20,000 (10; 256) 25.0 /
+  // 21.8, 16 of 800 - 4,096 (16; 256) 33.0 / 25.7, 70 of 500 (8; 280) 23.3 / 27.0, 64 of 3,000 - 4,000 (16; 1,024) 110 / 115,
+  // 64 of 512 - 8,192 (32; 1,024) 131 / 141, but 35 of 2,137 - 3,838 (20; 420) 48.9 / 48.1. More than 64 query rows make
+  // eight waves or ten, too many for two per CU.
   const bool two = row_waves <= 2 && (D == 64 ? n_wg <= 2 * kCus || long_pieces : n_wg <= kCus);
-  // Long pieces of requests of different lengths: with more workgroups than two per CU, those of the longest requests
-  // start first.  us per call in order of the request / by length: the 64 requests of 512 to 8,192 tokens above 144 /
-  // 120, at D = 128 148 / 130, 16 of 2,000 - 20,000 86 / 80.  Ranking costs most of a page's time: with pieces of 8 pages, 35 of
-  // 2,137 - 3,838 at D = 128 took 70.8 / 74.7.  Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
+  // Long pieces of requests of different lengths: with more workgroups than two per CU, those of the longest requests start
+  // first. us per call in order of the request / by length: the 64 requests of 512 to 8,192 tokens above 141 / 119, at D =
+  // 128 149 / 131, 16 of 2,000 - 20,000 84 / 77. Ranking costs most of a page's time: with pieces of 8 pages, 35 of 2,137 -
+  // 3,838 at D = 128 took 70.8 / 74.7. Up to 64 requests, which one wave can rank; with more, a CU sees many anyway.
   p.by_length = p.C > 1 && p.C <= 64 && n_wg > 2 * kCus && long_pieces;
-  // Copying waves: two, but with three row blocks at D = 128 one, because two workgroups of five waves share a CU's four SIMDs
-  // badly (us, one / two copying waves, 96 query rows: 64 requests of 512 - 8,192 tokens 144 / 151, 32 of 1,000 - 4,096 46 / 59, 128
-  // of 300 23.0 / 25.4; but D = 64 64 of 512 - 8,192 143 / 131, and D = 128 with one, two and four row blocks 133 / 131, 41.5 /
-  // 40.6 and 64.6 / 62.5 on such batches).
+  // Copying waves: two, but with three row blocks at D = 128 one, because two workgroups of five waves share a CU's four
+  // SIMDs badly (us, one / two copying waves, 96 query rows: 64 requests of 512 - 8,192 tokens 142 / 160, 32 of 1,000 - 4,096
+  // 47 / 63, 128 of 300 23.5 / 26.6; but D = 64 64 of 512 - 8,192 144 / 134, and D = 128 with one, two and four row blocks
+  // 123 / 119, 134 / 131 and 168 / 164 on that batch).
   const int copying = D == 128 && row_waves == 3 ? 1 : 2;
   const dim3 block((unsigned)(((two ? 2 : 1) * row_waves + copying) * 64));
   // (The bound of 576 threads, of which 384 are launched, has the compiler schedule for four waves per SIMD: 120
