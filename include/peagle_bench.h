@@ -28,6 +28,7 @@ typedef struct peagle_profile {
 
 /*
  * Measurement aid: the same work as peagle_attn_step_partitioned (Sec. 3.2 pass per segment),
+ * kernel by kernel (a step may run dQ and dK/dV as one grid; here they are launched apart, with the same results),
  * with a HIP event pair recorded on `stream` around every kernel launch.  Waits for the work
  * to finish, then fills `profile` (host).  Creates and destroys events; not for hot loops.
  */

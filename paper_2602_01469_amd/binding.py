@@ -373,7 +373,8 @@ def peagle_attn_step_partitioned(tm: TileMap, shape: Shape, seg_begin: int, seg_
 
 def peagle_attn_step_profiled(tm: TileMap, shape: Shape, seg_begin: int, seg_end: int, q, k, v, d_o, o, lse, dq,
                               dk_acc, dv_acc, workspace, stream=None) -> dict:
-    """Same work as peagle_attn_step_partitioned; returns {kind: (ms, launches)} from HIP events."""
+    """Same work as peagle_attn_step_partitioned, kernel by kernel (dQ and dK/dV never as one grid); returns
+    {kind: (ms, launches)} from HIP events."""
     import torch
     bf, f32 = torch.bfloat16, torch.float32
     T = tm.tokens(shape.L)

@@ -187,8 +187,10 @@ extern "C" int peagle_attn_bwd(const peagle_tilemap_t* tm, const peagle_shape_t*
   const BwdParams p = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, accumulate);
   const int acc_below = accumulate ? INT_MAX : 0;
   hipStream_t st = (hipStream_t)stream;
-  if (peagle::launch_dq(p, shape->D, st) != hipSuccess) return PEAGLE_EHIP;
-  return peagle::launch_dkdv(p, shape->D, sr.key_lo, sr.a_hi, acc_below, st) == hipSuccess ? PEAGLE_OK : PEAGLE_EHIP;
+  const bool one_grid = peagle::backward_in_one_grid(shape->D, p.mean_tiles, sr.rt_hi - sr.rt_lo, shape->Hq, false);
+  const hipError_t e = one_grid ? peagle::launch_row_terms(p, st) : peagle::launch_dq(p, shape->D, st);
+  if (e != hipSuccess) return PEAGLE_EHIP;
+  return peagle::launch_dkdv(p, shape->D, sr.key_lo, sr.a_hi, acc_below, one_grid, st) == hipSuccess ? PEAGLE_OK : PEAGLE_EHIP;
 }
 
 static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, int32_t seg_begin, int32_t seg_end,
@@ -233,11 +235,20 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
     if (n_seg++ == 0) rows = sr;
     else rows.rt_hi = sr.rt_hi;
   }
+  // (Timed kernel by kernel, dQ and dK/dV run apart.)
+  const bool one_grid = n_seg > 0 && !timer &&
+                        peagle::backward_in_one_grid(shape->D, mean_tiles(tm, shape->L), rows.rt_hi - rows.rt_lo, shape->Hq, true);
   if (n_seg > 0) {
-    const FwdParams fp = make_fwd(tm, shape, rows, q, k, v, o, lse, sf);
+    FwdParams fp = make_fwd(tm, shape, rows, q, k, v, o, lse, sf);
+    if (one_grid) {
+      const WsLayout w = ws_layout(tm, shape);
+      fp.d_o = (const __bf16*)d_o;
+      fp.delta = (float*)((char*)workspace + w.delta_off);
+      fp.nlse = (float*)((char*)workspace + w.nlse_off);
+    }
     if (peagle::launch_fwd(fp, shape->D, st, timer) != hipSuccess) return PEAGLE_EHIP;
     const BwdParams bp = make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, 0, rope_table, sf);
-    if (peagle::launch_dq(bp, shape->D, st, timer) != hipSuccess) return PEAGLE_EHIP;
+    if (!one_grid && peagle::launch_dq(bp, shape->D, st, timer) != hipSuccess) return PEAGLE_EHIP;
   }
   for (int32_t s = seg_begin; s < seg_begin + n_seg; ++s) {
     SegRange sr;
@@ -246,7 +257,7 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
     // Depth-0 keys below the segment start already hold earlier segments' sums: add to them.
     // Keys first seen by this segment (its own depth-0 range and its chains) are overwritten.
     const BwdParams bp = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, 0, rope_table, sf);
-    if (peagle::launch_dkdv(bp, shape->D, sr.key_lo, sr.a_hi, sr.a_lo, st, timer) != hipSuccess) return PEAGLE_EHIP;
+    if (peagle::launch_dkdv(bp, shape->D, sr.key_lo, sr.a_hi, sr.a_lo, one_grid, st, timer) != hipSuccess) return PEAGLE_EHIP;
   }
   if (seg_end == tm->S || tm->seg_bounds[seg_end] >= shape->L) {
     const size_t n = tokens_of(tm, shape) * shape->Hkv * shape->D;

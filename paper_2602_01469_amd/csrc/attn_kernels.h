@@ -22,6 +22,9 @@ struct FwdParams {
   int mean_tiles;      // mean length of the row tiles' lists over the whole length-L problem
   const __bf16* v_shared;  // null, or [Hkv, D]: the value row of every chain key (first-layer form; v then holds
                            // the depth-0 rows only)
+  const __bf16* d_o;       // null, or the backward's dO (a whole step): the forward then leaves the backward's per-row terms
+  float* delta;            // [Hq, T], as in BwdParams
+  float* nlse;
 };
 
 struct BwdParams {
@@ -34,8 +37,8 @@ struct BwdParams {
   __bf16* dq;
   float* dk_acc;       // [T, Hkv, D]
   float* dv_acc;
-  float* delta;        // workspace [Hq, T]: -rowsum(dO * O), written by the dQ kernel
-  float* nlse;         // workspace [Hq, T]: -lse / scale, written by the dQ kernel
+  float* delta;        // workspace [Hq, T]: -rowsum(dO * O), written by the dQ kernel or, for one grid, before it
+  float* nlse;         // workspace [Hq, T]: -lse / scale, likewise
   float* dk_part;      // workspace [Hq, L64, D]: per-query-head dK of the depth-0 keys
   float* dv_part;
   DeviceTileMap tm;
@@ -43,6 +46,7 @@ struct BwdParams {
   int rt_lo, rt_hi;
   int s_lo, s_hi, cropped;  // segment boundary indices of the row range; cropped: rt_hi cuts the last segment short
   int n_d0_items;       // filled by the launcher: depth-0 work items (key-tile pairs x query heads)
+  int n_chain_items;    // filled by the launcher: chain work items; dQ's, where it shares the grid, come behind
   int n_d0_tiles;       // filled by the launcher: depth-0 key tiles visible to the segment are [d0_tile_lo, n_d0_tiles)
   int d0_tile_lo;
   int clip_rows;        // filled by the launcher: [rt_lo, rt_hi) covers only part of the segments s_lo..s_hi
@@ -100,11 +104,17 @@ struct KernelTimer {
 };
 
 hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer* timer = nullptr);
+// Do dK/dV and dQ of a backward over n_row_tiles row tiles run as one grid?  terms_left: the forward of the same call leaves
+// the per-row terms; otherwise launch_row_terms() has to.
+bool backward_in_one_grid(int D, int mean_tiles, int n_row_tiles, int Hq, bool terms_left);
+// The per-row terms of the row range (D = 64).
+hipError_t launch_row_terms(const BwdParams& p, hipStream_t stream);
 // dQ of the row range, and the per-row terms that dK/dV consumes.
 hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer* timer = nullptr);
 // dK/dV of one segment.  a_hi: end anchor of the segment (depth-0 keys [0, a_hi) are visible); depth-0 keys with
-// anchor below acc_below are added to dk_acc/dv_acc, the others overwritten.
-hipError_t launch_dkdv(const BwdParams& p, int D, int key_lo, int a_hi, int acc_below, hipStream_t stream,
+// anchor below acc_below are added to dk_acc/dv_acc, the others overwritten.  with_dq (backward_in_one_grid()): dQ of the same
+// rows too.
+hipError_t launch_dkdv(const BwdParams& p, int D, int key_lo, int a_hi, int acc_below, bool with_dq, hipStream_t stream,
                        KernelTimer* timer = nullptr);
 // Dense bf16 MFMA issue loop on every CU: the measured matrix-core ceiling of the device, in TFLOP/s, on
 // constant small-integer operands or on changing pseudo-random ones (the chip clocks lower under the latter).

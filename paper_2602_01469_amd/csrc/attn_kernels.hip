@@ -276,20 +276,29 @@ __device__ __forceinline__ bool wave_sees_block(uint32_t mw) {
 // 8*(i/4) + 4g + i%4), times f, rounded to bf16.  The two lanes exchange halves so that each stores 16 bytes at a
 // time: half the store instructions of 8-byte pieces, which a row tile's end waits on (forward at 1,391 anchors 171 -> 165
 // us, dQ 249 -> 242; at 4,096 forward 1,112 -> 1,085, dQ 1,625 -> 1,603).
+__device__ __forceinline__ u32x4 row_piece_bf16(const f32x16& x, int q, float f) {  // features 16q + 8g + 0..7
+  u32x4 w;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const uint32_t even = pack_bf16(x[8 * q + 2 * j] * f, x[8 * q + 2 * j + 1] * f);
+    const uint32_t odd = pack_bf16(x[8 * q + 4 + 2 * j] * f, x[8 * q + 4 + 2 * j + 1] * f);
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(even, odd, false, false);
+    w[j] = r[0];
+    w[2 + j] = r[1];
+  }
+  return w;
+}
 __device__ __forceinline__ void store_row_bf16(__bf16* dst, const f32x16& x, float f, int g) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    u32x4 w;
+  for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4*>(dst + 16 * q + 8 * g) = row_piece_bf16(x, q, f);
+}
+
+// Eight more terms of a lane's half of rowsum(dO * O).  Every kernel that forms Delta adds in this order - pieces of 16
+// features up, the lane's eight of each, the halves last - so that Delta has the same bits wherever it is formed.
+__device__ __forceinline__ float add_delta8(float dl, bf16x8 dof, bf16x8 of) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t even = pack_bf16(x[8 * q + 2 * j] * f, x[8 * q + 2 * j + 1] * f);
-      const uint32_t odd = pack_bf16(x[8 * q + 4 + 2 * j] * f, x[8 * q + 4 + 2 * j + 1] * f);
-      const u32x2 r = __builtin_amdgcn_permlane32_swap(even, odd, false, false);
-      w[j] = r[0];
-      w[2 + j] = r[1];
-    }
-    *reinterpret_cast<u32x4*>(dst + 16 * q + 8 * g) = w;
-  }
+  for (int j = 0; j < 8; ++j) dl = __builtin_fmaf((float)dof[j], (float)of[j], dl);
+  return dl;
 }
 
 // Bit `pos` of w selects x, otherwise -inf.
@@ -448,12 +457,15 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
   const bool row_ok = row_token(tm, rt, r, p.L, tq_held);
 
   bf16x8 qf[NH][D / 16];
+  auto load_q = [&]() {
 #pragma unroll
-  for (int hh = 0; hh < NH; ++hh)
+    for (int hh = 0; hh < NH; ++hh)
 #pragma unroll
-    for (int st = 0; st < D / 16; ++st)
-      qf[hh][st] = as_frag(row_ok ? ld16(p.q + ((size_t)tq_held * p.Hq + h0 + hh) * D + st * 16 + g * 8)
-                                  : make_uint4(0, 0, 0, 0));
+      for (int st = 0; st < D / 16; ++st)
+        qf[hh][st] = as_frag(row_ok ? ld16(p.q + ((size_t)tq_held * p.Hq + h0 + hh) * D + st * 16 + g * 8)
+                                    : make_uint4(0, 0, 0, 0));
+  };
+  load_q();
 
   f32x16 o[NH][D / 32];
   float m[NH], lsum[NH], l_tot[NH];
@@ -522,10 +534,29 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
     const int l = LEAN ? lane_id() : lane, g = l >> 5;
     int tq = tq_held;
     if (LEAN ? row_token(tm, rt, wave * 32 + (l & 31), p.L, tq) : row_ok) {
-      __bf16* orow = p.o + ((size_t)tq * p.Hq + h0 + hh) * D;
+      const size_t off = ((size_t)tq * p.Hq + h0 + hh) * D;
+      const float lse = (m[hh] + __builtin_log2f(l_tot[hh])) * kLn2;
+      if (p.d_o) {  // the backward follows in the same call: leave its per-row terms, in the form it consumes
+        bf16x8 dof[D / 16];
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db) store_row_bf16(orow + db * 32, o[hh][db], inv, g);
-      if (g == 0) p.lse[(size_t)(h0 + hh) * p.T + tq] = (m[hh] + __builtin_log2f(l_tot[hh])) * kLn2;
+        for (int st = 0; st < D / 16; ++st) dof[st] = as_frag(ld16(p.d_o + off + st * 16 + g * 8));
+        float dl = 0.f;
+#pragma unroll
+        for (int st = 0; st < D / 16; ++st) {
+          const u32x4 w = row_piece_bf16(o[hh][st / 2], st % 2, inv);
+          *reinterpret_cast<u32x4*>(p.o + off + st * 16 + g * 8) = w;
+          dl = add_delta8(dl, dof[st], __builtin_bit_cast(bf16x8, w));
+        }
+        dl = sum_halves(dl);
+        if (g == 0) {
+          p.delta[(size_t)(h0 + hh) * p.T + tq] = -dl;
+          p.nlse[(size_t)(h0 + hh) * p.T + tq] = -(lse * kLog2e) / p.c_log2;
+        }
+      } else {
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) store_row_bf16(p.o + off + db * 32, o[hh][db], inv, g);
+      }
+      if (g == 0) p.lse[(size_t)(h0 + hh) * p.T + tq] = lse;
     }
   };
   pass(std::false_type{});
@@ -542,6 +573,7 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
   for (int hh = 0; hh < NH; ++hh)
     if (!(redo & (1 << hh))) store(hh);
   if (redo) {
+    if (LEAN) load_q();  // (not held over the stores above)
     pass(std::true_type{});
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh)
@@ -652,9 +684,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
       const uint4 z = make_uint4(0, 0, 0, 0);
       qf[hh][st] = as_frag(row_ok ? ld16(p.q + off + st * 16) : z);
       dof[hh][st] = as_frag(row_ok ? ld16(p.d_o + off + st * 16) : z);
-      const bf16x8 of = as_frag(row_ok ? ld16(p.o + off + st * 16) : z);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) dl = __builtin_fmaf((float)dof[hh][st][j], (float)of[j], dl);
+      dl = add_delta8(dl, dof[hh][st], as_frag(row_ok ? ld16(p.o + off + st * 16) : z));
     }
     dl = sum_halves(dl);
     delta[hh] = dl;
@@ -857,17 +887,19 @@ __device__ __forceinline__ void dq_pipe_body(DqPipe<D>& P, const char* k_dq, con
   }
 }
 
-template <int D, bool SV>
-__global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
+// TERMS: forms the per-row terms from O and writes them for the dK/dV kernel; otherwise they are there already.
+template <int D>
+constexpr int kDqPipeLds = 3 * 2 * kKeysPerTile * D * 2;
+template <int D, bool SV, bool TERMS>
+__device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base, int b) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr int N2 = D / 16;
-  __shared__ __attribute__((aligned(16))) char lds[3][2][kTileBytes];  // [buffer][K|V]
+  char (&lds)[3][2][kTileBytes] = *reinterpret_cast<char (*)[3][2][kTileBytes]>(lds_base);  // [buffer][K|V]
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
-  int b = blockIdx.x;
   const int kvh = b % p.Hkv;
   b /= p.Hkv;
   const int hc = b % group;
@@ -895,13 +927,11 @@ __global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
       const uint4 z = make_uint4(0, 0, 0, 0);
       qf[0][st] = as_frag(row_ok ? ld16(p.q + off + st * 16) : z);
       dof[0][st] = as_frag(row_ok ? ld16(p.d_o + off + st * 16) : z);
-      const bf16x8 of = as_frag(row_ok ? ld16(p.o + off + st * 16) : z);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) dl = __builtin_fmaf((float)dof[0][st][j], (float)of[j], dl);
+      if (TERMS) dl = add_delta8(dl, dof[0][st], as_frag(row_ok ? ld16(p.o + off + st * 16) : z));
     }
-    delta = sum_halves(dl);
+    delta = TERMS ? sum_halves(dl) : row_ok ? -p.delta[(size_t)h * p.T + tq] : 0.f;
     lse2 = row_ok ? p.lse[(size_t)h * p.T + tq] * kLog2e : 0.f;
-    if (row_ok && g == 0) {  // per-row terms in the form the dK/dV kernel consumes
+    if (TERMS && row_ok && g == 0) {  // per-row terms in the form the dK/dV kernel consumes
       p.delta[(size_t)h * p.T + tq] = -delta;
       p.nlse[(size_t)h * p.T + tq] = -lse2 / p.c_log2;
     }
@@ -1051,6 +1081,12 @@ __global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) store_row_bf16(drow + db * 32, dq[0][db], row_factor, g);
   }
+}
+
+template <int D, bool SV>
+__global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(16))) char lds[kDqPipeLds<D>];
+  dq_pipe_item<D, SV, true>(p, lds, blockIdx.x);
 }
 
 // =====================================================================================
@@ -1366,24 +1402,25 @@ __device__ __forceinline__ void dkdv_rowtile_chain(const char* q_lds, const char
 enum { kRowsWhole = 0, kRowsFar = 1, kRowsListed = 2, kRowsMost = 3, kRowsListedFar = 4 };
 template <int D>
 constexpr int kRowsApart = 4 * (512 / D);  // rows of the tile between two copies of a lane
+template <int D>
+constexpr int kDkdvLds = 2 * (2 * kRowsPerTile * D * 2 + 2 * kRowsPerTile * 4);  // two buffers of Q | dO | lse2 | delta
 template <int D, int ROWS, bool SV>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p) {
+__device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const int item) {
   constexpr bool LISTED = ROWS == kRowsListed || ROWS == kRowsListedFar;
   // Blocks that no row sees are left out at D = 64.  At D = 128, with one wave per SIMD, nothing covers the unpipelined
   // chain routine, and the second loop costs the first: dK/dV at 1,391 anchors 378 us with both, 338 with one pipelined
   // loop for all tiles, at 3,000 anchors 1,410 and 1,320.
   constexpr bool kSkips = D == 64;
   constexpr int kTileBytes = kRowsPerTile * D * 2;
-  constexpr int kBufBytes = 2 * kTileBytes + 2 * kRowsPerTile * 4;  // Q | dO | lse2 | delta
-  constexpr int kLdsBytes = 2 * kBufBytes;
-  __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
+  constexpr int kBufBytes = 2 * kTileBytes + 2 * kRowsPerTile * 4;
+  constexpr int kLdsBytes = kDkdvLds<D>;
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const int kblk = wave;  // 32-key block of the pair owned by this wave
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
 
-  int b = blockIdx.x;
+  int b = item;
   int kt0, n_tiles, kvh, h_lo, h_hi;  // first key tile of the pair, tiles present (1 or 2)
   const bool chain = b >= p.n_d0_items;
   if (!chain) {
@@ -1727,7 +1764,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
       static_assert(4 * D * 33 * 4 <= kLdsBytes, "the four waves' transposition buffers must fit");
       const bool have = tile_present && key_ok;
       const float* rope = p.rope_table && have ? p.rope_table + (size_t)token_position(tm, key_tok, p.L) * D : nullptr;
-      const int b_chain = (int)blockIdx.x - p.n_d0_items;
+      const int b_chain = item - p.n_d0_items;
       const int n_cpair = (tm.n_csub + 1) / 2;
       const size_t prow = ((size_t)(p.rt_lo + b_chain / p.Hkv / n_cpair) * n_cpair + (b_chain / p.Hkv) % n_cpair) * 4 + wave;
   #pragma unroll
@@ -1847,6 +1884,49 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   } else {
     run(std::false_type{});
     store(std::false_type{});
+  }
+}
+
+template <int D, int ROWS, bool SV>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<D>];
+  dkdv_item<D, ROWS, SV>(p, lds, blockIdx.x);
+}
+
+// dK/dV and dQ as one grid (D = 64), where both are short of workgroups: neither reads what the other writes once the
+// per-row terms are there (the forward of the same call leaves them, or row_terms_kernel), so dQ's workgroups fill the
+// slots that unequal dK/dV lists leave, and a launch of a few workgroups, a chain of memory round trips, is not waited for
+// before the next.  dQ's come last, heaviest row tiles first: dealt between the chain tiles of the same rows, whose Q and dO
+// they share, they were slower (step of 64 heads, L = 411 127 against 119 us, L = 4,096 4,775 against 4,730).
+// (p_dq: the same parameters once more.  Read from one block, the two halves' scalar registers are loaded together and held
+// together, more than there are.)
+template <int ROWS, bool SV>
+__global__ __launch_bounds__(256, 2) void bwd_kernel(BwdParams p, BwdParams p_dq) {
+  __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<64> > kDqPipeLds<64> ? kDkdvLds<64> : kDqPipeLds<64>];
+  const int n_dkdv = p.n_d0_items + p.n_chain_items;
+  const int b = blockIdx.x;
+  if (b < n_dkdv) dkdv_item<64, ROWS, SV>(p, lds, b);
+  else dq_pipe_item<64, SV, false>(p_dq, lds, b - n_dkdv);
+}
+
+// The per-row terms of a backward that no forward left them for (D = 64): two lanes per row and head, each with the pieces
+// of 8 features that the lanes of dq_pipe_kernel hold, added in the same order.  Bound by reading O and dO once.
+__global__ __launch_bounds__(256) void row_terms_kernel(BwdParams p) {
+  constexpr int D = 64;
+  const int rt = p.rt_lo + (int)blockIdx.x / p.Hq;
+  const int u = (int)blockIdx.x % p.Hq * kRowsPerTile + (int)(threadIdx.x >> 1), g = threadIdx.x & 1;
+  const int r = u / p.Hq, h = u - r * p.Hq;  // neighbouring lanes: neighbouring heads of a row
+  int tq;
+  if (!row_token(p.tm, rt, r, p.L, tq)) return;  // (both lanes of the row)
+  const size_t off = ((size_t)tq * p.Hq + h) * D + g * 8;
+  float dl = 0.f;
+#pragma unroll
+  for (int st = 0; st < D / 16; ++st) dl = add_delta8(dl, as_frag(ld16(p.d_o + off + st * 16)), as_frag(ld16(p.o + off + st * 16)));
+  dl += __shfl_xor(dl, 1);
+  if (g == 0) {
+    const size_t at = (size_t)h * p.T + tq;
+    p.delta[at] = -dl;
+    p.nlse[at] = -(p.lse[at] * kLog2e) / p.c_log2;
   }
 }
 
@@ -2384,6 +2464,7 @@ hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer
   return span.finish();
 }
 
+constexpr int kPlainMeanTiles = 24, kPlainWorkgroups = 2 * 3 * kCus;
 hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer* timer) {
   const int n_rt = p.rt_hi - p.rt_lo;
   if (n_rt <= 0) return hipSuccess;
@@ -2400,7 +2481,6 @@ hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer*
   // 83; few, L = 1,000, 4 heads (11; 252) 24 / 29, 16 heads (11; 1,008) 49 / 54, L = 2,048, K = 4, 16 heads (18; 1,024)
   // 73 / 75, L = 3,000, 8 heads (26; 1,504) 131 / 132; long lists, L = 4,096, 16 heads (35; 4,096) 422 / 427, 64 heads
   // (35; 16,384) 1,666 / 1,646, L = 8,000, 4 heads (65; 2,000) 376 / 392, sampled 8,192 (67) 3,195 / 3,277.
-  constexpr int kPlainMeanTiles = 24, kPlainWorkgroups = 2 * 3 * kCus;
   const int n_wg = n_rt * p.Hq;  // one query head per workgroup
   const bool plain = p.mean_tiles <= kPlainMeanTiles && n_wg >= kPlainWorkgroups;
   TimedSpan span(timer, kKindDq, stream);
@@ -2411,7 +2491,32 @@ hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer*
   return span.finish();
 }
 
-hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int acc_below, hipStream_t stream,
+// dK/dV and dQ as one grid, or dQ (which then also forms the per-row terms) before dK/dV?  At D = 128 a dK/dV workgroup has
+// a CU to itself, and dQ's would, too.  At D = 64 one grid wherever dQ would run its pipelined kernel anyway, and with
+// short lists (where the plain one runs three workgroups per CU, and the one grid two) as long as workgroups are few enough
+// that unequal lists and the launches' ends cost more.  us per step, dQ first / one grid (mean list; dQ workgroups): 4 heads
+// L = 256, K = 4 46.9 / 36.8 (4; 32), L = 1,000 164 / 148 (11; 252), L = 4,096 693 / 634 (35; 1,024), L = 16,000 4,990 / 4,740
+// (128; 4,000), packed 396 / 338 (12; 1,612), 16 heads L = 2,048 458 / 394 (19; 2,048), 64 heads L = 411 148 / 120 (6; 1,664),
+// L = 700 258 / 236 (8; 2,816), L = 1,000 412 / 403 (11; 4,032), L = 4,096 4,858 / 4,793 (35; 16,384), L = 20,480 106.5 / 106.3
+// ms; but L = 1,391 709 / 716 (14; 5,568), eight packed sequences 3,156 / 3,344 (12; 12,896).
+// A backward called by itself pays a pass over O and dO for the terms: 4 heads L = 4,096 664 / 607, 16 heads L = 2,048 455 /
+// 412, 64 heads L = 700 254 / 247; but L = 3,000 2,740 / 2,784.
+bool backward_in_one_grid(int D, int mean_tiles, int n_row_tiles, int Hq, bool terms_left) {
+  constexpr int kMostWorkgroups = 16 * kCus, kMostWithTermsPass = 12 * kCus;
+  const int n_wg = n_row_tiles * Hq;
+  if (D != 64) return false;
+  if (!terms_left) return n_wg <= kMostWithTermsPass;
+  return mean_tiles > kPlainMeanTiles || n_wg <= kMostWorkgroups;
+}
+
+hipError_t launch_row_terms(const BwdParams& p, hipStream_t stream) {
+  const int n_rt = p.rt_hi - p.rt_lo;
+  if (n_rt <= 0) return hipSuccess;
+  hipLaunchKernelGGL(row_terms_kernel, dim3((unsigned)(n_rt * p.Hq)), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int acc_below, bool with_dq, hipStream_t stream,
                        KernelTimer* timer) {
   BwdParams p = pin;
   const int n_rt = p.rt_hi - p.rt_lo;
@@ -2449,14 +2554,15 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
       p.d0_split = n_pairs - shrinking + p.d0_step;
       if (p.d0_split > n_pairs) p.d0_split = n_pairs;
     }
-    const int n_chain_items = (p.rt_hi - p.rt_lo) * ((p.tm.n_csub + 1) / 2) * p.Hkv;
+    p.n_chain_items = (p.rt_hi - p.rt_lo) * ((p.tm.n_csub + 1) / 2) * p.Hkv;
     {
-      const dim3 grid((unsigned)(p.n_d0_items + n_chain_items));
+      const dim3 grid((unsigned)(p.n_d0_items + p.n_chain_items + (with_dq ? (p.rt_hi - p.rt_lo) * p.Hq : 0)));
       TimedSpan span(timer, kKindDkDv, stream);
       auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p); };
       auto pick = [&](auto rows) {
         constexpr int ROWS = decltype(rows)::value;
-        if (D == 64) sv_dkdv ? go(dkdv_kernel<64, ROWS, true>) : go(dkdv_kernel<64, ROWS, false>);
+        if (with_dq) hipLaunchKernelGGL((sv_dkdv ? bwd_kernel<ROWS, true> : bwd_kernel<ROWS, false>), grid, dim3(256), 0, stream, p, p);
+        else if (D == 64) sv_dkdv ? go(dkdv_kernel<64, ROWS, true>) : go(dkdv_kernel<64, ROWS, false>);
         else sv_dkdv ? go(dkdv_kernel<128, ROWS, true>) : go(dkdv_kernel<128, ROWS, false>);
       };
       const int apart = D == 64 ? kRowsApart<64> : kRowsApart<128>;

@@ -1081,6 +1081,44 @@ def test_both_dq_kernels_give_the_same_bits(form, qscale):
             assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
 
 
+@pytest.mark.parametrize("qscale", [1.0, 40.0])
+@pytest.mark.parametrize("form", ["one_row", "one_tile", "dense", "k7", "k43", "packed", "sampled"])
+def test_backward_as_one_grid_gives_the_bits_of_kernels_launched_apart(form, qscale):
+    """A step runs dQ and dK/dV as one grid behind a forward that leaves the per-row terms; a profiled step launches them
+    apart; a backward called by itself forms the terms in a pass of its own.  The smallest problems, segments, every way of
+    finding rows, and (at the larger scale) rows outside the range of unnormalised probabilities: the same bits."""
+    print(f"case one grid {form} qscale={qscale}", flush=True)
+    small = {"one_row": (1, 8), "one_tile": (16, 8), "k43": (300, 43)}
+    tm, L, K = (pe.peagle_build_tilemap(*small[form], None, device=0), *small[form]) if form in small else _map_of(form)
+    S = tm.info()["S"]
+    T, Hq, Hkv, D = tm.tokens(L), 6, 2, 64
+    shape = pe.Shape(L, K, Hq, Hkv, D)
+    g = torch.Generator(device="cuda").manual_seed(341)
+    rnd = lambda H, f=1.0: (torch.randn(T, H, D, generator=g, device="cuda") * f).to(torch.bfloat16)
+    q, k, v, d_o = rnd(Hq, qscale), rnd(Hkv), rnd(Hkv), rnd(Hq)
+    ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
+
+    def results(call):
+        out = [torch.full_like(q, float("nan")), torch.full((Hq, T), float("nan"), device="cuda"), torch.full_like(q, float("nan")),
+               *(torch.full((T, Hkv, D), float("nan"), device="cuda") for _ in range(2))]
+        ws.fill_(255)  # (NaN: terms that nobody formed would show)
+        call(*out)
+        torch.cuda.synchronize()
+        return dict(zip(("o", "lse", "dq", "dk", "dv"), out))
+
+    def by_hand(o, lse, dq, dk, dv):
+        pe.peagle_attn_fwd(tm, shape, -1, q, k, v, o, lse)
+        pe.peagle_attn_bwd(tm, shape, -1, q, k, v, o, d_o, lse, dq, dk, dv, 0, ws)
+    step = results(lambda *out: pe.peagle_attn_step_partitioned(tm, shape, 0, S, q, k, v, d_o, *out, None, None, ws))
+    apart = results(lambda *out: pe.peagle_attn_step_profiled(tm, shape, 0, S, q, k, v, d_o, *out, ws))
+    calls = results(by_hand)
+    for n in step:
+        assert torch.isfinite(step[n]).all(), n
+        assert torch.equal(step[n], apart[n]), n
+        if S == 1 or n not in ("dk", "dv"):  # (segments are summed one by one, a call over all of them is not)
+            assert torch.equal(step[n], calls[n]), n
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(2, 1), (64, 32)])
 def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
     """Six hundred anchors alone (short lists, at many heads the plain dQ kernel) and packed in front of a sequence of five
