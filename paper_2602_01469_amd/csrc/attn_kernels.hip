@@ -161,6 +161,26 @@ __device__ __forceinline__ void dma_key_tile(uint32_t kd, uint32_t vd, const __b
   }
 }
 
+// The bitmask of a row tile's key tile, to LDS with the tile's copies: each wave the words of its own 32 rows.  (A mask word
+// loaded to a register where the tile is computed is waited for behind the next tile's copies, because a wave's accesses
+// complete in order: nothing of them was hidden in a masked tile, three of every row tile, or in any iteration of a chain
+// tile in the dK/dV kernel.  us, so / from LDS: packed 203 to 900 anchors, 64 heads 767 / 745, eight sequences 3,138 / 3,111,
+// L = 411 120 / 117.5, L = 1,391 722 / 713; L = 20,480 the same.)
+constexpr int kTileMaskBytes = kRowsPerTile * kMaskWordsPerRow * 4;
+__device__ __forceinline__ void dma_tile_mask(uint32_t mask_lds, const DeviceTileMap& tm, const TileEntry& en, int wave) {
+  if (en.mask_id < 0) return;
+  constexpr int kWords = kTileMaskBytes / 4 / 4;  // of a wave: one per lane
+  static_assert(kWords == 64, "a lane copies one word");
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+  dma4_untracked(uniform_ptr(tm.masks + ((size_t)en.mask_id * 4 + w) * kWords), lane_id() * 4u, mask_lds + w * (kWords * 4));
+}
+// ... and the words of row `row` (32-key blocks 0 and 1), shifted to the keys of the lane's half.
+__device__ __forceinline__ void tile_mask(const char* mask, int row, int g, uint32_t (&mw)[2]) {
+  const u32x2 w = *reinterpret_cast<const u32x2*>(mask + row * (kMaskWordsPerRow * 4));
+  mw[0] = w[0] >> (4 * g);
+  mw[1] = w[1] >> (4 * g);
+}
+
 // Row tile (128 rows of one query head) straight into its swizzled LDS image, same block/lane
 // assignment as dma_key_tile; rows that do not exist are filled from the zero page.  The rows a
 // lane copies are the same for every row tile, so their (depth, anchor) split - which costs an
@@ -439,9 +459,11 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
   constexpr bool LEAN = PER_SIMD == 3;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   __shared__ __attribute__((aligned(16))) char lds[2][2][kTileBytes];  // [buffer][K|V]
+  __shared__ __attribute__((aligned(16))) char lds_mask[2][kTileMaskBytes];
 
   const int tid = threadIdx.x, wave = LEAN ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
+  const uint32_t mask_lds = lds_scalar_addr(&lds_mask[0][0]);
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
   const int hpg = group / NH;
@@ -492,13 +514,16 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
     TileEntry cur = load_entry(tm.row_entries, e0);
     TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
     dma_key_tile<D, 4, SV, LEAN>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
+    dma_tile_mask(mask_lds, tm, cur, wave);
     dma_publish();
     // A row tile's list holds its full tiles first, then the partial ones: two loops (accumulators stay in place).
     int e = e0;
     auto full_tile = [&](int buf) {
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
-      if (e + 1 < e1)
+      if (e + 1 < e1) {
         dma_key_tile<D, 4, SV, LEAN>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+        dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
+      }
       const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
       fwd_tile<D, NH, false, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       dma_publish();
@@ -516,11 +541,13 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
     for (; e < e1; ++e) {
       const int buf = (e - e0) & 1;
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
-      if (e + 1 < e1)
+      if (e + 1 < e1) {
         dma_key_tile<D, 4, SV, LEAN>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+        dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
+      }
       const int l = LEAN ? lane_id() : lane;
-      const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + wave * 32 + (l & 31)) * 2);
-      const uint32_t mw[2] = {w[0] >> (4 * (l >> 5)), w[1] >> (4 * (l >> 5))};
+      uint32_t mw[2];
+      tile_mask(lds_mask[buf], wave * 32 + (l & 31), l >> 5, mw);
       fwd_tile_masked<D, NH, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       dma_publish();
       cur = nxt;
@@ -656,9 +683,11 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr bool kAsPipe = D == 64;
   __shared__ __attribute__((aligned(16))) char lds[2][2][kTileBytes];
+  __shared__ __attribute__((aligned(16))) char lds_mask[2][kTileMaskBytes];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
+  const uint32_t mask_lds = lds_scalar_addr(&lds_mask[0][0]);
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
   const int hpg = group / NH;
@@ -708,6 +737,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   TileEntry cur = load_entry(tm.row_entries, e0);
   TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
   dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
+  dma_tile_mask(mask_lds, tm, cur, wave);
 
   float row_factor = p.scale;
   int e_pipe = e0;  // end of the tiles that dq_pipe_kernel would run in its pipeline
@@ -727,8 +757,10 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
     for (; e < e_end; ++e) {
       const int buf = (e - e0) & 1;
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
-      if (e + 1 < e1)
+      if (e + 1 < e1) {
         dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+        dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
+      }
       const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
       dq_tile<D, NH, false, FROM_DELTA>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
       dma_publish();
@@ -741,10 +773,12 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   for (; e < e1; ++e) {
     const int buf = (e - e0) & 1;
     const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
-    if (e + 1 < e1)
+    if (e + 1 < e1) {
       dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
-    const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)cur.mask_id * kRowsPerTile + r) * 2);
-    const uint32_t mw[2] = {w[0] >> (4 * g), w[1] >> (4 * g)};
+      dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
+    }
+    uint32_t mw[2];
+    tile_mask(lds_mask[buf], r, g, mw);
     dq_tile<D, NH, true>(lds[buf][0], lds[buf][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
     dma_publish();
     cur = nxt;
@@ -889,15 +923,17 @@ __device__ __forceinline__ void dq_pipe_body(DqPipe<D>& P, const char* k_dq, con
 
 // TERMS: forms the per-row terms from O and writes them for the dK/dV kernel; otherwise they are there already.
 template <int D>
-constexpr int kDqPipeLds = 3 * 2 * kKeysPerTile * D * 2;
+constexpr int kDqPipeLds = 3 * (2 * kKeysPerTile * D * 2 + kTileMaskBytes);
 template <int D, bool SV, bool TERMS>
 __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base, int b) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr int N2 = D / 16;
   char (&lds)[3][2][kTileBytes] = *reinterpret_cast<char (*)[3][2][kTileBytes]>(lds_base);  // [buffer][K|V]
+  const char* lds_mask = lds_base + sizeof(lds);                                                      // [buffer]
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
+  const uint32_t mask_lds = lds_scalar_addr(lds_mask);
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
   const int kvh = b % p.Hkv;
@@ -952,7 +988,11 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
 
   // the first two tiles are on their way before anything else
   dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, t_cur.tile, p.L, wave, lane, p.v_shared);
-  if (e0 + 1 < e1) dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
+  dma_tile_mask(mask_lds, tm, t_cur, wave);
+  if (e0 + 1 < e1) {
+    dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
+    dma_tile_mask(mask_lds + kTileMaskBytes, tm, t_n1, wave);
+  }
 
   // unnormalised probabilities for the whole workgroup, or normalised ones for the whole workgroup
   const bool in_range = __builtin_fabsf(lse2) <= kDqLseRange;  // (false for NaN)
@@ -995,7 +1035,10 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
       // Every wave has left tile e-1 (its last reader was the body above) and has waited for its own copies of
       // tile e+1: after the barrier that buffer may be overwritten and tile e+1 may be read.
       dma_publish();
-      if (e + 2 < e1) dma_key_tile<D, 4, SV>(kl.k(BP), kl.v(BP), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
+      if (e + 2 < e1) {
+        dma_key_tile<D, 4, SV>(kl.k(BP), kl.v(BP), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
+        dma_tile_mask(mask_lds + BP * kTileMaskBytes, tm, t_n2, wave);
+      }
       dq_pipe_body<D, 1, LAST>(P, lds[B][0], lds[BN][0], lds[BN][1], lds[B][0], no, to, qf, dof, dq, ndelta16, c);
       t_cur = t_n1;
       t_n1 = t_n2;
@@ -1031,15 +1074,14 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
     for (; e < e_end; ++e) {
       const u32x2 ahead = fetch_entry(tm.row_entries, entry_at(e + 3));
       const int buf2 = buf == 0 ? 2 : buf - 1;
-      if (e + 2 < e1) dma_key_tile<D, 4, SV>(kl.k(buf2), kl.v(buf2), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
+      if (e + 2 < e1) {
+        dma_key_tile<D, 4, SV>(kl.k(buf2), kl.v(buf2), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
+        dma_tile_mask(mask_lds + buf2 * kTileMaskBytes, tm, t_n2, wave);
+      }
       const char* kt_lds = lds[0][0] + buf * (2 * kTileBytes);
       const char* vt_lds = kt_lds + kTileBytes;
       uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
-      if (MASKED) {
-        const u32x2 w = *reinterpret_cast<const u32x2*>(tm.masks + ((size_t)t_cur.mask_id * kRowsPerTile + r) * 2);
-        mw[0] = w[0] >> (4 * g);
-        mw[1] = w[1] >> (4 * g);
-      }
+      if (MASKED) tile_mask(lds_mask + buf * kTileMaskBytes, r, g, mw);
       dq_tile<D, 1, MASKED>(kt_lds, vt_lds, no, to, qf, dof, dq, lse_used, delta_used, mw, p.c_log2);
       dma_publish();
       t_cur = t_n1;
@@ -1403,7 +1445,7 @@ enum { kRowsWhole = 0, kRowsFar = 1, kRowsListed = 2, kRowsMost = 3, kRowsListed
 template <int D>
 constexpr int kRowsApart = 4 * (512 / D);  // rows of the tile between two copies of a lane
 template <int D>
-constexpr int kDkdvLds = 2 * (2 * kRowsPerTile * D * 2 + 2 * kRowsPerTile * 4);  // two buffers of Q | dO | lse2 | delta
+constexpr int kDkdvLds = 2 * (2 * kRowsPerTile * D * 2 + 2 * kRowsPerTile * 4 + 2 * kMaskWords * 4);  // see kBufBytes
 template <int D, int ROWS, bool SV>
 __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const int item) {
   constexpr bool LISTED = ROWS == kRowsListed || ROWS == kRowsListedFar;
@@ -1412,7 +1454,8 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   // loop for all tiles, at 3,000 anchors 1,410 and 1,320.
   constexpr bool kSkips = D == 64;
   constexpr int kTileBytes = kRowsPerTile * D * 2;
-  constexpr int kBufBytes = 2 * kTileBytes + 2 * kRowsPerTile * 4;
+  constexpr int kMaskAt = 2 * kTileBytes + 2 * kRowsPerTile * 4;  // Q | dO | lse2 | delta | masks of the pair's key tiles
+  constexpr int kBufBytes = kMaskAt + 2 * kMaskWords * 4;
   constexpr int kLdsBytes = kDkdvLds<D>;
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
@@ -1621,6 +1664,18 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
     }
   };
 
+  // The key-major bitmask of a row tile, if it has one, travels with its copies (see dma_tile_mask): one wave of each key tile
+  // copies it.
+  auto issue_mask = [&](int mask, int buf) {
+    const int id = __builtin_amdgcn_readfirstlane(mask);
+    if (id < 0 || (wave_s & 1)) return;
+    dma16_untracked(uniform_ptr(tm.masks_by_key + (size_t)id * kMaskWords), lane_id() * 16u,
+                    lds_addr0 + (uint32_t)buf * kBufBytes + kMaskAt + (wave_s >> 1) * (kMaskWords * 4));
+  };
+  auto key_mask = [&](int buf) {  // the lane's key: four words, one per 32-row unit
+    return *reinterpret_cast<const u32x4*>(lds + buf * kBufBytes + kMaskAt + (my_tile * kKeysPerTile + (kblk & 1) * 32 + ln) * 16);
+  };
+
   int ei_n = 0, hh_n = h_lo;        // iteration it+1 (its copy is issued now)
   int ei_a = 0, hh_a = h_lo;        // it+2 (its row tokens and mask are fetched now)
   int ei_b = 0, hh_b = h_lo;        // it+3 (its list entry is fetched now)
@@ -1635,6 +1690,7 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
       issue(h_lo, tok_n, 0);
     }
     mask_c = mask_of(0, take_entry(fetch_mask(0)));
+    issue_mask(mask_c, 0);
     step(ei_n, hh_n);
     step(ei_a, hh_a);
     step(ei_a, hh_a);
@@ -1674,6 +1730,7 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
                                  : (kNear || LISTED) && have1 && mask_c >= -1 && (LISTED || rows_of(rt_n) == full_rows);
       const bool have2 = it + 2 < n_iter, have3 = it + 3 < n_iter;
       Toks tok_a = tok_n;
+      if (have1) issue_mask(mask_n, buf ^ 1);
       if (LISTED) {
         if (have2) tok_a = row_tokens<D, 4, LISTED>(tm, rl, rt_a, p.L);
         if (have1 && !rides) issue(hh_n, tok_n, buf ^ 1);
@@ -1691,8 +1748,7 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
         const float* lse_lds = reinterpret_cast<const float*>(q_lds + 2 * kTileBytes);
         const float* delta_lds = lse_lds + kRowsPerTile;
         if (kSkips && CHAIN) {  // (chain tiles always carry a bitmask)
-          const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
-          const u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
+          const u32x4 cm = key_mask(buf);
           dkdv_rowtile_chain<D>(q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2, cm);
         } else if (mask_c == -1) {
           if (kNear && rides)
@@ -1704,10 +1760,7 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
           else if (ROWS == kRowsFar || D == 128)
             dkdv_rowtile_pipelined<D, 0>(NoCopies{}, q_lds, do_lds, lse_lds, delta_lds, no, to, kf, vf, dk, dv, g, p.c_log2);
         } else if (mask_c >= 0) {
-          // which of the tile's 128 rows see this lane's key: four words, one per 32-row unit
-          // (scalar base + small per-lane offset: no 64-bit per-lane address is kept across the loop)
-          const uint32_t* mbase = uniform_ptr(tm.masks_by_key + (size_t)__builtin_amdgcn_readfirstlane(mask_c) * kMaskWords);
-          u32x4 cm = *reinterpret_cast<const u32x4*>(mbase + ((kblk & 1) * 32 + ln) * 4);
+          u32x4 cm = key_mask(buf);  // which of the tile's 128 rows see this lane's key
           // (Shifted to the lane's half here, behind a statement the compiler cannot look through.  Left to itself it
           // tests the unshifted words against sixteen bits that it shifts up before the loop, keeps those in registers
           // across it, spills them, and reloads them behind the copies just issued.)
