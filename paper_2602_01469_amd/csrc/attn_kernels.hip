@@ -54,6 +54,21 @@ __device__ __forceinline__ bool key_token(const DeviceTileMap& tm, int kt, int r
   return e >= 1 && a < tm.A && j < L;
 }
 
+// Tokens of the keys row0, row0 + step, ... of key tile `kt`, -1 where one does not exist: a listed map's are all on their way
+// before the first is waited for.
+template <int N>
+__device__ __forceinline__ void key_tokens(const DeviceTileMap& tm, int kt, int row0, int step, int L, int (&tok)[N]) {
+  if (kt >= tm.n_d0 && tm.row_tok) {
+    const int32_t* list = tm.chain_tok + (size_t)(kt - tm.n_d0) * kKeysPerTile + row0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) tok[i] = list[i * step];
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (!key_token(tm, kt, row0 + i * step, L, tok[i])) tok[i] = -1;
+}
+
 // Token of row `r` of row tile `rt`; false if the row is padding or beyond the sequence.
 __device__ __forceinline__ bool row_token(const DeviceTileMap& tm, int rt, int r, int L, int& tok) {
   if (tm.row_tok) {  // sampled map: explicit list of the tile's rows
@@ -84,7 +99,18 @@ __device__ __forceinline__ TileEntry take_entry(u32x2 w) {
   en.mask_id = __builtin_amdgcn_readfirstlane((int)w1);
   return en;
 }
-__device__ __forceinline__ TileEntry load_entry(const TileEntry* list, int e) { return take_entry(fetch_entry(list, e)); }
+// An entry, or one of the map's integers, through the scalar path (index wave-uniform): what a workgroup starts with is
+// looked up without waiting for the vector loads issued before it, and several at a time.
+typedef const int32_t __attribute__((address_space(4))) * ConstInts;
+__device__ __forceinline__ int32_t const_int(const int32_t* list, int i) { return ((ConstInts)(uintptr_t)list)[i]; }
+__device__ __forceinline__ TileEntry const_entry(const TileEntry* list, int e) {
+  static_assert(sizeof(TileEntry) == 8, "an entry is two words");
+  const ConstInts w = (ConstInts)(uintptr_t)(list + e);
+  TileEntry en;
+  en.tile = w[0];
+  en.mask_id = w[1];
+  return en;
+}
 
 // LDS addresses of the K/V tile buffers of the row-stationary kernels, [slot][K|V][tile bytes], as plain scalar
 // integers: the address of slot 0 is taken once per kernel and everything else is integer arithmetic (taken
@@ -132,32 +158,21 @@ __device__ __forceinline__ void dma_key_tile(uint32_t kd, uint32_t vd, const __b
     return;
   }
   const int l = LEAN ? lane_id() : lane;
-  const int row_in_blk = l / (D / 8), phys = l % (D / 8);
-  if (SV && kt >= tm.n_d0) {
-    // First-layer form, chain tile: every key's value row is the one shared vector of its KV head.  (SV is a
-    // template flag: kernels of the ordinary step carry none of this.)
+  const int phys = l % (D / 8), row0 = wave * (512 / D) + l / (D / 8);
+  constexpr int kTogether = LEAN ? 1 : kBlocks / NW;
+  int tok[kTogether];
 #pragma unroll
-    for (int i = 0; i < kBlocks / NW; ++i) {
-      const int blk = i * NW + wave;
-      const int row = blk * (512 / D) + row_in_blk;
-      int tok;
-      const bool ok = key_token(tm, kt, row, L, tok);
-      const int chunk = (phys ^ swz<D>(row)) << 3;
-      const size_t off = ((size_t)(ok ? tok : 0) * Hkv + kvh) * D + chunk;
-      dma16_untracked(ok ? (const void*)(kbase + off) : tm.zeros, kd + i * NW * 1024);
-      dma16_untracked(ok ? (const void*)(v_shared + (size_t)kvh * D + chunk) : tm.zeros, vd + i * NW * 1024);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < kBlocks / NW; ++i) {
-      const int blk = i * NW + wave;
-      const int row = blk * (512 / D) + row_in_blk;
-      int tok;
-      const bool ok = key_token(tm, kt, row, L, tok);
-      const size_t off = ((size_t)(ok ? tok : 0) * Hkv + kvh) * D + ((phys ^ swz<D>(row)) << 3);
-      dma16_untracked(ok ? (const void*)(kbase + off) : tm.zeros, kd + i * NW * 1024);
-      dma16_untracked(ok ? (const void*)(vbase + off) : tm.zeros, vd + i * NW * 1024);
-    }
+  for (int i = 0; i < kBlocks / NW; ++i) {
+    if (i % kTogether == 0) key_tokens(tm, kt, row0 + i * NW * (512 / D), NW * (512 / D), L, tok);
+    const int t = tok[i % kTogether];
+    const bool ok = t >= 0;
+    const int chunk = (phys ^ swz<D>(row0 + i * NW * (512 / D))) << 3;
+    const size_t off = ((size_t)(ok ? t : 0) * Hkv + kvh) * D + chunk;
+    // First-layer form (SV; a template flag: kernels of the ordinary step carry none of this), chain tile: every key's value
+    // row is the one shared vector of its KV head.
+    const __bf16* v = SV && kt >= tm.n_d0 ? v_shared + (size_t)kvh * D + chunk : vbase + off;
+    dma16_untracked(ok ? (const void*)(kbase + off) : tm.zeros, kd + i * NW * 1024);
+    dma16_untracked(ok ? (const void*)v : tm.zeros, vd + i * NW * 1024);
   }
 }
 
@@ -474,27 +489,32 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
   const int rt = p.rt_hi - 1 - b / hpg;  // heaviest row tiles first
   const int h0 = kvh * group + hc * NH;
 
+  // The start of a workgroup is a chain of memory round trips - parameters, list bounds, entries, copies; tokens, rows -, and
+  // with short lists the other workgroups of the CU do not cover it.  What does not depend on one another is on its way
+  // together, here and in the backward's kernels: lookups go through the scalar path (a vector load that is waited for waits
+  // for the rows' loads before it), several at a time, and the rows are loaded without a branch for each.  us per step, one by
+  // one / so, 64 heads: packed 203 to 517 anchors 322 / 304, 203 to 900 745 / 713, eight packed sequences 3,111 / 3,056,
+  // L = 1,391 712 / 695, L = 4,096 4,893 / 4,861, L = 20,480 106.5 / 106.3 ms.
+  const int e0 = const_int(tm.row_ptr, rt), e1 = const_int(tm.row_ptr, rt + 1);
+  const int e_lead = e0 + const_int(tm.row_lead, rt);  // end of the leading run of full tiles
   const int r = wave * 32 + ln;  // row of the tile owned by this lane (shared with lane^32)
   int tq_held;
   const bool row_ok = row_token(tm, rt, r, p.L, tq_held);
 
+  // (A row that does not exist computes on token 0's: a lane's row meets no other lane's, and it is not stored.)
   bf16x8 qf[NH][D / 16];
   auto load_q = [&]() {
+    const __bf16* q = p.q + ((size_t)(row_ok ? tq_held : 0) * p.Hq + h0) * D + g * 8;
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh)
 #pragma unroll
-      for (int st = 0; st < D / 16; ++st)
-        qf[hh][st] = as_frag(row_ok ? ld16(p.q + ((size_t)tq_held * p.Hq + h0 + hh) * D + st * 16 + g * 8)
-                                    : make_uint4(0, 0, 0, 0));
+      for (int st = 0; st < D / 16; ++st) qf[hh][st] = as_frag(ld16(q + hh * D + st * 16));
   };
-  load_q();
 
   f32x16 o[NH][D / 32];
   float m[NH], lsum[NH], l_tot[NH];
   const NatOff<D> no = nat_offsets<D>(lane);
   const TrOff<D> to = tr_offsets<D>(lane);
-  const int e0 = tm.row_ptr[rt], e1 = tm.row_ptr[rt + 1];
-  const int e_lead = e0 + tm.row_lead[rt];  // end of the leading run of full tiles
 
   // One pass over the row tile's key tiles.  The first pass keeps the softmax reference at 0
   // (no running max: fewer vector instructions per score); it is exact as long as every row
@@ -511,8 +531,9 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
 #pragma unroll
       for (int db = 0; db < D / 32; ++db) o[hh][db] = zero16();
     }
-    TileEntry cur = load_entry(tm.row_entries, e0);
-    TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
+    TileEntry cur = const_entry(tm.row_entries, e0);
+    TileEntry nxt = const_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
+    if (!SAFE || LEAN) load_q();  // (lean: not held over the stores of the first pass)
     dma_key_tile<D, 4, SV, LEAN>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
     dma_tile_mask(mask_lds, tm, cur, wave);
     dma_publish();
@@ -600,7 +621,6 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
   for (int hh = 0; hh < NH; ++hh)
     if (!(redo & (1 << hh))) store(hh);
   if (redo) {
-    if (LEAN) load_q();  // (not held over the stores above)
     pass(std::true_type{});
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh)
@@ -698,26 +718,36 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   const int rt = p.rt_hi - 1 - b / hpg;
   const int h0 = kvh * group + hc * NH;
 
+  const int e0 = const_int(tm.row_ptr, rt), e1 = const_int(tm.row_ptr, rt + 1);  // (see fwd_kernel)
+  const int e_lead = e0 + const_int(tm.row_lead, rt);  // end of the leading run of full tiles
   const int r = wave * 32 + ln;
   int tq;
   const bool row_ok = row_token(tm, rt, r, p.L, tq);
+  TileEntry cur = const_entry(tm.row_entries, e0);
+  TileEntry nxt = const_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
 
-  bf16x8 qf[NH][D / 16], dof[NH][D / 16];
+  bf16x8 qf[NH][D / 16], dof[NH][D / 16], of[NH][D / 16];
   float lse2[NH], delta[NH];
 #pragma unroll
   for (int hh = 0; hh < NH; ++hh) {
     const size_t off = ((size_t)(row_ok ? tq : 0) * p.Hq + h0 + hh) * D + g * 8;
-    float dl = 0.f;
+    lse2[hh] = p.lse[(size_t)(h0 + hh) * p.T + (row_ok ? tq : 0)] * kLog2e;
 #pragma unroll
     for (int st = 0; st < D / 16; ++st) {
-      const uint4 z = make_uint4(0, 0, 0, 0);
-      qf[hh][st] = as_frag(row_ok ? ld16(p.q + off + st * 16) : z);
-      dof[hh][st] = as_frag(row_ok ? ld16(p.d_o + off + st * 16) : z);
-      dl = add_delta8(dl, dof[hh][st], as_frag(row_ok ? ld16(p.o + off + st * 16) : z));
+      qf[hh][st] = as_frag(ld16(p.q + off + st * 16));
+      dof[hh][st] = as_frag(ld16(p.d_o + off + st * 16));
+      of[hh][st] = as_frag(ld16(p.o + off + st * 16));
     }
+  }
+  dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
+  dma_tile_mask(mask_lds, tm, cur, wave);
+#pragma unroll
+  for (int hh = 0; hh < NH; ++hh) {
+    float dl = 0.f;
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) dl = add_delta8(dl, dof[hh][st], of[hh][st]);
     dl = sum_halves(dl);
     delta[hh] = dl;
-    lse2[hh] = row_ok ? p.lse[(size_t)(h0 + hh) * p.T + tq] * kLog2e : 0.f;
     if (row_ok && g == 0) {  // per-row terms in the form the dK/dV kernel consumes
       p.delta[(size_t)(h0 + hh) * p.T + tq] = -dl;
       p.nlse[(size_t)(h0 + hh) * p.T + tq] = -lse2[hh] / p.c_log2;
@@ -732,12 +762,6 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
 
   const NatOff<D> no = nat_offsets<D>(lane);
   const TrOff<D> to = tr_offsets<D>(lane);
-  const int e0 = tm.row_ptr[rt], e1 = tm.row_ptr[rt + 1];
-  const int e_lead = e0 + tm.row_lead[rt];  // end of the leading run of full tiles
-  TileEntry cur = load_entry(tm.row_entries, e0);
-  TileEntry nxt = load_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
-  dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
-  dma_tile_mask(mask_lds, tm, cur, wave);
 
   float row_factor = p.scale;
   int e_pipe = e0;  // end of the tiles that dq_pipe_kernel would run in its pipeline
@@ -746,7 +770,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
     if (unnormalised) {
       row_factor = exp2_fast(-lse2[0]) * p.scale;
       lse2[0] = 0.f;
-      e_pipe = e0 + tm.row_lead[rt] / 3 * 3;
+      e_pipe = e0 + (e_lead - e0) / 3 * 3;
     }
   }
   dma_publish();
@@ -942,9 +966,15 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
   const int rt = p.rt_hi - 1 - b / group;  // heaviest row tiles first
   const int h = kvh * group + hc;
 
+  const int e0 = const_int(tm.row_ptr, rt), e1 = const_int(tm.row_ptr, rt + 1);  // (see fwd_kernel)
+  const int n_lead = const_int(tm.row_lead, rt);  // leading full tiles
   const int r = wave * 32 + ln;  // row of the tile owned by this lane (shared with lane ^ 32)
   int tq;
   const bool row_ok = row_token(tm, rt, r, p.L, tq);
+  auto entry_at = [&](int e) { return e < e1 ? e : e1 - 1; };
+  TileEntry t_cur = const_entry(tm.row_entries, e0);
+  TileEntry t_n1 = const_entry(tm.row_entries, entry_at(e0 + 1));
+  TileEntry t_n2 = const_entry(tm.row_entries, entry_at(e0 + 2));
 
   // The K half of the buffer that the first pipelined body reads its (absent) predecessor from: that body
   // multiplies it by dS = 0, so it only has to be finite.
@@ -953,23 +983,35 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
     for (int i = tid; i < kTileBytes / 16; i += 256) z[i] = make_uint4(0, 0, 0, 0);
   }
 
-  bf16x8 qf[1][D / 16], dof[1][D / 16];
-  float lse2, delta;
+  bf16x8 qf[1][D / 16], dof[1][D / 16], of[D / 16];
+  const size_t at = (size_t)h * p.T + (row_ok ? tq : 0);
+  float lse2 = p.lse[at] * kLog2e, delta = TERMS ? 0.f : -p.delta[at];
   {
     const size_t off = ((size_t)(row_ok ? tq : 0) * p.Hq + h) * D + g * 8;
-    float dl = 0.f;
 #pragma unroll
     for (int st = 0; st < D / 16; ++st) {
-      const uint4 z = make_uint4(0, 0, 0, 0);
-      qf[0][st] = as_frag(row_ok ? ld16(p.q + off + st * 16) : z);
-      dof[0][st] = as_frag(row_ok ? ld16(p.d_o + off + st * 16) : z);
-      if (TERMS) dl = add_delta8(dl, dof[0][st], as_frag(row_ok ? ld16(p.o + off + st * 16) : z));
+      qf[0][st] = as_frag(ld16(p.q + off + st * 16));
+      dof[0][st] = as_frag(ld16(p.d_o + off + st * 16));
+      if (TERMS) of[st] = as_frag(ld16(p.o + off + st * 16));
     }
-    delta = TERMS ? sum_halves(dl) : row_ok ? -p.delta[(size_t)h * p.T + tq] : 0.f;
-    lse2 = row_ok ? p.lse[(size_t)h * p.T + tq] * kLog2e : 0.f;
-    if (TERMS && row_ok && g == 0) {  // per-row terms in the form the dK/dV kernel consumes
-      p.delta[(size_t)h * p.T + tq] = -delta;
-      p.nlse[(size_t)h * p.T + tq] = -lse2 / p.c_log2;
+  }
+
+  // the first two tiles are on their way before anything is computed
+  dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, t_cur.tile, p.L, wave, lane, p.v_shared);
+  dma_tile_mask(mask_lds, tm, t_cur, wave);
+  if (e0 + 1 < e1) {
+    dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
+    dma_tile_mask(mask_lds + kTileMaskBytes, tm, t_n1, wave);
+  }
+
+  if (TERMS) {
+    float dl = 0.f;
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) dl = add_delta8(dl, dof[0][st], of[st]);
+    delta = sum_halves(dl);
+    if (row_ok && g == 0) {  // per-row terms in the form the dK/dV kernel consumes
+      p.delta[at] = -delta;
+      p.nlse[at] = -lse2 / p.c_log2;
     }
   }
 
@@ -979,21 +1021,6 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
 
   const NatOff<D> no = nat_offsets<D>(lane);
   const TrOff<D> to = tr_offsets<D>(lane);
-  const int e0 = tm.row_ptr[rt], e1 = tm.row_ptr[rt + 1];
-  const int n_lead = tm.row_lead[rt];  // leading full tiles
-  auto entry_at = [&](int e) { return e < e1 ? e : e1 - 1; };
-  TileEntry t_cur = load_entry(tm.row_entries, e0);
-  TileEntry t_n1 = load_entry(tm.row_entries, entry_at(e0 + 1));
-  TileEntry t_n2 = load_entry(tm.row_entries, entry_at(e0 + 2));
-
-  // the first two tiles are on their way before anything else
-  dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, t_cur.tile, p.L, wave, lane, p.v_shared);
-  dma_tile_mask(mask_lds, tm, t_cur, wave);
-  if (e0 + 1 < e1) {
-    dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
-    dma_tile_mask(mask_lds + kTileMaskBytes, tm, t_n1, wave);
-  }
-
   // unnormalised probabilities for the whole workgroup, or normalised ones for the whole workgroup
   const bool in_range = __builtin_fabsf(lse2) <= kDqLseRange;  // (false for NaN)
   const bool unnormalised = __syncthreads_or(row_ok && !in_range) == 0;
@@ -1509,11 +1536,13 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   // starts inside a key tile's (ascending) list.  A launch that covers only part of its segments
   // (a cropped length, or one chunk of a long segment; dense maps only) cuts the range further by
   // position: the row tiles in a dense map's list are consecutive.
+  // (All of it wave-uniform and looked up through the scalar path, both tiles of the pair and the first entries at a time: the
+  // start of a workgroup is a chain of memory round trips, see fwd_kernel.)
   auto clip = [&](int t, int& lo_out, int& hi_out) {
     const int32_t* sp = tm.key_seg_ptr + (size_t)t * (tm.S + 1);
-    int lo = sp[p.s_lo], hi = sp[p.s_hi];
+    int lo = const_int(sp, p.s_lo), hi = const_int(sp, p.s_hi);
     if (p.clip_rows && lo < hi) {
-      const int first = tm.key_entries[lo].tile;
+      const int first = const_entry(tm.key_entries, lo).tile;
       const int nlo = lo + (p.rt_lo > first ? p.rt_lo - first : 0);
       const int nhi = lo + (p.rt_hi > first ? p.rt_hi - first : 0);
       lo = nlo < hi ? nlo : hi;
@@ -1524,8 +1553,10 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   };
   int e_lo, e_hi;            // list of the pair's first tile: drives the loop
   clip(kt0, e_lo, e_hi);
-  int my_lo = e_lo, my_hi = e_hi;
-  if (my_tile == 1 && tile_present) clip(kt, my_lo, my_hi);
+  int e_lo1 = e_lo, e_hi1 = e_hi;  // ... and of its second
+  if (n_tiles == 2) clip(kt0 + 1, e_lo1, e_hi1);
+  const bool second = my_tile == 1 && tile_present;
+  const int my_lo = second ? e_lo1 : e_lo, my_hi = second ? e_hi1 : e_hi;
   const int n_row_tiles = e_hi - e_lo;
   const int my_skip = tile_present ? n_row_tiles - (my_hi - my_lo) : n_row_tiles;  // leading row tiles that do not see my tile
   const int n_iter = n_row_tiles * (h_hi - h_lo);
@@ -1536,18 +1567,6 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   const bool key_ok = tile_present && key_token(tm, kt, (kblk & 1) * 32 + ln, p.L, key_tok);
   // first key of the wave (anchor; meaningful for depth-0 tiles only)
   const int key0 = __builtin_amdgcn_readfirstlane(kt * kKeysPerTile + (kblk & 1) * 32);
-  {
-    const size_t off = ((size_t)(key_ok ? key_tok : 0) * p.Hkv + kvh) * D + g * 8;
-#pragma unroll
-    for (int st = 0; st < D / 16; ++st) {
-      const uint4 z = make_uint4(0, 0, 0, 0);
-      const __bf16* vrow = SV && chain ? p.v_shared + (size_t)kvh * D + g * 8 : p.v + off;
-      const uint4 a = ld16(p.k + off + st * 16), c = ld16(vrow + st * 16);
-      kf[st] = as_frag(key_ok ? a : z);
-      vf[st] = as_frag(key_ok ? c : z);
-    }
-  }
-
   f32x16 dk[D / 32], dv[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) {
@@ -1649,10 +1668,11 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   // same time (they share them in L2) whether their lists are long or short.
   auto list_pos = [&](int ei) { return n_row_tiles - 1 - ei; };
   auto fetch_row_tile = [&](int ei) { return fetch_entry(tm.key_entries, e_lo + list_pos(ei)); };
-  auto fetch_mask = [&](int ei) {
+  auto mask_pos = [&](int ei) {
     const int li = list_pos(ei);
-    return fetch_entry(tm.key_entries, li >= my_skip ? my_lo + li - my_skip : e_lo + li);
+    return li >= my_skip ? my_lo + li - my_skip : e_lo + li;
   };
+  auto fetch_mask = [&](int ei) { return fetch_entry(tm.key_entries, mask_pos(ei)); };
   constexpr int kSkip = INT_MIN;
   auto mask_of = [&](int ei, const TileEntry& en) {  // (wave-uniform: through readfirstlane so that it stays scalar)
     return list_pos(ei) >= my_skip ? en.mask_id : kSkip;
@@ -1682,27 +1702,39 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   int rt_n = 0, rt_a = 0, mask_c = kSkip, mask_n = kSkip;
   Toks tok_n{};
   if (n_iter > 0) {
-    const int rt0 = take_entry(fetch_row_tile(0)).tile;
-    if (kNear) {
-      issue_near(h_lo, rt0, 0);
-    } else {
-      tok_n = row_tokens<D, 4, LISTED>(tm, rl, rt0, p.L);
-      issue(h_lo, tok_n, 0);
-    }
-    mask_c = mask_of(0, take_entry(fetch_mask(0)));
-    issue_mask(mask_c, 0);
     step(ei_n, hh_n);
     step(ei_a, hh_a);
     step(ei_a, hh_a);
     step(ei_b, hh_b);
     step(ei_b, hh_b);
     step(ei_b, hh_b);
-    if (n_iter > 1) {
-      rt_n = take_entry(fetch_row_tile(ei_n)).tile;
-      if (LISTED) tok_n = row_tokens<D, 4, LISTED>(tm, rl, rt_n, p.L);
-      mask_n = mask_of(ei_n, take_entry(fetch_mask(ei_n)));
+    auto mask_entry = [&](int ei) { return const_entry(tm.key_entries, __builtin_amdgcn_readfirstlane(mask_pos(ei))); };
+    const int rt0 = const_entry(tm.key_entries, e_lo + list_pos(0)).tile;
+    const TileEntry m0 = mask_entry(0), m1 = mask_entry(ei_n);
+    rt_n = const_entry(tm.key_entries, e_lo + list_pos(ei_n)).tile;
+    rt_a = const_entry(tm.key_entries, e_lo + list_pos(ei_a)).tile;
+    mask_c = mask_of(0, m0);
+    if (n_iter > 1) mask_n = mask_of(ei_n, m1);
+    if (kNear) {
+      issue_near(h_lo, rt0, 0);
+    } else {
+      tok_n = row_tokens<D, 4, LISTED>(tm, rl, rt0, p.L);
+      Toks tok_1 = tok_n;
+      if (LISTED) tok_1 = row_tokens<D, 4, LISTED>(tm, rl, rt_n, p.L);
+      issue(h_lo, tok_n, 0);
+      tok_n = tok_1;
     }
-    if (n_iter > 2) rt_a = take_entry(fetch_row_tile(ei_a)).tile;
+    issue_mask(mask_c, 0);
+  }
+  {  // (behind the first row tile's copies; a key that does not exist computes on token 0's, and is not stored: a lane's key
+     // meets no other lane's)
+    const size_t off = ((size_t)(key_ok ? key_tok : 0) * p.Hkv + kvh) * D + g * 8;
+    const __bf16* vrow = SV && chain ? p.v_shared + (size_t)kvh * D + g * 8 : p.v + off;
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) {
+      kf[st] = as_frag(ld16(p.k + off + st * 16));
+      vf[st] = as_frag(ld16(vrow + st * 16));
+    }
   }
   dma_publish();
 
