@@ -41,6 +41,30 @@ bool set_key_range(std::vector<uint32_t>& bits, int r, int64_t lo, int64_t hi) {
   return true;
 }
 
+// Key-major copies of `n` masks for the dK/dV kernel, whose lanes own keys: bit r%32 of word r/32 of key k is set iff row r sees
+// key k.  32 x 32 bits at a time: halves, quarters, ... exchanged across the diagonal, 80 exchanges instead of 1,024 single
+// bits (a sampled sequence has its own masks and pays for this in every step: us of a rebuild, bit by bit / so, 500 anchors, 55
+// masks, 240 / 14, 8,192 anchors, 938 masks, 4,800 / 280, beside 65 and 1,400 for everything else).
+void key_major_masks(const uint32_t* masks, int32_t n, uint32_t* out) {
+  constexpr int kWordsPerKey = kRowsPerTile / 32, kBlocks = kWordsPerKey * kMaskWordsPerRow;  // (side by side: vector code)
+  for (int32_t m = 0; m < n; ++m, masks += kMaskWords, out += kMaskWords) {
+    uint32_t a[32][kBlocks];
+    for (int r = 0; r < 32; ++r)
+      for (int w = 0; w < kWordsPerKey; ++w)
+        for (int kb = 0; kb < kMaskWordsPerRow; ++kb) a[r][kb * kWordsPerKey + w] = masks[(w * 32 + r) * kMaskWordsPerRow + kb];
+    for (uint32_t j = 16, low = 0x0000ffffu; j != 0; j >>= 1, low ^= low << j)
+      for (uint32_t r = 0; r < 32; r = (r + j + 1) & ~j)
+        for (int b = 0; b < kBlocks; ++b) {
+          const uint32_t t = ((a[r][b] >> j) ^ a[r + j][b]) & low;
+          a[r + j][b] ^= t;
+          a[r][b] ^= t << j;
+        }
+    for (int kb = 0; kb < kMaskWordsPerRow; ++kb)
+      for (int k = 0; k < 32; ++k)
+        for (int w = 0; w < kWordsPerKey; ++w) out[(kb * 32 + k) * kWordsPerKey + w] = a[k][kb * kWordsPerKey + w];
+  }
+}
+
 struct MaskPool {
   std::map<std::vector<uint32_t>, int32_t> index;
   std::vector<uint32_t>* storage;
@@ -167,19 +191,7 @@ int upload_map(peagle_tilemap* tm, hipStream_t stream, bool wait) {
   if (err == hipSuccess) {
     for (int i = 0; i < kArrays; ++i)
       if (sz[i] && src[i]) std::memcpy((char*)tm->staging + off[i], src[i], sz[i]);
-    // key-major copy of every mask for the dK/dV kernel, whose lanes own keys: word r/32 of key k has bit r%32
-    // set iff row r sees key k
-    uint32_t* mt = (uint32_t*)((char*)tm->staging + off[11]);
-    for (int32_t m = 0; m < tm->n_masks; ++m)
-      for (int k = 0; k < kKeysPerTile; ++k)
-        for (int w = 0; w < kRowsPerTile / 32; ++w) {
-          uint32_t bits = 0;
-          for (int b = 0; b < 32; ++b) {
-            const uint32_t rw = tm->masks[(size_t)m * kMaskWords + (size_t)(w * 32 + b) * kMaskWordsPerRow + k / 32];
-            bits |= ((rw >> (k % 32)) & 1u) << b;
-          }
-          mt[(size_t)m * kMaskWords + (size_t)k * (kRowsPerTile / 32) + w] = bits;
-        }
+    key_major_masks(tm->masks.data(), tm->n_masks, (uint32_t*)((char*)tm->staging + off[11]));
     err = hipMemcpyAsync(tm->dev_blob, tm->staging, total, hipMemcpyHostToDevice, stream);
   }
   if (err == hipSuccess) err = hipEventRecord((hipEvent_t)tm->copy_done, stream);
@@ -485,8 +497,10 @@ int fill_packed(peagle_tilemap* tm, const int32_t* depth_count_in, int32_t L, in
   std::vector<uint32_t> bits(kMaskWords);
   std::unordered_map<uint64_t, std::vector<int32_t>> by_hash;
   auto append_mask = [&](const std::vector<uint32_t>& m) {
-    uint64_t h = 1469598103934665603ull;
-    for (uint32_t w : m) h = (h ^ w) * 1099511628211ull;
+    uint64_t h = 0, part[4] = {1, 2, 3, 4};  // (four chains of multiplications side by side)
+    for (int i = 0; i < kMaskWords; i += 4)
+      for (int j = 0; j < 4; ++j) part[j] = (part[j] ^ m[i + j]) * 1099511628211ull;
+    for (uint64_t x : part) h = (h ^ x ^ x >> 32) * 1099511628211ull;
     std::vector<int32_t>& ids = by_hash[h];
     for (int32_t id : ids)
       if (std::memcmp(&tm->masks[(size_t)id * kMaskWords], m.data(), kMaskWords * sizeof(uint32_t)) == 0) return id;
