@@ -187,7 +187,7 @@ extern "C" int peagle_attn_bwd(const peagle_tilemap_t* tm, const peagle_shape_t*
   const BwdParams p = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, accumulate);
   const int acc_below = accumulate ? INT_MAX : 0;
   hipStream_t st = (hipStream_t)stream;
-  const bool one_grid = peagle::backward_in_one_grid(shape->D, p.mean_tiles, sr.rt_hi - sr.rt_lo, shape->Hq, false);
+  const bool one_grid = peagle::backward_in_one_grid(shape->D, p.mean_tiles, sr.rt_hi - sr.rt_lo, shape->Hq, false, false);
   const hipError_t e = one_grid ? peagle::launch_row_terms(p, st) : peagle::launch_dq(p, shape->D, st);
   if (e != hipSuccess) return PEAGLE_EHIP;
   return peagle::launch_dkdv(p, shape->D, sr.key_lo, sr.a_hi, acc_below, one_grid, st) == hipSuccess ? PEAGLE_OK : PEAGLE_EHIP;
@@ -237,7 +237,8 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
   }
   // (Timed kernel by kernel, dQ and dK/dV run apart.)
   const bool one_grid = n_seg > 0 && !timer &&
-                        peagle::backward_in_one_grid(shape->D, mean_tiles(tm, shape->L), rows.rt_hi - rows.rt_lo, shape->Hq, true);
+                        peagle::backward_in_one_grid(shape->D, mean_tiles(tm, shape->L), rows.rt_hi - rows.rt_lo, shape->Hq, true,
+                                                     sf.dk_part != nullptr);
   if (n_seg > 0) {
     FwdParams fp = make_fwd(tm, shape, rows, q, k, v, o, lse, sf);
     if (one_grid) {

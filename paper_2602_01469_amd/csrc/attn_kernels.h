@@ -105,8 +105,8 @@ struct KernelTimer {
 
 hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer* timer = nullptr);
 // Do dK/dV and dQ of a backward over n_row_tiles row tiles run as one grid?  terms_left: the forward of the same call leaves
-// the per-row terms; otherwise launch_row_terms() has to.
-bool backward_in_one_grid(int D, int mean_tiles, int n_row_tiles, int Hq, bool terms_left);
+// the per-row terms; otherwise launch_row_terms() has to.  sv: first-layer form.
+bool backward_in_one_grid(int D, int mean_tiles, int n_row_tiles, int Hq, bool terms_left, bool sv);
 // The per-row terms of the row range (D = 64).
 hipError_t launch_row_terms(const BwdParams& p, hipStream_t stream);
 // dQ of the row range, and the per-row terms that dK/dV consumes.

@@ -697,13 +697,16 @@ __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, 
 // them so, -Delta as the start value of dP in the tiles which that kernel pipelines - so that a row's dQ has the same
 // bits from either and the launcher may choose freely.  NH stays a named constant because dq_tile is written for NH
 // heads sharing the K / V fragments.)
-template <int D, bool SV>
-__global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
+// TERMS: as in dq_pipe_item.
+template <int D>
+constexpr int kDqLds = 2 * (2 * kKeysPerTile * D * 2 + kTileMaskBytes);
+template <int D, bool SV, bool TERMS>
+__device__ __forceinline__ void dq_item(const BwdParams& p, char* lds_base, int b) {
   constexpr int NH = 1;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr bool kAsPipe = D == 64;
-  __shared__ __attribute__((aligned(16))) char lds[2][2][kTileBytes];
-  __shared__ __attribute__((aligned(16))) char lds_mask[2][kTileMaskBytes];
+  char (&lds)[2][2][kTileBytes] = *reinterpret_cast<char (*)[2][2][kTileBytes]>(lds_base);  // [buffer][K|V]
+  char (&lds_mask)[2][kTileMaskBytes] = *reinterpret_cast<char (*)[2][kTileMaskBytes]>(lds_base + sizeof(lds));
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
@@ -711,7 +714,6 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   const DeviceTileMap& tm = p.tm;
   const int group = p.Hq / p.Hkv;
   const int hpg = group / NH;
-  int b = blockIdx.x;
   const int kvh = b % p.Hkv;
   b /= p.Hkv;
   const int hc = b % hpg;
@@ -732,17 +734,18 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
   for (int hh = 0; hh < NH; ++hh) {
     const size_t off = ((size_t)(row_ok ? tq : 0) * p.Hq + h0 + hh) * D + g * 8;
     lse2[hh] = p.lse[(size_t)(h0 + hh) * p.T + (row_ok ? tq : 0)] * kLog2e;
+    if (!TERMS) delta[hh] = -p.delta[(size_t)(h0 + hh) * p.T + (row_ok ? tq : 0)];
 #pragma unroll
     for (int st = 0; st < D / 16; ++st) {
       qf[hh][st] = as_frag(ld16(p.q + off + st * 16));
       dof[hh][st] = as_frag(ld16(p.d_o + off + st * 16));
-      of[hh][st] = as_frag(ld16(p.o + off + st * 16));
+      if (TERMS) of[hh][st] = as_frag(ld16(p.o + off + st * 16));
     }
   }
   dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
   dma_tile_mask(mask_lds, tm, cur, wave);
 #pragma unroll
-  for (int hh = 0; hh < NH; ++hh) {
+  for (int hh = 0; TERMS && hh < NH; ++hh) {
     float dl = 0.f;
 #pragma unroll
     for (int st = 0; st < D / 16; ++st) dl = add_delta8(dl, dof[hh][st], of[hh][st]);
@@ -845,6 +848,12 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
       for (int db = 0; db < D / 32; ++db) store_row_bf16(drow + db * 32, dq[hh][db], row_factor, g);
     }
   }
+}
+
+template <int D, bool SV>
+__global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(16))) char lds[kDqLds<D>];
+  dq_item<D, SV, true>(p, lds, blockIdx.x);
 }
 
 // =====================================================================================
@@ -1978,20 +1987,23 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(BwdParams p)
   dkdv_item<D, ROWS, SV>(p, lds, blockIdx.x);
 }
 
-// dK/dV and dQ as one grid (D = 64), where both are short of workgroups: neither reads what the other writes once the
+// dK/dV and dQ as one grid, where both are short of workgroups: neither reads what the other writes once the
 // per-row terms are there (the forward of the same call leaves them, or row_terms_kernel), so dQ's workgroups fill the
 // slots that unequal dK/dV lists leave, and a launch of a few workgroups, a chain of memory round trips, is not waited for
 // before the next.  dQ's come last, heaviest row tiles first: dealt between the chain tiles of the same rows, whose Q and dO
-// they share, they were slower (step of 64 heads, L = 411 127 against 119 us, L = 4,096 4,775 against 4,730).
+// they share, they were slower (step of 64 heads, L = 411 127 against 119 us, L = 4,096 4,775 against 4,730; chain tiles 4 or 16 row tiles ahead: L = 411 122 and
+// 116 against 115, others the same).
 // (p_dq: the same parameters once more.  Read from one block, the two halves' scalar registers are loaded together and held
 // together, more than there are.)
-template <int ROWS, bool SV>
-__global__ __launch_bounds__(256, 2) void bwd_kernel(BwdParams p, BwdParams p_dq) {
-  __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<64> > kDqPipeLds<64> ? kDkdvLds<64> : kDqPipeLds<64>];
+template <int D, int ROWS, bool SV>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_kernel(BwdParams p, BwdParams p_dq) {
+  constexpr int kDq = D == 64 ? kDqPipeLds<D> : kDqLds<D>;
+  __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<D> > kDq ? kDkdvLds<D> : kDq];
   const int n_dkdv = p.n_d0_items + p.n_chain_items;
   const int b = blockIdx.x;
-  if (b < n_dkdv) dkdv_item<64, ROWS, SV>(p, lds, b);
-  else dq_pipe_item<64, SV, false>(p_dq, lds, b - n_dkdv);
+  if (b < n_dkdv) dkdv_item<D, ROWS, SV>(p, lds, b);
+  else if constexpr (D == 64) dq_pipe_item<D, SV, false>(p_dq, lds, b - n_dkdv);
+  else dq_item<D, false, false>(p_dq, lds, b - n_dkdv);
 }
 
 // The per-row terms of a backward that no forward left them for (D = 64): two lanes per row and head, each with the pieces
@@ -2576,20 +2588,24 @@ hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer*
   return span.finish();
 }
 
-// dK/dV and dQ as one grid, or dQ (which then also forms the per-row terms) before dK/dV?  At D = 128 a dK/dV workgroup has
-// a CU to itself, and dQ's would, too.  At D = 64 one grid wherever dQ would run its pipelined kernel anyway, and with
+// dK/dV and dQ as one grid, or dQ (which then also forms the per-row terms) before dK/dV?  At D = 64 one grid wherever dQ would run its pipelined kernel anyway, and with
 // short lists (where the plain one runs three workgroups per CU, and the one grid two) as long as workgroups are few enough
 // that unequal lists and the launches' ends cost more.  us per step, dQ first / one grid (mean list; dQ workgroups): 4 heads
 // L = 256, K = 4 46.9 / 36.8 (4; 32), L = 1,000 164 / 148 (11; 252), L = 4,096 693 / 634 (35; 1,024), L = 16,000 4,990 / 4,740
 // (128; 4,000), packed 396 / 338 (12; 1,612), 16 heads L = 2,048 458 / 394 (19; 2,048), 64 heads L = 411 148 / 120 (6; 1,664),
 // L = 700 258 / 236 (8; 2,816), L = 1,000 412 / 403 (11; 4,032), L = 4,096 4,858 / 4,793 (35; 16,384), L = 20,480 106.5 / 106.3
 // ms; but L = 1,391 709 / 716 (14; 5,568), eight packed sequences 3,156 / 3,344 (12; 12,896).
-// A backward called by itself pays a pass over O and dO for the terms: 4 heads L = 4,096 664 / 607, 16 heads L = 2,048 455 /
+// At D = 128 a dK/dV workgroup has a CU to itself, and in one grid dQ's have, too, of which two share one otherwise: where
+// there are few.  4 heads L = 256, K = 4 67 / 50.7 (32 dQ workgroups), L = 1,000 252 / 215 (252), L = 4,096 1,109 / 966 (1,024),
+// packed 630 / 504 (1,612), L = 8,000 2,770 / 2,719 (2,000), 32 heads L = 128 68.6 / 54.8 (256), L = 500 201 / 176 (1,024),
+// L = 800 340 / 329 (1,600); but L = 1,000 442 / 459 (2,016), L = 1,391 727 / 793 (2,784), L = 4,096 4,899 / 5,360.  (The
+// first-layer form reads two forms of V there and stays apart.)
+// A backward called by itself at D = 64 pays a pass over O and dO for the terms: 4 heads L = 4,096 664 / 607, 16 heads L = 2,048 455 /
 // 412, 64 heads L = 700 254 / 247; but L = 3,000 2,740 / 2,784.
-bool backward_in_one_grid(int D, int mean_tiles, int n_row_tiles, int Hq, bool terms_left) {
-  constexpr int kMostWorkgroups = 16 * kCus, kMostWithTermsPass = 12 * kCus;
+bool backward_in_one_grid(int D, int mean_tiles, int n_row_tiles, int Hq, bool terms_left, bool sv) {
+  constexpr int kMostWorkgroups = 16 * kCus, kMostWithTermsPass = 12 * kCus, kMostD128 = 13 * kCus / 2;
   const int n_wg = n_row_tiles * Hq;
-  if (D != 64) return false;
+  if (D != 64) return !sv && terms_left && n_wg <= kMostD128;
   if (!terms_left) return n_wg <= kMostWithTermsPass;
   return mean_tiles > kPlainMeanTiles || n_wg <= kMostWorkgroups;
 }
@@ -2646,7 +2662,9 @@ hipError_t launch_dkdv(const BwdParams& pin, int D, int key_lo, int a_hi, int ac
       auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p); };
       auto pick = [&](auto rows) {
         constexpr int ROWS = decltype(rows)::value;
-        if (with_dq) hipLaunchKernelGGL((sv_dkdv ? bwd_kernel<ROWS, true> : bwd_kernel<ROWS, false>), grid, dim3(256), 0, stream, p, p);
+        auto both = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p, p); };
+        if (with_dq && D == 64) sv_dkdv ? both(bwd_kernel<64, ROWS, true>) : both(bwd_kernel<64, ROWS, false>);
+        else if (with_dq) both(bwd_kernel<128, ROWS, false>);
         else if (D == 64) sv_dkdv ? go(dkdv_kernel<64, ROWS, true>) : go(dkdv_kernel<64, ROWS, false>);
         else sv_dkdv ? go(dkdv_kernel<128, ROWS, true>) : go(dkdv_kernel<128, ROWS, false>);
       };

@@ -1081,17 +1081,17 @@ def test_both_dq_kernels_give_the_same_bits(form, qscale):
             assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
 
 
-@pytest.mark.parametrize("qscale", [1.0, 40.0])
+@pytest.mark.parametrize("D,qscale", [(64, 1.0), (64, 40.0), (128, 1.0)])
 @pytest.mark.parametrize("form", ["one_row", "one_tile", "dense", "k7", "k43", "packed", "sampled"])
-def test_backward_as_one_grid_gives_the_bits_of_kernels_launched_apart(form, qscale):
+def test_backward_as_one_grid_gives_the_bits_of_kernels_launched_apart(form, D, qscale):
     """A step runs dQ and dK/dV as one grid behind a forward that leaves the per-row terms; a profiled step launches them
-    apart; a backward called by itself forms the terms in a pass of its own.  The smallest problems, segments, every way of
+    apart; a backward called by itself forms the terms in a pass of its own (D = 64) or in dQ's kernel.  The smallest problems, segments, every way of
     finding rows, and (at the larger scale) rows outside the range of unnormalised probabilities: the same bits."""
-    print(f"case one grid {form} qscale={qscale}", flush=True)
+    print(f"case one grid {form} D={D} qscale={qscale}", flush=True)
     small = {"one_row": (1, 8), "one_tile": (16, 8), "k43": (300, 43)}
     tm, L, K = (pe.peagle_build_tilemap(*small[form], None, device=0), *small[form]) if form in small else _map_of(form)
     S = tm.info()["S"]
-    T, Hq, Hkv, D = tm.tokens(L), 6, 2, 64
+    T, Hq, Hkv = tm.tokens(L), 6, 2
     shape = pe.Shape(L, K, Hq, Hkv, D)
     g = torch.Generator(device="cuda").manual_seed(341)
     rnd = lambda H, f=1.0: (torch.randn(T, H, D, generator=g, device="cuda") * f).to(torch.bfloat16)
