@@ -126,7 +126,9 @@ int peagle_tilemap_expand_rows(const peagle_tilemap_t* tm, int32_t L, int32_t se
  * each PEAGLE_TILE_EMPTY / _FULL / _PARTIAL. */
 int peagle_tilemap_classes(const peagle_tilemap_t* tm, uint8_t* classes_out);
 
-/* Bytes of device scratch that peagle_attn_bwd / peagle_attn_step_partitioned need for this shape. */
+/* Bytes of device scratch that peagle_attn_bwd / peagle_attn_step_partitioned use for this shape.  Where several segments
+ * share a launch (few query heads) this includes a set of partial sums for each; a call accepts a workspace that has room
+ * for one set only (such as one made for a longer sequence of the same map), with the same results. */
 size_t peagle_workspace_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* shape);
 
 /*

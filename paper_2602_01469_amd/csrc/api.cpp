@@ -21,6 +21,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
   size_t delta_off, nlse_off, dk_off, dv_off, total;
+  size_t part;  // one of dK, dV
   int L64;
 };
 
@@ -29,17 +30,49 @@ size_t tokens_of(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
   return tm->sampled ? (size_t)tm->T_tokens : (size_t)s->L * s->K;
 }
 
+// Ranges of rows whose dK / dV are summed one by one: segments, or chunks of at most 128 row tiles (dense maps), in a step over
+// all segments or in a call over the whole sequence, whichever has more.
+int row_ranges(const peagle_tilemap_t* tm, int32_t L) {
+  if (tm->sampled) return tm->S;
+  int32_t by_segment = 0;
+  for (int32_t s = 0; s < tm->S && tm->seg_bounds[s] < L; ++s) {
+    const int32_t hi = tm->seg_bounds[s + 1] < L ? tm->seg_bounds[s + 1] : L;
+    by_segment += ((hi + tm->A - 1) / tm->A - tm->seg_bounds[s] / tm->A + 127) / 128;
+  }
+  const int32_t whole = ((L + tm->A - 1) / tm->A + 127) / 128;
+  return by_segment > whole ? by_segment : whole;
+}
+
 WsLayout ws_layout(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
   WsLayout w;
   w.L64 = (s->L + 63) / 64 * 64;
   const size_t T = tokens_of(tm, s);
-  const size_t part = (size_t)s->Hq * w.L64 * s->D * sizeof(float);
+  w.part = align256((size_t)s->Hq * w.L64 * s->D * sizeof(float));
   w.delta_off = 0;
   w.nlse_off = align256(T * s->Hq * sizeof(float));
   w.dk_off = w.nlse_off + align256(T * s->Hq * sizeof(float));
-  w.dv_off = w.dk_off + align256(part);
-  w.total = w.dv_off + align256(part);
+  w.dv_off = w.dk_off + w.part;
+  w.total = w.dv_off + w.part;
   return w;
+}
+
+// Further sets of dK / dV partials, behind everything else that a workspace holds (`base` bytes): as many as are worth having
+// for the problem, and as there is room for - a workspace of the base's size, say one made for a longer sequence, serves as well,
+// with a launch for each range of rows and the same results.
+size_t more_sets_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
+  const WsLayout w = ws_layout(tm, s);
+  return (size_t)(peagle::dkdv_part_sets(s->D, w.L64, s->Hq, row_ranges(tm, s->L)) - 1) * 2 * w.part;
+}
+struct MoreSets {
+  float* at = nullptr;
+  int sets = 1;  // all of them
+};
+MoreSets more_sets(const peagle_tilemap_t* tm, const peagle_shape_t* s, void* workspace, size_t ws_bytes, size_t base) {
+  const size_t want = more_sets_bytes(tm, s), room = ws_bytes - base;
+  MoreSets m;
+  m.at = (float*)((char*)workspace + base);
+  m.sets = 1 + (int)((want < room ? want : room) / (2 * ws_layout(tm, s).part));
+  return m;
 }
 
 int check_shape(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
@@ -59,6 +92,7 @@ struct SharedForm {
   const void* v_shared = nullptr;  // [Hkv, D]: the value row of every chain key
   float* dk_part = nullptr;        // per-wave sums of the chain keys' dK / dV, see BwdParams
   float* dv_part = nullptr;
+  size_t ws_base = 0;              // what this form's workspace holds before further sets of partials
   bool fwd_reads_v_tensor = false;  // `v` is a full [T, Hkv, D] tensor: the forward does not need v_shared
 };
 
@@ -94,7 +128,7 @@ FwdParams make_fwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const Se
 
 BwdParams make_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const SegRange& sr, const void* q,
                    const void* k, const void* v, const void* o, const void* d_o, const float* lse, void* dq,
-                   float* dk_acc, float* dv_acc, void* workspace, int chain_accumulate,
+                   float* dk_acc, float* dv_acc, void* workspace, const MoreSets& more, int chain_accumulate,
                    const float* rope_table = nullptr, const SharedForm& sf = SharedForm()) {
   const WsLayout w = ws_layout(tm, s);
   BwdParams p{};
@@ -114,6 +148,9 @@ BwdParams make_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const Se
   p.nlse = (float*)((char*)workspace + w.nlse_off);
   p.dk_part = (float*)((char*)workspace + w.dk_off);
   p.dv_part = (float*)((char*)workspace + w.dv_off);
+  p.part_more = more.at;
+  p.part_stride = w.part / sizeof(float);
+  p.part_sets = more.sets;
   p.tm = tm->dview;
   p.L = s->L;
   p.T = (int)tokens_of(tm, s);
@@ -155,7 +192,7 @@ RopeWs rope_ws(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
 
 extern "C" size_t peagle_workspace_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* shape) {
   if (check_shape(tm, shape) != PEAGLE_OK) return 0;
-  return ws_layout(tm, shape).total;
+  return ws_layout(tm, shape).total + more_sets_bytes(tm, shape);
 }
 
 extern "C" int peagle_attn_fwd(const peagle_tilemap_t* tm, const peagle_shape_t* shape, int32_t seg, const void* q,
@@ -182,15 +219,18 @@ extern "C" int peagle_attn_bwd(const peagle_tilemap_t* tm, const peagle_shape_t*
   SegRange sr;
   rc = peagle::resolve_segment(tm, shape->L, seg, &sr);
   if (rc != PEAGLE_OK) return rc;
-  if (!workspace || ws_bytes < ws_layout(tm, shape).total) return PEAGLE_EWORKSPACE;
+  const size_t base = ws_layout(tm, shape).total;
+  if (!workspace || ws_bytes < base) return PEAGLE_EWORKSPACE;
   if (tm->device < 0) return PEAGLE_ENODEVICE;
-  const BwdParams p = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, accumulate);
+  const BwdParams p = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace,
+                               more_sets(tm, shape, workspace, ws_bytes, base), accumulate);
   const int acc_below = accumulate ? INT_MAX : 0;
   hipStream_t st = (hipStream_t)stream;
   const bool one_grid = peagle::backward_in_one_grid(shape->D, p.mean_tiles, sr.rt_hi - sr.rt_lo, shape->Hq, false, false);
   const hipError_t e = one_grid ? peagle::launch_row_terms(p, st) : peagle::launch_dq(p, shape->D, st);
   if (e != hipSuccess) return PEAGLE_EHIP;
-  return peagle::launch_dkdv(p, shape->D, sr.key_lo, sr.a_hi, acc_below, one_grid, st) == hipSuccess ? PEAGLE_OK : PEAGLE_EHIP;
+  peagle::DkdvLauncher dkdv(p, shape->D, one_grid, st);
+  return dkdv.add(p, sr.key_lo, sr.a_hi, acc_below) == hipSuccess && dkdv.finish() == hipSuccess ? PEAGLE_OK : PEAGLE_EHIP;
 }
 
 static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, int32_t seg_begin, int32_t seg_end,
@@ -224,8 +264,10 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
   }
   // Forward and dQ own their rows and the segments' row tiles follow one another, so each runs as one launch over all
   // segments of the call: a launch of its own per segment leaves the chip filling and draining eight times instead of
-  // once (8,192 anchors in eight segments: fwd 4,419 -> 4,290, dQ 6,360 -> 6,245 us per step).  dK/dV run segment by segment, in order.
-  SegRange rows;
+  // once (8,192 anchors in eight segments: fwd 4,419 -> 4,290, dQ 6,360 -> 6,245 us per step).  dK/dV are summed segment
+  // by segment, in order.
+  const MoreSets more = more_sets(tm, shape, workspace, ws_bytes, sf.ws_base ? sf.ws_base : ws_need);
+  SegRange rows{};
   int32_t n_seg = 0;
   for (int32_t s = seg_begin; s < seg_end; ++s) {
     SegRange sr;
@@ -248,18 +290,21 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
       fp.nlse = (float*)((char*)workspace + w.nlse_off);
     }
     if (peagle::launch_fwd(fp, shape->D, st, timer) != hipSuccess) return PEAGLE_EHIP;
-    const BwdParams bp = make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, 0, rope_table, sf);
+    const BwdParams bp = make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, 0, rope_table, sf);
     if (!one_grid && peagle::launch_dq(bp, shape->D, st, timer) != hipSuccess) return PEAGLE_EHIP;
   }
+  peagle::DkdvLauncher dkdv(make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, 0, rope_table, sf),
+                            shape->D, one_grid, st, timer);
   for (int32_t s = seg_begin; s < seg_begin + n_seg; ++s) {
     SegRange sr;
     rc = peagle::resolve_segment(tm, shape->L, s, &sr);
     if (rc != PEAGLE_OK) return rc;
     // Depth-0 keys below the segment start already hold earlier segments' sums: add to them.
     // Keys first seen by this segment (its own depth-0 range and its chains) are overwritten.
-    const BwdParams bp = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, 0, rope_table, sf);
-    if (peagle::launch_dkdv(bp, shape->D, sr.key_lo, sr.a_hi, sr.a_lo, one_grid, st, timer) != hipSuccess) return PEAGLE_EHIP;
+    const BwdParams bp = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, 0, rope_table, sf);
+    if (dkdv.add(bp, sr.key_lo, sr.a_hi, sr.a_lo) != hipSuccess) return PEAGLE_EHIP;
   }
+  if (dkdv.finish() != hipSuccess) return PEAGLE_EHIP;
   if (seg_end == tm->S || tm->seg_bounds[seg_end] >= shape->L) {
     const size_t n = tokens_of(tm, shape) * shape->Hkv * shape->D;
     if (dk_bf16 && peagle::launch_cast_bf16(dk_acc, dk_bf16, n, st) != hipSuccess) return PEAGLE_EHIP;
@@ -335,7 +380,7 @@ extern "C" int peagle_rope_rotate(const peagle_tilemap_t* tm, const peagle_shape
 
 extern "C" size_t peagle_rope_workspace_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* shape) {
   if (check_shape(tm, shape) != PEAGLE_OK) return 0;
-  return rope_ws(tm, shape).total;
+  return rope_ws(tm, shape).total + more_sets_bytes(tm, shape);
 }
 
 extern "C" int peagle_attn_step_partitioned_rope(const peagle_tilemap_t* tm, const peagle_shape_t* shape,
@@ -373,7 +418,7 @@ SharedWs shared_ws(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
 
 extern "C" size_t peagle_rope_shared_workspace_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* shape) {
   if (check_shape(tm, shape) != PEAGLE_OK) return 0;
-  return shared_ws(tm, shape).total;
+  return shared_ws(tm, shape).total + more_sets_bytes(tm, shape);
 }
 
 extern "C" int peagle_attn_step_rope_shared(const peagle_tilemap_t* tm, const peagle_shape_t* shape, const void* q,
@@ -412,6 +457,7 @@ extern "C" int peagle_attn_step_rope_shared(const peagle_tilemap_t* tm, const pe
   sf.v_shared = v_shared;
   sf.dk_part = (float*)(ws + sw.pk_off);
   sf.dv_part = (float*)(ws + sw.pv_off);
+  sf.ws_base = sw.total;
   const void* v_arg = v0;
   if (shape->D != 64) {
     // (this size's forward and dQ kernels read every V row from a tensor: expand V for them)

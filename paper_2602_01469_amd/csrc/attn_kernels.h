@@ -27,6 +27,18 @@ struct FwdParams {
   float* nlse;
 };
 
+// Row tiles whose sums over the depth-0 keys make one set of partials (a segment, or a chunk of a long one), and the work on
+// those keys; filled by the launcher.
+struct DkdvRange {
+  int rt_lo, rt_hi, s_lo, s_hi;
+  int clip_rows;              // [rt_lo, rt_hi) covers only part of the segments s_lo..s_hi
+  int d0_tile_lo, n_d0_tiles; // depth-0 key tiles visible to the rows are [d0_tile_lo, n_d0_tiles)
+  int d0_split, d0_step;      // their pairs are dealt in passes, [0, d0_split) then d0_step at a time
+  int first_item;             // of the launch's work items, INT_MAX: no such range
+  int set;                    // of partials
+};
+constexpr int kMaxRanges = 4;  // of one launch
+
 struct BwdParams {
   const __bf16* q;
   const __bf16* k;
@@ -39,18 +51,18 @@ struct BwdParams {
   float* dv_acc;
   float* delta;        // workspace [Hq, T]: -rowsum(dO * O), written by the dQ kernel or, for one grid, before it
   float* nlse;         // workspace [Hq, T]: -lse / scale, likewise
-  float* dk_part;      // workspace [Hq, L64, D]: per-query-head dK of the depth-0 keys
+  float* dk_part;      // workspace [Hq, L64, D]: per-query-head dK of the depth-0 keys, of the first range of rows of a launch
   float* dv_part;
+  float* part_more;    // workspace [part_sets - 1][dK, dV][part_stride]: of the others
+  size_t part_stride;
+  int part_sets;       // as many ranges of rows as one launch may take
   DeviceTileMap tm;
   int L, T, Hq, Hkv, L64;
   int rt_lo, rt_hi;
   int s_lo, s_hi, cropped;  // segment boundary indices of the row range; cropped: rt_hi cuts the last segment short
-  int n_d0_items;       // filled by the launcher: depth-0 work items (key-tile pairs x query heads)
+  int n_d0_items;       // filled by the launcher: depth-0 work items (key-tile pairs x query heads) of all ranges
   int n_chain_items;    // filled by the launcher: chain work items; dQ's, where it shares the grid, come behind
-  int n_d0_tiles;       // filled by the launcher: depth-0 key tiles visible to the segment are [d0_tile_lo, n_d0_tiles)
-  int d0_tile_lo;
-  int clip_rows;        // filled by the launcher: [rt_lo, rt_hi) covers only part of the segments s_lo..s_hi
-  int d0_split, d0_step;  // filled by the launcher: depth-0 pairs are dealt in passes, [0, d0_split) then d0_step at a time
+  int clip_rows;        // filled by the launcher, as in DkdvRange: of all rows, for the chain items
   int near_rows;        // Q-shaped tensors and the [Hq, T] statistics span less than 4 GiB: row copies may use 32-bit offsets
   int mean_tiles;       // as in FwdParams
   int chain_accumulate; // chain keys: add to dk_acc/dv_acc instead of overwriting
@@ -64,6 +76,7 @@ struct BwdParams {
   const __bf16* v_shared;
   float* shared_dk_part;
   float* shared_dv_part;
+  DkdvRange range[kMaxRanges];  // filled by the launcher, in the order of their items
 };
 
 // Inference-side drafting step (Sec. 2 of the paper: all K draft positions in one forward pass): the K
@@ -111,11 +124,34 @@ bool backward_in_one_grid(int D, int mean_tiles, int n_row_tiles, int Hq, bool t
 hipError_t launch_row_terms(const BwdParams& p, hipStream_t stream);
 // dQ of the row range, and the per-row terms that dK/dV consumes.
 hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer* timer = nullptr);
-// dK/dV of one segment.  a_hi: end anchor of the segment (depth-0 keys [0, a_hi) are visible); depth-0 keys with
-// anchor below acc_below are added to dk_acc/dv_acc, the others overwritten.  with_dq (backward_in_one_grid()): dQ of the same
-// rows too.
-hipError_t launch_dkdv(const BwdParams& p, int D, int key_lo, int a_hi, int acc_below, bool with_dq, hipStream_t stream,
-                       KernelTimer* timer = nullptr);
+// dK/dV of segments, in order.  Up to part_sets ranges of rows - segments, or chunks of a long one - share a launch, and the
+// sum of their partials is taken range by range, as if each had been launched by itself.  with_dq (backward_in_one_grid()): dQ
+// of the same rows too.
+class DkdvLauncher {
+ public:
+  // p: everything but the rows
+  DkdvLauncher(const BwdParams& p, int D, bool with_dq, hipStream_t stream, KernelTimer* timer = nullptr)
+      : p_(p), D_(D), with_dq_(with_dq), stream_(stream), timer_(timer) {}
+  // Segment of the row tiles and segment boundaries in `rows`; key_lo: first depth-0 key it sees; a_hi: its end anchor
+  // (depth-0 keys [key_lo, a_hi) are visible); depth-0 keys with anchor below acc_below are added to dk_acc/dv_acc, the
+  // others overwritten.
+  hipError_t add(const BwdParams& rows, int key_lo, int a_hi, int acc_below);
+  hipError_t finish();  // launches what is left
+
+ private:
+  hipError_t add_range(int rt_lo, int rt_hi, const BwdParams& rows, bool clip, int key_lo, int a_hi, int acc_below);
+  BwdParams p_;
+  const int D_;
+  const bool with_dq_;
+  const hipStream_t stream_;
+  KernelTimer* const timer_;
+  int n_ = 0;                      // ranges waiting
+  DkdvRange range_[kMaxRanges];    // ... by set
+  int key_end_[kMaxRanges], acc_below_[kMaxRanges];
+};
+// Sets of partials worth having for a problem of n_ranges ranges of rows in all: several where a range's work items leave
+// slots idle.
+int dkdv_part_sets(int D, int L64, int Hq, int n_ranges);
 // Dense bf16 MFMA issue loop on every CU: the measured matrix-core ceiling of the device, in TFLOP/s, on
 // constant small-integer operands or on changing pseudo-random ones (the chip clocks lower under the latter).
 hipError_t measure_mfma_ceiling(hipStream_t stream, bool random_operands, float* tflops);

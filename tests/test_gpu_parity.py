@@ -1119,6 +1119,50 @@ def test_backward_as_one_grid_gives_the_bits_of_kernels_launched_apart(form, D, 
             assert torch.equal(step[n], calls[n]), n
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("form", ["six_segments", "cropped", "chunks", "sampled", "packed", "rope"])
+def test_segments_that_share_a_launch_give_the_bits_of_one_launch_each(form, D):
+    """Few heads: up to four segments (or chunks of a long one) share a launch and the sum of its partials; in a workspace with
+    room for one set of partials each has a launch and a sum of its own, as it has when a caller steps segment by segment."""
+    print(f"case shared launch {form} D={D}", flush=True)
+    K, L, Hq, Hkv = (32, 530, 2, 1) if form == "chunks" else (8, 1000, 4, 2)
+    bounds = [0, 520, 530] if form == "chunks" else [0, 160, 320, 336, 640, 800, 1000]
+    Lc = 650 if form == "cropped" else L                 # (ends inside the fifth segment)
+    if form == "sampled":
+        from peagle_inputs import cod_depth_counts
+        build = lambda b: pe.peagle_build_tilemap_sampled(cod_depth_counts(L, K, 0.8, 351), K, b, device=0)
+    elif form == "packed":
+        build = lambda b: pe.peagle_build_tilemap_packed([300, 33, 467, 200], K, None, b, device=0)
+    else:
+        build = lambda b: pe.peagle_build_tilemap(L, K, b, device=0)
+    tm, S = build(bounds), len(bounds) - 1
+    shape, T, rope = pe.Shape(Lc, K, Hq, Hkv, D), tm.tokens(Lc), form == "rope"
+    need = pe.peagle_rope_workspace_bytes if rope else pe.peagle_workspace_bytes
+    g = torch.Generator(device="cuda").manual_seed(349)
+    q, k, v, d_o = (torch.randn(T, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq))
+    table = torch.empty((pe.peagle_rope_positions(tm, Lc), 2, D // 2), device="cuda")
+    pe.peagle_rope_table(1e4, D, table.shape[0], table)
+
+    def results(n_bytes, steps):
+        ws = torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda")  # (NaN)
+        out = [torch.zeros_like(q), torch.zeros((Hq, T), device="cuda"), torch.zeros_like(q),
+               *(torch.full((T, Hkv, D), float("nan"), device="cuda") for _ in range(2))]
+        for a, b in steps:
+            if rope:
+                pe.peagle_attn_step_partitioned_rope(tm, shape, a, b, q, k, v, d_o, table, *out, None, None, ws)
+            else:
+                pe.peagle_attn_step_partitioned(tm, shape, a, b, q, k, v, d_o, *out, None, None, ws)
+        torch.cuda.synchronize()
+        return out
+
+    one_set = need(build(None), shape) if form != "chunks" else need(tm, shape) - 2 * 2 * Hq * 576 * D * 4
+    assert one_set < need(tm, shape)
+    want = results(one_set, [(s, s + 1) for s in range(S)])
+    for n_bytes in (need(tm, shape), one_set):
+        for got, ref in zip(results(n_bytes, [(0, S)]), want):
+            assert torch.isfinite(got).all() and torch.equal(got, ref)
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(2, 1), (64, 32)])
 def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
     """Six hundred anchors alone (short lists, at many heads the plain dQ kernel) and packed in front of a sequence of five
