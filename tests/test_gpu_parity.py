@@ -1119,6 +1119,27 @@ def test_backward_as_one_grid_gives_the_bits_of_kernels_launched_apart(form, D, 
             assert torch.equal(step[n], calls[n]), n
 
 
+@pytest.mark.parametrize("qscale", [1.0, 12.0, 40.0])
+@pytest.mark.parametrize("form", ["dense", "k7", "packed", "sampled"])
+def test_plain_dq_kernel_gives_the_bits_of_the_one_grid(form, qscale):
+    """Short lists and more than 4,096 dQ workgroups in one step - the plain dQ kernel, before dK/dV - against calls of one key /
+    value head's group each, which run dQ and dK/dV as one grid."""
+    print(f"case plain dq against one grid {form} qscale={qscale}", flush=True)
+    tm, L, K = _map_of(form)
+    T, Hq, Hkv, D = tm.tokens(L), 96, 48, 64
+    assert runs_plain_dq(tm, Hq) and tm.info()["n_row_tiles"] * Hq > 4096
+    g = torch.Generator(device="cuda").manual_seed(343)
+    rnd = lambda H, f=1.0: (torch.randn(T, H, D, generator=g, device="cuda") * f).to(torch.bfloat16)
+    q, k, v, d_o = rnd(Hq, qscale), rnd(Hkv), rnd(Hkv), rnd(Hq)
+    whole = _heads_run(tm, L, K, q, k, v, d_o)
+    for h in range(0, Hkv, 23):
+        a, b = slice(2 * h, 2 * h + 2), slice(h, h + 1)
+        part = _heads_run(tm, L, K, q[:, a].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(), d_o[:, a].contiguous())
+        for n, t in part.items():
+            assert torch.isfinite(t).all(), n
+            assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("form", ["six_segments", "cropped", "chunks", "sampled", "packed", "rope"])
 def test_segments_that_share_a_launch_give_the_bits_of_one_launch_each(form, D):

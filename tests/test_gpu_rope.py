@@ -414,6 +414,15 @@ def test_shared_chain_vectors_give_the_same_bits_from_both_dq_kernels():
     _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, 3090, range(0, Hkv, 6))
 
 
+def test_shared_chain_vectors_give_the_same_bits_from_the_plain_dq_kernel_and_the_one_grid():
+    """More than 4,096 dQ workgroups (the plain dQ kernel, before dK/dV) against one group at a time (one grid)."""
+    L, K, Hq, Hkv, D = 1500, 4, 96, 48, 64
+    print("case rope shared plain dq against one grid", flush=True)
+    tm = pe.peagle_build_tilemap(L, K, [0, 640, 1500], device=0)
+    assert runs_plain_dq(tm, Hq) and tm.info()["n_row_tiles"] * Hq > 4096
+    _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, 3095, range(0, Hkv, 23))
+
+
 @pytest.mark.parametrize("Hq,form", [(8, "two heads, two per CU"), (16, "two heads, three per CU")])
 def test_shared_chain_vectors_give_the_same_bits_from_every_forward(Hq, form):
     """Two-head workgroups of the forward that reads the shared value vector against one-head ones (each group alone)."""
