@@ -76,6 +76,43 @@ def test_full_row_tiles_of_dkdv_wait_for_no_load(code_objects):
     assert quiet == {f: 1 if f[0] in "03" else 2 for f in forms}
 
 
+def _tile_loops(disassembly):
+    """(kernel, instructions) of every innermost loop that holds at least 16 matrix instructions."""
+    kernel, start, code = "", 0, []
+    for line in disassembly.splitlines() + ["0 <end>:"]:
+        label = re.match(r"^([0-9a-f]+) <(\S+)>:", line)
+        if label:
+            back = set()
+            for at, text, target in code:
+                to = re.search(r"<\S+?\+0x([0-9a-f]+)>", target) if re.match(r"s_c?branch", text) else None
+                if to and start + int(to.group(1), 16) <= at:
+                    back.add((start + int(to.group(1), 16), at))
+            inner = []
+            for lo, hi in sorted(back, key=lambda r: r[1] - r[0]):
+                body = [text for at, text, _ in code if lo <= at <= hi]
+                if sum(x.startswith("v_mfma") for x in body) < 16 or any(lo <= a and b <= hi for a, b in inner):
+                    continue
+                inner.append((lo, hi))
+                yield kernel, body
+            start, kernel, code = int(label.group(1), 16), label.group(2), []
+        else:
+            m = re.match(r"\t(.*?)\s*// ([0-9A-F]+):?(.*)$", line)
+            if m:
+                code.append((int(m.group(2), 16), m.group(1), m.group(3)))
+
+
+def test_no_loop_over_tiles_loads_a_parameter(code_objects):
+    """Where one of two parameters is chosen, the compiler may choose between their addresses and load the result at each
+    use.  A scalar load in the loop over tiles makes the wait for it a wait for every LDS read in flight."""
+    seen = set()
+    for co in code_objects:
+        for kernel, body in _tile_loops(_tool("llvm-objdump", "-d", "--no-show-raw-insn", co)):
+            seen.add(kernel)
+            assert not [x for x in body if x.startswith("s_load")], kernel
+    for name in ("fwd_kernel", "dq_kernel", "dq_pipe_kernel", "dkdv_kernel", "bwd_kernel", "draft_decode_kernel"):
+        assert any(name in k for k in seen), name
+
+
 def test_no_kernel_spills(code_objects):
     """No kernel keeps registers in scratch memory: a reload inside a loop waits for the copies issued before it."""
     spilling, seen = {}, 0
