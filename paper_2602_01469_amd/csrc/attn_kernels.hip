@@ -469,7 +469,7 @@ __device__ __forceinline__ void fwd_tile_masked(const char* kt_lds, const char* 
 }
 
 template <int D, int NH, bool SV, int PER_SIMD>
-__global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_kernel(FwdParams p) {  // (one head: LDS has room for four)
   // Three workgroups per CU leave 168 registers: what only masked tiles and the last stores need is computed there.
   constexpr bool LEAN = PER_SIMD == 3;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
@@ -533,18 +533,20 @@ __global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
     }
     TileEntry cur = const_entry(tm.row_entries, e0);
     TileEntry nxt = const_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
+    const TileEntry masked = const_entry(tm.row_entries, e_lead < e1 ? e_lead : e0);
     if (!SAFE || LEAN) load_q();  // (lean: not held over the stores of the first pass)
     dma_key_tile<D, 4, SV, LEAN>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
-    dma_tile_mask(mask_lds, tm, cur, wave);
+    // (The first bitmask, if there is one, travels with the first tile, to where its own tile finds it: the loop over full tiles
+    // then has no test for one in front of its matrix instructions.  With the test / without, CU busy cycles of 10,816 anchors
+    // at D = 128 3.13e9 / 3.09e9; us of 20,480 anchors 23,720 / 23,600.  Not so in dq_item: 4.48e9 / 4.50e9 cycles.)
+    dma_tile_mask(mask_lds + ((e_lead - e0) & 1) * kTileMaskBytes, tm, masked, wave);
     dma_publish();
     // A row tile's list holds its full tiles first, then the partial ones: two loops (accumulators stay in place).
     int e = e0;
     auto full_tile = [&](int buf) {
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
-      if (e + 1 < e1) {
+      if (e + 1 < e1)
         dma_key_tile<D, 4, SV, LEAN>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
-        dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
-      }
       const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
       fwd_tile<D, NH, false, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       dma_publish();
@@ -984,6 +986,8 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
   TileEntry t_cur = const_entry(tm.row_entries, e0);
   TileEntry t_n1 = const_entry(tm.row_entries, entry_at(e0 + 1));
   TileEntry t_n2 = const_entry(tm.row_entries, entry_at(e0 + 2));
+  const TileEntry masked0 = const_entry(tm.row_entries, entry_at(e0 + n_lead));  // the first two with a bitmask, if there are any
+  const TileEntry masked1 = const_entry(tm.row_entries, entry_at(e0 + n_lead + 1));
 
   // The K half of the buffer that the first pipelined body reads its (absent) predecessor from: that body
   // multiplies it by dS = 0, so it only has to be finite.
@@ -1005,13 +1009,12 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
     }
   }
 
-  // the first two tiles are on their way before anything is computed
+  // the first two tiles are on their way before anything is computed, and the first two bitmasks, to where their tiles find them:
+  // the pipeline then has no test for one (with / without, us: 20,480 anchors 34,970 / 34,780, 8,000 5,690 / 5,657)
   dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, t_cur.tile, p.L, wave, lane, p.v_shared);
-  dma_tile_mask(mask_lds, tm, t_cur, wave);
-  if (e0 + 1 < e1) {
-    dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
-    dma_tile_mask(mask_lds + kTileMaskBytes, tm, t_n1, wave);
-  }
+  if (e0 + 1 < e1) dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
+  dma_tile_mask(mask_lds + n_lead % 3 * kTileMaskBytes, tm, masked0, wave);
+  dma_tile_mask(mask_lds + (n_lead + 1) % 3 * kTileMaskBytes, tm, masked1, wave);
 
   if (TERMS) {
     float dl = 0.f;
@@ -1071,10 +1074,7 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
       // Every wave has left tile e-1 (its last reader was the body above) and has waited for its own copies of
       // tile e+1: after the barrier that buffer may be overwritten and tile e+1 may be read.
       dma_publish();
-      if (e + 2 < e1) {
-        dma_key_tile<D, 4, SV>(kl.k(BP), kl.v(BP), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
-        dma_tile_mask(mask_lds + BP * kTileMaskBytes, tm, t_n2, wave);
-      }
+      if (e + 2 < e1) dma_key_tile<D, 4, SV>(kl.k(BP), kl.v(BP), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
       dq_pipe_body<D, 1, LAST>(P, lds[B][0], lds[BN][0], lds[BN][1], lds[B][0], no, to, qf, dof, dq, ndelta16, c);
       t_cur = t_n1;
       t_n1 = t_n2;
@@ -1112,7 +1112,7 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
       const int buf2 = buf == 0 ? 2 : buf - 1;
       if (e + 2 < e1) {
         dma_key_tile<D, 4, SV>(kl.k(buf2), kl.v(buf2), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
-        dma_tile_mask(mask_lds + buf2 * kTileMaskBytes, tm, t_n2, wave);
+        if (MASKED) dma_tile_mask(mask_lds + buf2 * kTileMaskBytes, tm, t_n2, wave);
       }
       const char* kt_lds = lds[0][0] + buf * (2 * kTileBytes);
       const char* vt_lds = kt_lds + kTileBytes;

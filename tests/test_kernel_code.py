@@ -113,6 +113,18 @@ def test_no_loop_over_tiles_loads_a_parameter(code_objects):
         assert any(name in k for k in seen), name
 
 
+def test_full_tiles_copy_no_bitmask(code_objects):
+    """The forward and the pipelined dQ kernel run a list's full tiles in a loop that copies whole K / V tiles (16 bytes a
+    lane; at least two tiles' or both forms' copies) and neither tests for nor copies a bitmask (4 bytes a lane)."""
+    seen = {}
+    for co in code_objects:
+        for kernel, body in _tile_loops(_tool("llvm-objdump", "-d", "--no-show-raw-insn", co)):
+            wide, narrow = (sum(x.startswith(f"global_load_lds_dword{w} ") for x in body) for w in ("x4", ""))
+            if re.search("fwd_kernel|dq_pipe_kernel", kernel) and wide >= 16 and sum(x.startswith("v_mfma") for x in body) >= 32:
+                seen[kernel] = seen.get(kernel, 0) + narrow
+    assert len(seen) == 9 and not any(seen.values()), seen
+
+
 def test_no_kernel_spills(code_objects):
     """No kernel keeps registers in scratch memory: a reload inside a loop waits for the copies issued before it."""
     spilling, seen = {}, 0
