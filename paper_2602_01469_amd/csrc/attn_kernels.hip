@@ -180,7 +180,7 @@ __device__ __forceinline__ void dma_key_tile(uint32_t kd, uint32_t vd, const __b
 // loaded to a register where the tile is computed is waited for behind the next tile's copies, because a wave's accesses
 // complete in order: nothing of them was hidden in a masked tile, three of every row tile, or in any iteration of a chain
 // tile in the dK/dV kernel.  us, so / from LDS: packed 203 to 900 anchors, 64 heads 767 / 745, eight sequences 3,138 / 3,111,
-// L = 411 120 / 117.5, L = 1,391 722 / 713; L = 20,480 the same.)
+// L = 411 120 / 117.5, L = 1,391 722 / 713; L = 20,480 the same, without a test for a mask in the loops over full tiles.)
 constexpr int kTileMaskBytes = kRowsPerTile * kMaskWordsPerRow * 4;
 __device__ __forceinline__ void dma_tile_mask(uint32_t mask_lds, const DeviceTileMap& tm, const TileEntry& en, int wave) {
   if (en.mask_id < 0) return;
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
   // together, here and in the backward's kernels: lookups go through the scalar path (a vector load that is waited for waits
   // for the rows' loads before it), several at a time, and the rows are loaded without a branch for each.  us per step, one by
   // one / so, 64 heads: packed 203 to 517 anchors 322 / 304, 203 to 900 745 / 713, eight packed sequences 3,111 / 3,056,
-  // L = 1,391 712 / 695, L = 4,096 4,893 / 4,861, L = 20,480 106.5 / 106.3 ms.
+  // L = 1,391 713 / 709; long lists the same (L = 4,096 4,931 / 4,924, L = 20,480 109.1 / 109.0 ms).
   const int e0 = const_int(tm.row_ptr, rt), e1 = const_int(tm.row_ptr, rt + 1);
   const int e_lead = e0 + const_int(tm.row_lead, rt);  // end of the leading run of full tiles
   const int r = wave * 32 + ln;  // row of the tile owned by this lane (shared with lane^32)
@@ -1161,10 +1161,10 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
   }
 }
 
-template <int D, bool SV>
+template <int D>
 __global__ __launch_bounds__(256, 2) void dq_pipe_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(16))) char lds[kDqPipeLds<D>];
-  dq_pipe_item<D, SV, true>(p, lds, blockIdx.x);
+  dq_pipe_item<D, false, true>(p, lds, blockIdx.x);
 }
 
 // =====================================================================================
@@ -2623,32 +2623,34 @@ hipError_t launch_dq(const BwdParams& p, int D, hipStream_t stream, KernelTimer*
   // no registers to spare (that instantiation spilled three times as much and ran 25 % slower), so there the
   // caller passes an expanded V in `v` for it; the dK/dV kernel takes the shared vector at either size.
   const bool sv = p.v_shared != nullptr && D == 64;
-  // D = 64: the plain kernel where the lists are short and the workgroups many - two full rounds of the three per CU
-  // that it runs -, the pipelined one elsewhere; a row's dQ has the same bits from both.  One launch in either case: the
-  // row tiles of one launch split between the two kernels by list length ran one launch after the other, each leaving
-  // the chip to drain (2,048 anchors, K = 4, 4 heads: 66 us).  us, pipelined / plain, by mean list length (workgroups):
-  // many workgroups, L = 411, 64 heads (6; 1,664) 57 / 52, L = 1,391, 64 heads (14; 5,568) 289 / 262, L = 1,000, 32
-  // heads (11; 2,016) 91 / 85, L = 2,048, 16 heads (19; 2,048) 132 / 128, packed to L = 6,420, 4 heads (12; 1,612) 90 /
-  // 83; few, L = 1,000, 4 heads (11; 252) 24 / 29, 16 heads (11; 1,008) 49 / 54, L = 2,048, K = 4, 16 heads (18; 1,024)
-  // 73 / 75, L = 3,000, 8 heads (26; 1,504) 131 / 132; long lists, L = 4,096, 16 heads (35; 4,096) 422 / 427, 64 heads
-  // (35; 16,384) 1,666 / 1,646, L = 8,000, 4 heads (65; 2,000) 376 / 392, sampled 8,192 (67) 3,195 / 3,277.
+  // D = 64: the plain kernel where the lists are short, the pipelined one elsewhere; a row's dQ has the same bits from both.  What
+  // runs as one grid with dK/dV (backward_in_one_grid()) does not come here: a step does with short lists and more than 4,096
+  // workgroups - the plain kernel -, a backward called by itself with more than 3,072, and a step timed kernel by kernel, which
+  // alone has few (below two full rounds of the plain kernel's three per CU it shows the pipelined one, as the one grid runs).
+  // One launch: the row tiles of one split between the two kernels by list length ran one after the other, each leaving the
+  // chip to drain (2,048 anchors, K = 4, 4 heads: 66 us).  us, pipelined / plain, by mean list length (workgroups): L = 1,391, 64
+  // heads (14; 5,568) 289 / 262; L = 4,096, 16 heads (35; 4,096) 422 / 427, 64 heads (35; 16,384) 1,666 / 1,646, sampled 8,192
+  // (67) 3,195 / 3,277.  (The first-layer form comes here with short lists only.)
   const int n_wg = n_rt * p.Hq;  // one query head per workgroup
-  const bool plain = p.mean_tiles <= kPlainMeanTiles && n_wg >= kPlainWorkgroups;
+  const bool plain = sv || (p.mean_tiles <= kPlainMeanTiles && n_wg >= kPlainWorkgroups);
   TimedSpan span(timer, kKindDq, stream);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(256), 0, stream, p); };
   if (D == 128) go(dq_kernel<128, false>);
   else if (plain) go(sv ? dq_kernel<64, true> : dq_kernel<64, false>);
-  else go(sv ? dq_pipe_kernel<64, true> : dq_pipe_kernel<64, false>);
+  else go(dq_pipe_kernel<64>);
   return span.finish();
 }
 
-// dK/dV and dQ as one grid, or dQ (which then also forms the per-row terms) before dK/dV?  At D = 64 one grid wherever dQ would run its pipelined kernel anyway, and with
-// short lists (where the plain one runs three workgroups per CU, and the one grid two) as long as workgroups are few enough
-// that unequal lists and the launches' ends cost more.  us per step, dQ first / one grid (mean list; dQ workgroups): 4 heads
-// L = 256, K = 4 46.9 / 36.8 (4; 32), L = 1,000 164 / 148 (11; 252), L = 4,096 693 / 634 (35; 1,024), L = 16,000 4,990 / 4,740
-// (128; 4,000), packed 396 / 338 (12; 1,612), 16 heads L = 2,048 458 / 394 (19; 2,048), 64 heads L = 411 148 / 120 (6; 1,664),
-// L = 700 258 / 236 (8; 2,816), L = 1,000 412 / 403 (11; 4,032), L = 4,096 4,858 / 4,793 (35; 16,384), L = 20,480 106.5 / 106.3
-// ms; but L = 1,391 709 / 716 (14; 5,568), eight packed sequences 3,156 / 3,344 (12; 12,896).
+// dK/dV and dQ as one grid, or dQ (which then also forms the per-row terms) before dK/dV?  At D = 64 one grid with long
+// lists, where dQ's half is the pipelined kernel (it gains at any number of workgroups: dQ's fill the end of dK/dV), and
+// with short lists (where the plain one runs three workgroups per CU, and the one grid two) as long as workgroups are few
+// enough that unequal lists and the launches' ends cost more.  us per step, dQ first / one grid (mean list; dQ workgroups):
+// 4 heads L = 256, K = 4 46.9 / 36.8 (4; 32), L = 1,000 164 / 148 (11; 252), L = 4,096 693 / 634 (35; 1,024), L = 16,000
+// 4,990 / 4,740 (128; 4,000), packed 396 / 338 (12; 1,612), 16 heads L = 2,048 458 / 394 (19; 2,048), 64 heads L = 411 148 /
+// 120 (6; 1,664), L = 700 258 / 236 (8; 2,816), L = 1,000 412 / 403 (11; 4,032), L = 3,000 2,657 / 2,611 (26; 12,032), L =
+// 4,096 4,749 / 4,670 (35; 16,384), L = 8,000 16.82 / 16.73 ms (65; 32,000), L = 16,000 65.04 / 64.80, L = 20,480 104.25 /
+// 103.84 (165; 81,920), in one segment 105.97 / 105.47, first-layer form L = 3,891 4,456 / 4,402, sampled 8,192 9,871 /
+// 9,821; but L = 1,391 709 / 716 (14; 5,568), eight packed sequences 3,156 / 3,344 (12; 12,896).
 // At D = 128 a dK/dV workgroup has a CU to itself, and in one grid dQ's have, too, of which two share one otherwise: where
 // there are few.  4 heads L = 256, K = 4 67 / 50.7 (32 dQ workgroups), L = 1,000 252 / 215 (252), L = 4,096 1,109 / 966 (1,024),
 // packed 630 / 504 (1,612), L = 8,000 2,770 / 2,719 (2,000), 32 heads L = 128 68.6 / 54.8 (256), L = 500 201 / 176 (1,024),
