@@ -57,13 +57,14 @@ def _matrix_stretches(disassembly):
 
 
 def test_full_row_tiles_of_dkdv_wait_for_no_load(code_objects):
-    """The D = 64 dK/dV kernel computes a row tile while the next one is copied to LDS: a stretch of matrix instructions that
+    """The D = 64 dK/dV items, in their own kernel and in one grid with dQ, compute a row tile while the next one is copied to
+    LDS: a stretch of matrix instructions that
     loads no register (the full row tiles, with the copies between their matrix instructions or issued before) must not wait
     for vector memory, which would be the next tile's copies."""
     riding, quiet = {}, {}
     for co in code_objects:
         for kernel, s in _matrix_stretches(_tool("llvm-objdump", "-d", "--no-show-raw-insn", co)):
-            rows = re.search(r"dkdv_kernelILi64ELi(\d)ELb(\d)E", kernel)
+            rows = re.search(r"(dkdv|bwd)_kernelILi64ELi(\d)ELb(\d)E", kernel)
             if not rows or any(re.match(r"(global|flat|scratch|buffer)_load(?!_lds)", x) for x in s):
                 continue
             seen = riding if any("_load_lds" in x for x in s) else quiet
@@ -71,9 +72,9 @@ def test_full_row_tiles_of_dkdv_wait_for_no_load(code_objects):
             assert not any("vmcnt" in x for x in s), kernel
     # with and without the shared vector: an unmasked body that copies in every form but the dense far one (1), and a masked
     # one (far: also the unmasked one) that does not; listed ones (2, 4) mask by the start of a sequence as well
-    forms = [(rows, sv) for rows in "01234" for sv in "01"]
-    assert riding == {f: 1 for f in forms if f[0] != "1"}
-    assert quiet == {f: 1 if f[0] in "03" else 2 for f in forms}
+    forms = [(kernel, rows, sv) for kernel in ("dkdv", "bwd") for rows in "01234" for sv in "01"]
+    assert riding == {f: 1 for f in forms if f[1] != "1"}
+    assert quiet == {f: 1 if f[1] in "03" else 2 for f in forms}
 
 
 def _tile_loops(disassembly):
