@@ -51,6 +51,8 @@ class Guarded:
     (333, 8, 4, 2, 64, [0, 160, 333]),        # L % 64 = 13, L % 16 = 13
     (130, 4, 2, 1, 128, None),                # two anchors past a key tile, D = 128
     (77, 3, 3, 3, 64, None),                  # odd K: a row tile holds 126 rows
+    (603, 8, 4, 2, 64, [0, 160, 320, 480, 603]),   # four sets of dK / dV partials, the last behind everything else
+    (530, 32, 2, 1, 128, [0, 520, 530]),      # three, two of them of one segment's chunks
 ])
 def test_training_step_stays_inside_its_buffers(L, K, Hq, Hkv, D, bounds):
     print(f"case guards step L={L} K={K} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
@@ -60,6 +62,9 @@ def test_training_step_stays_inside_its_buffers(L, K, Hq, Hkv, D, bounds):
     tm = pe.peagle_build_tilemap(L, K, bounds, device=0)
     shape = pe.Shape(L, K, Hq, Hkv, D)
     S = 1 if bounds is None else len(bounds) - 1
+    sets = {603: 4, 530: 3}.get(L, 1)
+    align = lambda n: (n + 255) // 256 * 256
+    assert pe.peagle_workspace_bytes(tm, shape) == 2 * align(T * Hq * 4) + sets * 2 * align(Hq * ((L + 63) // 64 * 64) * D * 4)
     g = Guarded()
     o = g.tensor("o", (T, Hq, D), torch.bfloat16)
     dq = g.tensor("dq", (T, Hq, D), torch.bfloat16)
