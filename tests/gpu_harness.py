@@ -77,9 +77,16 @@ def mean_list(tm):
     return (i["n_full"] + i["n_partial"]) / i["n_row_tiles"]
 
 
-def runs_plain_dq(tm, Hq):
-    """Which dQ kernel one launch over the whole map runs at D = 64 (short lists, many workgroups: the plain one)."""
-    return mean_list(tm) < 24 and tm.info()["n_row_tiles"] * Hq >= 2 * 3 * 256
+def dq_path(tm, Hq, call="step"):
+    """How a call over the whole map runs dQ at D = 64, by the launchers' rules: as "one grid" with dK/dV (dQ's half of it is
+    the pipelined form), or before it by the "plain" or the "pipelined" kernel.  call: "step", a "backward" by itself, or a
+    "profiled" step."""
+    i = tm.info()
+    n = i["n_row_tiles"]
+    mean, workgroups = (i["n_full"] + i["n_partial"] + n // 2) // n, n * Hq
+    if call == "step" and (mean > 24 or workgroups <= 16 * 256) or call == "backward" and workgroups <= 12 * 256:
+        return "one grid"
+    return "plain" if mean <= 24 and workgroups >= 2 * 3 * 256 else "pipelined"
 
 
 def fwd_form(tm, Hq, Hkv):

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2602_01469_amd as pe
-from gpu_harness import Run, bf16_to_f64, fwd_form, max_abs, mean_list, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
+from gpu_harness import Run, bf16_to_f64, dq_path, fwd_form, max_abs, mean_list, rand_bits, rel_l2, to_dev_bf16
 from oracle import peagle_oracle as orc
 from peagle_inputs import CONFIGS, bf16_bits_to_f64, make_inputs
 
@@ -198,15 +198,16 @@ def test_two_heads_per_forward_workgroup_match_oracle(Hq, Hkv):
         _check_against_oracle(part, _oracle(qb[:, a], kb[:, b], vb[:, b], dob[:, a], L, K, r.shape.scale), f"two heads, group {h}")
 
 
-@pytest.mark.parametrize("L,Hq", [(600, 4), (2000, 4), (2000, 36)])
+@pytest.mark.parametrize("L,Hq", [(600, 4), (2000, 4), (2000, 52)])
 @pytest.mark.parametrize("qscale", [10.0, 12.0, 40.0])
 def test_large_logits_take_the_running_max_path(qscale, L, Hq):
     """Scores far outside the exponent range that the forward's first pass (reference max fixed at
     0) can hold: the kernel must detect it and redo the row tile with the running-max form, with one head
-    per workgroup and (36 heads) with two.  The dQ kernel leaves its probabilities unnormalised only
+    per workgroup and (52 heads) with two.  The dQ kernel leaves its probabilities unnormalised only
     while |lse| <= 64 in log2 units: at the smaller scales some workgroups are inside that range and some
     outside, at the largest none is inside.  Both sequences are long enough for the pipelined kernel's
-    groups of three full tiles to occur; 36 heads take the plain one.  The first two KV heads against the oracle."""
+    groups of three full tiles to occur in the one grid; 52 heads take the plain kernel.  The first two KV heads against the
+    oracle."""
     K, Hkv, D = 4, Hq // 2, 64
     print(f"case large_logits qscale={qscale} L={L} Hq={Hq}", flush=True)
     T = L * K
@@ -214,7 +215,8 @@ def test_large_logits_take_the_running_max_path(qscale, L, Hq):
                        rand_bits((T, Hq, D), 303))
     tm = pe.peagle_build_tilemap(L, K, None, device=0)
     assert fwd_form(tm, Hq, Hkv) == ("one head" if Hq == 4 else "two heads, three per CU")
-    assert (mean_list(tm) < 10) == (L == 600) and (mean_list(tm) > 11) == (L == 2000) and runs_plain_dq(tm, Hq) == (Hq == 36)
+    assert (mean_list(tm) < 10) == (L == 600) and (mean_list(tm) > 11) == (L == 2000)
+    assert dq_path(tm, Hq, "backward") == ("plain" if Hq == 52 else "one grid")
     r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
     r.fwd()
     r.bwd()
@@ -235,14 +237,17 @@ def test_large_logits_take_the_running_max_path(qscale, L, Hq):
         assert rel_l2(got[n], ref[n]) <= GRAD_REL, n
 
 
-def _heads_run(tm, L, K, q, k, v, d_o):
-    """A step over the heads given, [T, H, D] tensors on the device."""
+def _heads_run(tm, L, K, q, k, v, d_o, profiled=False):
+    """A step (profiled: its kernels launched apart) over the heads given, [T, H, D] tensors on the device."""
     shape = pe.Shape(L, K, q.shape[1], k.shape[1], q.shape[2])
     o, dq = (torch.full_like(q, float("nan")) for _ in range(2))
     lse = torch.full((q.shape[1], q.shape[0]), float("nan"), device="cuda")
     dk, dv = (torch.full(k.shape, float("nan"), device="cuda") for _ in range(2))
     ws = torch.empty(pe.peagle_workspace_bytes(tm, shape), dtype=torch.uint8, device="cuda")
-    pe.peagle_attn_step_partitioned(tm, shape, 0, tm.info()["S"], q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
+    if profiled:
+        pe.peagle_attn_step_profiled(tm, shape, 0, tm.info()["S"], q, k, v, d_o, o, lse, dq, dk, dv, ws)
+    else:
+        pe.peagle_attn_step_partitioned(tm, shape, 0, tm.info()["S"], q, k, v, d_o, o, lse, dq, dk, dv, None, None, ws)
     torch.cuda.synchronize()
     return {"o": o, "dq": dq, "lse": lse.t(), "dk": dk, "dv": dv}
 
@@ -1011,7 +1016,7 @@ def test_every_way_dkdv_finds_its_rows(K, L, D):
 
 @pytest.mark.parametrize("qscale", [1.0, 12.0])
 def test_pipelined_dq_over_lists_of_every_length(qscale):
-    """Lists of 3 to 34 key tiles at D = 64, few workgroups: the pipelined dQ kernel with every remainder of its groups of
+    """Lists of 3 to 34 key tiles at D = 64, few workgroups: the pipelined dQ (in the one grid) with every remainder of its groups of
     three tiles and (large logits) with normalised and unnormalised probabilities.  The whole sequence, its segments one
     by one and a crop agree bit for bit."""
     L, K, Hq, Hkv, D, bounds = 2000, 4, 2, 1, 64, [0, 1472, 1568, 2000]
@@ -1020,7 +1025,7 @@ def test_pipelined_dq_over_lists_of_every_length(qscale):
     qb, kb, vb, dob = (rand_bits((T, Hq, D), 320, qscale), rand_bits((T, Hkv, D), 321), rand_bits((T, Hkv, D), 322),
                        rand_bits((T, Hq, D), 323))
     tm = pe.peagle_build_tilemap(L, K, bounds, device=0)
-    assert not runs_plain_dq(tm, Hq)
+    assert dq_path(tm, Hq) == "one grid"
     r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
     r.step(0, 3)
     got = r.results()
@@ -1061,21 +1066,22 @@ def _map_of(form):
 @pytest.mark.parametrize("qscale", [1.0, 12.0, 40.0])
 @pytest.mark.parametrize("form", ["dense", "k7", "packed", "sampled"])
 def test_both_dq_kernels_give_the_same_bits(form, qscale):
-    """Forty query heads in one call (many workgroups: the plain dQ kernel at D = 64) against the same heads in calls of one
-    key / value head's group each (few workgroups: the pipelined kernel).  At the larger scales some or all workgroups
+    """Kernels launched apart: forty query heads in one call (many workgroups: the plain dQ kernel at D = 64) against the same heads
+    in calls of one key / value head's group each (few workgroups: the pipelined kernel).  At the larger scales some or all workgroups
     have row sums outside the range of unnormalised probabilities."""
     print(f"case dq kernels {form} qscale={qscale}", flush=True)
     tm, L, K = _map_of(form)
     T, Hq, Hkv, D = tm.tokens(L), 40, 20, 64
-    assert runs_plain_dq(tm, Hq) and not runs_plain_dq(tm, Hq // Hkv)
+    assert dq_path(tm, Hq, "profiled") == "plain" and dq_path(tm, Hq // Hkv, "profiled") == "pipelined"
     g = torch.Generator(device="cuda").manual_seed(335)
     rnd = lambda H, f=1.0: (torch.randn(T, H, D, generator=g, device="cuda") * f).to(torch.bfloat16)
     q, k, v, d_o = rnd(Hq, qscale), rnd(Hkv), rnd(Hkv), rnd(Hq)
 
-    whole = _heads_run(tm, L, K, q, k, v, d_o)
+    whole = _heads_run(tm, L, K, q, k, v, d_o, profiled=True)
     for h in range(0, Hkv, 3):
         a, b = slice(h * (Hq // Hkv), (h + 1) * (Hq // Hkv)), slice(h, h + 1)
-        part = _heads_run(tm, L, K, q[:, a].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(), d_o[:, a].contiguous())
+        part = _heads_run(tm, L, K, q[:, a].contiguous(), k[:, b].contiguous(), v[:, b].contiguous(), d_o[:, a].contiguous(),
+                          profiled=True)
         for n, t in part.items():
             assert torch.isfinite(t).all(), n
             assert torch.equal(whole[n][:, b if n in ("dk", "dv") else a], t), n
@@ -1127,7 +1133,7 @@ def test_plain_dq_kernel_gives_the_bits_of_the_one_grid(form, qscale):
     print(f"case plain dq against one grid {form} qscale={qscale}", flush=True)
     tm, L, K = _map_of(form)
     T, Hq, Hkv, D = tm.tokens(L), 96, 48, 64
-    assert runs_plain_dq(tm, Hq) and tm.info()["n_row_tiles"] * Hq > 4096
+    assert dq_path(tm, Hq) == "plain" and dq_path(tm, Hq // Hkv) == "one grid"
     g = torch.Generator(device="cuda").manual_seed(343)
     rnd = lambda H, f=1.0: (torch.randn(T, H, D, generator=g, device="cuda") * f).to(torch.bfloat16)
     q, k, v, d_o = rnd(Hq, qscale), rnd(Hkv), rnd(Hkv), rnd(Hq)
@@ -1184,14 +1190,46 @@ def test_segments_that_share_a_launch_give_the_bits_of_one_launch_each(form, D):
             assert torch.isfinite(got).all() and torch.equal(got, ref)
 
 
-@pytest.mark.parametrize("Hq,Hkv", [(2, 1), (64, 32)])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_chunks_that_share_a_launch_in_a_backward_by_itself(accumulate, D):
+    """A backward over a segment of two chunks with few heads: both share a launch where the workspace has room for two sets of
+    partials, and with accumulate the first set that holds a key adds to what the caller's tensors hold.  The same bits as
+    with a launch and a sum for each."""
+    print(f"case shared launch backward accumulate={accumulate} D={D}", flush=True)
+    K, L, Hq, Hkv = 32, 530, 2, 1
+    tm, shape, T = pe.peagle_build_tilemap(L, K, None, device=0), pe.Shape(L, K, Hq, Hkv, D), L * K
+    g = torch.Generator(device="cuda").manual_seed(353)
+    q, k, v, d_o = (torch.randn(T, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq))
+    old = [torch.randn(T, Hkv, D, generator=g, device="cuda") for _ in range(2)]
+    o, lse = torch.empty_like(q), torch.empty((Hq, T), device="cuda")
+    pe.peagle_attn_fwd(tm, shape, -1, q, k, v, o, lse)
+
+    def results(n_bytes, accumulate):
+        ws = torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda")  # (NaN)
+        out = [torch.full_like(q, float("nan")), *(t.clone() for t in old)]
+        pe.peagle_attn_bwd(tm, shape, -1, q, k, v, o, d_o, lse, *out, accumulate, ws)
+        torch.cuda.synchronize()
+        return out
+    need = pe.peagle_workspace_bytes(tm, shape)
+    one_set = 2 * T * Hq * 4 + 2 * Hq * 576 * D * 4      # (whole multiples of 256 bytes)
+    assert need == one_set + 2 * Hq * 576 * D * 4
+    got, ref = results(need, accumulate), results(one_set, accumulate)
+    for a, b in zip(got, ref):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+    if accumulate:      # (an fp32 sum of the same terms in another order, and two subtractions: five roundings of 2^-24)
+        for a, b, t in zip(got[1:], results(need, 0)[1:], old):
+            assert (a - b - t).abs().max() <= 5 * 2.0 ** -24 * float((b.abs() + t.abs()).max())
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(2, 1), (112, 56)])
 def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
     """Six hundred anchors alone (short lists, at many heads the plain dQ kernel) and packed in front of a sequence of five
-    thousand (long lists, the pipelined one)."""
+    thousand (long lists, the pipelined form in one grid)."""
     K, D, own, other = 8, 64, 600, 5000
     print(f"case packed neighbours Hq={Hq}", flush=True)
     maps = [pe.peagle_build_tilemap_packed(lens, K, device=0) for lens in ([own], [own, other])]
-    assert runs_plain_dq(maps[0], Hq) == (Hq == 64) and not runs_plain_dq(maps[1], Hq)
+    assert dq_path(maps[0], Hq) == ("plain" if Hq == 112 else "one grid") and dq_path(maps[1], Hq) == "one grid"
     g = torch.Generator(device="cuda").manual_seed(337)
     L = own + other
     full = [torch.randn(K, L, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq)]
@@ -1206,5 +1244,5 @@ def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
 def test_sampled_map_of_long_lists_runs_the_pipelined_dq():
     from peagle_inputs import cod_depth_counts
     tm = pe.peagle_build_tilemap_sampled(cod_depth_counts(3000, 4, 0.8, 395), 4, None, device=0)
-    assert mean_list(tm) > 24 and not runs_plain_dq(tm, 2)
+    assert mean_list(tm) > 24 and dq_path(tm, 2) == "one grid"
     test_sampled_sequences_match_oracle("long_lists", 3000, 4, 2, 1, 64, 0.8, 395, None)

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2602_01469_amd as pe
-from gpu_harness import Run, SampledRun, attach_rope, bf16_to_f64, fwd_form, max_abs, rand_bits, rel_l2, runs_plain_dq, to_dev_bf16
+from gpu_harness import Run, SampledRun, attach_rope, bf16_to_f64, dq_path, fwd_form, max_abs, rand_bits, rel_l2, to_dev_bf16
 from oracle import peagle_oracle as orc
 from peagle_inputs import CONFIGS, bf16_bits_to_f64, cod_depth_counts, f32_to_bf16_bits, make_inputs
 from test_gpu_parity import (FWD_REL, GRAD_REL, LSE_ABS, PART_REL, _check_against_oracle, _check_o_abs)
@@ -368,8 +368,8 @@ def test_rope_step_with_shared_chain_vectors_matches_oracle(name, seq_lens, K, H
 
 
 def test_shared_chain_vectors_with_lists_of_every_length():
-    """The pipelined dQ kernel (few workgroups) over lists that do and do not fill its groups of three."""
-    assert not runs_plain_dq(pe.peagle_build_tilemap(1800, 4, [0, 640, 1800], device=-1), 2)
+    """The pipelined dQ (few workgroups: in the one grid) over lists that do and do not fill its groups of three."""
+    assert dq_path(pe.peagle_build_tilemap(1800, 4, [0, 640, 1800], device=-1), 2) == "one grid"
     test_rope_step_with_shared_chain_vectors_matches_oracle("dense_long_lists", (1800,), 4, 2, 1, 64, None, 3080,
                                                             [0, 640, 1800], True)
 
@@ -405,12 +405,12 @@ def _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, seed, groups):
             assert torch.equal(whole[n][:, a if n in ("o", "lse", "dq") else b], t), n
 
 
-def test_shared_chain_vectors_give_the_same_bits_from_both_dq_kernels():
-    """Forty query heads at once (the plain dQ kernel) against one group at a time (the pipelined one), first-layer form."""
+def test_shared_chain_vectors_give_the_same_bits_from_all_heads_at_once():
+    """Forty query heads at once against one group at a time, first-layer form: one grid either way, full and nearly empty."""
     L, K, Hq, Hkv, D = 1500, 4, 40, 20, 64
-    print("case rope shared dq kernels", flush=True)
+    print("case rope shared all heads at once", flush=True)
     tm = pe.peagle_build_tilemap(L, K, [0, 640, 1500], device=0)
-    assert runs_plain_dq(tm, Hq) and not runs_plain_dq(tm, Hq // Hkv)
+    assert dq_path(tm, Hq) == dq_path(tm, Hq // Hkv) == "one grid"
     _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, 3090, range(0, Hkv, 6))
 
 
@@ -419,7 +419,7 @@ def test_shared_chain_vectors_give_the_same_bits_from_the_plain_dq_kernel_and_th
     L, K, Hq, Hkv, D = 1500, 4, 96, 48, 64
     print("case rope shared plain dq against one grid", flush=True)
     tm = pe.peagle_build_tilemap(L, K, [0, 640, 1500], device=0)
-    assert runs_plain_dq(tm, Hq) and tm.info()["n_row_tiles"] * Hq > 4096
+    assert dq_path(tm, Hq) == "plain" and dq_path(tm, Hq // Hkv) == "one grid"
     _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, 3095, range(0, Hkv, 23))
 
 
