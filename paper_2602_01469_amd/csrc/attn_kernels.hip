@@ -1767,8 +1767,8 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
     }
     issue_mask(mask_c, 0);
   }
-  {  // (behind the first row tile's copies; a key that does not exist computes on token 0's, and is not stored: a lane's key
-     // meets no other lane's)
+  {  // (behind the first row tile's copies; a key that does not exist computes on token 0's: a lane's key meets no other lane's,
+     // and what it leaves is not stored, in the first-layer form counts as zero, and among the partials is not summed)
     const size_t off = ((size_t)(key_ok ? key_tok : 0) * p.Hkv + kvh) * D + g * 8;
     const __bf16* vrow = SV && chain ? p.v_shared + (size_t)kvh * D + g * 8 : p.v + off;
 #pragma unroll
