@@ -41,7 +41,7 @@ typedef enum peagle_status {
   PEAGLE_EBOUNDS = -4,      /* segment bounds not strictly increasing from 0 to L_max, or an inner bound
                                is not a multiple of the anchors-per-row-tile */
   PEAGLE_EUNSUPPORTED = -5, /* head_dim not in {64, 128}, K > 128, unknown layout */
-  PEAGLE_EWORKSPACE = -6,   /* workspace missing or smaller than peagle_workspace_bytes() */
+  PEAGLE_EWORKSPACE = -6,   /* workspace missing or too small, see peagle_workspace_bytes() */
   PEAGLE_EHIP = -7,         /* a HIP runtime call failed (allocation, copy, launch) */
   PEAGLE_ENODEVICE = -8     /* the tile map was built host-only (device < 0) and cannot be used to launch */
 } peagle_status;
@@ -128,7 +128,9 @@ int peagle_tilemap_classes(const peagle_tilemap_t* tm, uint8_t* classes_out);
 
 /* Bytes of device scratch that peagle_attn_bwd / peagle_attn_step_partitioned use for this shape.  Where several segments
  * share a launch (few query heads) this includes a set of partial sums for each; a call accepts a workspace that has room
- * for one set only (such as one made for a longer sequence of the same map), with the same results. */
+ * for one set only (such as one made for a longer sequence of the same map), with the same results and more launches.  A set
+ * takes 2 * round_up(4 * Hq * round_up(L, 64) * D, 256) bytes, the rest 2 * round_up(4 * T * Hq, 256): with one set that is the
+ * smallest size accepted.  (The rotary and first-layer workspaces below hold the same sets: fewer make them smaller alike.) */
 size_t peagle_workspace_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* shape);
 
 /*

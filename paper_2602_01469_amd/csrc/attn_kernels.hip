@@ -2673,17 +2673,18 @@ hipError_t launch_row_terms(const BwdParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Where a range's key-tile pairs x heads are few, the next ranges' fill the slots, and the launches' ends are fewer: up to 768
-// items in the last range (512 run at once) at D = 64, 512 (256) at D = 128.  us per step, a launch per range / up to four
-// together (items of the last): 4 heads L = 2,500 in segments of 1,024 368 / 206 (80), L = 4,096 631 / 351 (128), by itself 610 /
-// 399, L = 8,000 in segments of 2,048 1,490 / 1,140 (252), L = 16,000 4,880 / 4,360 (500), L = 20,480 in segments of 1,024 8,490 /
-// 7,250 (640), sampled L = 3,000 328 / 281, 16 heads L = 4,096 1,343 / 1,247 (512), 64 heads L = 1,500 834 / 826 (768); but
-// L = 2,048 1,404 / 1,417 (1,024), L = 4,096 4,927 / 4,997 (2,048); D = 128 4 heads L = 4,096 968 / 732 (128), 32 heads L = 2,048
-// 1,458 / 1,436 (512).  The partials of every set beyond the first are as large as the problem's depth-0 keys x heads in fp32;
-// sequences of up to 512 anchors, which are hardly cut into segments, need no more workspace than one range does.
+// Where a range's key-tile pairs x heads are few, the next ranges' fill the slots, and the launches' ends are fewer: up to
+// 768 items in the last range (512 run at once) at D = 64, 512 (256) at D = 128.  us per step, a launch per range / up to
+// four together (items of the last): 4 heads L = 256 in segments of 64 86 / 33 (8), of 128 66 / 40, L = 512 of 128 127 / 46
+// (16; D = 128 174 / 64), L = 2,500 of 1,024 368 / 206 (80), L = 4,096 631 / 351 (128), by itself 610 / 399, L = 8,000 in
+// segments of 2,048 1,490 / 1,140 (252), L = 16,000 4,880 / 4,360 (500), L = 20,480 in segments of 1,024 8,490 / 7,250
+// (640), sampled L = 3,000 328 / 281, 16 heads L = 4,096 1,343 / 1,247 (512), 64 heads L = 1,500 834 / 826 (768); but L =
+// 2,048 1,404 / 1,417 (1,024), L = 4,096 4,927 / 4,997 (2,048); D = 128 4 heads L = 4,096 968 / 732 (128), 32 heads L =
+// 2,048 1,458 / 1,436 (512).  The partials of every set beyond the first are as large as the problem's depth-0 keys x heads
+// in fp32.
 int dkdv_part_sets(int D, int L64, int Hq, int n_ranges) {
   const int64_t items = (int64_t)((L64 / kKeysPerTile + 1) / 2) * Hq;
-  const int most = L64 <= 512 || items > (D == 64 ? 3 : 2) * kCus ? 1 : kMaxRanges;
+  const int most = items > (D == 64 ? 3 : 2) * kCus ? 1 : kMaxRanges;
   return n_ranges < most ? (n_ranges < 1 ? 1 : n_ranges) : most;
 }
 

@@ -62,7 +62,7 @@ def test_training_step_stays_inside_its_buffers(L, K, Hq, Hkv, D, bounds):
     tm = pe.peagle_build_tilemap(L, K, bounds, device=0)
     shape = pe.Shape(L, K, Hq, Hkv, D)
     S = 1 if bounds is None else len(bounds) - 1
-    sets = {603: 4, 530: 3}.get(L, 1)
+    sets = {333: 2, 603: 4, 530: 3}.get(L, 1)
     align = lambda n: (n + 255) // 256 * 256
     assert pe.peagle_workspace_bytes(tm, shape) == 2 * align(T * Hq * 4) + sets * 2 * align(Hq * ((L + 63) // 64 * 64) * D * 4)
     g = Guarded()

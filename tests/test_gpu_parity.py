@@ -1147,13 +1147,15 @@ def test_plain_dq_kernel_gives_the_bits_of_the_one_grid(form, qscale):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("form", ["six_segments", "cropped", "chunks", "sampled", "packed", "rope"])
+@pytest.mark.parametrize("form", ["short", "six_segments", "cropped", "chunks", "sampled", "packed", "rope"])
 def test_segments_that_share_a_launch_give_the_bits_of_one_launch_each(form, D):
     """Few heads: up to four segments (or chunks of a long one) share a launch and the sum of its partials; in a workspace with
     room for one set of partials each has a launch and a sum of its own, as it has when a caller steps segment by segment."""
     print(f"case shared launch {form} D={D}", flush=True)
     K, L, Hq, Hkv = (32, 530, 2, 1) if form == "chunks" else (8, 1000, 4, 2)
     bounds = [0, 520, 530] if form == "chunks" else [0, 160, 320, 336, 640, 800, 1000]
+    if form == "short":
+        L, bounds = 150, [0, 16, 64, 80, 128, 150]       # (launches of four segments and of one)
     Lc = 650 if form == "cropped" else L                 # (ends inside the fifth segment)
     if form == "sampled":
         from peagle_inputs import cod_depth_counts

@@ -637,6 +637,19 @@ def test_decode_input_generator_scatters_the_context_over_pages():
             assert np.array_equal(inp["v_pages"][page, :, t % 64], inp["v_ctx"][c][t])
 
 
+def test_short_sequences_in_segments_get_a_set_of_partials_each():
+    """Few heads: up to four segments share a dK/dV launch, however short the sequence, and the workspace has room for them."""
+    align = lambda n: (n + 255) // 256 * 256
+    for D in (64, 128):
+        for L, bounds in ((256, [0, 128, 256]), (200, [0, 64, 128, 200]), (90, [0, 16, 32, 48, 64, 90])):
+            tm, shape = pe.peagle_build_tilemap(L, 8, bounds, device=-1), pe.Shape(L, 8, 4, 2, D)
+            sets = min(len(bounds) - 1, 4)
+            part = 2 * align(4 * shape.Hq * ((L + 63) // 64 * 64) * D)
+            assert pe.peagle_workspace_bytes(tm, shape) == 2 * align(4 * L * 8 * shape.Hq) + sets * part
+            copies = align(L * 8 * shape.Hq * D * 2) + align(L * 8 * shape.Hkv * D * 2)
+            assert pe.peagle_rope_workspace_bytes(tm, shape) == pe.peagle_workspace_bytes(tm, shape) + copies
+
+
 def test_rope_shared_entry_point_validates_before_launch():
     lib = pe.load_library()
     tm = pe.peagle_build_tilemap(256, 8, [0, 128, 256], device=-1)
@@ -648,7 +661,9 @@ def test_rope_shared_entry_point_validates_before_launch():
                                                 one, one, one, one, one, one, ws, None)
     assert call(k_shared=None) == -2
     assert call(n_pos=262) == -3
-    assert call(ws=pe.peagle_rope_workspace_bytes(tm, ok)) == -6       # the rotary workspace alone is too small
+    one_range = pe.peagle_build_tilemap(256, 8, None, device=-1)        # (one set of dK / dV partials, the least a call accepts)
+    assert call(ws=pe.peagle_rope_workspace_bytes(one_range, ok)) == -6  # the rotary workspace alone is too small
+    assert call(ws=pe.peagle_rope_shared_workspace_bytes(one_range, ok) - 1) == -6
     assert call() == -8
     need = pe.peagle_rope_shared_workspace_bytes(tm, ok)
     # beside the rotary workspace: one fp32 row of Hkv x D per wave (4) of each of the 16 row tiles' chain-tile
