@@ -119,6 +119,8 @@ FwdParams make_fwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const Se
   p.T = (int)tokens_of(tm, s);
   p.Hq = s->Hq;
   p.Hkv = s->Hkv;
+  p.group = s->Hq / s->Hkv;
+  p.by_kv = peagle::make_divisor(s->Hkv);
   p.rt_lo = sr.rt_lo;
   p.rt_hi = sr.rt_hi;
   p.c_log2 = s->scale * 1.4426950408889634f;
@@ -156,6 +158,9 @@ BwdParams make_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const Se
   p.T = (int)tokens_of(tm, s);
   p.Hq = s->Hq;
   p.Hkv = s->Hkv;
+  p.group = s->Hq / s->Hkv;
+  p.by_kv = peagle::make_divisor(s->Hkv);
+  p.by_group = peagle::make_divisor(p.group);
   p.L64 = w.L64;
   p.rt_lo = sr.rt_lo;
   p.rt_hi = sr.rt_hi;

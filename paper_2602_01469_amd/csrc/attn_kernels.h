@@ -18,6 +18,8 @@ struct FwdParams {
   DeviceTileMap tm;
   int L, T, Hq, Hkv;
   int rt_lo, rt_hi;    // row tiles of the segment
+  int group;           // query heads per KV head
+  Divisor by_kv, by_heads;  // by Hkv; by the workgroups that share a KV head and a row tile (filled by the launcher)
   float c_log2;        // softmax scale * log2(e)
   int mean_tiles;      // mean length of the row tiles' lists over the whole length-L problem
   const __bf16* v_shared;  // null, or [Hkv, D]: the value row of every chain key (first-layer form; v then holds
@@ -58,6 +60,8 @@ struct BwdParams {
   int part_sets;       // as many ranges of rows as one launch may take
   DeviceTileMap tm;
   int L, T, Hq, Hkv, L64;
+  int group;            // query heads per KV head
+  Divisor by_kv, by_group;
   int rt_lo, rt_hi;
   int s_lo, s_hi, cropped;  // segment boundary indices of the row range; cropped: rt_hi cuts the last segment short
   int n_d0_items;       // filled by the launcher: depth-0 work items (key-tile pairs x query heads) of all ranges

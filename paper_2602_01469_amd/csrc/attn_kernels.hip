@@ -33,6 +33,15 @@ constexpr float kNegInit = -1.0e30f;
 // C layout of a transposed score block: keys 8*(i/4) + 4g + i%4, i = 0..15.
 constexpr uint32_t kLaneKeyBits = 0x0f0f0f0fu;
 
+// n / d and, in its place, n % d; n wave-uniform and below 2^31 (see Divisor).
+__device__ __forceinline__ int split_by(int& n, const Divisor& d) {
+  const uint32_t q = (uint32_t)(((uint64_t)(uint32_t)n * d.mul) >> d.shift);
+  n -= (int)(q * d.d);
+  return (int)q;
+}
+// x / d for x < 128, r = small_reciprocal(d)
+__device__ __forceinline__ int small_quotient(int x, uint32_t r) { return (int)(__umul24((uint32_t)x, r) >> 16); }
+
 // Token (row of the [T, H, D] tensors) of key `row` of key tile `kt`; false if that key does not
 // exist in a length-L problem.
 __device__ __forceinline__ bool key_token(const DeviceTileMap& tm, int kt, int row, int L, int& tok) {
@@ -45,9 +54,9 @@ __device__ __forceinline__ bool key_token(const DeviceTileMap& tm, int kt, int r
     tok = tm.chain_tok[(size_t)cid * kKeysPerTile + row];
     return tok >= 0;
   }
-  const int R = cid / tm.n_csub;
+  const int R = cid >> (tm.n_csub - 1);  // (one or two chain tiles a row tile)
   const int ck = (cid - R * tm.n_csub) * kKeysPerTile + row;
-  const int a = ck / tm.chain_slots;
+  const int a = small_quotient(ck, tm.slots_reciprocal);
   const int e = tm.chain_first + ck - a * tm.chain_slots;
   const int j = R * tm.A + a;
   tok = e * L + j;
@@ -75,7 +84,7 @@ __device__ __forceinline__ bool row_token(const DeviceTileMap& tm, int rt, int r
     tok = tm.row_tok[(size_t)rt * kRowsPerTile + r];
     return tok >= 0;
   }
-  const int a = r / tm.K, i = rt * tm.A + a;
+  const int a = small_quotient(r, tm.k_reciprocal), i = rt * tm.A + a;
   tok = (r - a * tm.K) * L + i;
   return a < tm.A && i < L;
 }
@@ -131,49 +140,70 @@ __device__ __forceinline__ int lane_id() {
   return l;
 }
 
-// Key tile straight into its swizzled LDS image (K and V): wave w of NW fills the 1 KiB blocks
-// w, w + NW, ...; lane l of block b owns LDS bytes [1024 b + 16 l, +16), i.e. tile row
-// b*(512/D) + l/(D/8) and physical chunk l%(D/8), and fetches the logical chunk that lives there.
-// LEAN: the lane's coordinates in tiles that need an address per lane are computed anew rather than held in registers.
-template <int D, int NW, bool SV = false, bool LEAN = false>
-__device__ __forceinline__ void dma_key_tile(uint32_t kd, uint32_t vd, const __bf16* kbase, const __bf16* vbase,
-                                             int Hkv, int kvh, const DeviceTileMap& tm, int kt, int L, int wave,
-                                             int lane, const __bf16* v_shared = nullptr) {
-  // kd, vd: LDS byte addresses of this wave's first block of the K and of the V image (tile address + 1024 *
-  // wave), as wave-uniform integers - see KeyTileLds
-  constexpr int kBlocks = kKeysPerTile * D * 2 / 1024;
-  static_assert(kBlocks % NW == 0, "tile must split evenly over the waves");
-  if (kt < tm.n_d0 && (kt + 1) * kKeysPerTile <= L) {
-    // A whole tile of depth-0 keys: the rows a lane copies are NW * 512/D apart (a multiple of the swizzle
-    // period), so its byte offset from each copy's first row is one value, the same for every tile, and the
-    // rest of the address is wave-uniform.
-    const int row0 = wave * (512 / D) + lane / (D / 8);
-    const uint32_t voff = (uint32_t)((row0 * Hkv) * D + ((lane % (D / 8) ^ swz<D>(row0)) << 3)) * 2u;
+// Key tiles straight into their swizzled LDS images (K and V): wave w of NW fills the 1 KiB blocks w, w + NW, ...; lane l of
+// block b owns LDS bytes [1024 b + 16 l, +16), i.e. tile row b*(512/D) + l/(D/8) and physical chunk l%(D/8), and fetches the
+// logical chunk that lives there.
+// kd, vd: LDS byte addresses of this wave's first block of the K and of the V image (tile address + 1024 * wave), as
+// wave-uniform integers - see KeyTileLds.
+// A tile of depth-0 keys.  The rows a lane copies are NW * 512/D apart (a multiple of the swizzle period), so its byte offset
+// from each copy's first row is one value, the same for every whole tile, and the rest of the address is wave-uniform.  Rows
+// past the end of the sequence are read from its last row: no row of the problem sees them, and what zero times a NaN of the
+// last key reaches, the last key itself has reached (a wave that takes the block of the one takes the block of the other).
+template <int D, int NW>
+__device__ __forceinline__ void dma_d0_tile(uint32_t kd, uint32_t vd, const __bf16* kbase, const __bf16* vbase, int Hkv, int kvh,
+                                            int kt, int L, int wave, int lane) {
+  constexpr int kCopies = kKeysPerTile * D * 2 / 1024 / NW, kApart = NW * (512 / D);
+  static_assert(kCopies * NW * 1024 == kKeysPerTile * D * 2, "tile must split evenly over the waves");
+  const int row0 = wave * (512 / D) + lane / (D / 8);
+  const uint32_t chunk = (uint32_t)((lane % (D / 8) ^ swz<D>(row0)) << 4), stride = (uint32_t)(Hkv * D * 2);
+  if ((kt + 1) * kKeysPerTile <= L) {
+    const uint32_t voff = (uint32_t)row0 * stride + chunk;
 #pragma unroll
-    for (int i = 0; i < kBlocks / NW; ++i) {
-      const size_t first = ((size_t)(kt * kKeysPerTile + i * NW * (512 / D)) * Hkv + kvh) * D;
+    for (int i = 0; i < kCopies; ++i) {
+      const size_t first = ((size_t)(kt * kKeysPerTile + i * kApart) * Hkv + kvh) * D;
       dma16_untracked(uniform_ptr(kbase + first), voff, kd + i * NW * 1024);
       dma16_untracked(uniform_ptr(vbase + first), voff, vd + i * NW * 1024);
     }
     return;
   }
-  const int l = LEAN ? lane_id() : lane;
-  const int phys = l % (D / 8), row0 = wave * (512 / D) + l / (D / 8);
-  constexpr int kTogether = LEAN ? 1 : kBlocks / NW;
-  int tok[kTogether];
+  const int at = kt * kKeysPerTile < L ? kt * kKeysPerTile : L - 1;  // (a cropped sequence's last row tile may list a tile past it)
+  const size_t first = ((size_t)at * Hkv + kvh) * D;
+  const int last = L - 1 - at;
 #pragma unroll
-  for (int i = 0; i < kBlocks / NW; ++i) {
-    if (i % kTogether == 0) key_tokens(tm, kt, row0 + i * NW * (512 / D), NW * (512 / D), L, tok);
-    const int t = tok[i % kTogether];
-    const bool ok = t >= 0;
-    const int chunk = (phys ^ swz<D>(row0 + i * NW * (512 / D))) << 3;
-    const size_t off = ((size_t)(ok ? t : 0) * Hkv + kvh) * D + chunk;
-    // First-layer form (SV; a template flag: kernels of the ordinary step carry none of this), chain tile: every key's value
-    // row is the one shared vector of its KV head.
-    const __bf16* v = SV && kt >= tm.n_d0 ? v_shared + (size_t)kvh * D + chunk : vbase + off;
+  for (int i = 0; i < kCopies; ++i) {
+    const int row = row0 + i * kApart;
+    const uint32_t voff = (uint32_t)(row < last ? row : last) * stride + chunk;
+    dma16_untracked(uniform_ptr(kbase + first), voff, kd + i * NW * 1024);
+    dma16_untracked(uniform_ptr(vbase + first), voff, vd + i * NW * 1024);
+  }
+}
+
+// A tile of chain keys.  SV (first-layer form; a template flag: kernels of the ordinary step carry none of this): every key's
+// value row is the one shared vector of its KV head.
+template <int D, int NW, bool SV>
+__device__ __forceinline__ void dma_chain_tile(uint32_t kd, uint32_t vd, const __bf16* kbase, const __bf16* vbase, int Hkv, int kvh,
+                                               const DeviceTileMap& tm, int kt, int L, int wave, int lane, const __bf16* v_shared) {
+  constexpr int kCopies = kKeysPerTile * D * 2 / 1024 / NW, kApart = NW * (512 / D);
+  const int phys = lane % (D / 8), row0 = wave * (512 / D) + lane / (D / 8);
+  int tok[kCopies];
+  key_tokens(tm, kt, row0, kApart, L, tok);
+#pragma unroll
+  for (int i = 0; i < kCopies; ++i) {
+    const bool ok = tok[i] >= 0;
+    const int chunk = (phys ^ swz<D>(row0 + i * kApart)) << 3;
+    const size_t off = ((size_t)(ok ? tok[i] : 0) * Hkv + kvh) * D + chunk;
+    const __bf16* v = SV ? v_shared + (size_t)kvh * D + chunk : vbase + off;
     dma16_untracked(ok ? (const void*)(kbase + off) : tm.zeros, kd + i * NW * 1024);
     dma16_untracked(ok ? (const void*)v : tm.zeros, vd + i * NW * 1024);
   }
+}
+
+// Either.
+template <int D, int NW, bool SV>
+__device__ __forceinline__ void dma_key_tile(uint32_t kd, uint32_t vd, const __bf16* kbase, const __bf16* vbase, int Hkv, int kvh,
+                                             const DeviceTileMap& tm, int kt, int L, int wave, int lane, const __bf16* v_shared) {
+  if (kt < tm.n_d0) dma_d0_tile<D, NW>(kd, vd, kbase, vbase, Hkv, kvh, kt, L, wave, lane);
+  else dma_chain_tile<D, NW, SV>(kd, vd, kbase, vbase, Hkv, kvh, tm, kt, L, wave, lane, v_shared);
 }
 
 // The bitmask of a row tile's key tile, to LDS with the tile's copies: each wave the words of its own 32 rows.  (A mask word
@@ -194,6 +224,25 @@ __device__ __forceinline__ void tile_mask(const char* mask, int row, int g, uint
   const u32x2 w = *reinterpret_cast<const u32x2*>(mask + row * (kMaskWordsPerRow * 4));
   mw[0] = w[0] >> (4 * g);
   mw[1] = w[1] >> (4 * g);
+}
+
+// The chain tiles that end a row tile's list (none to two).  At D = 64 the row-stationary kernels take them first and together:
+// a wave sees one block of 32 of the 128 chain slots (or two), so as iterations of their own each was a copy and a barrier for
+// half of the workgroup's waves.  Both travel with the first tile of depth-0 keys, which the workgroup waits for anyway, into
+// buffers that the loop uses later (one more than it needs, 51 KB in all: still three workgroups a CU).  us, last / first:
+// L = 1,391 704.9 / 702.5, L = 4,096 4,810 / 4,786, eight packed sequences 3,077 / 3,067.  (D = 128: no LDS for two.)
+struct ChainTiles {
+  int n;
+  TileEntry tile[2];
+};
+__device__ __forceinline__ ChainTiles chain_tiles(const DeviceTileMap& tm, int e0, int e1) {
+  const TileEntry a = const_entry(tm.row_entries, e1 - 2 > e0 ? e1 - 2 : e0), b = const_entry(tm.row_entries, e1 - 1);
+  ChainTiles c;
+  const bool two = e1 - 2 > e0 && a.tile >= tm.n_d0;  // (a list starts with a tile of depth-0 keys)
+  c.n = two ? 2 : b.tile >= tm.n_d0 ? 1 : 0;
+  c.tile[0] = two ? a : b;
+  c.tile[1] = b;
+  return c;
 }
 
 // Row tile (128 rows of one query head) straight into its swizzled LDS image, same block/lane
@@ -218,14 +267,14 @@ __device__ __forceinline__ RowDmaLane<D, NW> row_dma_lane(const DeviceTileMap& t
 #pragma unroll
   for (int i = 0; i < RowDmaLane<D, NW>::kPer; ++i) {
     const int row = (i * NW + wave) * (512 / D) + row_in_blk;
-    const int a = row / tm.K;  // (a sampled map has no fixed geometry; rows come from its list)
+    const int a = small_quotient(row, tm.k_reciprocal);  // (a sampled map has no fixed geometry; rows come from its list)
     r.tok0[i] = (row - a * tm.K) * L + a;
     r.a[i] = a < tm.A ? a : (1 << 30);
     r.row[i] = row;
     r.chunk[i] = (phys ^ swz<D>(row)) << 3;
   }
   const int srow = (wave & 1) * 64 + lane;
-  const int sa = srow / tm.K;
+  const int sa = small_quotient(srow, tm.k_reciprocal);
   r.stat_tok0 = (srow - sa * tm.K) * L + sa;
   r.stat_a = sa < tm.A ? sa : (1 << 30);
   r.stat_row = srow;
@@ -244,7 +293,7 @@ __device__ __forceinline__ RowDmaOffsets<D, NW> row_dma_offsets(const DeviceTile
   RowDmaOffsets<D, NW> r;
   const int row_in_blk = lane / (D / 8), phys = lane % (D / 8);
   auto token = [&](int row) {
-    const int a = row / tm.K;
+    const int a = small_quotient(row, tm.k_reciprocal);
     return (uint32_t)((row - a * tm.K) * L + a);
   };
 #pragma unroll
@@ -329,16 +378,28 @@ __device__ __forceinline__ void store_row_bf16(__bf16* dst, const f32x16& x, flo
 }
 
 // Eight more terms of a lane's half of rowsum(dO * O).  Every kernel that forms Delta adds in this order - pieces of 16
-// features up, the lane's eight of each, the halves last - so that Delta has the same bits wherever it is formed.
+// features up, the lane's eight of each pair by pair, the halves last - so that Delta has the same bits wherever it is formed.
+// (v_dot2_f32_bf16: the products exact, sums in fp32; against 64 bits 3.4e-8 over 32 features of normal data where
+// unpacking and a chain of 32 fused multiply-adds, 96 instructions instead of 16, is off by 3.5e-8.)
 __device__ __forceinline__ float add_delta8(float dl, bf16x8 dof, bf16x8 of) {
+  const u32x4 a = __builtin_bit_cast(u32x4, dof), b = __builtin_bit_cast(u32x4, of);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) dl = __builtin_fmaf((float)dof[j], (float)of[j], dl);
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t x = a[j], y = b[j];
+    dl = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, y), dl, false);
+  }
   return dl;
 }
 
 // Bit `pos` of w selects x, otherwise -inf.
 __device__ __forceinline__ float mask_sel(float x, uint32_t w, int pos) {
   return ((w >> pos) & 1u) ? x : -__builtin_inff();
+}
+
+// x where bit `pos` of w is set, otherwise 0.
+__device__ __forceinline__ float mask_zero(float x, uint32_t w, int pos) {
+  const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)w, pos, 1);
+  return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & keep);
 }
 
 __device__ __forceinline__ float max16(const f32x16& s) {
@@ -473,21 +534,19 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
   // Three workgroups per CU leave 168 registers: what only masked tiles and the last stores need is computed there.
   constexpr bool LEAN = PER_SIMD == 3;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
-  __shared__ __attribute__((aligned(16))) char lds[2][2][kTileBytes];  // [buffer][K|V]
-  __shared__ __attribute__((aligned(16))) char lds_mask[2][kTileMaskBytes];
+  constexpr bool kChainFirst = D == 64;
+  constexpr int kBufs = kChainFirst ? 3 : 2;
+  __shared__ __attribute__((aligned(16))) char lds[kBufs][2][kTileBytes];  // [buffer][K|V]
+  __shared__ __attribute__((aligned(16))) char lds_mask[kChainFirst ? 4 : 2][kTileMaskBytes];  // of buffers 0 and 1, of the chain tiles
 
   const int tid = threadIdx.x, wave = LEAN ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
   const uint32_t mask_lds = lds_scalar_addr(&lds_mask[0][0]);
   const DeviceTileMap& tm = p.tm;
-  const int group = p.Hq / p.Hkv;
-  const int hpg = group / NH;
-  int b = blockIdx.x;
-  const int kvh = b % p.Hkv;
-  b /= p.Hkv;
-  const int hc = b % hpg;
-  const int rt = p.rt_hi - 1 - b / hpg;  // heaviest row tiles first
-  const int h0 = kvh * group + hc * NH;
+  int kvh = blockIdx.x;
+  int hc = split_by(kvh, p.by_kv);
+  const int rt = p.rt_hi - 1 - split_by(hc, p.by_heads);  // heaviest row tiles first
+  const int h0 = kvh * p.group + hc * NH;
 
   // The start of a workgroup is a chain of memory round trips - parameters, list bounds, entries, copies; tokens, rows -, and
   // with short lists the other workgroups of the CU do not cover it.  What does not depend on one another is on its way
@@ -495,7 +554,7 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
   // for the rows' loads before it), several at a time, and the rows are loaded without a branch for each.  us per step, one by
   // one / so, 64 heads: packed 203 to 517 anchors 322 / 304, 203 to 900 745 / 713, eight packed sequences 3,111 / 3,056,
   // L = 1,391 713 / 709; long lists the same (L = 4,096 4,931 / 4,924, L = 20,480 109.1 / 109.0 ms).
-  const int e0 = const_int(tm.row_ptr, rt), e1 = const_int(tm.row_ptr, rt + 1);
+  const int e0 = const_int(tm.row_ptr, rt), e_end = const_int(tm.row_ptr, rt + 1);
   const int e_lead = e0 + const_int(tm.row_lead, rt);  // end of the leading run of full tiles
   const int r = wave * 32 + ln;  // row of the tile owned by this lane (shared with lane^32)
   int tq_held;
@@ -516,6 +575,11 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
   const NatOff<D> no = nat_offsets<D>(lane);
   const TrOff<D> to = tr_offsets<D>(lane);
 
+  auto copy_tile = [&](int buf, int kt) {
+    if (kChainFirst) dma_d0_tile<D, 4>(kl.k(buf), kl.v(buf), p.k, p.v, p.Hkv, kvh, kt, p.L, wave, lane);
+    else dma_key_tile<D, 4, SV>(kl.k(buf), kl.v(buf), p.k, p.v, p.Hkv, kvh, tm, kt, p.L, wave, lane, p.v_shared);
+  };
+
   // One pass over the row tile's key tiles.  The first pass keeps the softmax reference at 0
   // (no running max: fewer vector instructions per score); it is exact as long as every row
   // sum stays inside the fp32 / bf16 exponent range.  If any row of a head leaves [2^-100, 2^100]
@@ -531,22 +595,44 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
 #pragma unroll
       for (int db = 0; db < D / 32; ++db) o[hh][db] = zero16();
     }
+    ChainTiles ch{};
+    if (kChainFirst) ch = chain_tiles(tm, e0, e_end);
+    const int e1 = e_end - ch.n;  // (the chain tiles come first)
     TileEntry cur = const_entry(tm.row_entries, e0);
-    TileEntry nxt = const_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
-    const TileEntry masked = const_entry(tm.row_entries, e_lead < e1 ? e_lead : e0);
+    TileEntry nxt = const_entry(tm.row_entries, e0 + 1 < e_end ? e0 + 1 : e0);
+    TileEntry masked = const_entry(tm.row_entries, e_lead < e_end ? e_lead : e0);
+    if (e_lead >= e1) masked.mask_id = -1;
     if (!SAFE || LEAN) load_q();  // (lean: not held over the stores of the first pass)
-    dma_key_tile<D, 4, SV, LEAN>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
+    if (kChainFirst) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (i < ch.n) {
+          dma_chain_tile<D, 4, SV>(kl.k(1 + i), kl.v(1 + i), p.k, p.v, p.Hkv, kvh, tm, ch.tile[i].tile, p.L, wave, LEAN ? lane_id() : lane, p.v_shared);
+          dma_tile_mask(mask_lds + (2 + i) * kTileMaskBytes, tm, ch.tile[i], wave);
+        }
+    }
+    copy_tile(0, cur.tile);
     // (The first bitmask, if there is one, travels with the first tile, to where its own tile finds it: the loop over full tiles
     // then has no test for one in front of its matrix instructions.  With the test / without, CU busy cycles of 10,816 anchors
     // at D = 128 3.13e9 / 3.09e9; us of 20,480 anchors 23,720 / 23,600.  Not so in dq_item: 4.48e9 / 4.50e9 cycles.)
     dma_tile_mask(mask_lds + ((e_lead - e0) & 1) * kTileMaskBytes, tm, masked, wave);
     dma_publish();
+    if (kChainFirst && ch.n > 0) {
+      const int l = LEAN ? lane_id() : lane;
+#pragma unroll 1
+      for (int i = 0; i < ch.n; ++i) {
+        uint32_t mw[2];
+        tile_mask(lds_mask[2 + i], wave * 32 + (l & 31), l >> 5, mw);
+        fwd_tile_masked<D, NH, SAFE>(lds[1 + i][0], lds[1 + i][1], no, to, qf, o, m, lsum, mw, p.c_log2);
+      }
+      __syncthreads();  // buffer 1 may be overwritten
+    }
     // A row tile's list holds its full tiles first, then the partial ones: two loops (accumulators stay in place).
     int e = e0;
     auto full_tile = [&](int buf) {
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
       if (e + 1 < e1)
-        dma_key_tile<D, 4, SV, LEAN>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+        copy_tile(buf ^ 1, nxt.tile);
       const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
       fwd_tile<D, NH, false, SAFE>(lds[buf][0], lds[buf][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       dma_publish();
@@ -565,7 +651,7 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
       const int buf = (e - e0) & 1;
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
       if (e + 1 < e1) {
-        dma_key_tile<D, 4, SV, LEAN>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+        copy_tile(buf ^ 1, nxt.tile);
         dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
       }
       const int l = LEAN ? lane_id() : lane;
@@ -668,14 +754,11 @@ __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, 
     bf16x8 dsb[NH][2];
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) {
-      if (MASKED) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[hh][i] = mask_sel(s[hh][i], mw[kb], 8 * (i / 4) + (i % 4));
-      }
       const float nl = -lse2[hh], dl = delta[hh];
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float pr = exp2_fast(__builtin_fmaf(s[hh][i], c, nl));
+        float pr = exp2_fast(__builtin_fmaf(s[hh][i], c, nl));
+        if (MASKED) pr = mask_zero(pr, mw[kb], 8 * (i / 4) + (i % 4));
         s[hh][i] = pr * (FROM_DELTA ? dp[hh][i] : dp[hh][i] - dl);
       }
       dsb[hh][0] = pack8(s[hh], 0);
@@ -701,34 +784,37 @@ __device__ __forceinline__ void dq_tile(const char* kt_lds, const char* vt_lds, 
 // heads sharing the K / V fragments.)
 // TERMS: as in dq_pipe_item.
 template <int D>
-constexpr int kDqLds = 2 * (2 * kKeysPerTile * D * 2 + kTileMaskBytes);
+constexpr int kDqLds = (D == 64 ? 3 : 2) * 2 * kKeysPerTile * D * 2 + (D == 64 ? 4 : 2) * kTileMaskBytes;
 template <int D, bool SV, bool TERMS>
 __device__ __forceinline__ void dq_item(const BwdParams& p, char* lds_base, int b) {
   constexpr int NH = 1;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr bool kAsPipe = D == 64;
-  char (&lds)[2][2][kTileBytes] = *reinterpret_cast<char (*)[2][2][kTileBytes]>(lds_base);  // [buffer][K|V]
-  char (&lds_mask)[2][kTileMaskBytes] = *reinterpret_cast<char (*)[2][kTileMaskBytes]>(lds_base + sizeof(lds));
+  constexpr bool kChainFirst = D == 64;
+  constexpr int kBufs = kChainFirst ? 3 : 2, kMasks = kChainFirst ? 4 : 2;  // (see fwd_kernel)
+  char (&lds)[kBufs][2][kTileBytes] = *reinterpret_cast<char (*)[kBufs][2][kTileBytes]>(lds_base);  // [buffer][K|V]
+  char (&lds_mask)[kMasks][kTileMaskBytes] = *reinterpret_cast<char (*)[kMasks][kTileMaskBytes]>(lds_base + sizeof(lds));
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
   const uint32_t mask_lds = lds_scalar_addr(&lds_mask[0][0]);
   const DeviceTileMap& tm = p.tm;
-  const int group = p.Hq / p.Hkv;
-  const int hpg = group / NH;
-  const int kvh = b % p.Hkv;
-  b /= p.Hkv;
-  const int hc = b % hpg;
-  const int rt = p.rt_hi - 1 - b / hpg;
-  const int h0 = kvh * group + hc * NH;
+  static_assert(NH == 1, "by_group counts workgroups of one head");
+  int kvh = b;
+  int hc = split_by(kvh, p.by_kv);
+  const int rt = p.rt_hi - 1 - split_by(hc, p.by_group);
+  const int h0 = kvh * p.group + hc;
 
-  const int e0 = const_int(tm.row_ptr, rt), e1 = const_int(tm.row_ptr, rt + 1);  // (see fwd_kernel)
+  const int e0 = const_int(tm.row_ptr, rt), e_end = const_int(tm.row_ptr, rt + 1);  // (see fwd_kernel)
   const int e_lead = e0 + const_int(tm.row_lead, rt);  // end of the leading run of full tiles
   const int r = wave * 32 + ln;
   int tq;
   const bool row_ok = row_token(tm, rt, r, p.L, tq);
+  ChainTiles ch{};
+  if (kChainFirst) ch = chain_tiles(tm, e0, e_end);
+  const int e1 = e_end - ch.n;  // (the chain tiles come first)
   TileEntry cur = const_entry(tm.row_entries, e0);
-  TileEntry nxt = const_entry(tm.row_entries, e0 + 1 < e1 ? e0 + 1 : e0);
+  TileEntry nxt = const_entry(tm.row_entries, e0 + 1 < e_end ? e0 + 1 : e0);
 
   bf16x8 qf[NH][D / 16], dof[NH][D / 16], of[NH][D / 16];
   float lse2[NH], delta[NH];
@@ -744,7 +830,19 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, char* lds_base, int 
       if (TERMS) of[hh][st] = as_frag(ld16(p.o + off + st * 16));
     }
   }
-  dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, cur.tile, p.L, wave, lane, p.v_shared);
+  auto copy_tile = [&](int buf, int kt) {
+    if (kChainFirst) dma_d0_tile<D, 4>(kl.k(buf), kl.v(buf), p.k, p.v, p.Hkv, kvh, kt, p.L, wave, lane);
+    else dma_key_tile<D, 4, SV>(kl.k(buf), kl.v(buf), p.k, p.v, p.Hkv, kvh, tm, kt, p.L, wave, lane, p.v_shared);
+  };
+  if (kChainFirst) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (i < ch.n) {
+        dma_chain_tile<D, 4, SV>(kl.k(1 + i), kl.v(1 + i), p.k, p.v, p.Hkv, kvh, tm, ch.tile[i].tile, p.L, wave, lane, p.v_shared);
+        dma_tile_mask(mask_lds + (2 + i) * kTileMaskBytes, tm, ch.tile[i], wave);
+      }
+  }
+  copy_tile(0, cur.tile);
   dma_tile_mask(mask_lds, tm, cur, wave);
 #pragma unroll
   for (int hh = 0; TERMS && hh < NH; ++hh) {
@@ -779,6 +877,15 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, char* lds_base, int 
     }
   }
   dma_publish();
+  if (kChainFirst && ch.n > 0) {
+#pragma unroll 1
+    for (int i = 0; i < ch.n; ++i) {
+      uint32_t mw[2];
+      tile_mask(lds_mask[2 + i], r, g, mw);
+      dq_tile<D, NH, true>(lds[1 + i][0], lds[1 + i][1], no, to, qf, dof, dq, lse2, delta, mw, p.c_log2);
+    }
+    __syncthreads();  // buffer 1 may be overwritten
+  }
 
   int e = e0;
   auto full_tiles = [&](int e_end, auto from_delta_tag) {  // leading full tiles: counted loop, no mask branch
@@ -787,7 +894,7 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, char* lds_base, int 
       const int buf = (e - e0) & 1;
       const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
       if (e + 1 < e1) {
-        dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+        copy_tile(buf ^ 1, nxt.tile);
         dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
       }
       const uint32_t mw[2] = {0xffffffffu, 0xffffffffu};
@@ -803,7 +910,7 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, char* lds_base, int 
     const int buf = (e - e0) & 1;
     const u32x2 ahead = fetch_entry(tm.row_entries, e + 2 < e1 ? e + 2 : e);
     if (e + 1 < e1) {
-      dma_key_tile<D, 4, SV>(kl.k(buf ^ 1), kl.v(buf ^ 1), p.k, p.v, p.Hkv, kvh, tm, nxt.tile, p.L, wave, lane, p.v_shared);
+      copy_tile(buf ^ 1, nxt.tile);
       dma_tile_mask(mask_lds + (buf ^ 1) * kTileMaskBytes, tm, nxt, wave);
     }
     uint32_t mw[2];
@@ -958,43 +1065,36 @@ __device__ __forceinline__ void dq_pipe_body(DqPipe<D>& P, const char* k_dq, con
 
 // TERMS: forms the per-row terms from O and writes them for the dK/dV kernel; otherwise they are there already.
 template <int D>
-constexpr int kDqPipeLds = 3 * (2 * kKeysPerTile * D * 2 + kTileMaskBytes);
+constexpr int kDqPipeLds = 4 * 2 * kKeysPerTile * D * 2 + 5 * kTileMaskBytes;
 template <int D, bool SV, bool TERMS>
 __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base, int b) {
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr int N2 = D / 16;
-  char (&lds)[3][2][kTileBytes] = *reinterpret_cast<char (*)[3][2][kTileBytes]>(lds_base);  // [buffer][K|V]
-  const char* lds_mask = lds_base + sizeof(lds);                                                      // [buffer]
+  char (&lds)[4][2][kTileBytes] = *reinterpret_cast<char (*)[4][2][kTileBytes]>(lds_base);  // [buffer][K|V]
+  const char* lds_mask = lds_base + sizeof(lds);                                                      // [buffer], then the chain tiles'
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const KeyTileLds<D> kl(&lds[0][0][0], wave);
   const uint32_t mask_lds = lds_scalar_addr(lds_mask);
   const DeviceTileMap& tm = p.tm;
-  const int group = p.Hq / p.Hkv;
-  const int kvh = b % p.Hkv;
-  b /= p.Hkv;
-  const int hc = b % group;
-  const int rt = p.rt_hi - 1 - b / group;  // heaviest row tiles first
-  const int h = kvh * group + hc;
+  int kvh = b;
+  int hc = split_by(kvh, p.by_kv);
+  const int rt = p.rt_hi - 1 - split_by(hc, p.by_group);  // heaviest row tiles first
+  const int h = kvh * p.group + hc;
 
-  const int e0 = const_int(tm.row_ptr, rt), e1 = const_int(tm.row_ptr, rt + 1);  // (see fwd_kernel)
+  const int e0 = const_int(tm.row_ptr, rt), e_end = const_int(tm.row_ptr, rt + 1);  // (see fwd_kernel)
   const int n_lead = const_int(tm.row_lead, rt);  // leading full tiles
   const int r = wave * 32 + ln;  // row of the tile owned by this lane (shared with lane ^ 32)
   int tq;
   const bool row_ok = row_token(tm, rt, r, p.L, tq);
-  auto entry_at = [&](int e) { return e < e1 ? e : e1 - 1; };
+  const ChainTiles ch = chain_tiles(tm, e0, e_end);
+  const int e1 = e_end - ch.n;  // (the chain tiles come first)
+  auto entry_at = [&](int e) { return e < e_end ? e : e_end - 1; };
   TileEntry t_cur = const_entry(tm.row_entries, e0);
   TileEntry t_n1 = const_entry(tm.row_entries, entry_at(e0 + 1));
   TileEntry t_n2 = const_entry(tm.row_entries, entry_at(e0 + 2));
   const TileEntry masked0 = const_entry(tm.row_entries, entry_at(e0 + n_lead));  // the first two with a bitmask, if there are any
   const TileEntry masked1 = const_entry(tm.row_entries, entry_at(e0 + n_lead + 1));
-
-  // The K half of the buffer that the first pipelined body reads its (absent) predecessor from: that body
-  // multiplies it by dS = 0, so it only has to be finite.
-  {
-    uint4* z = reinterpret_cast<uint4*>(lds[2][0]);
-    for (int i = tid; i < kTileBytes / 16; i += 256) z[i] = make_uint4(0, 0, 0, 0);
-  }
 
   bf16x8 qf[1][D / 16], dof[1][D / 16], of[D / 16];
   const size_t at = (size_t)h * p.T + (row_ok ? tq : 0);
@@ -1011,10 +1111,16 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
 
   // the first two tiles are on their way before anything is computed, and the first two bitmasks, to where their tiles find them:
   // the pipeline then has no test for one (with / without, us: 20,480 anchors 34,970 / 34,780, 8,000 5,690 / 5,657)
-  dma_key_tile<D, 4, SV>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, tm, t_cur.tile, p.L, wave, lane, p.v_shared);
-  if (e0 + 1 < e1) dma_key_tile<D, 4, SV>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, tm, t_n1.tile, p.L, wave, lane, p.v_shared);
+  dma_d0_tile<D, 4>(kl.k(0), kl.v(0), p.k, p.v, p.Hkv, kvh, t_cur.tile, p.L, wave, lane);
+  if (e0 + 1 < e1) dma_d0_tile<D, 4>(kl.k(1), kl.v(1), p.k, p.v, p.Hkv, kvh, t_n1.tile, p.L, wave, lane);
   dma_tile_mask(mask_lds + n_lead % 3 * kTileMaskBytes, tm, masked0, wave);
   dma_tile_mask(mask_lds + (n_lead + 1) % 3 * kTileMaskBytes, tm, masked1, wave);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (i < ch.n) {
+      dma_chain_tile<D, 4, SV>(kl.k(2 + i), kl.v(2 + i), p.k, p.v, p.Hkv, kvh, tm, ch.tile[i].tile, p.L, wave, lane, p.v_shared);
+      dma_tile_mask(mask_lds + (3 + i) * kTileMaskBytes, tm, ch.tile[i], wave);
+    }
 
   if (TERMS) {
     float dl = 0.f;
@@ -1041,7 +1147,21 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
   const float row_factor = (unnormalised ? exp2_fast(-lse2) : 1.f) * p.scale;
   const int n_groups = unnormalised ? n_lead / 3 : 0;  // groups of three pipelined tiles
 
-  dma_publish();  // tiles e0 and e0+1 have landed (and the zero fill above is visible)
+  dma_publish();  // tiles e0 and e0+1 have landed, and the chain tiles
+#pragma unroll 1
+  for (int i = 0; i < ch.n; ++i) {
+    uint32_t mw[2];
+    tile_mask(lds_mask + (3 + i) * kTileMaskBytes, r, g, mw);
+    dq_tile<D, 1, true>(lds[2 + i][0], lds[2 + i][1], no, to, qf, dof, dq, lse_used, delta_used, mw, p.c_log2);
+  }
+  __syncthreads();  // buffer 2 may be overwritten
+  if (n_groups > 0) {
+    // The K half of the buffer that the first pipelined body reads its (absent) predecessor from: that body multiplies it by
+    // dS = 0, so it only has to be finite.
+    uint4* z = reinterpret_cast<uint4*>(lds[2][0]);
+    for (int i = tid; i < kTileBytes / 16; i += 256) z[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+  }
   int e = e0;
 
   if (n_groups > 0) {
@@ -1074,7 +1194,7 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
       // Every wave has left tile e-1 (its last reader was the body above) and has waited for its own copies of
       // tile e+1: after the barrier that buffer may be overwritten and tile e+1 may be read.
       dma_publish();
-      if (e + 2 < e1) dma_key_tile<D, 4, SV>(kl.k(BP), kl.v(BP), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
+      if (e + 2 < e1) dma_d0_tile<D, 4>(kl.k(BP), kl.v(BP), p.k, p.v, p.Hkv, kvh, t_n2.tile, p.L, wave, lane);
       dq_pipe_body<D, 1, LAST>(P, lds[B][0], lds[BN][0], lds[BN][1], lds[B][0], no, to, qf, dof, dq, ndelta16, c);
       t_cur = t_n1;
       t_n1 = t_n2;
@@ -1111,7 +1231,7 @@ __device__ __forceinline__ void dq_pipe_item(const BwdParams& p, char* lds_base,
       const u32x2 ahead = fetch_entry(tm.row_entries, entry_at(e + 3));
       const int buf2 = buf == 0 ? 2 : buf - 1;
       if (e + 2 < e1) {
-        dma_key_tile<D, 4, SV>(kl.k(buf2), kl.v(buf2), p.k, p.v, p.Hkv, kvh, tm, t_n2.tile, p.L, wave, lane, p.v_shared);
+        dma_d0_tile<D, 4>(kl.k(buf2), kl.v(buf2), p.k, p.v, p.Hkv, kvh, t_n2.tile, p.L, wave, lane);
         if (MASKED) dma_tile_mask(mask_lds + buf2 * kTileMaskBytes, tm, t_n2, wave);
       }
       const char* kt_lds = lds[0][0] + buf * (2 * kTileBytes);
@@ -1501,7 +1621,7 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
   const int kblk = wave;  // 32-key block of the pair owned by this wave
   const DeviceTileMap& tm = p.tm;
-  const int group = p.Hq / p.Hkv;
+  const int group = p.group;
 
   // the item's range (field by field: a struct chosen as a whole is copied through scratch memory)
   auto of_range = [&](int DkdvRange::* field, int n) {
@@ -1532,16 +1652,16 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
     // ones fill the slots that free up (one pass - d0_split = pair count - when all lists are
     // equally long).
     const int n_pairs = (rg.n_d0_tiles - rg.d0_tile_lo + 1) / 2;
-    kvh = b % p.Hkv;
-    b /= p.Hkv;
+    kvh = b;
+    b = split_by(kvh, p.by_kv);
     int first = 0, count = rg.d0_split;
     while (b >= count * group) {  // at most a few passes
       b -= count * group;
       first += count;
       count = n_pairs - first < rg.d0_step ? n_pairs - first : rg.d0_step;
     }
-    const int pair = first + b % count;
     const int head = b / count;
+    const int pair = first + b - head * count;
     kt0 = rg.d0_tile_lo + 2 * pair;
     h_lo = kvh * group + head;
     h_hi = h_lo + 1;
@@ -1553,12 +1673,10 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
     rg.s_hi = p.s_hi;
     rg.clip_rows = p.clip_rows;
     b = item - p.n_d0_items;
-    kvh = b % p.Hkv;
-    b /= p.Hkv;
-    const int n_cpair = (tm.n_csub + 1) / 2;
-    const int sub0 = 2 * (b % n_cpair);
-    kt0 = tm.n_d0 + (p.rt_lo + b / n_cpair) * tm.n_csub + sub0;
-    n_tiles = sub0 + 1 < tm.n_csub ? 2 : 1;
+    kvh = b;
+    b = split_by(kvh, p.by_kv);  // (a row tile has at most two chain tiles: one pair)
+    kt0 = tm.n_d0 + (p.rt_lo + b) * tm.n_csub;
+    n_tiles = tm.n_csub;
     h_lo = kvh * group;
     h_hi = h_lo + group;
   }
@@ -1890,9 +2008,8 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
       static_assert(4 * D * 33 * 4 <= kLdsBytes, "the four waves' transposition buffers must fit");
       const bool have = tile_present && key_ok;
       const float* rope = p.rope_table && have ? p.rope_table + (size_t)token_position(tm, key_tok, p.L) * D : nullptr;
-      const int b_chain = item - p.n_d0_items;
-      const int n_cpair = (tm.n_csub + 1) / 2;
-      const size_t prow = ((size_t)(p.rt_lo + b_chain / p.Hkv / n_cpair) * n_cpair + (b_chain / p.Hkv) % n_cpair) * 4 + wave;
+      int b_chain = item - p.n_d0_items;
+      const size_t prow = (size_t)(p.rt_lo + split_by(b_chain, p.by_kv)) * 4 + wave;
   #pragma unroll
       for (int which = 0; which < 2; ++which) {  // 0: dK, 1: dV
         if (which == 0 && rope) {
@@ -2069,15 +2186,15 @@ struct PartSets {
 };
 template <int D, int SETS>
 __global__ __launch_bounds__(256) void reduce_partials_kernel(BwdParams p, PartSets sets) {
-  const int group = p.Hq / p.Hkv;
+  constexpr int kTogether = 4;  // heads whose loads are on their way together
+  const int group = p.group;
   const size_t per = (size_t)(sets.key_hi - sets.key_lo) * p.Hkv * (D / 4);
   for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < 2 * per; idx += (size_t)gridDim.x * blockDim.x) {
     const int which = idx >= per;
-    size_t rem = which ? idx - per : idx;
+    const size_t rem = which ? idx - per : idx;
     const int c4 = rem % (D / 4);
-    rem /= (D / 4);
-    const int kvh = rem % p.Hkv;
-    const int j = sets.key_lo + (int)(rem / p.Hkv);
+    int kvh = (int)(rem / (D / 4));  // (K rows of all keys: fewer than 2^31)
+    const int j = sets.key_lo + split_by(kvh, p.by_kv);
     // With rotary embedding the summed dK is turned back to the unrotated keys' frame: the thread of
     // a lower-half piece also sums its partner piece of the upper half and stores both.
     const bool turn = !which && p.rope_table != nullptr;
@@ -2090,10 +2207,25 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(BwdParams p, PartS
       if (SETS > 1 && (i >= sets.n || j < sets.key_first[i] || j >= sets.key_end[i])) continue;
       const float* part = part_of(p, i, which);
       f32x4 sum = {0.f, 0.f, 0.f, 0.f}, sum_hi = {0.f, 0.f, 0.f, 0.f};
-      for (int hh = 0; hh < group; ++hh) {
-        const float* src = part + (((size_t)(kvh * group + hh) * p.L64 + j) * D + c4 * 4);
-        sum += *reinterpret_cast<const f32x4*>(src);
-        if (turn) sum_hi += *reinterpret_cast<const f32x4*>(src + D / 2);
+      const float* src = part + (((size_t)(kvh * group) * p.L64 + j) * D + c4 * 4);
+      const size_t head = (size_t)p.L64 * D;
+      int hh = 0;
+      for (; hh + kTogether <= group; hh += kTogether) {
+        f32x4 x[kTogether], y[kTogether];
+#pragma unroll
+        for (int u = 0; u < kTogether; ++u) {
+          x[u] = *reinterpret_cast<const f32x4*>(src + (hh + u) * head);
+          if (turn) y[u] = *reinterpret_cast<const f32x4*>(src + (hh + u) * head + D / 2);
+        }
+#pragma unroll
+        for (int u = 0; u < kTogether; ++u) {
+          sum += x[u];
+          if (turn) sum_hi += y[u];
+        }
+      }
+      for (; hh < group; ++hh) {
+        sum += *reinterpret_cast<const f32x4*>(src + hh * head);
+        if (turn) sum_hi += *reinterpret_cast<const f32x4*>(src + hh * head + D / 2);
       }
       if (turn) {
         const float* rope = p.rope_table + (size_t)token_position(p.tm, j, p.L) * D + c4 * 4;  // depth-0 key j is token j
@@ -2601,7 +2733,9 @@ hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer
   if (D == 128 && sv) return hipErrorInvalidValue;  // (D = 128 has no such instantiation: its callers expand V instead)
   TimedSpan span(timer, kKindFwd, stream);
   auto go = [&](auto kernel, int heads) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_rt * (p.Hq / heads))), dim3(256), 0, stream, p);
+    FwdParams fp = p;
+    fp.by_heads = make_divisor(p.group / heads);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_rt * (p.Hq / heads))), dim3(256), 0, stream, fp);
   };
   if (D == 128) {
     go(fwd_kernel<128, 1, false, 2>, 1);
@@ -2763,7 +2897,7 @@ hipError_t DkdvLauncher::finish() {
     if (sets.key_first[r.set] < sets.key_lo) sets.key_lo = sets.key_first[r.set];
     if (sets.key_end[r.set] > sets.key_hi) sets.key_hi = sets.key_end[r.set];
   }
-  p.n_chain_items = (p.rt_hi - p.rt_lo) * ((p.tm.n_csub + 1) / 2) * p.Hkv;
+  p.n_chain_items = p.tm.n_csub > 0 ? (p.rt_hi - p.rt_lo) * p.Hkv : 0;
   const bool sv_dkdv = p.shared_dk_part != nullptr;  // (first-layer form)
   const bool listed_map = p.tm.row_tok != nullptr;
   {

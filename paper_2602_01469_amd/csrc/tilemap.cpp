@@ -217,6 +217,8 @@ int upload_map(peagle_tilemap* tm, hipStream_t stream, bool wait) {
   tm->dview.K = tm->K;
   tm->dview.chain_slots = tm->chain_slots;
   tm->dview.chain_first = tm->chain_first;
+  tm->dview.k_reciprocal = peagle::small_reciprocal(tm->K);
+  tm->dview.slots_reciprocal = peagle::small_reciprocal(tm->chain_slots);
   tm->dview.S = tm->S;
   tm->dview.n_row_tiles = tm->n_row_tiles;
   tm->dview.n_d0 = tm->n_d0;

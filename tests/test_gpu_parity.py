@@ -1248,3 +1248,25 @@ def test_sampled_map_of_long_lists_runs_the_pipelined_dq():
     tm = pe.peagle_build_tilemap_sampled(cod_depth_counts(3000, 4, 0.8, 395), 4, None, device=0)
     assert mean_list(tm) > 24 and dq_path(tm, 2) == "one grid"
     test_sampled_sequences_match_oracle("long_lists", 3000, 4, 2, 1, 64, 0.8, 395, None)
+
+
+@pytest.mark.parametrize("K,L,L_max,Hq,Hkv", [(1, 60, 300, 3, 3), (1, 130, 300, 10, 5), (3, 50, 200, 15, 5), (3, 43, 130, 7, 1),
+                                              (8, 65, 128, 11, 11), (5, 77, 77, 9, 3), (2, 65, 200, 12, 6), (128, 2, 3, 5, 5)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_key_tiles_at_and_past_the_end_of_a_cropped_sequence(D, K, L, L_max, Hq, Hkv):
+    """A row tile of more anchors than the sequence has left lists key tiles that the sequence ends in, or that lie wholly past
+    it (K = 1 and 3), whose rows the copies must not look for; none, one and two chain tiles, which a row tile takes first;
+    numbers of heads of which none is a power of two."""
+    seed = 360 + K + L
+    print(f"case end of sequence: K={K} L={L} of {L_max} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
+    qb, kb, vb, dob = (rand_bits((L * K, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
+    tm = pe.peagle_build_tilemap(L_max, K, None, device=0)
+    ref = _oracle(qb, kb, vb, dob, L, K, pe.Shape(L, K, Hq, Hkv, D).scale)
+    for whole_step in (True, False):
+        r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
+        if whole_step:
+            r.step(0, 1)
+        else:
+            r.fwd()
+            r.bwd()
+        _check_against_oracle(r.results(), ref, f"end K={K} L={L} D={D}")
