@@ -100,7 +100,10 @@ struct DecodeParams {
   float* part_ml;              // workspace [C, Hkv, n_splits, 3, rows_pad]: reference max (log2), row sum, flag
   int C, K, Hq, Hkv, n_pages, max_pages, rows_pad;
   int n_splits;                // pieces the workspace is laid out for; the launcher replaces it by draft_pieces()
-  int by_length;               // filled by the launcher: requests take the workgroups by falling context length (C <= 64)
+  int group;                   // filled by the launcher, like what follows: query heads per KV head,
+  uint32_t group_reciprocal;   // its small_reciprocal()
+  Divisor by_splits;
+  int by_length;               // requests take the workgroups by falling context length (C <= 64)
   float c_log2;
 };
 hipError_t launch_draft_decode(const DecodeParams& p, int D, hipStream_t stream);

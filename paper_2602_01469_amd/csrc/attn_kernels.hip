@@ -2301,7 +2301,7 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
   const bool copies_v = wave > n_compute;  // (a copying wave: V rather than K)
   const bool copies_both = D == 128 && kGroups == 1 && (int)(blockDim.x >> 6) == n_compute + 1;  // (three row blocks: see the launcher)
   const int split = blockIdx.x, kvh = blockIdx.y;
-  const int group = p.Hq / p.Hkv;
+  const int group = p.group;
   const int n_rows = p.K * group;
 
   // Request of this workgroup: workgroups start in the order of blockIdx.z, and the requests take them by falling
@@ -2330,7 +2330,8 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
   bool bad = n_ctx < 0 || n_ctx > p.max_pages * kKeysPerTile;
   n_ctx = n_ctx < 0 ? 0 : (n_ctx > p.max_pages * kKeysPerTile ? p.max_pages * kKeysPerTile : n_ctx);
   const int n_pg = (n_ctx + kKeysPerTile - 1) / kKeysPerTile;
-  const int per = (n_pg + p.n_splits - 1) / p.n_splits;
+  int up = n_pg + p.n_splits - 1;
+  const int per = split_by(up, p.by_splits);
   const int p0 = split * per < n_pg ? split * per : n_pg;
   const int p1 = p0 + per < n_pg ? p0 + per : n_pg;
   const int n_tiles = (p1 - p0) + (split == 0 ? 1 : 0);  // split 0 also takes the new keys
@@ -2426,7 +2427,7 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
   const int grp = wave / n_row_waves;                    // which of the kGroups
   const int r = (wave - grp * n_row_waves) * 32 + ln;    // query row of this lane (shared with lane ^ 32)
   const bool row_ok = r < n_rows;
-  const int depth = row_ok ? r / group : 0, head = kvh * group + (row_ok ? r - depth * group : 0);
+  const int depth = row_ok ? small_quotient(r, p.group_reciprocal) : 0, head = kvh * group + (row_ok ? r - depth * group : 0);
   bf16x8 qf[1][D / 16];
   {
     const __bf16* qrow = p.q_new + (((size_t)c * p.K + depth) * p.Hq + head) * D + g * 8;
@@ -2532,78 +2533,71 @@ __global__ __launch_bounds__(kThreads) void draft_decode_kernel(DecodeParams p) 
 // kLanes threads per (request, KV head, row, 4 features), kEach splits per thread, all of a thread's loads issued
 // before the first is used: the kernel's time is one memory round trip (two passes over the splits, and all status
 // words set by one workgroup, took 6.2 / 8.9 / 13.6 us for 4 x 16, 2 x 32 and 64 x 2 requests x splits; this 4.3 /
-// 4.0 / 6.3).  The threads of a row sit D/4 lanes apart and are merged by lane exchange.  The wave of a request's
+// 4.0 / 6.3).  Request and KV head are grid dimensions: taken from a row number, three 64-bit divisions stood before the first
+// load.  us per drafting step with them / so: 4 requests of 2,048 - 4,096 tokens 12.6 / 11.8, 2 of 10,800 - 20,000 at D = 128
+// 20.9 / 20.1, 16 of 1,000 13.4 / 12.8, 64 of 512 - 8,192 118.5 / 117.2 (the main kernel without divisions included).  The threads of a row sit D/4 lanes apart and are merged by lane exchange.  The wave of a request's
 // first row of KV head 0 also sets its status word: every KV head's workgroups look at the same block-table entries,
 // so head 0's records tell.
 template <int D, int kLanes, int kEach>
 __global__ __launch_bounds__(256) void draft_decode_combine_kernel(DecodeParams p) {
   constexpr int kPerRow = (D / 4) * kLanes, kRowsPerWave = 64 / kPerRow;
   static_assert(kPerRow <= 64, "the threads of a row are one wave's");
-  const int group = p.Hq / p.Hkv;
-  const int n_rows = p.K * group;
+  const int n_rows = p.K * p.group;
   const int lane = threadIdx.x & 63;
   const int c4 = lane % (D / 4), sl = lane / (D / 4) % kLanes;
-  const size_t n = (size_t)p.C * p.Hkv * n_rows;
-  const size_t wave0 = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const size_t n_waves = (size_t)gridDim.x * (blockDim.x >> 6);
-  for (size_t first = wave0 * kRowsPerWave; first < n; first += n_waves * kRowsPerWave) {
-    const size_t row = first + lane / kPerRow;
-    const bool ok = row < n;
-    size_t rem = ok ? row : n - 1;
-    const int r = (int)(rem % n_rows);
-    rem /= n_rows;
-    const int kvh = (int)(rem % p.Hkv);
-    const int c = (int)(rem / p.Hkv);
-    const size_t rec0 = ((size_t)c * p.Hkv + kvh) * p.n_splits;
-    const float* ml0 = p.part_ml + rec0 * 3 * p.rows_pad + r;
-    const float* o0 = p.part_o + (rec0 * p.rows_pad + r) * D + c4 * 4;
-    float mv[kEach], lv[kEach];
-    f32x4 ov[kEach];
+  const int kvh = blockIdx.y, c = blockIdx.z;
+  const int row = ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * kRowsPerWave + lane / kPerRow;
+  const bool ok = row < n_rows;
+  const int r = ok ? row : n_rows - 1;
+  const size_t rec0 = ((size_t)c * p.Hkv + kvh) * p.n_splits;
+  const float* ml0 = p.part_ml + rec0 * 3 * p.rows_pad + r;
+  const float* o0 = p.part_o + (rec0 * p.rows_pad + r) * D + c4 * 4;
+  float mv[kEach], lv[kEach];
+  f32x4 ov[kEach];
 #pragma unroll
-    for (int j = 0; j < kEach; ++j) {  // (splits past the last are read as the last and weigh nothing)
-      const int s = sl * kEach + j < p.n_splits ? sl * kEach + j : p.n_splits - 1;
-      mv[j] = ml0[(size_t)s * 3 * p.rows_pad];
-      lv[j] = ml0[(size_t)s * 3 * p.rows_pad + p.rows_pad];
-      ov[j] = *reinterpret_cast<const f32x4*>(o0 + (size_t)s * p.rows_pad * D);
-    }
-    bool any = false;
-    const bool flags = p.status && ok && r == 0 && kvh == 0;
-    if (flags) {
-      for (int s = lane % kPerRow; s < p.n_splits; s += kPerRow) any |= ml0[((size_t)s * 3 + 2) * p.rows_pad] != 0.f;
-    }
-    float M = mv[0];
+  for (int j = 0; j < kEach; ++j) {  // (splits past the last are read as the last and weigh nothing)
+    const int s = sl * kEach + j < p.n_splits ? sl * kEach + j : p.n_splits - 1;
+    mv[j] = ml0[(size_t)s * 3 * p.rows_pad];
+    lv[j] = ml0[(size_t)s * 3 * p.rows_pad + p.rows_pad];
+    ov[j] = *reinterpret_cast<const f32x4*>(o0 + (size_t)s * p.rows_pad * D);
+  }
+  bool any = false;
+  const bool flags = p.status && ok && r == 0 && kvh == 0;
+  if (flags) {
+    for (int s = lane % kPerRow; s < p.n_splits; s += kPerRow) any |= ml0[((size_t)s * 3 + 2) * p.rows_pad] != 0.f;
+  }
+  float M = mv[0];
 #pragma unroll
-    for (int j = 1; j < kEach; ++j) M = __builtin_fmaxf(M, mv[j]);
+  for (int j = 1; j < kEach; ++j) M = __builtin_fmaxf(M, mv[j]);
 #pragma unroll
-    for (int x = D / 4; x < kPerRow; x <<= 1) M = __builtin_fmaxf(M, __shfl_xor(M, x));
-    float L = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int x = D / 4; x < kPerRow; x <<= 1) M = __builtin_fmaxf(M, __shfl_xor(M, x));
+  float L = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < kEach; ++j) {
-      const float w = sl * kEach + j < p.n_splits ? exp2_fast(mv[j] - M) : 0.f;
-      L = __builtin_fmaf(lv[j], w, L);
-      acc += ov[j] * w;
-    }
+  for (int j = 0; j < kEach; ++j) {
+    const float w = sl * kEach + j < p.n_splits ? exp2_fast(mv[j] - M) : 0.f;
+    L = __builtin_fmaf(lv[j], w, L);
+    acc += ov[j] * w;
+  }
 #pragma unroll
-    for (int x = D / 4; x < kPerRow; x <<= 1) {
-      L += __shfl_xor(L, x);
+  for (int x = D / 4; x < kPerRow; x <<= 1) {
+    L += __shfl_xor(L, x);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] += __shfl_xor(acc[j], x);
-    }
-    const float inv = 1.0f / L;
-    const int depth = r / group, head = kvh * group + (r - depth * group);
-    if (ok && sl == 0) {
-      u32x2 w2;
-      w2[0] = pack_bf16(acc[0] * inv, acc[1] * inv);
-      w2[1] = pack_bf16(acc[2] * inv, acc[3] * inv);
-      *reinterpret_cast<u32x2*>(p.o + (((size_t)c * p.K + depth) * p.Hq + head) * D + c4 * 4) = w2;
-      if (c4 == 0) p.lse[((size_t)c * p.Hq + head) * p.K + depth] = (M + __builtin_log2f(L)) * kLn2;
-    }
-    const uint64_t votes = __builtin_amdgcn_ballot_w64(any);
-    if (flags && lane % kPerRow == 0) {
-      const uint64_t row_lanes = kPerRow == 64 ? ~0ull : ((1ull << (kPerRow & 63)) - 1) << lane;
-      p.status[c] = (votes & row_lanes) != 0 ? 1 : 0;
-    }
+    for (int j = 0; j < 4; ++j) acc[j] += __shfl_xor(acc[j], x);
+  }
+  const float inv = 1.0f / L;
+  const int depth = small_quotient(r, p.group_reciprocal), head = kvh * p.group + (r - depth * p.group);
+  if (ok && sl == 0) {
+    u32x2 w2;
+    w2[0] = pack_bf16(acc[0] * inv, acc[1] * inv);
+    w2[1] = pack_bf16(acc[2] * inv, acc[3] * inv);
+    *reinterpret_cast<u32x2*>(p.o + (((size_t)c * p.K + depth) * p.Hq + head) * D + c4 * 4) = w2;
+    if (c4 == 0) p.lse[((size_t)c * p.Hq + head) * p.K + depth] = (M + __builtin_log2f(L)) * kLn2;
+  }
+  const uint64_t votes = __builtin_amdgcn_ballot_w64(any);
+  if (flags && lane % kPerRow == 0) {
+    const uint64_t row_lanes = kPerRow == 64 ? ~0ull : ((1ull << (kPerRow & 63)) - 1) << lane;
+    p.status[c] = (votes & row_lanes) != 0 ? 1 : 0;
   }
 }
 
@@ -2966,6 +2960,9 @@ int draft_pieces(int64_t wgs_per_piece, int max_pages, int laid_out, int D) {
 hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t stream) {
   DecodeParams p = pin;
   p.n_splits = draft_pieces((int64_t)p.C * p.Hkv, p.max_pages, p.n_splits, D);
+  p.group = p.Hq / p.Hkv;
+  p.group_reciprocal = small_reciprocal(p.group);
+  p.by_splits = make_divisor(p.n_splits);
   const int row_waves = p.rows_pad / 32;  // 1 .. 4
   const dim3 grid((unsigned)p.n_splits, (unsigned)p.Hkv, (unsigned)p.C);
   const int64_t n_wg = (int64_t)p.C * p.Hkv * p.n_splits;
@@ -3004,10 +3001,9 @@ hipError_t launch_draft_decode(const DecodeParams& pin, int D, hipStream_t strea
   if (e != hipSuccess || p.n_splits == 1) return e;
   // threads per row and splits per thread: n_splits is at most 32
   auto merge = [&](auto kernel, int rows_per_wave) {
-    const size_t waves = ((size_t)p.C * p.Hkv * p.K * (p.Hq / p.Hkv) + rows_per_wave - 1) / rows_per_wave;
-    size_t blocks = (waves + 3) / 4;
-    if (blocks > kCus * 16) blocks = kCus * 16;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+    const int per_block = 4 * rows_per_wave;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((p.K * p.group + per_block - 1) / per_block), (unsigned)p.Hkv, (unsigned)p.C), dim3(256),
+                       0, stream, p);
   };
   if (D == 64) {
     if (p.n_splits <= 2) merge(draft_decode_combine_kernel<64, 1, 2>, 4);
