@@ -306,6 +306,10 @@ def _ptr(t, name: str, dtype, shape):
     """Device pointer of a torch tensor after checking dtype / shape / contiguity."""
     if t is None:
         return None
+    # (A drafting step passes ten tensors and takes the GPU less time than the host needs for them: what is right is found
+    # so with one test, and the pointer goes to ctypes as the integer it is.)
+    if t.dtype is dtype and t.shape == shape and t.is_contiguous() and t.is_cuda:
+        return t.data_ptr()
     if t.dtype != dtype:
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
     if tuple(t.shape) != tuple(shape):
@@ -314,13 +318,14 @@ def _ptr(t, name: str, dtype, shape):
         raise ValueError(f"{name}: must be contiguous")
     if not t.is_cuda:
         raise ValueError(f"{name}: must live on the GPU")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is None:  # (torch.cuda.current_stream().cuda_stream without the object in between)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return C.c_void_p(stream.cuda_stream)
 
 
 def peagle_attn_fwd(tm: TileMap, shape: Shape, seg: int, q, k, v, o, lse, stream=None) -> None:
@@ -348,7 +353,7 @@ def peagle_attn_bwd(tm: TileMap, shape: Shape, seg: int, q, k, v, o, d_o, lse, d
         tm.handle, shape.c(), seg, _ptr(q, "q", bf, qs), _ptr(k, "k", bf, ks), _ptr(v, "v", bf, ks),
         _ptr(o, "o", bf, qs), _ptr(d_o, "d_o", bf, qs), _ptr(lse, "lse", f32, (shape.Hq, T)),
         _ptr(dq, "dq", bf, qs), _ptr(dk_acc, "dk_acc", f32, ks), _ptr(dv_acc, "dv_acc", f32, ks), int(accumulate),
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_ptr(stream))
+        workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     if rc != 0:
         raise PeagleError(rc, "peagle_attn_bwd")
 
@@ -366,7 +371,7 @@ def peagle_attn_step_partitioned(tm: TileMap, shape: Shape, seg_begin: int, seg_
         _ptr(d_o, "d_o", bf, qs), _ptr(o, "o", bf, qs), _ptr(lse, "lse", f32, (shape.Hq, T)),
         _ptr(dq, "dq", bf, qs), _ptr(dk_acc, "dk_acc", f32, ks), _ptr(dv_acc, "dv_acc", f32, ks),
         _ptr(dk_bf16, "dk_bf16", bf, ks), _ptr(dv_bf16, "dv_bf16", bf, ks),
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_ptr(stream))
+        workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     if rc != 0:
         raise PeagleError(rc, "peagle_attn_step_partitioned")
 
@@ -384,7 +389,7 @@ def peagle_attn_step_profiled(tm: TileMap, shape: Shape, seg_begin: int, seg_end
         tm.handle, shape.c(), seg_begin, seg_end, _ptr(q, "q", bf, qs), _ptr(k, "k", bf, ks), _ptr(v, "v", bf, ks),
         _ptr(d_o, "d_o", bf, qs), _ptr(o, "o", bf, qs), _ptr(lse, "lse", f32, (shape.Hq, T)),
         _ptr(dq, "dq", bf, qs), _ptr(dk_acc, "dk_acc", f32, ks), _ptr(dv_acc, "dv_acc", f32, ks),
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_ptr(stream), C.byref(prof))
+        workspace.data_ptr(), workspace.numel(), _stream_ptr(stream), C.byref(prof))
     if rc != 0:
         raise PeagleError(rc, "peagle_attn_step_profiled")
     return {name: (float(prof.ms[i]), int(prof.launches[i])) for i, name in enumerate(KERNEL_KINDS)}
@@ -454,7 +459,7 @@ def peagle_attn_step_partitioned_rope(tm: TileMap, shape: Shape, seg_begin: int,
     args, ks = _rope_step_args(tm, shape, seg_begin, seg_end, q, k, v, d_o, rope_table, o, lse, dq, dk_acc, dv_acc)
     rc = load_library().peagle_attn_step_partitioned_rope(
         *args, _ptr(dk_bf16, "dk_bf16", torch.bfloat16, ks), _ptr(dv_bf16, "dv_bf16", torch.bfloat16, ks),
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_ptr(stream))
+        workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     if rc != 0:
         raise PeagleError(rc, "peagle_attn_step_partitioned_rope")
 
@@ -464,7 +469,7 @@ def peagle_attn_step_rope_profiled(tm: TileMap, shape: Shape, seg_begin: int, se
     """Same work as peagle_attn_step_partitioned_rope; returns {kind: (ms, launches)} from HIP events."""
     args, _ = _rope_step_args(tm, shape, seg_begin, seg_end, q, k, v, d_o, rope_table, o, lse, dq, dk_acc, dv_acc)
     prof = _ProfileC()
-    rc = load_library().peagle_attn_step_rope_profiled(*args, C.c_void_p(workspace.data_ptr()), workspace.numel(),
+    rc = load_library().peagle_attn_step_rope_profiled(*args, workspace.data_ptr(), workspace.numel(),
                                                        _stream_ptr(stream), C.byref(prof))
     if rc != 0:
         raise PeagleError(rc, "peagle_attn_step_rope_profiled")
@@ -493,7 +498,7 @@ def peagle_attn_step_rope_shared(tm: TileMap, shape: Shape, q, k0, k_shared, v0,
         _ptr(rope_table, "rope_table", f32, (n_pos, 2, shape.D // 2)), n_pos, _ptr(o, "o", bf, qs),
         _ptr(lse, "lse", f32, (shape.Hq, T)), _ptr(dq, "dq", bf, qs), _ptr(dk0, "dk0", f32, k0s),
         _ptr(dv0, "dv0", f32, k0s), _ptr(dk_shared, "dk_shared", f32, kss), _ptr(dv_shared, "dv_shared", f32, kss),
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_ptr(stream))
+        workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     if rc != 0:
         raise PeagleError(rc, "peagle_attn_step_rope_shared")
 
@@ -505,10 +510,14 @@ class DecodeShape:
                  scale: Optional[float] = None):
         self.C, self.K, self.Hq, self.Hkv, self.D, self.n_pages, self.max_pages = C_, K, Hq, Hkv, D, n_pages, max_pages
         self.scale = float(scale) if scale is not None else 1.0 / float(np.sqrt(D))
+        self._packed = (None, None)  # field values, and the structure made of them
 
     def c(self):
-        return C.byref(_DecodeShapeC(self.C, self.K, self.Hq, self.Hkv, self.D, self.scale, self.n_pages,
-                                     self.max_pages))
+        fields = (self.C, self.K, self.Hq, self.Hkv, self.D, self.scale, self.n_pages, self.max_pages)
+        packed = self._packed
+        if packed[0] != fields:
+            packed = self._packed = (fields, _DecodeShapeC(*fields))
+        return C.byref(packed[1])
 
 
 def peagle_draft_decode_splits(shape: DecodeShape) -> int:
@@ -536,7 +545,7 @@ def peagle_draft_decode(shape: DecodeShape, q_new, k_new, v_new, k_pages, v_page
         _ptr(v_pages, "v_pages", bf, pool), _ptr(block_table, "block_table", i32, (s.C, s.max_pages)),
         _ptr(ctx_len, "ctx_len", i32, (s.C,)), _ptr(o, "o", bf, (s.C, s.K, s.Hq, s.D)),
         _ptr(lse, "lse", f32, (s.C, s.Hq, s.K)), _ptr(status, "status", i32, (s.C,)),
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_ptr(stream))
+        workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     if rc != 0:
         raise PeagleError(rc, "peagle_draft_decode")
 

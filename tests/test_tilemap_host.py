@@ -669,3 +669,17 @@ def test_rope_shared_entry_point_validates_before_launch():
     # beside the rotary workspace: one fp32 row of Hkv x D per wave (4) of each of the 16 row tiles' chain-tile
     # workgroups, for dK and for dV - and no [T, Hkv, D] tensor of any kind (D = 64)
     assert need == pe.peagle_rope_workspace_bytes(tm, ok) + 2 * (16 * 4) * (2 * 64) * 4
+
+
+def test_a_drafting_step_shape_follows_its_fields():
+    """The structure that the C ABI is given is kept between calls; it has to be made anew when a field changes."""
+    s = pe.DecodeShape(4, 7, 64, 8, 64, 100, 16)
+    base = pe.peagle_draft_decode_workspace_bytes(s)
+    assert base == pe.peagle_draft_decode_workspace_bytes(pe.DecodeShape(4, 7, 64, 8, 64, 100, 16))
+    for field, value in (("C", 5), ("K", 12), ("D", 128), ("max_pages", 100)):
+        was = getattr(s, field)
+        setattr(s, field, value)
+        fresh = pe.DecodeShape(s.C, s.K, s.Hq, s.Hkv, s.D, s.n_pages, s.max_pages)
+        assert pe.peagle_draft_decode_workspace_bytes(s) == pe.peagle_draft_decode_workspace_bytes(fresh) != base, field
+        setattr(s, field, was)
+        assert pe.peagle_draft_decode_workspace_bytes(s) == base
