@@ -30,17 +30,25 @@ size_t tokens_of(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
   return tm->sampled ? (size_t)tm->T_tokens : (size_t)s->L * s->K;
 }
 
-// Ranges of rows whose dK / dV are summed one by one: segments, or chunks of at most 128 row tiles (dense maps), in a step over
-// all segments or in a call over the whole sequence, whichever has more.
-int row_ranges(const peagle_tilemap_t* tm, int32_t L) {
-  if (tm->sampled) return tm->S;
-  int32_t by_segment = 0;
-  for (int32_t s = 0; s < tm->S && tm->seg_bounds[s] < L; ++s) {
-    const int32_t hi = tm->seg_bounds[s + 1] < L ? tm->seg_bounds[s + 1] : L;
-    by_segment += ((hi + tm->A - 1) / tm->A - tm->seg_bounds[s] / tm->A + 127) / 128;
-  }
-  const int32_t whole = ((L + tm->A - 1) / tm->A + 127) / 128;
-  return by_segment > whole ? by_segment : whole;
+// Ranges of rows whose dK / dV are summed one by one: segments, or chunks of a long one (dense maps), of a step over all
+// segments or of a call over the whole sequence.  Chunks are longer where there are more ranges already.
+struct RowRanges {
+  int n;
+  peagle::ChunkSplit split;
+};
+RowRanges row_ranges(const peagle_tilemap_t* tm, const peagle_shape_t* sh, bool by_segment) {
+  if (tm->sampled) return {by_segment ? tm->S : 1, {1, 1}};
+  const int32_t L = sh->L, S = by_segment ? tm->S : 1;
+  auto count = [&](const peagle::ChunkSplit& split) {
+    int n = 0;
+    for (int32_t s = 0; s < S && (!by_segment || tm->seg_bounds[s] < L); ++s) {
+      const int32_t lo = by_segment ? tm->seg_bounds[s] : 0, hi = by_segment && tm->seg_bounds[s + 1] < L ? tm->seg_bounds[s + 1] : L;
+      n += peagle::dkdv_chunks((hi + tm->A - 1) / tm->A - lo / tm->A, split);
+    }
+    return n;
+  };
+  const peagle::ChunkSplit split = peagle::dkdv_chunk_split(sh->D, (L + 63) / 64 * 64, sh->Hq, count({1, 1}));
+  return {count(split), split};
 }
 
 WsLayout ws_layout(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
@@ -61,7 +69,8 @@ WsLayout ws_layout(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
 // with a launch for each range of rows and the same results.
 size_t more_sets_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
   const WsLayout w = ws_layout(tm, s);
-  return (size_t)(peagle::dkdv_part_sets(s->D, w.L64, s->Hq, row_ranges(tm, s->L)) - 1) * 2 * w.part;
+  const int by_segment = row_ranges(tm, s, true).n, whole = row_ranges(tm, s, false).n;
+  return (size_t)(peagle::dkdv_part_sets(s->D, w.L64, s->Hq, by_segment > whole ? by_segment : whole) - 1) * 2 * w.part;
 }
 struct MoreSets {
   float* at = nullptr;
@@ -130,10 +139,11 @@ FwdParams make_fwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const Se
 
 BwdParams make_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const SegRange& sr, const void* q,
                    const void* k, const void* v, const void* o, const void* d_o, const float* lse, void* dq,
-                   float* dk_acc, float* dv_acc, void* workspace, const MoreSets& more, int chain_accumulate,
+                   float* dk_acc, float* dv_acc, void* workspace, const MoreSets& more, const peagle::ChunkSplit& chunk_split, int chain_accumulate,
                    const float* rope_table = nullptr, const SharedForm& sf = SharedForm()) {
   const WsLayout w = ws_layout(tm, s);
   BwdParams p{};
+  p.chunk_split = chunk_split;
   p.v_shared = (const __bf16*)sf.v_shared;
   p.shared_dk_part = sf.dk_part;
   p.shared_dv_part = sf.dv_part;
@@ -228,7 +238,7 @@ extern "C" int peagle_attn_bwd(const peagle_tilemap_t* tm, const peagle_shape_t*
   if (!workspace || ws_bytes < base) return PEAGLE_EWORKSPACE;
   if (tm->device < 0) return PEAGLE_ENODEVICE;
   const BwdParams p = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace,
-                               more_sets(tm, shape, workspace, ws_bytes, base), accumulate);
+                               more_sets(tm, shape, workspace, ws_bytes, base), row_ranges(tm, shape, seg >= 0).split, accumulate);
   const int acc_below = accumulate ? INT_MAX : 0;
   hipStream_t st = (hipStream_t)stream;
   const bool one_grid = peagle::backward_in_one_grid(shape->D, p.mean_tiles, sr.rt_hi - sr.rt_lo, shape->Hq, false, false);
@@ -272,6 +282,7 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
   // once (8,192 anchors in eight segments: fwd 4,419 -> 4,290, dQ 6,360 -> 6,245 us per step).  dK/dV are summed segment
   // by segment, in order.
   const MoreSets more = more_sets(tm, shape, workspace, ws_bytes, sf.ws_base ? sf.ws_base : ws_need);
+  const peagle::ChunkSplit split = row_ranges(tm, shape, true).split;
   SegRange rows{};
   int32_t n_seg = 0;
   for (int32_t s = seg_begin; s < seg_end; ++s) {
@@ -295,10 +306,10 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
       fp.nlse = (float*)((char*)workspace + w.nlse_off);
     }
     if (peagle::launch_fwd(fp, shape->D, st, timer) != hipSuccess) return PEAGLE_EHIP;
-    const BwdParams bp = make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, 0, rope_table, sf);
+    const BwdParams bp = make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, split, 0, rope_table, sf);
     if (!one_grid && peagle::launch_dq(bp, shape->D, st, timer) != hipSuccess) return PEAGLE_EHIP;
   }
-  peagle::DkdvLauncher dkdv(make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, 0, rope_table, sf),
+  peagle::DkdvLauncher dkdv(make_bwd(tm, shape, rows, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, split, 0, rope_table, sf),
                             shape->D, one_grid, st, timer);
   for (int32_t s = seg_begin; s < seg_begin + n_seg; ++s) {
     SegRange sr;
@@ -306,7 +317,7 @@ static int step_impl(const peagle_tilemap_t* tm, const peagle_shape_t* shape, in
     if (rc != PEAGLE_OK) return rc;
     // Depth-0 keys below the segment start already hold earlier segments' sums: add to them.
     // Keys first seen by this segment (its own depth-0 range and its chains) are overwritten.
-    const BwdParams bp = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, 0, rope_table, sf);
+    const BwdParams bp = make_bwd(tm, shape, sr, q, k, v, o, d_o, lse, dq, dk_acc, dv_acc, workspace, more, split, 0, rope_table, sf);
     if (dkdv.add(bp, sr.key_lo, sr.a_hi, sr.a_lo) != hipSuccess) return PEAGLE_EHIP;
   }
   if (dkdv.finish() != hipSuccess) return PEAGLE_EHIP;

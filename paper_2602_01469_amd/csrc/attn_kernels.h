@@ -41,6 +41,12 @@ struct DkdvRange {
 };
 constexpr int kMaxRanges = 4;  // of one launch
 
+// How many chunks at most a range of rows may be cut into to fill the chip: by the slots that its work items leave, and by
+// the sets of partials that a launch sums.
+struct ChunkSplit {
+  int by_slots, by_sets;
+};
+
 struct BwdParams {
   const __bf16* q;
   const __bf16* k;
@@ -58,6 +64,7 @@ struct BwdParams {
   float* part_more;    // workspace [part_sets - 1][dK, dV][part_stride]: of the others
   size_t part_stride;
   int part_sets;       // as many ranges of rows as one launch may take
+  ChunkSplit chunk_split;  // see dkdv_chunks()
   DeviceTileMap tm;
   int L, T, Hq, Hkv, L64;
   int group;            // query heads per KV head
@@ -156,6 +163,10 @@ class DkdvLauncher {
   DkdvRange range_[kMaxRanges];    // ... by set
   int key_end_[kMaxRanges], acc_below_[kMaxRanges];
 };
+// Chunks that dK/dV of a range of a dense map's row tiles is run over, split: dkdv_chunk_split() of the problem and of the
+// number of ranges that it has of itself.
+int dkdv_chunks(int n_row_tiles, const ChunkSplit& split);
+ChunkSplit dkdv_chunk_split(int D, int L64, int Hq, int n_ranges);
 // Sets of partials worth having for a problem of n_ranges ranges of rows in all: several where a range's work items leave
 // slots idle.
 int dkdv_part_sets(int D, int L64, int Hq, int n_ranges);

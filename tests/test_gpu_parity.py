@@ -1270,3 +1270,49 @@ def test_key_tiles_at_and_past_the_end_of_a_cropped_sequence(D, K, L, L_max, Hq,
             r.fwd()
             r.bwd()
         _check_against_oracle(r.results(), ref, f"end K={K} L={L} D={D}")
+
+
+@pytest.mark.parametrize("L,L_max,bounds,Hq,sets", [
+    (64, 64, None, 4, 1), (66, 66, None, 4, 2), (130, 300, None, 5, 3), (252, 252, None, 4, 3), (256, 256, None, 4, 4),
+    (66, 66, None, 3, 1), (200, 200, [0, 100, 200], 4, 4), (210, 210, [0, 60, 180, 210], 4, 3), (130, 130, None, 60, 1),
+    (160, 160, None, 60, 3)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_few_heads_run_a_range_of_rows_in_chunks(D, L, L_max, bounds, Hq, sets):
+    """K = 32, four anchors a row tile: 16, 17, 33 (cropped), 63 and 64 row tiles of few heads in one to four chunks that share a
+    launch, two and three segments, fewer heads than are cut for, and sixty heads, whose work items leave slots for one chunk
+    where lists are short and for three (at D = 128 two) where they are not."""
+    K, Hkv, seed = 32, 1 if Hq < 60 else 10, 370
+    if (D, L) == (128, 160):
+        sets = 2
+    print(f"case chunks of few heads L={L} of {L_max} Hq={Hq} D={D} bounds={bounds}", flush=True)
+    T, S = L * K, 1 if bounds is None else len(bounds) - 1
+    tm, shape = pe.peagle_build_tilemap(L_max, K, bounds, device=0), pe.Shape(L, K, Hq, Hkv, D)
+    part = 2 * Hq * ((L + 63) // 64 * 64) * D * 4           # (whole multiples of 256 bytes)
+    base = 2 * ((T * Hq * 4 + 255) // 256 * 256)
+    need = pe.peagle_workspace_bytes(tm, shape)
+    assert need == base + sets * part
+    qb, kb, vb, dob = (rand_bits((T, H, D), seed + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
+
+    def results(n_bytes, whole):
+        r = Run(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
+        r.ws = torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda")  # (NaN)
+        if whole:
+            r.step(0, S)
+        else:
+            r.fwd()
+            r.bwd()
+        return r.results()
+    got = results(need, True)
+    one = results(base + part, True)                        # a launch and a sum for each chunk: the same bits
+    for n in got:
+        assert np.array_equal(got[n], one[n]), n
+    calls = results(need, False)
+    if S == 1:
+        for n in got:
+            assert np.array_equal(got[n], calls[n]), n
+    if Hq <= 5:
+        ref = _oracle(qb, kb, vb, dob, L, K, shape.scale)
+        _check_against_oracle(got, ref, f"chunks {L} {Hq} {D}")
+        _check_against_oracle(calls, ref, f"chunks by calls {L} {Hq} {D}")
+        for n in ("dK", "dV"):                              # no key left out or counted twice at a chunk boundary
+            assert max_abs(got[n], ref[n]) <= 2e-2 * np.abs(ref[n]).max(), n
