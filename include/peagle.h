@@ -127,7 +127,7 @@ int peagle_tilemap_expand_rows(const peagle_tilemap_t* tm, int32_t L, int32_t se
 int peagle_tilemap_classes(const peagle_tilemap_t* tm, uint8_t* classes_out);
 
 /* Bytes of device scratch that peagle_attn_bwd / peagle_attn_step_partitioned use for this shape.  Where several segments
- * share a launch (few query heads) this includes a set of partial sums for each; a call accepts a workspace that has room
+ * or parts of one share a launch (few query heads) this includes a set of partial sums for each; a call accepts a workspace that has room
  * for one set only (such as one made for a longer sequence of the same map), with the same results and more launches.  A set
  * takes 2 * round_up(4 * Hq * round_up(L, 64) * D, 256) bytes, the rest 2 * round_up(4 * T * Hq, 256): with one set that is the
  * smallest size accepted.  (The rotary and first-layer workspaces below hold the same sets: fewer make them smaller alike.) */

@@ -30,24 +30,28 @@ size_t tokens_of(const peagle_tilemap_t* tm, const peagle_shape_t* s) {
   return tm->sampled ? (size_t)tm->T_tokens : (size_t)s->L * s->K;
 }
 
-// Ranges of rows whose dK / dV are summed one by one: segments, or chunks of a long one (dense maps), of a step over all
-// segments or of a call over the whole sequence.  Chunks are longer where there are more ranges already.
+// Ranges of rows whose dK / dV are summed one by one: segments, or chunks of one, of a step over all segments or of a call over
+// the whole sequence.
 struct RowRanges {
   int n;
   peagle::ChunkSplit split;
 };
 RowRanges row_ranges(const peagle_tilemap_t* tm, const peagle_shape_t* sh, bool by_segment) {
-  if (tm->sampled) return {by_segment ? tm->S : 1, {1, 1}};
   const int32_t L = sh->L, S = by_segment ? tm->S : 1;
   auto count = [&](const peagle::ChunkSplit& split) {
     int n = 0;
     for (int32_t s = 0; s < S && (!by_segment || tm->seg_bounds[s] < L); ++s) {
       const int32_t lo = by_segment ? tm->seg_bounds[s] : 0, hi = by_segment && tm->seg_bounds[s + 1] < L ? tm->seg_bounds[s + 1] : L;
-      n += peagle::dkdv_chunks((hi + tm->A - 1) / tm->A - lo / tm->A, split);
+      const int32_t n_rt = !tm->sampled  ? (hi + tm->A - 1) / tm->A - lo / tm->A
+                           : by_segment ? tm->seg_rt[s + 1] - tm->seg_rt[s]
+                                        : tm->n_row_tiles;
+      n += peagle::dkdv_chunks(n_rt, split, tm->sampled, tm->dview.longest_list);
     }
     return n;
   };
-  const peagle::ChunkSplit split = peagle::dkdv_chunk_split(sh->D, (L + 63) / 64 * 64, sh->Hq, count({1, 1}));
+  peagle::ChunkSplit split{1, 1};
+  const int n = count(split);
+  if (n > 0) split = peagle::dkdv_chunk_split(sh->D, (L + 63) / 64 * 64, sh->Hq, n);
   return {count(split), split};
 }
 

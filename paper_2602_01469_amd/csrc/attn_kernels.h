@@ -163,9 +163,9 @@ class DkdvLauncher {
   DkdvRange range_[kMaxRanges];    // ... by set
   int key_end_[kMaxRanges], acc_below_[kMaxRanges];
 };
-// Chunks that dK/dV of a range of a dense map's row tiles is run over, split: dkdv_chunk_split() of the problem and of the
-// number of ranges that it has of itself.
-int dkdv_chunks(int n_row_tiles, const ChunkSplit& split);
+// Chunks that dK/dV of a range of row tiles is run over (listed: of a sampled or packed map), split: dkdv_chunk_split() of the
+// problem and of the number of ranges that it has of itself.
+int dkdv_chunks(int n_row_tiles, const ChunkSplit& split, bool listed, int longest_list);
 ChunkSplit dkdv_chunk_split(int D, int L64, int Hq, int n_ranges);
 // Sets of partials worth having for a problem of n_ranges ranges of rows in all: several where a range's work items leave
 // slots idle.

@@ -2831,20 +2831,22 @@ int dkdv_part_sets(int D, int L64, int Hq, int n_ranges) {
   return n_ranges < most ? (n_ranges < 1 ? 1 : n_ranges) : most;
 }
 
-// A key-tile pair's workgroup walks its row tiles one after the other, 1.8 us each at D = 64, and with few heads the longest
-// walk is the whole of dK/dV: 63 of 4 heads' L = 1,000 are 115 of a step's 140 us, while most slots are idle.  So a range of
-// rows is cut into chunks, up to the four whose partials one launch sums, while
+// A key-tile pair's workgroup walks its row tiles one after the other, 1.9 us each at D = 64, and with few heads the longest
+// walk is the whole of dK/dV: the 63 of 4 heads' L = 1,000 are most of a step's 140 us, while most slots are idle.  So a range
+// of rows is cut into chunks, up to the four whose partials one launch sums, while
 //  - the work items of all chunks run at once (512 slots at D = 64, 256 at D = 128).  16 heads L = 3,000, 384 items: 660 us in
 //    two chunks, 665 in three; 8 heads L = 3,000, 192: 344 and 350; D = 128 4 heads L = 4,096, 128: 683 and 702 in four;
 //  - with short lists (under 40 row tiles) a quarter of them do: 64 heads L = 400, 256 items, 102 us in one chunk and 106 in
 //    two, 32 heads at D = 128, 128 items, 127.5 and 133;
-//  - a chunk has 16 row tiles (8 to 15 gain less than a quarter; the fourth chunk from 64 on, so that its partials, a quarter of
-//    the workspace's, are worth it: 63 row tiles 70 us in three, 63 in four);
+//  - there is one chunk for 16 row tiles (the fourth from 64 on, so that its partials, a quarter of the workspace's, are worth
+//    it: 63 row tiles 70 us in three, 63 in four), in sampled and packed maps up to three;
+//  - a chunk of a packed batch cuts its lists at all, being no longer than 4/3 of the longest (seven sequences of 300 to 800
+//    anchors, 4 heads, 166 us, in three chunks 170);
 //  - the problem's segments leave sets (4 heads L = 4,096 in four segments 328 us, with each in two chunks 340).
 // us per step, uncut / so: 4 heads L = 300 54.6 / 40.5, L = 600 91 / 51, L = 1,000 140 / 70, L = 1,391 187 / 82, L = 2,048 269 /
 // 119, L = 4,096 in two segments 377 / 338, K = 4 L = 2,500 185 / 97, K = 5 L = 1,200 117 / 63; 16 heads L = 700 113 / 72, L =
 // 2,048 390 / 333; 32 heads L = 700 137 / 118; D = 128 4 heads L = 600 137 / 72, L = 1,391 283 / 124, 8 heads L = 2,048 464 /
-// 394.  A key's sums then have other last bits than the same heads' in a call of many.  From four query heads on, which is the
+// 394; 4 heads, sampled L = 1,500 125 / 70, L = 3,000 239 / 137, packed 200 and 300 anchors 70 / 53, 3,000 and 100 416 / 220.  A key's sums then have other last bits than the same heads' in a call of many.  From four query heads on, which is the
 // smallest drafter: parts of a call of up to three heads keep the bits that they have in the whole.
 constexpr int kSplitHeads = 4, kSplitRowTiles = 16, kShortLists = 40;
 ChunkSplit dkdv_chunk_split(int D, int L64, int Hq, int n_ranges) {
@@ -2852,17 +2854,19 @@ ChunkSplit dkdv_chunk_split(int D, int L64, int Hq, int n_ranges) {
   if (Hq < kSplitHeads) return {1, 1};
   return {(int)((D == 64 ? 2 : 1) * kCus / items), kMaxRanges / n_ranges};
 }
-int dkdv_chunks(int n_row_tiles, const ChunkSplit& split) {
-  const int least = (n_row_tiles + 127) / 128;
+int dkdv_chunks(int n_row_tiles, const ChunkSplit& split, bool listed, int longest_list) {
+  const int least = listed ? 1 : (n_row_tiles + 127) / 128;
   int n = n_row_tiles < kShortLists ? split.by_slots / 4 : split.by_slots;
   if (n > split.by_sets) n = split.by_sets;
   int worth = (n_row_tiles + kSplitRowTiles - 1) / kSplitRowTiles;
-  if (worth == kMaxRanges && n_row_tiles < kMaxRanges * kSplitRowTiles) --worth;
+  const int most = listed || n_row_tiles < kMaxRanges * kSplitRowTiles ? kMaxRanges - 1 : kMaxRanges;
+  if (worth > most) worth = most;
   if (n > worth) n = worth;
-  return n < least ? least : n;
+  if (n <= least || (n_row_tiles + n - 1) / n > 4 * (longest_list / 3)) return least;
+  return n;
 }
 
-// dK/dV of a dense map runs over equal chunks of at most 128 row tiles (few heads: more, see above), each with a set of partials of its
+// dK/dV of a dense map runs over equal chunks of at most 128 row tiles (few heads: more and shorter ones, see above), each with a set of partials of its
 // own, later chunks adding to what the earlier ones wrote.  The key tiles below a chunk's first anchor have equally long
 // lists, which balances the workgroups the way the paper's segments do; but a small last chunk leaves most of the
 // chip idle, and every chunk writes and sums all partials again.  dK/dV + reduction, us, chunks of 64 / up to 128:
@@ -2874,12 +2878,14 @@ hipError_t DkdvLauncher::add(const BwdParams& rows, int key_lo, int a_hi, int ac
   if (n_rt <= 0) return hipSuccess;
   const int A = p_.tm.A;
   const bool listed_map = p_.tm.row_tok != nullptr;
-  const int n_chunks = listed_map ? 1 : dkdv_chunks(n_rt, p_.chunk_split), chunk = (n_rt + n_chunks - 1) / n_chunks;
+  const int n_chunks = dkdv_chunks(n_rt, p_.chunk_split, listed_map, p_.tm.longest_list), chunk = (n_rt + n_chunks - 1) / n_chunks;
   for (int c0 = rows.rt_lo; c0 < rows.rt_hi; c0 += chunk) {
     const int c1 = c0 + chunk < rows.rt_hi ? c0 + chunk : rows.rt_hi;
     const bool partial = c0 != rows.rt_lo || c1 != rows.rt_hi;
     const int c_a_hi = listed_map || c1 * A > a_hi ? a_hi : c1 * A;
-    const int c_acc = c0 == rows.rt_lo || acc_below == INT_MAX ? acc_below : (acc_below > c0 * A ? acc_below : c0 * A);
+    // (where a listed row tile ends is not known here: its first chunk leaves every key's sum, zero if no row of it sees the key)
+    const int c_start = listed_map ? a_hi : c0 * A;
+    const int c_acc = c0 == rows.rt_lo || acc_below == INT_MAX ? acc_below : (acc_below > c_start ? acc_below : c_start);
     const hipError_t e = add_range(c0, c1, rows, rows.cropped || partial, key_lo, c_a_hi, c_acc);
     if (e != hipSuccess) return e;
   }

@@ -62,6 +62,7 @@ struct DeviceTileMap {
   int32_t chain_slots, chain_first;  // dense maps: chain slot ck of a row tile is anchor ck / chain_slots of the tile,
                                      // depth chain_first + ck % chain_slots (depth 0: the slot is unused)
   uint32_t k_reciprocal, slots_reciprocal;  // small_reciprocal() of K and of chain_slots
+  int32_t longest_list;              // (for the launchers) of the depth-0 key tiles' lists; 0: the row tiles of one don't follow one another
 };
 
 }  // namespace peagle

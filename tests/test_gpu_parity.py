@@ -1316,3 +1316,44 @@ def test_few_heads_run_a_range_of_rows_in_chunks(D, L, L_max, bounds, Hq, sets):
         _check_against_oracle(calls, ref, f"chunks by calls {L} {Hq} {D}")
         for n in ("dK", "dV"):                              # no key left out or counted twice at a chunk boundary
             assert max_abs(got[n], ref[n]) <= 2e-2 * np.abs(ref[n]).max(), n
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("form,sets", [("sampled", 3), ("two_segments", 4), ("algorithm1", 4), ("one_sequence", 3), ("many_short", 1),
+                                       ("long_beside_short", 3)])
+def test_few_heads_of_listed_maps_run_in_chunks(form, sets, D):
+    """Sampled and packed maps of four heads: a range of rows in chunks whose lists are cut by position, in pieces of a list, of a
+    sequence or between sequences, and not where many short sequences make the lists short already.  In a workspace with
+    room for one set of partials each chunk has a launch of its own: the same bits."""
+    from peagle_inputs import cod_depth_counts
+    print(f"case chunks of listed maps {form} D={D}", flush=True)
+    Hq, Hkv, seed = 4, 1, 380
+    if form in ("sampled", "two_segments", "algorithm1"):
+        L, K = 1050, 7
+        bounds = None if form == "sampled" else [0, 400, 1050]
+        sets -= bounds is not None and D == 128             # (half the slots: the first segment stays whole)
+        count, assign = cod_depth_counts(L, K, 0.9, seed), int(form == "algorithm1")
+        tm = pe.peagle_build_tilemap_sampled(count, K, bounds, device=0, assignment=assign)
+        test_sampled_sequences_match_oracle(form, L, K, Hq, Hkv, D, 0.9, seed, bounds)
+    else:
+        K = 8 if form == "many_short" else 16
+        lens = {"one_sequence": [330], "many_short": [64] * 10, "long_beside_short": [20, 290, 3, 41]}[form]
+        L = sum(lens)
+        tm = pe.peagle_build_tilemap_packed(lens, K, device=0)
+        test_packed_batches_match_oracle(form, lens, K, Hq, Hkv, D, None, seed, None, 0)
+    S, T, shape = tm.info()["S"], tm.tokens(L), pe.Shape(L, K, Hq, Hkv, D)
+    part = 2 * Hq * ((L + 63) // 64 * 64) * D * 4
+    base = 2 * ((T * Hq * 4 + 255) // 256 * 256)
+    assert pe.peagle_workspace_bytes(tm, shape) == base + sets * part
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v, d_o = (torch.randn(T, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq))
+
+    def results(n_bytes):
+        ws = torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda")  # (NaN)
+        out = [torch.full_like(q, float("nan")), torch.full((Hq, T), float("nan"), device="cuda"), torch.full_like(q, float("nan")),
+               *(torch.full((T, Hkv, D), float("nan"), device="cuda") for _ in range(2))]
+        pe.peagle_attn_step_partitioned(tm, shape, 0, S, q, k, v, d_o, *out, None, None, ws)
+        torch.cuda.synchronize()
+        return out
+    for a, b in zip(results(pe.peagle_workspace_bytes(tm, shape)), results(base + part)):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
