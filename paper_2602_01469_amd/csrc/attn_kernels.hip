@@ -983,8 +983,9 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(BwdParams p) {
 // exact as long as 2^(c s) cannot leave the fp32 range, which |lse| <= 64 (log2 units) guarantees for
 // every key of the row; a workgroup with a row outside that range (or a non-finite lse) takes the plain
 // routine with the normalised probabilities for all its tiles.
-// Tiles that carry a bitmask (the diagonal and chain tiles that end a row tile's list) and the up to two
-// full tiles left over by the groups of three go through dq_tile, in the same buffers.
+// Tiles that carry a bitmask (the chain tiles, which are taken first, from the buffer the pipeline reaches last and one
+// more, and the diagonal tiles that end a row tile's list) and the up to two full tiles left over by the groups of three go
+// through dq_tile.
 // =====================================================================================
 constexpr int kDqAhead = 2;
 
