@@ -229,8 +229,9 @@ __device__ __forceinline__ void tile_mask(const char* mask, int row, int g, uint
 // The chain tiles that end a row tile's list (none to two).  At D = 64 the row-stationary kernels take them first and together:
 // a wave sees one block of 32 of the 128 chain slots (or two), so as iterations of their own each was a copy and a barrier for
 // half of the workgroup's waves.  Both travel with the first tile of depth-0 keys, which the workgroup waits for anyway, into
-// buffers that the loop uses later (one more than it needs, 51 KB in all: still three workgroups a CU).  us, last / first:
-// L = 1,391 704.9 / 702.5, L = 4,096 4,810 / 4,786, eight packed sequences 3,077 / 3,067.  (D = 128: no LDS for two.)
+// buffers that the loop uses later (one more than it needs, 52 KB in all: still three workgroups a CU; where four are wanted,
+// the forward of one head, there are two buffers, see there).  us per step, last / first: L = 1,391 704.9 / 702.5, L = 4,096
+// 4,810 / 4,786, eight packed sequences 3,077 / 3,067.  (D = 128: no LDS for two.)
 struct ChainTiles {
   int n;
   TileEntry tile[2];
@@ -529,13 +530,17 @@ __device__ __forceinline__ void fwd_tile_masked(const char* kt_lds, const char* 
   }
 }
 
+// PER_SIMD: workgroups per CU, which registers and LDS both allow.
 template <int D, int NH, bool SV, int PER_SIMD>
-__global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_kernel(FwdParams p) {  // (one head: LDS has room for four)
-  // Three workgroups per CU leave 168 registers: what only masked tiles and the last stores need is computed there.
-  constexpr bool LEAN = PER_SIMD == 3;
+__global__ __launch_bounds__(256, PER_SIMD) void fwd_kernel(FwdParams p) {
+  // Two heads in three workgroups per CU leave 168 registers: what only masked tiles and the last stores need is computed there.
+  constexpr bool LEAN = NH == 2 && PER_SIMD == 3;
   constexpr int kTileBytes = kKeysPerTile * D * 2;
   constexpr bool kChainFirst = D == 64;
-  constexpr int kBufs = kChainFirst ? 3 : 2;
+  // (Four workgroups per CU have two buffers, 37 KB in all: of two chain tiles the first then stands in the buffer that the first
+  // tile of depth-0 keys is copied to while the second is computed.)
+  constexpr bool kTwoBufs = kChainFirst && PER_SIMD == 4;
+  constexpr int kBufs = kChainFirst && !kTwoBufs ? 3 : 2;
   __shared__ __attribute__((aligned(16))) char lds[kBufs][2][kTileBytes];  // [buffer][K|V]
   __shared__ __attribute__((aligned(16))) char lds_mask[kChainFirst ? 4 : 2][kTileMaskBytes];  // of buffers 0 and 1, of the chain tiles
 
@@ -603,15 +608,18 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
     TileEntry masked = const_entry(tm.row_entries, e_lead < e_end ? e_lead : e0);
     if (e_lead >= e1) masked.mask_id = -1;
     if (!SAFE || LEAN) load_q();  // (lean: not held over the stores of the first pass)
+    const bool first_waits = kTwoBufs && ch.n == 2;
+    const int chain_buf = first_waits ? 0 : 1;
     if (kChainFirst) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
         if (i < ch.n) {
-          dma_chain_tile<D, 4, SV>(kl.k(1 + i), kl.v(1 + i), p.k, p.v, p.Hkv, kvh, tm, ch.tile[i].tile, p.L, wave, LEAN ? lane_id() : lane, p.v_shared);
+          dma_chain_tile<D, 4, SV>(kl.k(chain_buf + i), kl.v(chain_buf + i), p.k, p.v, p.Hkv, kvh, tm, ch.tile[i].tile, p.L, wave,
+                                   LEAN ? lane_id() : lane, p.v_shared);
           dma_tile_mask(mask_lds + (2 + i) * kTileMaskBytes, tm, ch.tile[i], wave);
         }
     }
-    copy_tile(0, cur.tile);
+    if (!first_waits) copy_tile(0, cur.tile);
     // (The first bitmask, if there is one, travels with the first tile, to where its own tile finds it: the loop over full tiles
     // then has no test for one in front of its matrix instructions.  With the test / without, CU busy cycles of 10,816 anchors
     // at D = 128 3.13e9 / 3.09e9; us of 20,480 anchors 23,720 / 23,600.  Not so in dq_item: 4.48e9 / 4.50e9 cycles.)
@@ -621,11 +629,17 @@ __global__ __launch_bounds__(256, D == 64 && NH == 1 ? 4 : PER_SIMD) void fwd_ke
       const int l = LEAN ? lane_id() : lane;
 #pragma unroll 1
       for (int i = 0; i < ch.n; ++i) {
+        if (first_waits && i == 1) {
+          __syncthreads();  // buffer 0 may be overwritten
+          copy_tile(0, cur.tile);
+        }
         uint32_t mw[2];
         tile_mask(lds_mask[2 + i], wave * 32 + (l & 31), l >> 5, mw);
-        fwd_tile_masked<D, NH, SAFE>(lds[1 + i][0], lds[1 + i][1], no, to, qf, o, m, lsum, mw, p.c_log2);
+        fwd_tile_masked<D, NH, SAFE>(lds[chain_buf + i][0], lds[chain_buf + i][1], no, to, qf, o, m, lsum, mw, p.c_log2);
       }
-      __syncthreads();  // buffer 1 may be overwritten
+      // buffer 1 may be overwritten (two buffers: and tile e0 has landed)
+      if (kTwoBufs) dma_publish();
+      else __syncthreads();
     }
     // A row tile's list holds its full tiles first, then the partial ones: two loops (accumulators stay in place).
     int e = e0;
@@ -2663,23 +2677,34 @@ namespace {
 
 constexpr int kCus = 256;  // compute units of the device
 
-// The forward's form at D = 64, by the mean length of the row tiles' lists and the number of workgroups of two query heads
-// (which share K/V tiles): one head per workgroup (four per CU) where lists are short - the workgroups cover one another's
-// first loads and last stores - or two-head workgroups too few to fill the chip; two heads at three per CU where there are
-// at least four for each; two heads at two per CU (registers to schedule with) in between.  A head's results do not
-// depend on the choice.  Forward us, one head / two heads at two per CU / at three, by (mean list; two-head workgroups):
-//   short lists: 64 heads, L = 700 (8; 1,408) 58 / 65 / 65, L = 1,000 (11; 2,016) 100 / 98 / 97;
-//   few: 4 heads, L = 1,391 (13; 174) 30 / 37 / 40, L = 2,048 (19; 256) 40 / 47 / 52, L = 4,096 (35; 512) 88 / 92 / 98, eight packed
-//     sequences (12; 806) 59 / 67 / 67;  in between: L = 8,000 (65; 1,000) 268 / 261 / 270;
-//   many: 16 heads, L = 2,048 (19; 1,024) 86 / 85 / 84, L = 4,096 (35; 2,048) 287 / 272 / 271; 64 heads, L = 1,391 (13; 2,784) 166 /
-//     159 / 151, eight packed sequences (12; 12,896) 715 / 751 / 674, L = 4,096 (35; 8,192) 1,124 / 1,057 / 1,031, L = 20,480 (165;
-//     40,960) 25,720 / 24,000 / 23,810.
-constexpr int kOneHeadMeanTiles = 10, kFewMeanTiles = 24;
-enum class FwdForm { kOneHead, kTwoHeads, kTwoHeadsThreePerCu };
-inline FwdForm pick_fwd_form(int group, int mean_tiles, int two_head_wgs) {
-  if (group % 2 != 0 || mean_tiles <= kOneHeadMeanTiles || two_head_wgs <= 2 * kCus) return FwdForm::kOneHead;
-  if (two_head_wgs >= 4 * kCus) return FwdForm::kTwoHeadsThreePerCu;
-  return mean_tiles <= kFewMeanTiles ? FwdForm::kOneHead : FwdForm::kTwoHeads;
+// The forward's form at D = 64, by the number of workgroups of one query head and the mean length of the row tiles' lists: two
+// heads per workgroup (which share K/V tiles) at three per CU where there are at least eight workgroups of one head for each CU
+// (lists of up to four tiles: twelve); one head where there are fewer, to fill the chip; two heads at two per CU (registers
+// to schedule with) in between with long lists.  A head's results do not depend on the choice.  Forward us, one head / two
+// heads at two per CU / at three, by (mean list; workgroups of one head):
+//   many: 64 heads, L = 700 (8; 2,816) 57 / 54 / 52, L = 1,391 (13; 5,568) 168 / 158 / 156, L = 4,096 (35; 16,384) 1,213 / 1,156 / 1,128, L =
+//     20,480 (165; 81,920) 28,010 / 26,310 / 26,000, eight packed sequences of 203 to 517 anchors (6; 11,072) 186 / 183 / 168, of 64 to 1,728
+//     (12; 25,800) 753 / 727 / 690; 16 heads, L = 2,048 (19; 2,048) 88.5 / 83.7 / 84.5, L = 4,096 (35; 4,096) 303 / 290 / 289;
+//   very short lists: K = 32, 64 heads L = 128 (4; 2,048) 27.6 / 29.5 / 28.3, but L = 330, 32 heads (5; 2,656) 39.6 / 41.3 / 37.7, sixty
+//     packed sequences of 16 anchors, K = 8 (3; 3,840) 40.1 / 43.1 / 38.2;
+//   few: 4 heads, L = 1,391 (13; 348) 21.7 / 29.8 / 33.9, L = 2,048 (19; 512) 31.1 / 40.1 / 45.8, L = 4,096 (35; 1,024) 86 / 91 / 96, packed 64 to
+//     1,728 (12; 1,612) 56 / 59 / 63; 16 heads, L = 1,391 (13; 1,392) 46.1 / 48.3 / 48.4;
+//   in between: 8 heads, L = 3,000 (26; 1,504) 87 / 88 / 93, L = 4,000 (33; 2,000) 145 / 138 / 143; 4 heads, L = 8,000 (65; 2,000) 280 / 270 / 279.
+// One head runs three workgroups per CU (148 registers, a third buffer) where that many run at once, and, while lists are long and
+// unequal, up to four per CU; else four (128 registers, two buffers).  Forward us, three / four, by (mean list; workgroups):
+//   4 heads, K = 4 L = 2,048 (19; 256) 27.1 / 30.2, L = 1,391 (13; 348) 21.7 / 23.7, L = 2,048 (19; 512) 30.6 / 32.5, 64 heads L = 128
+//     (4; 512) 9.2 / 9.5, 16 heads L = 700 (7; 704) 18.3 / 18.9, 4 heads L = 3,000 (26; 752) 53.3 / 53.1;
+//   long: 6 heads L = 2,500 (22; 942) 51.4 / 53.1, 4 heads L = 4,096 (34; 1,024) 83.6 / 86.9;  but 64 heads L = 200 (4; 832) 15.3 / 13.7,
+//     16 heads L = 1,000 (10; 1,008) 31.2 / 29.5, 64 heads L = 256 (5; 1,024) 18.9 / 16.3, 12 heads L = 1,391 (13; 1,044) 38.8 / 37.2;
+//   many: 64 heads L = 411 (6; 1,664) 30.3 / 28.4; 24 heads in groups of three L = 2,500 (22; 3,768) 180 / 176, L = 8,192 (66; 12,288) 1,673 / 1,632.
+constexpr int kShortMeanTiles = 4, kFewMeanTiles = 24, kLongMeanTiles = 14;
+enum class FwdForm { kOneHead, kOneHeadThreePerCu, kTwoHeads, kTwoHeadsThreePerCu };
+inline FwdForm pick_fwd_form(int group, int mean_tiles, int n_wg) {
+  const bool three_per_cu = n_wg <= 3 * kCus || (n_wg <= 4 * kCus && mean_tiles > kLongMeanTiles);
+  const FwdForm one_head = three_per_cu ? FwdForm::kOneHeadThreePerCu : FwdForm::kOneHead;
+  if (group % 2 != 0 || n_wg <= 4 * kCus) return one_head;
+  if (n_wg >= (mean_tiles <= kShortMeanTiles ? 12 : 8) * kCus) return FwdForm::kTwoHeadsThreePerCu;
+  return mean_tiles <= kFewMeanTiles ? one_head : FwdForm::kTwoHeads;
 }
 
 struct TimedSpan {
@@ -2750,8 +2775,9 @@ hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t stream, KernelTimer
   if (D == 128) {
     go(fwd_kernel<128, 1, false, 2>, 1);
   } else {
-    switch (pick_fwd_form(p.Hq / p.Hkv, p.mean_tiles, n_rt * (p.Hq / 2))) {
-      case FwdForm::kOneHead: go(sv ? fwd_kernel<64, 1, true, 2> : fwd_kernel<64, 1, false, 2>, 1); break;
+    switch (pick_fwd_form(p.group, p.mean_tiles, n_rt * p.Hq)) {
+      case FwdForm::kOneHeadThreePerCu: go(sv ? fwd_kernel<64, 1, true, 3> : fwd_kernel<64, 1, false, 3>, 1); break;
+      case FwdForm::kOneHead: go(sv ? fwd_kernel<64, 1, true, 4> : fwd_kernel<64, 1, false, 4>, 1); break;
       case FwdForm::kTwoHeads: go(sv ? fwd_kernel<64, 2, true, 2> : fwd_kernel<64, 2, false, 2>, 2); break;
       case FwdForm::kTwoHeadsThreePerCu: go(sv ? fwd_kernel<64, 2, true, 3> : fwd_kernel<64, 2, false, 3>, 2); break;
     }

@@ -91,10 +91,16 @@ def dq_path(tm, Hq, call="step"):
 
 def fwd_form(tm, Hq, Hkv):
     """Which forward one launch over the whole map runs at D = 64: query heads per workgroup, workgroups per CU."""
-    mean, two_head_wgs = int(mean_list(tm) + 0.5), tm.info()["n_row_tiles"] * (Hq // 2)
-    if Hq // Hkv % 2 or mean <= 10 or two_head_wgs <= 512 or (two_head_wgs < 1024 and mean <= 24):
+    mean, n_wg = int(mean_list(tm) + 0.5), tm.info()["n_row_tiles"] * Hq
+    if Hq // Hkv % 2 or n_wg <= 1024 or n_wg < (3072 if mean <= 4 else 2048) and mean <= 24:
         return "one head"
-    return "two heads, three per CU" if two_head_wgs >= 1024 else "two heads, two per CU"
+    return "two heads, three per CU" if n_wg >= (3072 if mean <= 4 else 2048) else "two heads, two per CU"
+
+
+def one_head_per_cu(tm, Hq):
+    """Workgroups per CU of the forward of one head per workgroup."""
+    n_wg = tm.info()["n_row_tiles"] * Hq
+    return 3 if n_wg <= 768 or n_wg <= 1024 and int(mean_list(tm) + 0.5) > 14 else 4
 
 
 def rel_l2(a, b):

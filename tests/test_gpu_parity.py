@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2602_01469_amd as pe
-from gpu_harness import Run, bf16_to_f64, dq_path, fwd_form, max_abs, mean_list, rand_bits, rel_l2, to_dev_bf16
+from gpu_harness import Run, bf16_to_f64, dq_path, fwd_form, max_abs, mean_list, one_head_per_cu, rand_bits, rel_l2, to_dev_bf16
 from oracle import peagle_oracle as orc
 from peagle_inputs import CONFIGS, bf16_bits_to_f64, make_inputs
 
@@ -1357,3 +1357,35 @@ def test_few_heads_of_listed_maps_run_in_chunks(form, sets, D):
         return out
     for a, b in zip(results(pe.peagle_workspace_bytes(tm, shape)), results(base + part)):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("K,L,L_max,Hq,Hkv", [(1, 1500, 1500, 90, 30), (2, 1000, 1300, 66, 22), (8, 400, 400, 45, 15), (5, 37, 5000, 513, 171)])
+def test_one_head_forwards_of_three_and_four_per_cu_give_the_same_bits(K, L, L_max, Hq, Hkv):
+    """Odd groups, which the forward takes one head at a time: more than 1,024 workgroups (four per CU: two tile buffers, in the
+    first of which a chain tile stands before the first tile of depth-0 keys) against each of some groups alone (three per CU,
+    three buffers), with no, one and two chain tiles, a cropped sequence, and half of the heads done again with the running max;
+    the first and the last group against the oracle too."""
+    D, n = 64, Hq // Hkv
+    print(f"case one-head forwards K={K} L={L} of {L_max} Hq={Hq}", flush=True)
+    tm, used = (pe.peagle_build_tilemap(x, K, None, device=d) for x, d in ((L_max, 0), (L, -1)))
+    assert used.info()["n_row_tiles"] * Hq > 1024 and one_head_per_cu(used, Hq) == 4 and one_head_per_cu(used, n) == 3
+    qb, kb, vb, dob = (rand_bits((L * K, H, D), 390 + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
+    q, k, v = (to_dev_bf16(x) for x in (qb, kb, vb))
+    q[:, 1::2] *= 32.0                                  # (a power of two: exact)
+
+    def fwd(q, k, v):
+        o, lse = torch.full_like(q, float("nan")), torch.full((q.shape[1], L * K), float("nan"), device="cuda")
+        pe.peagle_attn_fwd(tm, pe.Shape(L, K, q.shape[1], k.shape[1], D), -1, q, k, v, o, lse)
+        torch.cuda.synchronize()
+        return o, lse
+    o, lse = fwd(q, k, v)
+    for h in sorted({0, 1, Hkv // 2, Hkv - 1}):
+        a, b = slice(h * n, (h + 1) * n), slice(h, h + 1)
+        o1, lse1 = fwd(*(t.contiguous() for t in (q[:, a], k[:, b], v[:, b])))
+        assert torch.isfinite(o1).all() and torch.equal(o[:, a], o1) and torch.equal(lse[a], lse1), h
+        if h in (0, Hkv - 1):
+            heads = q[:, a].contiguous()
+            ref = _oracle(heads.view(torch.int16).cpu().numpy().view(np.uint16), kb[:, b], vb[:, b], dob[:, a], L, K,
+                          pe.Shape(L, K, n, 1, D).scale)
+            assert rel_l2(bf16_to_f64(o1), ref["O"]) <= FWD_REL, h
+            assert max_abs(lse1.double().cpu().numpy(), ref["LSE"]) <= LSE_ABS + 2e-6 * np.abs(ref["LSE"]).max(), h

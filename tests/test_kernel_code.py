@@ -123,7 +123,26 @@ def test_full_tiles_copy_no_bitmask(code_objects):
             wide, narrow = (sum(x.startswith(f"global_load_lds_dword{w} ") for x in body) for w in ("x4", ""))
             if re.search("fwd_kernel|dq_pipe_kernel", kernel) and wide >= 16 and sum(x.startswith("v_mfma") for x in body) >= 32:
                 seen[kernel] = seen.get(kernel, 0) + narrow
-    assert len(seen) == 8 and not any(seen.values()), seen  # (seven forwards, one dQ)
+    assert len(seen) == 10 and not any(seen.values()), seen  # (nine forwards, one dQ)
+
+
+def test_the_workgroups_that_a_launch_bound_means_fit_a_cu(code_objects):
+    """256 threads are one wave for each of a CU's four SIMDs, so that n workgroups of them share 512 registers a lane and 160 KB of
+    LDS.  The row-stationary kernels rest on the number that their launch bound names: short lists are covered by the other
+    workgroups of the CU."""
+    per_cu = {r"fwd_kernelILi64ELi\dELb\dELi(\d)E": None, r"fwd_kernelILi128ELi\dELb\dELi(\d)E": None, r"dq_kernelILi64E": 3,
+              r"dq_kernelILi128E": 2, r"dq_pipe_kernelILi64E": 2, r"(?:dkdv|bwd)_kernelILi64E": 2}
+    seen = set()
+    for co in code_objects:
+        notes = _tool("llvm-readobj", "--notes", co)
+        for lds, name, vgprs in re.findall(r"\.group_segment_fixed_size:\s+(\d+).*?\.name:\s+(\S+).*?\.vgpr_count:\s+(\d+)", notes, re.S):
+            for kernel, n in per_cu.items():
+                m = re.search(kernel, name)
+                if m:
+                    n = n or int(m.group(1))
+                    seen.add((kernel, n))
+                    assert int(lds) * n <= 160 * 1024 and int(vgprs) * n <= 512, (name, lds, vgprs)
+    assert {n for k, n in seen if k.startswith("fwd_kernelILi64")} == {2, 3, 4} and len({k for k, _ in seen}) == len(per_cu), seen
 
 
 def test_no_kernel_spills(code_objects):
