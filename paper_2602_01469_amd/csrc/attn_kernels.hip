@@ -2216,7 +2216,11 @@ struct PartSets {
 };
 template <int D, int SETS>
 __global__ __launch_bounds__(256) void reduce_partials_kernel(BwdParams p, PartSets sets) {
-  constexpr int kTogether = 4;  // heads whose loads are on their way together
+  // Heads whose loads are on their way together.  Several sets of partials are those of few heads, whose threads have one round
+  // trip after the other before them: us, one / four, 4 heads L = 1,000 5.7 / 4.7, L = 2,048 7.5 / 4.7, 16 heads 8.9 / 7.7, 4 heads in
+  // segments of 1,024 8.6 / 6.2, D = 128 7.4 / 4.9.  One set is summed at the memory system's rate, and loses where it is long: 64 heads
+  // L = 20,480 814 / 862 (ten launches), 32 heads at D = 128 L = 10,816 318 / 335, L = 2,048 12.8 / 13.1 (L = 4,096 88 / 85).
+  constexpr int kTogether = SETS > 1 ? 4 : 1;
   const int group = p.group;
   const size_t per = (size_t)(sets.key_hi - sets.key_lo) * p.Hkv * (D / 4);
   for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < 2 * per; idx += (size_t)gridDim.x * blockDim.x) {

@@ -155,3 +155,21 @@ def test_no_kernel_spills(code_objects):
             if int(size):
                 spilling[name] = int(size)
     assert seen >= 30 and not spilling
+
+
+def test_how_many_loads_the_sum_of_partials_has_on_their_way(code_objects):
+    """16-byte loads between two waits: four heads' (with rotary embedding eight) where several sets of partials are summed, one
+    head's (two) where one is."""
+    most = {}
+    for co in code_objects:
+        kernel, run = "", 0
+        for line in _tool("llvm-objdump", "-d", "--no-show-raw-insn", co).splitlines():
+            label = re.match(r"^[0-9a-f]+ <(\S+)>:", line)
+            if label:
+                kernel, run = label.group(1), 0
+            sets = re.search(r"reduce_partials_kernelILi(\d+)ELi(\d)E", kernel)
+            if not sets:
+                continue
+            run = 0 if "vmcnt" in line else run + ("global_load_dwordx4" in line)
+            most[sets.groups()] = max(most.get(sets.groups(), 0), run)
+    assert most == {(d, n): 2 if n == "1" else 8 for d in ("64", "128") for n in ("1", "4")}
