@@ -2214,13 +2214,8 @@ struct PartSets {
   int n, key_lo, key_hi;  // sets, and all their keys
   int key_first[kMaxRanges], key_end[kMaxRanges], acc_below[kMaxRanges];
 };
-template <int D, int SETS>
+template <int D, int SETS, int TOGETHER>  // TOGETHER: heads whose loads are on their way together
 __global__ __launch_bounds__(256) void reduce_partials_kernel(BwdParams p, PartSets sets) {
-  // Heads whose loads are on their way together.  Several sets of partials are those of few heads, whose threads have one round
-  // trip after the other before them: us, one / four, 4 heads L = 1,000 5.7 / 4.7, L = 2,048 7.5 / 4.7, 16 heads 8.9 / 7.7, 4 heads in
-  // segments of 1,024 8.6 / 6.2, D = 128 7.4 / 4.9.  One set is summed at the memory system's rate, and loses where it is long: 64 heads
-  // L = 20,480 814 / 862 (ten launches), 32 heads at D = 128 L = 10,816 318 / 335, L = 2,048 12.8 / 13.1 (L = 4,096 88 / 85).
-  constexpr int kTogether = SETS > 1 ? 4 : 1;
   const int group = p.group;
   const size_t per = (size_t)(sets.key_hi - sets.key_lo) * p.Hkv * (D / 4);
   for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < 2 * per; idx += (size_t)gridDim.x * blockDim.x) {
@@ -2244,15 +2239,15 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(BwdParams p, PartS
       const float* src = part + (((size_t)(kvh * group) * p.L64 + j) * D + c4 * 4);
       const size_t head = (size_t)p.L64 * D;
       int hh = 0;
-      for (; hh + kTogether <= group; hh += kTogether) {
-        f32x4 x[kTogether], y[kTogether];
+      for (; hh + TOGETHER <= group; hh += TOGETHER) {
+        f32x4 x[TOGETHER], y[TOGETHER];
 #pragma unroll
-        for (int u = 0; u < kTogether; ++u) {
+        for (int u = 0; u < TOGETHER; ++u) {
           x[u] = *reinterpret_cast<const f32x4*>(src + (hh + u) * head);
           if (turn) y[u] = *reinterpret_cast<const f32x4*>(src + (hh + u) * head + D / 2);
         }
 #pragma unroll
-        for (int u = 0; u < kTogether; ++u) {
+        for (int u = 0; u < TOGETHER; ++u) {
           sum += x[u];
           if (turn) sum_hi += y[u];
         }
@@ -3004,8 +2999,21 @@ hipError_t DkdvLauncher::finish() {
   const dim3 grid((unsigned)blocks), block(256);
   TimedSpan span(timer_, kKindReduce, stream_);
   auto sum = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream_, p, sets); };
-  if (D == 64) n == 1 ? sum(reduce_partials_kernel<64, 1>) : sum(reduce_partials_kernel<64, kMaxRanges>);
-  else n == 1 ? sum(reduce_partials_kernel<128, 1>) : sum(reduce_partials_kernel<128, kMaxRanges>);
+  // Four heads' loads together where the sum is short or of several sets (which are those of few heads): a thread's time is then
+  // one round trip after the other.  One set of 128 MiB or more is summed at the memory system's rate, and loses.  us per launch, one /
+  // four: 64 heads, 128 anchors 4.9 / 4.5, 1,000 9.1 / 8.0, K = 4 2,048 12.6 / 13.1, in segments of 1,024 to 8,192 11.2, 18.7, 26.6,
+  // 32.8 / 10.8, 17.4, 25.4, 32.3 (the first 4,096), of 2,048 to 20,480 43.5, 58, 72, 150 / 44.8, 61, 77, 158 (6,144, 8,192, 10,240, 20,480
+  // anchors); 32 heads at D = 128, 2,048 anchors 18.0 / 16.7, 4,096 31 / 32.5, 10,240 74 / 82; several sets, one after the other / four: 4 heads
+  // 1,000 anchors 5.7 / 4.7, 2,048 7.5 / 4.7, in segments of 1,024 8.6 / 6.1, 16 heads 8.9 / 7.4.
+  constexpr size_t kLongSum = (size_t)128 << 20;
+  const bool longer = 2 * (size_t)(sets.key_hi - sets.key_lo) * p.Hq * D * sizeof(float) >= kLongSum;
+  auto form = [&](auto d) {
+    constexpr int DD = decltype(d)::value;
+    if (n > 1) sum(reduce_partials_kernel<DD, kMaxRanges, 4>);
+    else longer ? sum(reduce_partials_kernel<DD, 1, 1>) : sum(reduce_partials_kernel<DD, 1, 4>);
+  };
+  if (D == 64) form(std::integral_constant<int, 64>{});
+  else form(std::integral_constant<int, 128>{});
   return span.finish();
 }
 

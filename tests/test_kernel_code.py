@@ -158,8 +158,8 @@ def test_no_kernel_spills(code_objects):
 
 
 def test_how_many_loads_the_sum_of_partials_has_on_their_way(code_objects):
-    """16-byte loads between two waits: four heads' (with rotary embedding eight) where several sets of partials are summed, one
-    head's (two) where one is."""
+    """16-byte loads between two waits: one head's (with rotary embedding two) in the form for long sums of one set of partials,
+    four heads' (eight) in the others."""
     most = {}
     for co in code_objects:
         kernel, run = "", 0
@@ -167,9 +167,9 @@ def test_how_many_loads_the_sum_of_partials_has_on_their_way(code_objects):
             label = re.match(r"^[0-9a-f]+ <(\S+)>:", line)
             if label:
                 kernel, run = label.group(1), 0
-            sets = re.search(r"reduce_partials_kernelILi(\d+)ELi(\d)E", kernel)
+            sets = re.search(r"reduce_partials_kernelILi(\d+)ELi(\d)ELi(\d)E", kernel)
             if not sets:
                 continue
             run = 0 if "vmcnt" in line else run + ("global_load_dwordx4" in line)
             most[sets.groups()] = max(most.get(sets.groups(), 0), run)
-    assert most == {(d, n): 2 if n == "1" else 8 for d in ("64", "128") for n in ("1", "4")}
+    assert most == {(d, *form): loads for d in ("64", "128") for form, loads in ((("1", "1"), 2), (("1", "4"), 8), (("4", "4"), 8))}
