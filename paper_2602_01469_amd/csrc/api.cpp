@@ -1,5 +1,6 @@
 // C-ABI entry points: host-side validation and the sequence-partition driver (Sec. 3.2 of the
 // paper: forward and dQ over all segments of a call, then dK/dV segment by segment, accumulated in fp32).
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <mutex>
@@ -36,20 +37,37 @@ struct RowRanges {
   int n;
   peagle::ChunkSplit split;
 };
+// Chunks that dK/dV of the row tiles [rt_lo, rt_hi) is run over.
+int chunks_of(const peagle_tilemap_t* tm, const peagle::ChunkSplit& split, int Hq, int rt_lo, int rt_hi) {
+  const int n = peagle::dkdv_chunks(rt_hi - rt_lo, split, tm->sampled);
+  if (!tm->sampled || n == 1) return n;
+  if (!tm->rows_follow) return 1;  // (lists are cut by position)
+  const int chunk = (rt_hi - rt_lo + n - 1) / n;
+  int whole = 0, cut = 0;  // the longest walk of a pair of key tiles, which the first one's list drives
+  int64_t total = 0;
+  for (int32_t t = 0; t < tm->n_d0; t += 2) {
+    if (tm->key_ptr[t] == tm->key_ptr[t + 1]) continue;
+    const int first = std::max(rt_lo, (int)tm->key_entries[tm->key_ptr[t]].tile);
+    const int end = std::min(rt_hi, (int)tm->key_entries[tm->key_ptr[t + 1] - 1].tile + 1);
+    whole = std::max(whole, end - first);
+    total += std::max(0, end - first) * Hq;
+    for (int c = rt_lo; c < rt_hi; c += chunk) cut = std::max(cut, std::min(end, c + chunk) - std::max(first, c));
+  }
+  return peagle::dkdv_chunks_pay(n, chunk, split, whole, cut, total) ? n : 1;
+}
 RowRanges row_ranges(const peagle_tilemap_t* tm, const peagle_shape_t* sh, bool by_segment) {
   const int32_t L = sh->L, S = by_segment ? tm->S : 1;
   auto count = [&](const peagle::ChunkSplit& split) {
     int n = 0;
     for (int32_t s = 0; s < S && (!by_segment || tm->seg_bounds[s] < L); ++s) {
       const int32_t lo = by_segment ? tm->seg_bounds[s] : 0, hi = by_segment && tm->seg_bounds[s + 1] < L ? tm->seg_bounds[s + 1] : L;
-      const int32_t n_rt = !tm->sampled  ? (hi + tm->A - 1) / tm->A - lo / tm->A
-                           : by_segment ? tm->seg_rt[s + 1] - tm->seg_rt[s]
-                                        : tm->n_row_tiles;
-      n += peagle::dkdv_chunks(n_rt, split, tm->sampled, tm->dview.longest_list);
+      if (!tm->sampled) n += chunks_of(tm, split, sh->Hq, lo / tm->A, (hi + tm->A - 1) / tm->A);
+      else if (by_segment) n += chunks_of(tm, split, sh->Hq, tm->seg_rt[s], tm->seg_rt[s + 1]);
+      else n += chunks_of(tm, split, sh->Hq, 0, tm->n_row_tiles);
     }
     return n;
   };
-  peagle::ChunkSplit split{1, 1};
+  peagle::ChunkSplit split{1, 0, 1};
   const int n = count(split);
   if (n > 0) split = peagle::dkdv_chunk_split(sh->D, (L + 63) / 64 * 64, sh->Hq, n);
   return {count(split), split};
@@ -147,7 +165,7 @@ BwdParams make_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* s, const Se
                    const float* rope_table = nullptr, const SharedForm& sf = SharedForm()) {
   const WsLayout w = ws_layout(tm, s);
   BwdParams p{};
-  p.chunk_split = chunk_split;
+  p.n_chunks = chunks_of(tm, chunk_split, s->Hq, sr.rt_lo, sr.rt_hi);
   p.v_shared = (const __bf16*)sf.v_shared;
   p.shared_dk_part = sf.dk_part;
   p.shared_dv_part = sf.dv_part;

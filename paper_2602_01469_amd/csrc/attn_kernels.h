@@ -44,7 +44,7 @@ constexpr int kMaxRanges = 4;  // of one launch
 // How many chunks at most a range of rows may be cut into to fill the chip: by the slots that its work items leave, and by
 // the sets of partials that a launch sums.
 struct ChunkSplit {
-  int by_slots, by_sets;
+  int items, slots, by_sets;
 };
 
 struct BwdParams {
@@ -64,7 +64,7 @@ struct BwdParams {
   float* part_more;    // workspace [part_sets - 1][dK, dV][part_stride]: of the others
   size_t part_stride;
   int part_sets;       // as many ranges of rows as one launch may take
-  ChunkSplit chunk_split;  // see dkdv_chunks()
+  int n_chunks;        // that dK/dV of the row range is run over, see dkdv_chunks()
   DeviceTileMap tm;
   int L, T, Hq, Hkv, L64;
   int group;            // query heads per KV head
@@ -163,10 +163,13 @@ class DkdvLauncher {
   DkdvRange range_[kMaxRanges];    // ... by set
   int key_end_[kMaxRanges], acc_below_[kMaxRanges];
 };
-// Chunks that dK/dV of a range of row tiles is run over (listed: of a sampled or packed map), split: dkdv_chunk_split() of the
-// problem and of the number of ranges that it has of itself.
-int dkdv_chunks(int n_row_tiles, const ChunkSplit& split, bool listed, int longest_list);
+// Chunks that dK/dV of a range of row tiles is run over (listed: of a sampled or packed map, if dkdv_chunks_pay()), split:
+// dkdv_chunk_split() of the problem and of the number of ranges that it has of itself.
+int dkdv_chunks(int n_row_tiles, const ChunkSplit& split, bool listed);
 ChunkSplit dkdv_chunk_split(int D, int L64, int Hq, int n_ranges);
+// Whether n chunks of `chunk` row tiles pay that leave `cut` row tiles of the longest walk of a key-tile pair, which is `whole`;
+// total: row tiles that all walks of the range take together.
+bool dkdv_chunks_pay(int n, int chunk, const ChunkSplit& split, int whole, int cut, int64_t total);
 // Sets of partials worth having for a problem of n_ranges ranges of rows in all: several where a range's work items leave
 // slots idle.
 int dkdv_part_sets(int D, int L64, int Hq, int n_ranges);

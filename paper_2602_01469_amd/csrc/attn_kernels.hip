@@ -1701,8 +1701,9 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
 
   // row tiles that see a key tile, clipped to [rt_lo, rt_hi): the map stores where each segment
   // starts inside a key tile's (ascending) list.  A launch that covers only part of its segments
-  // (a cropped length, or one chunk of a long segment; dense maps only) cuts the range further by
-  // position: the row tiles in a dense map's list are consecutive.
+  // (a cropped length, or one chunk of a segment) cuts the range further by position: the row tiles
+  // of a list are consecutive in a dense map, and in a listed one that is run in chunks (the
+  // builder looks, see peagle_tilemap::rows_follow).
   // (All of it wave-uniform and looked up through the scalar path, both tiles of the pair and the first entries at a time: the
   // start of a workgroup is a chain of memory round trips, see fwd_kernel.)
   auto clip = [&](int t, int& lo_out, int& hi_out) {
@@ -2866,8 +2867,14 @@ int dkdv_part_sets(int D, int L64, int Hq, int n_ranges) {
 //    two, 32 heads at D = 128, 128 items, 127.5 and 133;
 //  - there is one chunk for 16 row tiles (the fourth from 64 on, so that its partials, a quarter of the workspace's, are worth
 //    it: 63 row tiles 70 us in three, 63 in four), in sampled and packed maps up to three;
-//  - a chunk of a packed batch cuts its lists at all, being no longer than 4/3 of the longest (seven sequences of 300 to 800
-//    anchors, 4 heads, 166 us, in three chunks 170);
+//  - the chunks of a sampled or packed map cut its longest walk, by a sixteenth at least: where a boundary falls between sequences
+//    they do not (400, 300 and 90 anchors, 32 heads, 100 us and 104 in two, 16 heads at D = 128 126 and 131; seven sequences of 331 to
+//    1,388, K = 4, 4 heads, 125 and 154 in three), where it falls inside the long ones they do (363, 170, 701 and 226, 8 heads at D = 128,
+//    walks of 46 and 31 row tiles, 189 and 147 in two; 164 to 1,446, 4 heads at D = 128, 389 and 288).  Where all slots are taken and
+//    the walks fill a fifth of the longest one's time, a chunk is also shorter than that one, by an eighth (16 heads, seven sequences
+//    of 61 to 785, walks of 48 and 36, chunks of 58, 165 and 176; but 8 heads at D = 128, 56, 578 and 1,288, walks of 90 and 61, chunks of
+//    61, 367 and 314); and where the longest walk is short, they fill less than a quarter of its time (16 heads at D = 128, 603, 53
+//    and 364, walks of 38 and 33, 179 and 206);
 //  - the problem's segments leave sets (4 heads L = 4,096 in four segments 328 us, with each in two chunks 340).
 // us per step, uncut / so: 4 heads L = 300 54.6 / 40.5, L = 600 91 / 51, L = 1,000 140 / 70, L = 1,391 187 / 82, L = 2,048 269 /
 // 119, L = 4,096 in two segments 377 / 338, K = 4 L = 2,500 185 / 97, K = 5 L = 1,200 117 / 63; 16 heads L = 700 113 / 72, L =
@@ -2877,19 +2884,24 @@ int dkdv_part_sets(int D, int L64, int Hq, int n_ranges) {
 constexpr int kSplitHeads = 4, kSplitRowTiles = 16, kShortLists = 40;
 ChunkSplit dkdv_chunk_split(int D, int L64, int Hq, int n_ranges) {
   const int64_t items = (int64_t)((L64 / kKeysPerTile + 1) / 2) * Hq;
-  if (Hq < kSplitHeads) return {1, 1};
-  return {(int)((D == 64 ? 2 : 1) * kCus / items), kMaxRanges / n_ranges};
+  const int slots = (D == 64 ? 2 : 1) * kCus;
+  if (Hq < kSplitHeads || items > slots) return {1, 0, 1};
+  return {(int)items, slots, kMaxRanges / n_ranges};
 }
-int dkdv_chunks(int n_row_tiles, const ChunkSplit& split, bool listed, int longest_list) {
-  const int least = listed ? 1 : (n_row_tiles + 127) / 128;
-  int n = n_row_tiles < kShortLists ? split.by_slots / 4 : split.by_slots;
+int dkdv_chunks(int n_row_tiles, const ChunkSplit& split, bool listed) {
+  const int least = listed ? 1 : (n_row_tiles + 127) / 128, by_slots = split.slots / split.items;
+  int n = n_row_tiles < kShortLists ? by_slots / 4 : by_slots;
   if (n > split.by_sets) n = split.by_sets;
   int worth = (n_row_tiles + kSplitRowTiles - 1) / kSplitRowTiles;
   const int most = listed || n_row_tiles < kMaxRanges * kSplitRowTiles ? kMaxRanges - 1 : kMaxRanges;
   if (worth > most) worth = most;
   if (n > worth) n = worth;
-  if (n <= least || (n_row_tiles + n - 1) / n > 4 * (longest_list / 3)) return least;
-  return n;
+  return n > least ? n : least;
+}
+bool dkdv_chunks_pay(int n, int chunk, const ChunkSplit& split, int whole, int cut, int64_t total) {
+  if (16 * cut > 15 * whole) return false;
+  if (16 * n * split.items > 15 * split.slots && 8 * chunk > 7 * whole && 5 * total > (int64_t)split.slots * whole) return false;
+  return whole >= 3 * kSplitRowTiles || 17 * total <= (int64_t)4 * split.slots * whole;
 }
 
 // dK/dV of a dense map runs over equal chunks of at most 128 row tiles (few heads: more and shorter ones, see above), each with a set of partials of its
@@ -2904,7 +2916,7 @@ hipError_t DkdvLauncher::add(const BwdParams& rows, int key_lo, int a_hi, int ac
   if (n_rt <= 0) return hipSuccess;
   const int A = p_.tm.A;
   const bool listed_map = p_.tm.row_tok != nullptr;
-  const int n_chunks = dkdv_chunks(n_rt, p_.chunk_split, listed_map, p_.tm.longest_list), chunk = (n_rt + n_chunks - 1) / n_chunks;
+  const int chunk = (n_rt + rows.n_chunks - 1) / rows.n_chunks;
   for (int c0 = rows.rt_lo; c0 < rows.rt_hi; c0 += chunk) {
     const int c1 = c0 + chunk < rows.rt_hi ? c0 + chunk : rows.rt_hi;
     const bool partial = c0 != rows.rt_lo || c1 != rows.rt_hi;

@@ -121,14 +121,10 @@ void build_key_lists(peagle_tilemap* tm) {
   tm->key_entries.reserve(tm->key_ptr[tm->n_key_tiles]);
   for (int32_t t = 0; t < tm->n_key_tiles; ++t) tm->key_entries.insert(tm->key_entries.end(), lists[t].begin(), lists[t].end());
 
-  bool follow = true;
-  tm->dview.longest_list = 0;
-  for (int32_t t = 0; t < tm->n_d0; ++t) {
-    const int32_t lo = tm->key_ptr[t], hi = tm->key_ptr[t + 1];
-    tm->dview.longest_list = std::max(tm->dview.longest_list, hi - lo);
-    for (int32_t e = lo + 1; e < hi; ++e) follow &= tm->key_entries[e].tile == tm->key_entries[e - 1].tile + 1;
-  }
-  if (!follow) tm->dview.longest_list = 0;
+  tm->rows_follow = true;
+  for (int32_t t = 0; t < tm->n_d0; ++t)
+    for (int32_t e = tm->key_ptr[t] + 1; e < tm->key_ptr[t + 1]; ++e)
+      tm->rows_follow &= tm->key_entries[e].tile == tm->key_entries[e - 1].tile + 1;
 
   // per key tile: where the row tiles of each segment start inside its list
   tm->key_seg_ptr.resize((size_t)tm->n_key_tiles * (tm->S + 1));

@@ -62,7 +62,6 @@ struct DeviceTileMap {
   int32_t chain_slots, chain_first;  // dense maps: chain slot ck of a row tile is anchor ck / chain_slots of the tile,
                                      // depth chain_first + ck % chain_slots (depth 0: the slot is unused)
   uint32_t k_reciprocal, slots_reciprocal;  // small_reciprocal() of K and of chain_slots
-  int32_t longest_list;              // (for the launchers) of the depth-0 key tiles' lists; 0: the row tiles of one don't follow one another
 };
 
 }  // namespace peagle
@@ -88,6 +87,7 @@ struct peagle_tilemap {
   std::vector<int32_t> key_ptr;
   std::vector<peagle::TileEntry> key_entries;
   std::vector<int32_t> key_seg_ptr;              // n_key_tiles * (S+1)
+  bool rows_follow = false;                      // the row tiles of each depth-0 key tile's list follow one another
   std::vector<uint32_t> masks;                   // n_masks * kMaskWords
   int64_t n_full = 0, n_partial = 0;
   int32_t n_masks = 0;

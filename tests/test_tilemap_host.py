@@ -683,3 +683,22 @@ def test_a_drafting_step_shape_follows_its_fields():
         assert pe.peagle_draft_decode_workspace_bytes(s) == pe.peagle_draft_decode_workspace_bytes(fresh) != base, field
         setattr(s, field, was)
         assert pe.peagle_draft_decode_workspace_bytes(s) == base
+
+
+@pytest.mark.parametrize("lens,K,Hq,D,sets", [
+    ([400, 300, 90], 8, 32, 64, 1),                                  # a boundary between the sequences: the longest walk stays
+    ([400, 300, 90], 8, 16, 128, 1),
+    ([400, 300, 90], 8, 16, 64, 3),                                  # three chunks, two boundaries inside sequences
+    ([364, 523, 229, 592, 1077, 162, 1299], 8, 4, 64, 1),            # chunks of 80 row tiles, the longest walk 74
+    ([164, 274, 785, 61, 67, 124, 553], 8, 16, 64, 1),               # every slot taken, chunks longer than the longest walk
+    ([56, 578, 1288], 8, 8, 128, 2),                                 # every slot taken, the longest walk cut by a third
+    ([363, 170, 701, 226], 8, 8, 128, 2),                            # chunks of 47, walks of 46 row tiles, but cut where long
+    ([128, 792], 7, 16, 128, 1),                                     # every slot taken, a short longest walk, long others
+    ([367, 194, 226, 232, 1549, 1304], 4, 4, 128, 2),                # every slot taken, for a short part of the longest walk
+    ([404, 447], 7, 32, 64, 1), ([254, 1375], 5, 4, 64, 3), ([330], 8, 4, 64, 2), ([330], 8, 3, 64, 1)])
+def test_chunks_of_packed_maps_cut_the_longest_walk(lens, K, Hq, D, sets):
+    """Sets of partials that the workspace is laid out for, by the chunks that dK/dV of a packed map is cut into."""
+    tm, L = pe.peagle_build_tilemap_packed(lens, K, device=-1), sum(lens)
+    part = 2 * Hq * ((L + 63) // 64 * 64) * D * 4
+    base = 2 * ((tm.tokens(L) * Hq * 4 + 255) // 256 * 256)
+    assert pe.peagle_workspace_bytes(tm, pe.Shape(L, K, Hq, 1, D)) == base + sets * part
