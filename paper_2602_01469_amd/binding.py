@@ -510,14 +510,10 @@ class DecodeShape:
                  scale: Optional[float] = None):
         self.C, self.K, self.Hq, self.Hkv, self.D, self.n_pages, self.max_pages = C_, K, Hq, Hkv, D, n_pages, max_pages
         self.scale = float(scale) if scale is not None else 1.0 / float(np.sqrt(D))
-        self._packed = (None, None)  # field values, and the structure made of them
 
     def c(self):
-        fields = (self.C, self.K, self.Hq, self.Hkv, self.D, self.scale, self.n_pages, self.max_pages)
-        packed = self._packed
-        if packed[0] != fields:
-            packed = self._packed = (fields, _DecodeShapeC(*fields))
-        return C.byref(packed[1])
+        # (made anew for each call, half a microsecond: equal fields are not fields that the structure accepts, 4.0 and 4)
+        return C.byref(_DecodeShapeC(self.C, self.K, self.Hq, self.Hkv, self.D, self.scale, self.n_pages, self.max_pages))
 
 
 def peagle_draft_decode_splits(shape: DecodeShape) -> int:

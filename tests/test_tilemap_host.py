@@ -672,7 +672,7 @@ def test_rope_shared_entry_point_validates_before_launch():
 
 
 def test_a_drafting_step_shape_follows_its_fields():
-    """The structure that the C ABI is given is kept between calls; it has to be made anew when a field changes."""
+    """The structure that the C ABI is given holds the fields as they are at the call, whatever they were at an earlier one."""
     s = pe.DecodeShape(4, 7, 64, 8, 64, 100, 16)
     base = pe.peagle_draft_decode_workspace_bytes(s)
     assert base == pe.peagle_draft_decode_workspace_bytes(pe.DecodeShape(4, 7, 64, 8, 64, 100, 16))
@@ -702,3 +702,20 @@ def test_chunks_of_packed_maps_cut_the_longest_walk(lens, K, Hq, D, sets):
     part = 2 * Hq * ((L + 63) // 64 * 64) * D * 4
     base = 2 * ((tm.tokens(L) * Hq * 4 + 255) // 256 * 256)
     assert pe.peagle_workspace_bytes(tm, pe.Shape(L, K, Hq, 1, D)) == base + sets * part
+
+
+def test_a_drafting_step_shape_refuses_after_a_call_what_it_refuses_before():
+    """Sizes that equal the earlier ones but are no integers, and a shape whose attributes were saved without any other state."""
+    s = pe.DecodeShape(4, 7, 64, 8, 64, 100, 16)
+    need = pe.peagle_draft_decode_workspace_bytes(s)
+    for field in ("C", "K", "Hq", "Hkv", "D", "n_pages", "max_pages"):
+        was = getattr(s, field)
+        setattr(s, field, float(was))
+        with pytest.raises(TypeError):
+            pe.peagle_draft_decode_workspace_bytes(s)
+        setattr(s, field, was)
+        assert pe.peagle_draft_decode_workspace_bytes(s) == need
+    saved = {f: getattr(s, f) for f in ("C", "K", "Hq", "Hkv", "D", "scale", "n_pages", "max_pages")}
+    restored = pe.DecodeShape.__new__(pe.DecodeShape)
+    restored.__dict__.update(saved)
+    assert pe.peagle_draft_decode_workspace_bytes(restored) == need
