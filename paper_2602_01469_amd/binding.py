@@ -323,9 +323,10 @@ def _ptr(t, name: str, dtype, shape):
 
 def _stream_ptr(stream):
     import torch
-    if stream is None:  # (torch.cuda.current_stream().cuda_stream without the object in between)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return C.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (not a public name: the stream without an object for it)
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def peagle_attn_fwd(tm: TileMap, shape: Shape, seg: int, q, k, v, o, lse, stream=None) -> None:

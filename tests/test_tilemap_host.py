@@ -719,3 +719,17 @@ def test_a_drafting_step_shape_refuses_after_a_call_what_it_refuses_before():
     restored = pe.DecodeShape.__new__(pe.DecodeShape)
     restored.__dict__.update(saved)
     assert pe.peagle_draft_decode_workspace_bytes(restored) == need
+
+
+@pytest.mark.parametrize("raw", [True, False])
+def test_the_current_stream_with_and_without_torchs_raw_accessor(monkeypatch, raw):
+    import torch
+    from types import SimpleNamespace
+    from paper_2602_01469_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x1230))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    if raw:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x4560 + device, raising=False)
+    assert binding._stream_ptr(None) == (0x4563 if raw else 0x1230)
+    assert binding._stream_ptr(SimpleNamespace(cuda_stream=0x7890)).value == 0x7890
