@@ -127,8 +127,9 @@ int peagle_tilemap_expand_rows(const peagle_tilemap_t* tm, int32_t L, int32_t se
 int peagle_tilemap_classes(const peagle_tilemap_t* tm, uint8_t* classes_out);
 
 /* Bytes of device scratch that peagle_attn_bwd / peagle_attn_step_partitioned use for this shape.  Where several segments
- * or parts of one share a launch (few query heads) this includes a set of partial sums for each; a call accepts a workspace that has room
- * for one set only (such as one made for a longer sequence of the same map), with the same results and more launches.  A set
+ * or parts of one share a launch (few query heads) this includes a set of partial sums for each; a call accepts a workspace
+ * that has room for one set only (such as one made for a longer sequence of the same map), with the same results and more
+ * launches.  A set
  * takes 2 * round_up(4 * Hq * round_up(L, 64) * D, 256) bytes, the rest 2 * round_up(4 * T * Hq, 256): with one set that is the
  * smallest size accepted.  (The rotary and first-layer workspaces below hold the same sets: fewer make them smaller alike.) */
 size_t peagle_workspace_bytes(const peagle_tilemap_t* tm, const peagle_shape_t* shape);
@@ -159,6 +160,12 @@ int peagle_attn_fwd(const peagle_tilemap_t* tm, const peagle_shape_t* shape, int
  *   accumulate 0: touched dK/dV elements are overwritten; 1: added to (caller zeroed or holds
  *              earlier segments' sums)
  *   workspace  device, >= peagle_workspace_bytes(); contents undefined before and after
+ *
+ * The same call gives the same bits each time, in a workspace of any accepted size.  O, LSE and dQ of a row do not depend on
+ * the other heads or on the segments of a call.  dK and dV are fp32 sums over rows, and how these are grouped depends on the call
+ * (here and in the steps below): on its segments, on the length, on the number of query heads - a call of four or more that
+ * would leave the device idle sums shorter ranges of rows apart - and with that, in a packed batch, on the sequences beside a
+ * sequence.  A key's sums may then differ in their last bits, as sums of the same terms in another order do.
  */
 int peagle_attn_bwd(const peagle_tilemap_t* tm, const peagle_shape_t* shape, int32_t seg, const void* q,
                     const void* k, const void* v, const void* o, const void* d_o, const float* lse, void* dq,

@@ -2879,8 +2879,10 @@ int dkdv_part_sets(int D, int L64, int Hq, int n_ranges) {
 // us per step, uncut / so: 4 heads L = 300 54.6 / 40.5, L = 600 91 / 51, L = 1,000 140 / 70, L = 1,391 187 / 82, L = 2,048 269 /
 // 119, L = 4,096 in two segments 377 / 338, K = 4 L = 2,500 185 / 97, K = 5 L = 1,200 117 / 63; 16 heads L = 700 113 / 72, L =
 // 2,048 390 / 333; 32 heads L = 700 137 / 118; D = 128 4 heads L = 600 137 / 72, L = 1,391 283 / 124, 8 heads L = 2,048 464 /
-// 394; 4 heads, sampled L = 1,500 125 / 70, L = 3,000 239 / 137, packed 200 and 300 anchors 70 / 53, 3,000 and 100 416 / 220.  A key's sums then have other last bits than the same heads' in a call of many.  From four query heads on, which is the
-// smallest drafter: parts of a call of up to three heads keep the bits that they have in the whole.
+// 394; 4 heads, sampled L = 1,500 125 / 70, L = 3,000 239 / 137, packed 200 and 300 anchors 70 / 53, 3,000 and 100
+// 416 / 220.  A key's sums then have other last bits than the same heads' in a call of many.  From four query heads on, which is the
+// smallest drafter; calls of one to three would be faster in chunks too (three heads L = 2,048 take what four took uncut), and are left
+// in one range so that parts of a call, taken up to three heads at a time, keep the bits that they have in the whole.
 constexpr int kSplitHeads = 4, kSplitRowTiles = 16, kShortLists = 40;
 ChunkSplit dkdv_chunk_split(int D, int L64, int Hq, int n_ranges) {
   const int64_t items = (int64_t)((L64 / kKeysPerTile + 1) / 2) * Hq;

@@ -874,7 +874,8 @@ def test_partitioned_step_replays_from_a_hip_graph():
 @pytest.mark.parametrize("D,Hq,Hkv", [(64, 128, 2), (128, 64, 2)])
 def test_tensors_beyond_4_gib_equal_their_halves(D, Hq, Hkv):
     """Q-shaped tensors just over 4 GiB (row copies then form 64-bit addresses) against the same problem with the query
-    heads in two calls of half the size: heads do not interact, so every result has the same bits."""
+    heads in two calls of half the size: heads do not interact, and dK/dV run over the same ranges of rows in either call (the
+    work items take every slot), so every result has the same bits."""
     L, K = 2049, 128
     T = L * K
     assert T * Hq * D * 2 >= 1 << 32 > T * Hq * D
@@ -1227,7 +1228,8 @@ def test_chunks_that_share_a_launch_in_a_backward_by_itself(accumulate, D):
 @pytest.mark.parametrize("Hq,Hkv", [(2, 1), (112, 56)])
 def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
     """Six hundred anchors alone (short lists, at many heads the plain dQ kernel) and packed in front of a sequence of five
-    thousand (long lists, the pipelined form in one grid)."""
+    thousand (long lists, the pipelined form in one grid).  With these numbers of heads dK/dV run in one range of rows in both;
+    the next test has those with which they do not."""
     K, D, own, other = 8, 64, 600, 5000
     print(f"case packed neighbours Hq={Hq}", flush=True)
     maps = [pe.peagle_build_tilemap_packed(lens, K, device=0) for lens in ([own], [own, other])]
@@ -1241,6 +1243,32 @@ def test_a_sequence_keeps_its_bits_whatever_it_is_packed_with(Hq, Hkv):
         results.append({m: r[m].view(K, n, -1, D)[:, :own] for m in ("o", "dq", "dk", "dv")})
     for m in results[0]:
         assert torch.equal(results[0][m], results[1][m]), m
+
+
+@pytest.mark.parametrize("Hq,alone,packed", [(4, 3, 2), (8, 3, 1)])
+def test_the_last_bits_of_a_sequences_key_gradients_may_depend_on_what_it_is_packed_with(Hq, alone, packed):
+    """The same sequence with four and eight heads: dK/dV run in three chunks alone and in two or one packed.  O, LSE and dQ
+    have the same bits; a key's gradients are sums of the same fp32 terms in another grouping."""
+    K, D, Hkv, own, other = 8, 64, 1, 600, 5000
+    print(f"case packed neighbours, chunks Hq={Hq}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(338)
+    L = own + other
+    full = [torch.randn(K, L, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq)]
+    results = []
+    for lens, n, sets in (([own], own, alone), ([own, other], L, packed)):
+        tm = pe.peagle_build_tilemap_packed(lens, K, device=0)
+        part, base = 2 * Hq * ((n + 63) // 64 * 64) * D * 4, 2 * ((tm.tokens(n) * Hq * 4 + 255) // 256 * 256)
+        assert pe.peagle_workspace_bytes(tm, pe.Shape(n, K, Hq, Hkv, D)) == base + sets * part
+        r = _heads_run(tm, n, K, *(t[:, :n].reshape(K * n, t.shape[2], D).contiguous() for t in full))
+        results.append({m: r[m].view(K, n, r[m].shape[1], -1)[:, :own] for m in r})
+    for m in ("o", "lse", "dq"):
+        assert torch.equal(results[0][m], results[1][m]), m
+    # Each of the two sums takes a rounding for every 16 rows, head and chunk, of a partial sum that is, root mean square,
+    # no larger than the whole sum of terms of either sign.
+    roundings = own * K // 16 + Hq + 3
+    for m in ("dk", "dv"):
+        a, b = (r[m].double().cpu().numpy() for r in results)
+        assert 0 < rel_l2(a, b) <= 2 * roundings * 2.0 ** -24, m
 
 
 def test_sampled_map_of_long_lists_runs_the_pipelined_dq():
