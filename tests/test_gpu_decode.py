@@ -298,15 +298,11 @@ def test_draft_decode_with_one_piece_and_with_more(D, pages):
     assert np.array_equal(o2[others], o[others]) and np.array_equal(lse2[others], lse[others])
 
 
-@pytest.mark.parametrize("K,Hq,Hkv", [(1, 3, 3), (3, 5, 1), (5, 21, 3), (16, 8, 1), (43, 9, 3)])
+@pytest.mark.parametrize("K,Hq,Hkv", [(1, 3, 3), (3, 5, 1), (5, 21, 3), (16, 8, 1), (42, 9, 3)])
 @pytest.mark.parametrize("D,ctx,at_least", [(64, 800, 2), (64, 1500, 3), (64, 4000, 9), (128, 600, 2), (128, 1200, 3), (128, 4000, 9)])
 def test_draft_decode_merges_pieces_of_any_number_of_rows(D, ctx, at_least, K, Hq, Hkv):
-    """One, 15, 35, 128 and 129 - 128 is the most - rows per KV head, none a whole number of the merging workgroups' rows but
+    """One, 15, 35, 128 (the most) and 126 rows per KV head, none a whole number of the merging workgroups' rows but
     the fourth; two to sixteen pieces, so that each form of the merging kernel runs; one request with a bad page."""
-    if K * (Hq // Hkv) > 128:
-        with pytest.raises(pe.PeagleError):
-            pe.peagle_draft_decode_workspace_bytes(pe.DecodeShape(2, K, Hq, Hkv, D, 8, -(-ctx // 64)))
-        return
     print(f"case decode merge ctx={ctx} K={K} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
     inp = make_decode_inputs((ctx, ctx // 3), K, Hq, Hkv, D, 1600 + K)
     r = DecodeRun(inp, K, Hq, Hkv, D)
@@ -316,3 +312,9 @@ def test_draft_decode_merges_pieces_of_any_number_of_rows(D, ctx, at_least, K, H
     _check(inp, o, lse, r.shape.scale, f"merge {ctx} {K}")
     r.bt[1, 1] = r.shape.n_pages
     assert r.run()[2].tolist() == [0, 1]
+
+
+def test_draft_decode_refuses_more_than_128_rows_per_kv_head():
+    assert pe.peagle_draft_decode_workspace_bytes(pe.DecodeShape(2, 42, 9, 3, 64, 8, 8)) > 0
+    with pytest.raises(pe.PeagleError):
+        pe.peagle_draft_decode_workspace_bytes(pe.DecodeShape(2, 43, 9, 3, 64, 8, 8))

@@ -1185,8 +1185,10 @@ def test_segments_that_share_a_launch_give_the_bits_of_one_launch_each(form, D):
         torch.cuda.synchronize()
         return out
 
-    one_set = need(build(None), shape) if form != "chunks" else need(tm, shape) - 2 * 2 * Hq * 576 * D * 4
-    assert one_set < need(tm, shape)
+    part, rest = 2 * Hq * ((Lc + 63) // 64 * 64) * D * 4, 2 * ((T * Hq * 4 + 255) // 256 * 256)
+    sets = (pe.peagle_workspace_bytes(tm, shape) - rest) // part
+    assert pe.peagle_workspace_bytes(tm, shape) == rest + sets * part and sets == (3 if form == "chunks" else 4)
+    one_set = need(tm, shape) - (sets - 1) * part
     want = results(one_set, [(s, s + 1) for s in range(S)])
     for n_bytes in (need(tm, shape), one_set):
         for got, ref in zip(results(n_bytes, [(0, S)]), want):
@@ -1417,3 +1419,49 @@ def test_one_head_forwards_of_three_and_four_per_cu_give_the_same_bits(K, L, L_m
                           pe.Shape(L, K, n, 1, D).scale)
             assert rel_l2(bf16_to_f64(o1), ref["O"]) <= FWD_REL, h
             assert max_abs(lse1.double().cpu().numpy(), ref["LSE"]) <= LSE_ABS + 2e-6 * np.abs(ref["LSE"]).max(), h
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("form,seg,sets", [("dense", -1, 3), ("sampled", -1, 3), ("second_segment", 1, None), ("packed", -1, 3)])
+def test_chunks_of_few_heads_in_a_backward_by_itself(form, seg, sets, D):
+    """peagle_attn_bwd of four heads over a range of rows in chunks, with accumulate 0 and 1 on what the caller's tensors hold: the
+    same bits with room for one set of partials (a launch and a sum for each chunk), and with accumulate what they held added."""
+    from peagle_inputs import cod_depth_counts
+    print(f"case chunks in a backward {form} D={D}", flush=True)
+    Hq, Hkv, K = 4, 1, {"dense": 32, "packed": 16}.get(form, 7)
+    if form == "dense":
+        L, tm = 252, pe.peagle_build_tilemap(252, K, None, device=0)
+    elif form == "packed":
+        lens = [20, 290, 3, 41]
+        L, tm = sum(lens), pe.peagle_build_tilemap_packed(lens, K, device=0)
+    else:
+        L, bounds = 1050, [0, 400, 1050] if seg >= 0 else None
+        tm = pe.peagle_build_tilemap_sampled(cod_depth_counts(L, K, 0.9, 385), K, bounds, device=0)
+    shape, T = pe.Shape(L, K, Hq, Hkv, D), tm.tokens(L)
+    part, rest = 2 * Hq * ((L + 63) // 64 * 64) * D * 4, 2 * ((T * Hq * 4 + 255) // 256 * 256)
+    need = pe.peagle_workspace_bytes(tm, shape)
+    assert need == rest + (sets or (4 if D == 64 else 3)) * part
+    g = torch.Generator(device="cuda").manual_seed(386)
+    q, k, v, d_o = (torch.randn(T, H, D, generator=g, device="cuda").to(torch.bfloat16) for H in (Hq, Hkv, Hkv, Hq))
+    old = [torch.randn(T, Hkv, D, generator=g, device="cuda") for _ in range(2)]
+    o, lse = torch.zeros_like(q), torch.zeros((Hq, T), device="cuda")
+    pe.peagle_attn_fwd(tm, shape, seg, q, k, v, o, lse)
+
+    def results(n_bytes, accumulate):
+        ws = torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda")  # (NaN)
+        out = [torch.zeros_like(q), *(t.clone() for t in old)]
+        pe.peagle_attn_bwd(tm, shape, seg, q, k, v, o, d_o, lse, *out, accumulate, ws)
+        torch.cuda.synchronize()
+        return out
+    plain, added = results(need, 0), results(need, 1)
+    for accumulate, got in ((0, plain), (1, added)):
+        for a, b in zip(got, results(rest + part, accumulate)):
+            assert torch.isfinite(a).all() and torch.equal(a, b), accumulate
+    assert torch.equal(plain[0], added[0])
+    for a, b, t in zip(added[1:], plain[1:], old):
+        # (three chunks added to the tensor, three to each other, two subtractions: eight roundings of sums that are at most
+        # twice what the result and the tensor are; keys that no row of the call sees are left as they were)
+        seen = (b != t).any(dim=2).any(dim=1)
+        assert seen.any() and (seg < 0) <= bool(seen.all())
+        assert torch.equal(a[~seen], t[~seen])
+        assert (a - b - t)[seen].abs().max() <= 16 * 2.0 ** -24 * float(b.abs().max() + t.abs().max())

@@ -431,3 +431,51 @@ def test_shared_chain_vectors_give_the_same_bits_from_every_forward(Hq, form):
     tm = pe.peagle_build_tilemap(L, K, None, device=0)
     assert fwd_form(tm, Hq, Hkv) == form and fwd_form(tm, Hq // Hkv, 1) == "one head"
     _shared_whole_and_groups(tm, L, K, Hq, Hkv, D, 3100, range(Hkv))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("form", ["dense", "sampled", "packed"])
+def test_rope_step_in_chunks_of_few_heads(form, D):
+    """Four heads, a range of rows in three chunks: the reduction turns the sum of every set's dK before it adds it, as
+    in a workspace with room for one set, where each chunk has a launch: the same bits; and the plain step on rotated inputs, its
+    dQ and dK turned back."""
+    Hq, Hkv, K = 4, 1, {"dense": 32, "packed": 16}.get(form, 7)
+    print(f"case rope chunks {form} D={D}", flush=True)
+    if form == "dense":
+        L = 252
+        tm, tokens = pe.peagle_build_tilemap(L, K, None, device=0), None
+    elif form == "packed":
+        lens = [20, 290, 3, 41]
+        L, tm, tokens = sum(lens), pe.peagle_build_tilemap_packed(lens, K, device=0), orc.packed_tokens(lens, K, None)
+    else:
+        L, count = 1050, cod_depth_counts(1050, K, 0.9, 387)
+        tm, tokens = pe.peagle_build_tilemap_sampled(count, K, None, device=0), orc.cod_tokens(count)
+    T, shape = tm.tokens(L), pe.Shape(L, K, Hq, Hkv, D)
+    part, rest = 2 * Hq * ((L + 63) // 64 * 64) * D * 4, 2 * ((T * Hq * 4 + 255) // 256 * 256)
+    assert pe.peagle_workspace_bytes(tm, shape) == rest + 3 * part
+    qb, kb, vb, dob = (rand_bits((T, H, D), 960 + i) for i, H in enumerate((Hq, Hkv, Hkv, Hq)))
+    run = lambda: (Run if form == "dense" else SampledRun)(tm, L, K, Hq, Hkv, D, qb, kb, vb, dob)
+    r = attach_rope(run(), BASE)
+    full = r.ws.numel()
+    results = []
+    for n_bytes in (full, full - 2 * part):
+        r.ws = torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda")  # (NaN)
+        for t in (r.o, r.lse, r.dq, r.dk, r.dv):
+            t.fill_(float("nan"))
+        r.step_rope(0, 1)
+        results.append(r.results())
+    got, one = results
+    for n in ("O", "LSE", "dQ", "dK", "dV"):
+        assert np.isfinite(got[n]).all() and np.array_equal(got[n], one[n]), n
+    q_rot, k_rot = torch.empty_like(r.q), torch.empty_like(r.k)
+    pe.peagle_rope_rotate(tm, r.shape, r.q, r.rope_table, q_rot)
+    pe.peagle_rope_rotate(tm, pe.Shape(L, K, Hkv, Hkv, D), r.k, r.rope_table, k_rot)
+    p = run()
+    p.q, p.k = q_rot, k_rot
+    p.step(0, 1)
+    plain = p.results()
+    for n in ("O", "LSE", "dV"):
+        assert np.array_equal(plain[n], got[n]), n
+    pos = orc.position_ids(L, K, tokens)
+    assert rel_l2(got["dK"], orc.rope_rotate(plain["dK"], pos, BASE, inverse=True)) <= 1e-6   # fp32 sums turned back in fp32
+    assert rel_l2(got["dQ"], orc.rope_rotate(plain["dQ"], pos, BASE, inverse=True)) <= 6e-3   # bf16 before turning
