@@ -2691,16 +2691,19 @@ constexpr int kCus = 256;  // compute units of the device
 //     1,728 (12; 1,612) 56 / 59 / 63; 16 heads, L = 1,391 (13; 1,392) 46.1 / 48.3 / 48.4;
 //   in between: 8 heads, L = 3,000 (26; 1,504) 87 / 88 / 93, L = 4,000 (33; 2,000) 145 / 138 / 143; 4 heads, L = 8,000 (65; 2,000) 280 / 270 / 279.
 // One head runs three workgroups per CU (148 registers, a third buffer) where that many run at once, and, while lists are long and
-// unequal, up to four per CU; else four (128 registers, two buffers).  Forward us, three / four, by (mean list; workgroups):
+// unequal, up to four per CU, and with short lists where four per CU would leave a quarter of a second round; else four (128
+// registers, two buffers).  Forward us, three / four, by (mean list; workgroups):
 //   4 heads, K = 4 L = 2,048 (19; 256) 27.1 / 30.2, L = 1,391 (13; 348) 21.7 / 23.7, L = 2,048 (19; 512) 30.6 / 32.5, 64 heads L = 128
 //     (4; 512) 9.2 / 9.5, 16 heads L = 700 (7; 704) 18.3 / 18.9, 4 heads L = 3,000 (26; 752) 53.3 / 53.1;
 //   long: 6 heads L = 2,500 (22; 942) 51.4 / 53.1, 4 heads L = 4,096 (34; 1,024) 83.6 / 86.9;  but 64 heads L = 200 (4; 832) 15.3 / 13.7,
 //     16 heads L = 1,000 (10; 1,008) 31.2 / 29.5, 64 heads L = 256 (5; 1,024) 18.9 / 16.3, 12 heads L = 1,391 (13; 1,044) 38.8 / 37.2;
+//   a quarter of a round (in a step, under the profiler): K = 7, 32 heads L = 600 (7; 1,088) 29.1 / 30.6, 64 heads L = 330 (5; 1,216) 25.9 /
+//     27.1, K = 8 L = 300 (5; 1,216) 24.0 / 24.3, but 64 heads L = 330 (5; 1,344) 26.5 / 26.4, 16 heads L = 1,200 (12; 1,200) 43.7 / 42.5;
 //   many: 64 heads L = 411 (6; 1,664) 30.3 / 28.4; 24 heads in groups of three L = 2,500 (22; 3,768) 180 / 176, L = 8,192 (66; 12,288) 1,673 / 1,632.
-constexpr int kShortMeanTiles = 4, kFewMeanTiles = 24, kLongMeanTiles = 14;
+constexpr int kShortMeanTiles = 4, kFewMeanTiles = 24, kLongMeanTiles = 14, kTailMeanTiles = 8;
 enum class FwdForm { kOneHead, kOneHeadThreePerCu, kTwoHeads, kTwoHeadsThreePerCu };
 inline FwdForm pick_fwd_form(int group, int mean_tiles, int n_wg) {
-  const bool three_per_cu = n_wg <= 3 * kCus || (n_wg <= 4 * kCus && mean_tiles > kLongMeanTiles);
+  const bool three_per_cu = n_wg <= 3 * kCus || (n_wg <= 4 * kCus ? mean_tiles > kLongMeanTiles : n_wg < 5 * kCus && mean_tiles <= kTailMeanTiles);
   const FwdForm one_head = three_per_cu ? FwdForm::kOneHeadThreePerCu : FwdForm::kOneHead;
   if (group % 2 != 0 || n_wg <= 4 * kCus) return one_head;
   if (n_wg >= (mean_tiles <= kShortMeanTiles ? 12 : 8) * kCus) return FwdForm::kTwoHeadsThreePerCu;

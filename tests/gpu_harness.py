@@ -99,8 +99,8 @@ def fwd_form(tm, Hq, Hkv):
 
 def one_head_per_cu(tm, Hq):
     """Workgroups per CU of the forward of one head per workgroup."""
-    n_wg = tm.info()["n_row_tiles"] * Hq
-    return 3 if n_wg <= 768 or n_wg <= 1024 and int(mean_list(tm) + 0.5) > 14 else 4
+    n_wg, mean = tm.info()["n_row_tiles"] * Hq, int(mean_list(tm) + 0.5)
+    return 3 if n_wg <= 768 or (mean > 14 if n_wg <= 1024 else n_wg < 1280 and mean <= 8) else 4
 
 
 def rel_l2(a, b):
