@@ -397,7 +397,7 @@ __device__ __forceinline__ float mask_sel(float x, uint32_t w, int pos) {
   return ((w >> pos) & 1u) ? x : -__builtin_inff();
 }
 
-// x where bit `pos` of w is set, otherwise 0.
+// x where bit `pos` of w is set, otherwise 0 (whatever x is: the exponential of a score that the row does not see may be infinite).
 __device__ __forceinline__ float mask_zero(float x, uint32_t w, int pos) {
   const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)w, pos, 1);
   return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & keep);
@@ -1675,7 +1675,7 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
       first += count;
       count = n_pairs - first < rg.d0_step ? n_pairs - first : rg.d0_step;
     }
-    const int head = b / count;
+    const int head = b / count;  // (a division: count is the pass's)
     const int pair = first + b - head * count;
     kt0 = rg.d0_tile_lo + 2 * pair;
     h_lo = kvh * group + head;
@@ -1853,7 +1853,8 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* lds, const i
   // (The row tiles of a dense map's list follow one another, and their place says whether they carry a bitmask: of the list only
   // the ids of bitmasks are looked up in the loop, 30 to 45 instructions fewer an iteration with the offsets in 32 bits.  us per
   // step, from the list / so: L = 4,096 4,841 / 4,811, first-layer form L = 3,891 4,641 / 4,632, 4 heads L = 1,000 141.2 / 139.6,
-  // 32 heads at D = 128 L = 1,000 445 / 440, L = 10,816 31,520 / 31,420; listed maps, which keep their lists, the same.)
+  // 32 heads at D = 128 L = 1,000 445 / 440, L = 10,816 31,520 / 31,420; the same: listed maps, which keep their lists, and at D = 128 K = 5 and 7, two of
+  // whose registers moved to accumulation registers, dK/dV of 32 heads L = 1,391 220 / 218 and 301 / 300.)
   auto whole_tile = [&](int rt) { return !LISTED && !chain && rt * tm.A >= my_keys_end; };
   auto mask_pos = [&](int ei) {
     const int li = list_pos(ei);
